@@ -39,9 +39,10 @@ void fp6_tuning_set_split_k(int split_k);
 
 /*
  * Tuning hook for benchmarks and tests: force the block tile of the kernel used for N > 64:
- * block_rows in {128, 256} output channels x block_tokens in {64, 128} tokens; any
- * other pair restores the automatic choice.  fp16_linear uses 128 rows where 256 is
- * asked for.  Process-wide; affects the workspace size queries as well.
+ * block_rows in {128, 256} output channels x block_tokens in {64, 128} tokens, or 256 x 256; any
+ * other pair restores the automatic choice.  Where a weight format lacks a shape the next smaller one
+ * is used (fp16_linear and 64 tokens: 128 rows; group scales: 256 x 128 and 128 x 64).
+ * Process-wide; affects the workspace size queries as well.
  */
 void fp6_tuning_set_tile(int block_rows, int block_tokens);
 

@@ -7,6 +7,7 @@
 
 #include "fp6_device.hpp"
 #include "linear_stream.hpp"
+#include "linear_block.hpp"
 #include "linear_tiled.hpp"
 #include "pack_unpack.hpp"
 
@@ -194,6 +195,77 @@ bool allow_dynamic_lds(const void *kernel, size_t bytes, std::atomic<uint64_t> &
 
 std::atomic<int> g_forced_tile{0};  // 0 = automatic, else rows * 1024 + tokens (tuning hook)
 
+// ---- block kernel (prompt-sized N: fp16 weights, group-wise scales, and large products) -----------------------
+
+// Block shapes: {rows, tokens}.  Costs are ns per run of 32 columns with every CU busy (K = 8192, 16384 x 2048 outputs),
+// for fp16 weights and for 6-bit weights with group scales.
+struct BlockCfg {
+    int rows, tokens;
+    double fp16_ns, group_ns;
+};
+constexpr int kBlockCfgs = 4, kBlock256x256 = 0;
+constexpr BlockCfg kBlockCfg[kBlockCfgs] = {{256, 256, 924, 0}, {256, 128, 632, 485}, {128, 128, 333, 293}, {128, 64, 228, 0}};
+// BlockShape<RT, NT, WM, WN, WK, SR, XST, WD, ADB> of each, for run-staged (fp16) and packed weights
+template <bool RUN_STAGED, int C>
+struct BlockShapeOf;
+template <> struct BlockShapeOf<false, 0> { typedef BlockShape<4, 8, 4, 2, 1, 1, 6, 1, false> type; };
+template <> struct BlockShapeOf<false, 1> { typedef BlockShape<4, 4, 4, 2, 1, 2, 5, 1, true> type; };
+template <> struct BlockShapeOf<false, 2> { typedef BlockShape<4, 4, 2, 2, 2, 1, 5, 2, true> type; };
+template <> struct BlockShapeOf<false, 3> { typedef BlockShape<4, 2, 2, 2, 2, 1, 6, 2, true> type; };
+template <> struct BlockShapeOf<true, 0> { typedef BlockShape<4, 8, 4, 2, 1, 1, 4, 1, true> type; };
+template <> struct BlockShapeOf<true, 1> { typedef BlockShape<4, 4, 4, 2, 1, 1, 6, 1, true> type; };
+template <> struct BlockShapeOf<true, 2> { typedef BlockShape<4, 4, 2, 2, 2, 1, 4, 1, true> type; };
+template <> struct BlockShapeOf<true, 3> { typedef BlockShape<4, 2, 2, 2, 2, 1, 6, 1, true> type; };
+constexpr int kBlockWaves = 8;
+
+// the source through which the block kernel reads a weight format
+template <class Src>
+struct BlockSourceOf;
+template <> struct BlockSourceOf<PackedFp6Source> { typedef BlockFp6Source type; };
+template <> struct BlockSourceOf<PackedFp6GroupSource> { typedef BlockFp6GroupSource type; };
+template <> struct BlockSourceOf<PackedFp5Source> { typedef BlockFp5Source type; };
+template <> struct BlockSourceOf<PackedFp4Source> { typedef BlockFp4Source type; };
+template <> struct BlockSourceOf<PackedFp3Source> { typedef BlockFp3Source type; };
+template <> struct BlockSourceOf<PlainFp16Source> { typedef BlockFp16Source type; };
+
+struct BlockPlan {
+    int cfg;  // -1: the tiled kernel instead
+    int split;
+    int row_blocks, n_blocks, chunk;  // chunk: (row block, k slice) units per XCD
+    size_t counter_bytes, partial_bytes;
+    size_t total_bytes() const { return split > 1 ? counter_bytes + partial_bytes : 0; }
+};
+
+enum class Weights { kPacked, kGrouped, kFp16 };
+template <class Src>
+constexpr Weights weights_of()
+{
+    return std::is_same_v<Src, PlainFp16Source> ? Weights::kFp16
+                                                : std::is_same_v<Src, PackedFp6GroupSource> ? Weights::kGrouped : Weights::kPacked;
+}
+
+BlockPlan block_plan_of(int cfg, int64_t M, int64_t N, int64_t K)
+{
+    BlockPlan p;
+    p.cfg = cfg;
+    const BlockCfg &b = kBlockCfg[cfg];
+    const int64_t KT = K / kTileK;
+    p.row_blocks = (int)((M + b.rows - 1) / b.rows);
+    p.n_blocks = (int)((N + b.tokens - 1) / b.tokens);
+    int64_t s = g_forced_split.load(std::memory_order_relaxed);
+    if (s <= 0)
+        s = kCus / ((int64_t)p.row_blocks * p.n_blocks);  // one block per CU
+    const int64_t max_split = KT >= 8 ? KT / 4 : 1;  // at least four k-tiles per slice
+    s = s > max_split ? max_split : s;
+    s = s > 16 ? 16 : s;
+    p.split = (int)(s < 1 ? 1 : s);
+    p.chunk = (int)(((int64_t)p.row_blocks * p.split + 7) / 8);
+    const size_t tiles = (size_t)p.row_blocks * p.n_blocks;
+    p.counter_bytes = (tiles * kBlockWaves * sizeof(int) + 255) / 256 * 256;  // one arrival counter per wave tile
+    p.partial_bytes = (size_t)p.split * tiles * b.rows * b.tokens * sizeof(float);
+    return p;
+}
+
 struct TiledPlan {
     TileShape tile;
     int split;
@@ -203,7 +275,8 @@ struct TiledPlan {
     size_t total_bytes() const { return split > 1 ? counter_bytes + partial_bytes : 0; }
 };
 
-TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, bool tall_tile_ok)
+// smallest: only the 128 x 64 block (weights with group scales)
+TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, bool smallest)
 {
     TiledPlan p;
     const int64_t row_tiles = M / kTileRows;
@@ -216,8 +289,8 @@ TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, bool tall_tile_ok)
         p.tile = kTile128x64;  // few row blocks: small blocks and little split-K (measured on 8192-row layers)
     else
         p.tile = kTile256x128;  // the shape that moves the fewest bytes per MFMA
-    if (p.tile.rows() == 256 && p.tile.tokens() == 128 && !tall_tile_ok)  // this weight source does not fit 2 x 8 tiles per wave in registers
-        p.tile = kTile128x128;
+    if (smallest)
+        p.tile = kTile128x64;
     p.row_blocks = (int)((M + p.tile.rows() - 1) / p.tile.rows());
     p.n_blocks = (int)((N + p.tile.tokens() - 1) / p.tile.tokens());
     int64_t s = g_forced_split.load(std::memory_order_relaxed);
@@ -238,6 +311,103 @@ TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, bool tall_tile_ok)
     return p;
 }
 
+// What a call of more than kStreamMaxN tokens launches: the block kernel where `block.cfg` is set, else the tiled one.
+struct PromptPlan {
+    TiledPlan tiled;
+    BlockPlan block;
+    bool is_block() const { return block.cfg >= 0; }
+    int split() const { return is_block() ? block.split : tiled.split; }
+    size_t counter_bytes() const { return is_block() ? block.counter_bytes : tiled.counter_bytes; }
+    size_t partial_bytes() const { return split() > 1 ? (is_block() ? block.partial_bytes : tiled.partial_bytes) : 0; }
+    size_t total_bytes() const { return split() > 1 ? counter_bytes() + partial_bytes() : 0; }
+};
+
+// Estimated time of a block plan, ns: rounds of 256 blocks at the measured cost per run, a fixed part per round, and for
+// split-K what the last arrival reads (its tile of every slice, at the ~50 GB/s one CU gets) and what all slices write.
+double block_cost(const BlockPlan &p, int64_t K, Weights kind)
+{
+    const BlockCfg &b = kBlockCfg[p.cfg];
+    const double blocks = (double)p.row_blocks * p.n_blocks * p.split;
+    const double rounds = (double)(((int64_t)blocks + kCus - 1) / kCus);
+    const double runs = 8.0 * (double)((K / kTileK + p.split - 1) / p.split);
+    const double ns = rounds * (runs * (kind == Weights::kFp16 ? b.fp16_ns : b.group_ns) + 8000.0);
+    return p.split == 1 ? ns : ns + (double)p.split * b.rows * b.tokens * 4.0 / 50.0 + (double)p.partial_bytes * 1.5e-4;
+}
+
+// Which kernel and block (us, this kernel against the tiled one in the same process):
+//   per-row packed weights: the 256 x 256 block where its tiles nearly fill the chip in no more rounds than the tiled
+//     kernel's 256 x 128 blocks, at 1.08x their rate (6 bits: 57344 x 8192, N = 4096 2774 against 3155; 28672 x 8192,
+//     N = 512 193 against 205; 8192 x 22016, N = 2048 521 against 566) - with fewer tiles it needs split-K where the
+//     smaller block needs less of it or none (8192 x 8192, N = 1024 127 against 110);
+//   group scales: always, except few rows and few tokens (8192 x 8192, N = 100: 31 against 30; 4096 x 4096 17 against
+//     13; but 28672 x 8192, N = 201 120 against 166, 16384 x 8192, N = 2048 497 against 740);
+//   fp16 weights: always (9216 x 9216, N = 256 84 against 163; 16384 x 8192, N = 2048 473 against 1176; 8192 x 8192,
+//     N = 100 44 against 49).
+// Among its blocks the cheapest by block_cost().
+PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind)
+{
+    PromptPlan p;
+    p.block.cfg = -1;
+    p.tiled = plan_tiled(M, N, K, kind == Weights::kGrouped);
+    const int forced = g_forced_tile.load(std::memory_order_relaxed);
+    if (forced > 0) {
+        const int rows = forced / 1024, tokens = forced % 1024;
+        int cfg = -1;
+        if (tokens == 256)
+            cfg = kind == Weights::kGrouped ? 1 : kBlock256x256;
+        else if (kind != Weights::kPacked && tokens == 128)
+            cfg = rows == 256 ? 1 : 2;
+        else if (kind == Weights::kFp16)
+            cfg = 3;
+        if (cfg >= 0)
+            p.block = block_plan_of(cfg, M, N, K);
+        return p;
+    }
+    const int64_t row_blocks = (M + 255) / 256;
+    if (kind == Weights::kPacked) {
+        const int64_t tiles = row_blocks * ((N + 255) / 256), halves = row_blocks * ((N + 127) / 128);
+        const int64_t rounds = (tiles + kCus - 1) / kCus, half_rounds = (halves + kCus - 1) / kCus;
+        if (tiles >= 192 && 2 * rounds * 100 <= half_rounds * 108)
+            p.block = block_plan_of(kBlock256x256, M, N, K);
+        return p;
+    }
+    if (kind == Weights::kGrouped && N <= 128 && row_blocks < 64)
+        return p;
+    double best = 0.0;
+    // with group scales the 256 x 256 block does not fit the registers, the 128 x 64 one loses to the tiled kernel
+    const bool fp16 = kind == Weights::kFp16;
+    for (int c = fp16 ? 0 : 1; c < (fp16 ? kBlockCfgs : kBlockCfgs - 1); ++c) {
+        const BlockPlan b = block_plan_of(c, M, N, K);
+        const double cost = block_cost(b, K, kind);
+        if (p.block.cfg < 0 || cost < best) {
+            p.block = b;
+            best = cost;
+        }
+    }
+    return p;
+}
+
+template <class Src, int C>
+fp6_status launch_block_cfg(const BlockPlan &p, const void *weights, const void *scales, const void *X, void *Y, int64_t M,
+                            int64_t N, int64_t K, float4_t *partials, int *counters, const Epilogue &epi, hipStream_t stream)
+{
+    typedef typename BlockSourceOf<Src>::type Source;
+    typedef typename BlockShapeOf<Source::kRunStaged, C>::type Shape;
+    static_assert(Shape::BM == kBlockCfg[C].rows && Shape::BN == kBlockCfg[C].tokens && Shape::WAVES == kBlockWaves,
+                  "the table and the shape disagree");
+    auto kernel = linear_block_kernel<Source, Shape>;
+    constexpr size_t lds = Shape::template lds_bytes<Source>();
+    static_assert(lds <= 160 * 1024, "activation ring and weight tiles exceed the LDS of a CU");
+    static std::atomic<uint64_t> lds_done{0};  // per instantiation
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds, lds_done))
+        return FP6_ERR_HIP;
+    const dim3 grid((unsigned)(8 * p.chunk * p.n_blocks)), block(Shape::kThreads);
+    hipLaunchKernelGGL(kernel, grid, block, lds, stream, weights, static_cast<const half_t *>(scales),
+                       static_cast<const half_t *>(X), static_cast<half_t *>(Y), (int)M, (int)N, (int)K, p.split,
+                       p.n_blocks, p.row_blocks, p.chunk, partials, counters, epi);
+    return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
+}
+
 template <class Src, int RT, int NT, int WM, int WN>
 fp6_status launch_tiled_cfg(const TiledPlan &p, const void *weights, const void *scales, const void *X, void *Y,
                             int64_t M, int64_t N, int64_t K, float4_t *partials, int *counters, const Epilogue &epi,
@@ -256,72 +426,92 @@ fp6_status launch_tiled_cfg(const TiledPlan &p, const void *weights, const void 
     return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
 }
 
-// The tiled kernel addresses the activations with 32-bit byte offsets, so one launch takes at most this many
+// Both kernels address the activations with 32-bit byte offsets, so one launch takes at most this many
 // tokens (a multiple of the widest block); longer inputs are processed in chunks on the same stream.
-int64_t tiled_chunk_tokens(int64_t K)
+int64_t prompt_chunk_tokens(int64_t K)
 {
     const int64_t fit = ((1ll << 31) - 1) / (2 * K);
     return fit >= 128 ? fit / 128 * 128 : fit;  // shape_ok() admits K < 2^24 only: at least 64 tokens fit
 }
 
-// Workspace of the tiled path: the largest over the chunks a call is cut into (the last, shorter chunk may
+// Workspace of a prompt-sized call: the largest over the chunks a call is cut into (the last, shorter chunk may
 // use more k slices than the full ones).
-size_t tiled_workspace_bytes(int64_t M, int64_t N, int64_t K, bool tall_tile_ok)
+size_t prompt_workspace_bytes(int64_t M, int64_t N, int64_t K, Weights kind)
 {
-    const int64_t chunk = tiled_chunk_tokens(K);
+    const int64_t chunk = prompt_chunk_tokens(K);
     if (chunk <= 0)
         return 0;
     if (N <= chunk)
-        return plan_tiled(M, N, K, tall_tile_ok).total_bytes();
-    size_t bytes = plan_tiled(M, chunk, K, tall_tile_ok).total_bytes();
+        return plan_prompt(M, N, K, kind).total_bytes();
+    size_t bytes = plan_prompt(M, chunk, K, kind).total_bytes();
     const int64_t last = N % chunk;
     if (last > 0) {
-        const size_t b = plan_tiled(M, last, K, tall_tile_ok).total_bytes();
+        const size_t b = plan_prompt(M, last, K, kind).total_bytes();
         bytes = b > bytes ? b : bytes;
     }
     return bytes;
 }
 
 template <class Src>
-fp6_status launch_tiled_chunk(const void *weights, const void *scales, const void *X, void *Y, int64_t M, int64_t N,
+fp6_status launch_prompt_chunk(const void *weights, const void *scales, const void *X, void *Y, int64_t M, int64_t N,
                               int64_t K, const WorkspaceRef &workspace, const Epilogue &epi, hipStream_t stream)
 {
-    const TiledPlan p = plan_tiled(M, N, K, Src::kTallTile);
+    const PromptPlan p = plan_prompt(M, N, K, weights_of<Src>());
     SplitBuffers buf;
-    const fp6_status fits = workspace.view(p.counter_bytes, p.split > 1 ? p.partial_bytes : 0, buf);
+    const fp6_status fits = workspace.view(p.counter_bytes(), p.partial_bytes(), buf);
     if (fits != FP6_OK)
         return fits;
     int *counters = buf.counters;
     float4_t *partials = reinterpret_cast<float4_t *>(buf.partials);
-    const TileShape &t = p.tile;
+    if (p.is_block()) {
+        const BlockPlan &b = p.block;
+#define FP6_BLOCK_CASE(C_)                                                                                         \
+    if (b.cfg == C_)                                                                                               \
+        return launch_block_cfg<Src, C_>(b, weights, scales, X, Y, M, N, K, partials, counters, epi, stream);
+        if constexpr (weights_of<Src>() != Weights::kGrouped) {
+            FP6_BLOCK_CASE(0)
+        }
+        if constexpr (weights_of<Src>() != Weights::kPacked) {
+            FP6_BLOCK_CASE(1)
+            FP6_BLOCK_CASE(2)
+        }
+        if constexpr (weights_of<Src>() == Weights::kFp16) {
+            FP6_BLOCK_CASE(3)
+        }
+#undef FP6_BLOCK_CASE
+        return FP6_ERR_SHAPE;  // not reached: plan_prompt only picks the blocks above
+    }
+    const TileShape &t = p.tiled.tile;
 #define FP6_TILED_CASE(RT_, NT_, WM_, WN_)                                                                        \
     if (t.rt == RT_ && t.nt == NT_ && t.wm == WM_ && t.wn == WN_)                                                 \
-        return launch_tiled_cfg<Src, RT_, NT_, WM_, WN_>(p, weights, scales, X, Y, M, N, K, partials, counters, epi, \
+        return launch_tiled_cfg<Src, RT_, NT_, WM_, WN_>(p.tiled, weights, scales, X, Y, M, N, K, partials, counters, epi, \
                                                          stream);
-    FP6_TILED_CASE(2, 4, 4, 2)
-    FP6_TILED_CASE(2, 4, 4, 1)
-    FP6_TILED_CASE(2, 4, 8, 1)
-    if constexpr (Src::kTallTile) {
+    if constexpr (weights_of<Src>() != Weights::kFp16) {
+        FP6_TILED_CASE(2, 4, 4, 1)
+    }
+    if constexpr (weights_of<Src>() == Weights::kPacked) {
+        FP6_TILED_CASE(2, 4, 4, 2)
+        FP6_TILED_CASE(2, 4, 8, 1)
         FP6_TILED_CASE(2, 8, 8, 1)
     }
 #undef FP6_TILED_CASE
-    return FP6_ERR_SHAPE;  // not reached: plan_tiled only picks the shapes above
+    return FP6_ERR_SHAPE;  // not reached: plan_prompt only picks the shapes above
 }
 
 template <class Src>
-fp6_status launch_tiled(const void *weights, const void *scales, const void *X, void *Y, int64_t M, int64_t N,
+fp6_status launch_prompt(const void *weights, const void *scales, const void *X, void *Y, int64_t M, int64_t N,
                         int64_t K, const WorkspaceRef &workspace, const Epilogue &epi, hipStream_t stream)
 {
-    const int64_t chunk = tiled_chunk_tokens(K);
+    const int64_t chunk = prompt_chunk_tokens(K);
     if (chunk <= 0)
         return FP6_ERR_SHAPE;  // one token's activations exceed a 32-bit byte offset
     // every chunk's plan must fit before anything is launched (a full chunk and the shorter last one)
     for (int64_t n : {N < chunk ? N : chunk, N > chunk ? N % chunk : (int64_t)0}) {
         if (n <= 0)
             continue;
-        const TiledPlan p = plan_tiled(M, n, K, Src::kTallTile);
+        const PromptPlan p = plan_prompt(M, n, K, weights_of<Src>());
         SplitBuffers unused;
-        const fp6_status fits = workspace.view(p.counter_bytes, p.split > 1 ? p.partial_bytes : 0, unused);
+        const fp6_status fits = workspace.view(p.counter_bytes(), p.partial_bytes(), unused);
         if (fits != FP6_OK)
             return fits;
     }
@@ -332,7 +522,7 @@ fp6_status launch_tiled(const void *weights, const void *scales, const void *X, 
         Epilogue e = epi;
         if (e.residual)
             e.residual += n0 * Mout;
-        const fp6_status st = launch_tiled_chunk<Src>(weights, scales, static_cast<const half_t *>(X) + n0 * K,
+        const fp6_status st = launch_prompt_chunk<Src>(weights, scales, static_cast<const half_t *>(X) + n0 * K,
                                                       static_cast<half_t *>(Y) + n0 * Mout, M, n, K, workspace, e,
                                                       stream);
         if (st != FP6_OK)
@@ -466,16 +656,16 @@ fp6_status static_plan(int64_t M, int64_t N, int64_t K, size_t &counter_bytes)
             counter_bytes = p.counter_bytes;
         return probe.view(p.counter_bytes, p.split > 1 ? p.partial_bytes : 0, unused);
     }
-    const int64_t chunk = tiled_chunk_tokens(K);
+    const int64_t chunk = prompt_chunk_tokens(K);
     if (chunk <= 0)
         return FP6_ERR_SHAPE;
     for (int64_t n : {N < chunk ? N : chunk, N > chunk ? N % chunk : (int64_t)0}) {
         if (n <= 0)
             continue;
-        const TiledPlan p = plan_tiled(M, n, K, PackedFp6Source::kTallTile);
-        if (p.split > 1 && p.counter_bytes > counter_bytes)
-            counter_bytes = p.counter_bytes;
-        const fp6_status fits = probe.view(p.counter_bytes, p.split > 1 ? p.partial_bytes : 0, unused);
+        const PromptPlan p = plan_prompt(M, n, K, Weights::kPacked);
+        if (p.split() > 1 && p.counter_bytes() > counter_bytes)
+            counter_bytes = p.counter_bytes();
+        const fp6_status fits = probe.view(p.counter_bytes(), p.partial_bytes(), unused);
         if (fits != FP6_OK)
             return fits;
     }
@@ -496,7 +686,7 @@ fp6_status packed_linear_impl(const void *packed, const void *scales_f16, const 
         || !aligned16(epi.residual))
         return FP6_ERR_ALIGN;
     if (N > kStreamMaxN)
-        return launch_tiled<Src>(packed, scales_f16, X_f16, Y_f16, M, N, K, ws, epi, static_cast<hipStream_t>(stream));
+        return launch_prompt<Src>(packed, scales_f16, X_f16, Y_f16, M, N, K, ws, epi, static_cast<hipStream_t>(stream));
     return launch_stream<typename Src::StreamSource>(packed, scales_f16, X_f16, Y_f16, M, N, K, ws, epi,
                                                      static_cast<hipStream_t>(stream));
 }
@@ -526,8 +716,11 @@ size_t fp6_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
     if (!packed_shape_ok(M, K) || N <= 0)
         return 0;
-    return N <= kStreamMaxN ? plan_stream(M, N, K, true).total_bytes()
-                            : tiled_workspace_bytes(M, N, K, PackedFp6Source::kTallTile);
+    if (N <= kStreamMaxN)
+        return plan_stream(M, N, K, true).total_bytes();
+    // fp6g_linear asks here too
+    const size_t bytes = prompt_workspace_bytes(M, N, K, Weights::kPacked), grouped = prompt_workspace_bytes(M, N, K, Weights::kGrouped);
+    return bytes > grouped ? bytes : grouped;
 }
 
 size_t fp16_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
@@ -535,14 +728,15 @@ size_t fp16_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
     if (!shape_ok(M, K) || N <= 0)
         return 0;
     return N <= kStreamMaxN ? plan_stream(M, N, K, false).total_bytes()
-                            : tiled_workspace_bytes(M, N, K, PlainFp16Source::kTallTile);
+                            : prompt_workspace_bytes(M, N, K, Weights::kFp16);
 }
 
 void fp6_tuning_set_split_k(int split_k) { g_forced_split.store(split_k < 0 ? 0 : split_k); }
 
 void fp6_tuning_set_tile(int block_rows, int block_tokens)
 {
-    const bool known = (block_rows == 128 || block_rows == 256) && (block_tokens == 64 || block_tokens == 128);
+    const bool known = ((block_rows == 128 || block_rows == 256) && (block_tokens == 64 || block_tokens == 128))
+                       || (block_rows == 256 && block_tokens == 256);
     g_forced_tile.store(known ? block_rows * 1024 + block_tokens : 0);
 }
 
@@ -703,7 +897,7 @@ size_t fp3_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
     if (!packed_shape_ok(M, K) || N <= 0)
         return 0;
     return N <= kStreamMaxN ? plan_stream(M, N, K, true, PackedFp3Source::StreamSource::kTileCols).total_bytes()
-                            : tiled_workspace_bytes(M, N, K, PackedFp3Source::kTallTile);
+                            : prompt_workspace_bytes(M, N, K, Weights::kPacked);
 }
 
 fp6_status fp3_quantize_pack(const void *W_f16, int64_t M, int64_t K, void *packed, void *scales_f16, void *stream)
@@ -791,7 +985,7 @@ fp6_status fp16_linear(const void *W_f16, const void *X_f16, void *Y_f16, int64_
         return FP6_ERR_ALIGN;
     const WorkspaceRef ws{workspace, workspace_bytes, false};
     if (N > kStreamMaxN)
-        return launch_tiled<PlainFp16Source>(W_f16, nullptr, X_f16, Y_f16, M, N, K, ws, Epilogue{nullptr, nullptr, 0},
+        return launch_prompt<PlainFp16Source>(W_f16, nullptr, X_f16, Y_f16, M, N, K, ws, Epilogue{nullptr, nullptr, 0},
                                              static_cast<hipStream_t>(stream));
     return launch_stream<PlainFp16Source::StreamSource>(W_f16, nullptr, X_f16, Y_f16, M, N, K, ws, Epilogue{nullptr, nullptr, 0},
                                           static_cast<hipStream_t>(stream));

@@ -1,5 +1,5 @@
 // Device-side building blocks shared by the gfx950 kernels: the packed tile layout,
-// the register-level e3m2 -> fp16 de-quantization, and the two weight sources (packed
+// the register-level e3m2 -> fp16 de-quantization, and the weight sources (packed
 // 6-bit and plain fp16) that the linear-layer kernels are instantiated with.
 //
 // Packed layout, version 3 (this library's own; the paper's Section 5.2 only asks that
@@ -43,6 +43,7 @@ typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef float float16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -247,7 +248,6 @@ struct PackedFp6Source {
     static constexpr int kLdsTileBytes = 0;  // tiles in flight live in registers
     static constexpr int kTileCols = kTileK;  // columns of one weight tile in the streaming kernel
     static constexpr bool kHasScale = true;
-    static constexpr bool kTallTile = true;  // a wave tile of 2 row tiles x 8 token tiles (64 accumulator registers) is affordable
     static constexpr int kLoads = 3;
     // bytes from one k-tile of the slice to the next
     __device__ static __forceinline__ int tile_stride(int64_t RT) { return (int)(RT * kTileBytes); }
@@ -299,7 +299,6 @@ struct PackedFp6GroupSource {
     static constexpr int kLdsTileBytes = 0;  // tiles in flight live in registers
     static constexpr int kTileCols = kTileK;  // columns of one weight tile in the streaming kernel
     static constexpr bool kHasScale = false;  // no per-row factor in the epilogue
-    static constexpr bool kTallTile = false;  // the scales and their multiplies leave no room for the 2 x 8 wave tile
     static constexpr int kLoads = 4;
     struct Tile {
         u32x4 p0, p1, p2;
@@ -393,7 +392,6 @@ struct PackedFp5Source {
     static constexpr int kLdsTileBytes = 0;  // tiles in flight live in registers
     static constexpr int kTileCols = kTileK;  // columns of one weight tile in the streaming kernel
     static constexpr bool kHasScale = true;
-    static constexpr bool kTallTile = true;
     static constexpr int kLoads = 3;
     static constexpr int kTileBytes5 = 2560;
     __device__ static __forceinline__ int tile_stride(int64_t RT) { return (int)(RT * kTileBytes5); }
@@ -468,7 +466,6 @@ struct PackedFp4Source {
     static constexpr int kLdsTileBytes = 0;  // tiles in flight live in registers
     static constexpr int kTileCols = kTileK;  // columns of one weight tile in the streaming kernel
     static constexpr bool kHasScale = true;
-    static constexpr bool kTallTile = true;
     static constexpr int kLoads = 2;
     static constexpr int kTileBytes4 = 2048;
     __device__ static __forceinline__ int tile_stride(int64_t RT) { return (int)(RT * kTileBytes4); }
@@ -539,7 +536,6 @@ struct PackedFp3WideSource {
     static constexpr int kLdsTileBytes = 0;  // tiles in flight live in registers
     static constexpr int kTileCols = 512;
     static constexpr bool kHasScale = true;
-    static constexpr bool kTallTile = true;
     static constexpr int kLoads = 3;
     __device__ static __forceinline__ int tile_stride(int64_t RT) { return (int)(RT * kTileBytes3); }
     __device__ static __forceinline__ int k_offset(int f, int q) { return f * 32 + q * 8; }
@@ -585,7 +581,6 @@ struct PackedFp3Source {
     static constexpr int kLdsTileBytes = 0;
     static constexpr int kTileCols = kTileK;
     static constexpr bool kHasScale = true;
-    static constexpr bool kTallTile = true;
     static constexpr int kLoads = 2;
     __device__ static __forceinline__ int k_offset(int f, int q) { return f * 32 + q * 8; }
     struct Stream {
@@ -626,61 +621,15 @@ struct PackedFp3Source {
     }
 };
 
+// Row-major fp16 weights as the host names them (the kernels read them through StagedFp16Source and, beyond the
+// streaming kernel's token counts, BlockFp16Source).
 struct StagedFp16Source;
 struct PlainFp16Source {
-    typedef StagedFp16Source StreamSource;  // the source the streaming kernel uses for this format
-    typedef SimpleStream<PlainFp16Source> Stream;
-    static constexpr bool kPackedConfigs = false;  // which table of kernel configurations the host uses
-    struct Tile {
-        u32x4 v[8];
-    };
-    static constexpr int kLdsTileBytes = 0;  // tiles in flight live in registers
-    static constexpr int kTileCols = kTileK;  // columns of one weight tile in the streaming kernel
-    static constexpr bool kHasScale = false;
-    static constexpr bool kTallTile = false;
-    static constexpr int kLoads = 8;
-    __device__ static __forceinline__ int tile_stride(int64_t /*RT*/) { return kTileK * 2; }  // row-major W
-    // the four lane groups of a row read four adjacent 16-byte pieces (64 contiguous bytes per row
-    // and load instruction); plain (cached) loads, so the other half of each line is an L1/L2 hit
-    __device__ static __forceinline__ int k_offset(int f, int q) { return f * 32 + q * 8; }
-    // the 16 rows of the row tile; tiles past the slice are neutralised by zero activations
-    __device__ static __forceinline__ rsrc_t slice_rsrc(const void *base, int64_t row_tile, int /*kt_first*/,
-                                                        int /*kt_step*/, int /*n_tiles*/, int64_t /*RT*/, int64_t K)
-    {
-        return make_rsrc(static_cast<const half_t *>(base) + row_tile * kTileRows * K, (uint32_t)(kTileRows * K * 2));
-    }
-    __device__ static __forceinline__ int lane_offset(int lane, int kt0, int K)
-    {
-        const int r = lane & 15, q = lane >> 4;
-        return (r * K + kt0 * kTileK + q * 8) * 2;
-    }
-    __device__ static __forceinline__ void issue(Tile &t, rsrc_t rs, int off)
-    {
-        t.v[0] = issue_load_b128<0, false>(rs, off);
-        t.v[1] = issue_load_b128<64, false>(rs, off);
-        t.v[2] = issue_load_b128<128, false>(rs, off);
-        t.v[3] = issue_load_b128<192, false>(rs, off);
-        t.v[4] = issue_load_b128<256, false>(rs, off);
-        t.v[5] = issue_load_b128<320, false>(rs, off);
-        t.v[6] = issue_load_b128<384, false>(rs, off);
-        t.v[7] = issue_load_b128<448, false>(rs, off);
-    }
-    __device__ static __forceinline__ void pin_tile(Tile &t)
-    {
-#pragma unroll
-        for (int f = 0; f < 8; ++f)
-            pin(t.v[f]);
-    }
-    template <int G>
-    __device__ static __forceinline__ void fragments(const Tile &t, half8_t &even_run, half8_t &odd_run)
-    {
-        even_run = bit_cast<half8_t>(t.v[2 * G]);
-        odd_run = bit_cast<half8_t>(t.v[2 * G + 1]);
-    }
+    typedef StagedFp16Source StreamSource;
 };
 
 // fp16 weights for the streaming kernel, staged through LDS.  Loading the A operand of a row-major fp16
-// matrix straight into registers (PlainFp16Source) makes every load instruction touch 16 rows x 64 bytes:
+// matrix straight into registers makes every load instruction touch 16 rows x 64 bytes:
 // half a cache line per row and request.  Here a copy instruction (global -> LDS, no registers) fetches
 // 8 rows x 128 bytes - eight whole lines - and the wave reads its A fragments back from LDS.  The region is
 // private to the wave (its own copies, its own reads): the wait for the copies is all the synchronisation
@@ -703,7 +652,6 @@ struct StagedFp16Source {
     typedef StagedFp16Source StreamSource;  // the source the streaming kernel uses for this format
     static constexpr bool kPackedConfigs = false;
     static constexpr bool kHasScale = false;
-    static constexpr bool kTallTile = false;
     static constexpr int kLoads = 8;
     static constexpr int kLdsTileBytes = 8192;
     static constexpr int kTileCols = kTileK;
