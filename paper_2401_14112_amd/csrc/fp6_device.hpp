@@ -164,6 +164,26 @@ __device__ __forceinline__ void issue_load_to_lds_b128(rsrc_t rsrc, int lane_off
                      : : "s"(lds_base), "v"(lane_off), "s"(rsrc), "n"(IMM) : "memory");
 }
 
+// ---- split-K partial tiles ---------------------------------------------------
+// Written and read 16 bytes per lane, each access performed at the point where all CUs of the device agree: the cache
+// bits (sc1) are those of an agent-scope atomic access, which only comes in pieces of up to 8 bytes.  The address unit
+// takes as long for a 4-byte access per lane as for a 16-byte one.  (The streaming kernel keeps its 4-byte accesses:
+// 16 bytes cost it 1.5 us at 32 and 64 tokens.)
+typedef __amdgpu_buffer_rsrc_t partial_rsrc_t;
+constexpr int kAgentScope = 16;  // sc1
+__device__ __forceinline__ partial_rsrc_t partial_buffer(void *p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x00020000);
+}
+__device__ __forceinline__ void agent_store(partial_rsrc_t r, int off, const float4_t &v)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(bit_cast<u32x4>(v), r, off, 0, kAgentScope);
+}
+__device__ __forceinline__ float4_t agent_load(partial_rsrc_t r, int off)
+{
+    return bit_cast<float4_t>(__builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kAgentScope));
+}
+
 // ---- activation tile layout in LDS -----------------------------------------
 // One MFMA step needs, for its 16 token columns n and 4 lane groups q, the 8 consecutive columns
 // X[n][k_offset(f, q) ..+8]: 64 pieces of 16 bytes = 1 KB per (token tile, run).  Inside that 1 KB,

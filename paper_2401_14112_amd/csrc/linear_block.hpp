@@ -272,13 +272,6 @@ __device__ __forceinline__ void block_barrier()
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// partial sums of split-K: 16 bytes per lane, performed where all CUs of the device agree (agent scope)
-constexpr int kAgentScope = 16;  // sc1
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(void *p, int bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x00020000);
-}
-
 template <class Src, class Shape>
 __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     const void *__restrict__ weights, const half_t *__restrict__ scales, const half_t *__restrict__ X, half_t *Y, int M,
@@ -661,15 +654,15 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     const int64_t tiles = (int64_t)row_blocks * n_blocks;
     constexpr int WAVE_BYTES = OWN * 1024;
     auto slice_of = [&](int s) {
-        return buffer_of(reinterpret_cast<uint8_t *>(partials) + ((s * tiles + tile_id) * WAVES + wave) * WAVE_BYTES, WAVE_BYTES);
+        return partial_buffer(reinterpret_cast<uint8_t *>(partials) + ((s * tiles + tile_id) * WAVES + wave) * WAVE_BYTES, WAVE_BYTES);
     };
     auto live = [&](int o) { return tile_col(o) < N && tile_row(o) < M; };  // the same for every lane
     {
-        const __amdgpu_buffer_rsrc_t dst = slice_of(split);
+        const partial_rsrc_t dst = slice_of(split);
 #pragma unroll
         for (int o = 0; o < OWN; ++o)
             if (live(o))
-                __builtin_amdgcn_raw_buffer_store_b128(bit_cast<u32x4>(own[o]), dst, o * 1024 + lane * 16, 0, kAgentScope);
+                agent_store(dst, o * 1024 + lane * 16, own[o]);
     }
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's partial stores are done
@@ -692,20 +685,20 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
         for (int o = 0; o < OG; ++o)
             sum[o] = (float4_t){0.f, 0.f, 0.f, 0.f};
         for (int s0 = 0; s0 < S; s0 += kPartialBatch) {
-            u32x4 part[kPartialBatch][OG];
+            float4_t part[kPartialBatch][OG];
 #pragma unroll
             for (int u = 0; u < kPartialBatch; ++u) {
-                const __amdgpu_buffer_rsrc_t src = slice_of(s0 + u < S ? s0 + u : S - 1);
+                const partial_rsrc_t src = slice_of(s0 + u < S ? s0 + u : S - 1);
 #pragma unroll
                 for (int o = 0; o < OG; ++o)
-                    part[u][o] = __builtin_amdgcn_raw_buffer_load_b128(src, (o0 + o) * 1024 + lane * 16, 0, kAgentScope);
+                    part[u][o] = agent_load(src, (o0 + o) * 1024 + lane * 16);
             }
 #pragma unroll
             for (int u = 0; u < kPartialBatch; ++u)
                 if (s0 + u < S)
 #pragma unroll
                     for (int o = 0; o < OG; ++o)
-                        sum[o] += bit_cast<float4_t>(part[u][o]);
+                        sum[o] += part[u][o];
         }
 #pragma unroll
         for (int o = 0; o < OG; ++o)
