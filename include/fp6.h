@@ -100,7 +100,14 @@ fp6_status fp6_unpack(const void *packed, const void *scales_f16, int64_t M, int
 size_t fp6_linear_workspace_bytes(int64_t M, int64_t N, int64_t K);
 size_t fp16_linear_workspace_bytes(int64_t M, int64_t N, int64_t K);
 
-/* Zero-fill a workspace with a kernel on `stream` (graph-capturable). */
+/*
+ * Bytes at the start of a workspace that have to be zero before its first use: the arrival counters of every call in
+ * this library for the shape (a multiple of 256; the whole workspace may be smaller).  The partial sums behind them
+ * may hold anything, so a caller that makes a workspace for one call need not clear all of it.
+ */
+size_t fp6_workspace_zero_bytes(int64_t M, int64_t N, int64_t K);
+
+/* Zero-fill a workspace (or its first bytes) with a kernel on `stream` (graph-capturable). */
 fp6_status fp6_workspace_init(void *workspace, size_t workspace_bytes, void *stream);
 
 /*

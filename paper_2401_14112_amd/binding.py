@@ -8,6 +8,7 @@ cannot be built, or a tensor is not on the GPU, the call raises.
 from __future__ import annotations
 
 import ctypes
+from functools import lru_cache
 from pathlib import Path
 from typing import Optional, Tuple
 
@@ -51,6 +52,8 @@ def load_library():
     L.fp6_linear_workspace_bytes.argtypes = [i64, i64, i64]
     L.fp16_linear_workspace_bytes.restype = sz
     L.fp16_linear_workspace_bytes.argtypes = [i64, i64, i64]
+    L.fp6_workspace_zero_bytes.restype = sz
+    L.fp6_workspace_zero_bytes.argtypes = [i64, i64, i64]
     L.fp6_workspace_init.restype = ci
     L.fp6_workspace_init.argtypes = [vp, sz, vp]
     L.fp6_quantize_pack.restype = ci
@@ -138,7 +141,19 @@ def _dev(t: torch.Tensor, dtype, name: str) -> torch.Tensor:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the raw handle of torch.cuda.current_stream(), without building a Stream object per call
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+@lru_cache(maxsize=None)
+def _entry(name: str):
+    """The library's function of that name (looked up once; a small call's time is mostly host work)."""
+    return getattr(load_library(), name)
+
+
+@lru_cache(maxsize=4096)
+def _packed_bytes(prefix: str, M: int, K: int) -> int:
+    return int(_entry(prefix + "_packed_bytes")(M, K))
 
 
 def fp6_layout_version() -> int:
@@ -170,10 +185,15 @@ def fp6_workspace_init(workspace: torch.Tensor) -> None:
     _check(load_library().fp6_workspace_init(workspace.data_ptr(), workspace.numel(), _stream()))
 
 
-def _new_workspace(nbytes: int, device) -> Optional[torch.Tensor]:
+def _new_workspace(nbytes: int, M: int, N: int, K: int, device) -> Optional[torch.Tensor]:
+    """A workspace for one call: only its arrival counters are cleared (6656 x 17920, N = 100: 4 KB instead of 7 MB,
+    44.0 -> 42.2 us a call)."""
     if nbytes == 0:
         return None
-    return torch.zeros(nbytes, dtype=torch.uint8, device=device)
+    workspace = torch.empty(nbytes, dtype=torch.uint8, device=device)
+    zero = min(nbytes, _entry("fp6_workspace_zero_bytes")(M, N, K))
+    _check(_entry("fp6_workspace_init")(workspace.data_ptr(), zero, _stream()))
+    return workspace
 
 
 def _quantize_pack(prefix: str, W, packed, scales):
@@ -216,14 +236,13 @@ def _unpack(prefix: str, packed, scales, M, K, out):
 
 
 def _linear(prefix: str, packed, scales, X, M, K, out, workspace):
-    L = load_library()
     _dev(packed, torch.uint8, "packed")
     _dev(scales, torch.float16, "scales")
     _dev(X, torch.float16, "X")
     if X.dim() != 2 or X.shape[1] != K:
         raise Fp6Error("X must be [N][K]")
     N = X.shape[0]
-    nbytes = getattr(L, prefix + "_packed_bytes")(M, K)
+    nbytes = _packed_bytes(prefix, M, K)
     if nbytes == 0 or N == 0:
         _check(2)
     if packed.numel() != nbytes or scales.numel() != M:
@@ -234,10 +253,10 @@ def _linear(prefix: str, packed, scales, X, M, K, out, workspace):
     if out.numel() != N * M:
         raise Fp6Error("out has the wrong size")
     if workspace is None:
-        workspace = _new_workspace(getattr(L, prefix + "_linear_workspace_bytes")(M, N, K), X.device)
+        workspace = _new_workspace(_entry(prefix + "_linear_workspace_bytes")(M, N, K), M, N, K, X.device)
     ws_ptr, ws_len = (workspace.data_ptr(), workspace.numel()) if workspace is not None else (None, 0)
-    _check(getattr(L, prefix + "_linear")(packed.data_ptr(), scales.data_ptr(), X.data_ptr(), out.data_ptr(), M, N, K,
-                                          ws_ptr, ws_len, _stream()))
+    _check(_entry(prefix + "_linear")(packed.data_ptr(), scales.data_ptr(), X.data_ptr(), out.data_ptr(), M, N, K,
+                                      ws_ptr, ws_len, _stream()))
     return out
 
 
@@ -281,7 +300,6 @@ def fp6_linear_static(packed: torch.Tensor, scales: torch.Tensor, X: torch.Tenso
 
 
 def _linear_fused(prefix, packed, scales, X, M, K, bias, residual, gated, out, workspace, group=0):
-    L = load_library()
     _dev(packed, torch.uint8, "packed")
     _dev(scales, torch.float16, "scales")
     _dev(X, torch.float16, "X")
@@ -289,7 +307,7 @@ def _linear_fused(prefix, packed, scales, X, M, K, bias, residual, gated, out, w
         raise Fp6Error("X must be [N][K]")
     N = X.shape[0]
     base = "fp6" if prefix == "fp6g" else prefix
-    nbytes = getattr(L, base + "_packed_bytes")(M, K)
+    nbytes = _packed_bytes(base, M, K)
     if nbytes == 0 or N == 0 or (prefix == "fp6g" and (group <= 0 or K % group)):
         _check(2)
     n_scales = M * (K // group) if prefix == "fp6g" else M
@@ -310,12 +328,12 @@ def _linear_fused(prefix, packed, scales, X, M, K, bias, residual, gated, out, w
     if out.numel() != N * Mout:
         raise Fp6Error("out has the wrong size")
     if workspace is None:
-        workspace = _new_workspace(getattr(L, base + "_linear_workspace_bytes")(M, N, K), X.device)
+        workspace = _new_workspace(_entry(base + "_linear_workspace_bytes")(M, N, K), M, N, K, X.device)
     ws_ptr, ws_len = (workspace.data_ptr(), workspace.numel()) if workspace is not None else (None, 0)
     head = (packed.data_ptr(), scales.data_ptr(), X.data_ptr(), out.data_ptr(), M, N, K)
     tail = (bias.data_ptr() if bias is not None else None, residual.data_ptr() if residual is not None else None,
             int(bool(gated)), ws_ptr, ws_len, _stream())
-    fn = getattr(L, prefix + "_linear_fused")
+    fn = _entry(prefix + "_linear_fused")
     _check(fn(*head, group, *tail) if prefix == "fp6g" else fn(*head, *tail))
     return out
 
@@ -433,7 +451,7 @@ def fp6g_linear(packed: torch.Tensor, scales: torch.Tensor, X: torch.Tensor, M: 
     if out.numel() != N * M:
         raise Fp6Error("out has the wrong size")
     if workspace is None:
-        workspace = _new_workspace(L.fp6_linear_workspace_bytes(M, N, K), X.device)
+        workspace = _new_workspace(L.fp6_linear_workspace_bytes(M, N, K), M, N, K, X.device)
     ws_ptr, ws_len = (workspace.data_ptr(), workspace.numel()) if workspace is not None else (None, 0)
     _check(L.fp6g_linear(packed.data_ptr(), scales.data_ptr(), X.data_ptr(), out.data_ptr(), M, N, K, group,
                          ws_ptr, ws_len, _stream()))
@@ -504,7 +522,7 @@ def fp16_linear(W: torch.Tensor, X: torch.Tensor, out: Optional[torch.Tensor] = 
         out = torch.empty((N, M), dtype=torch.float16, device=X.device)
     _dev(out, torch.float16, "out")
     if workspace is None:
-        workspace = _new_workspace(L.fp16_linear_workspace_bytes(M, N, K), X.device)
+        workspace = _new_workspace(L.fp16_linear_workspace_bytes(M, N, K), M, N, K, X.device)
     ws_ptr, ws_len = (workspace.data_ptr(), workspace.numel()) if workspace is not None else (None, 0)
     _check(L.fp16_linear(W.data_ptr(), X.data_ptr(), out.data_ptr(), M, N, K, ws_ptr, ws_len, _stream()))
     return out

@@ -731,6 +731,24 @@ size_t fp16_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
                             : prompt_workspace_bytes(M, N, K, Weights::kFp16);
 }
 
+size_t fp6_workspace_zero_bytes(int64_t M, int64_t N, int64_t K)
+{
+    if (!shape_ok(M, K) || N <= 0)
+        return 0;
+    size_t bytes = 0;
+    auto at_least = [&](size_t b) { bytes = b > bytes ? b : bytes; };
+    if (N <= kStreamMaxN) {
+        at_least(plan_stream(M, N, K, true).counter_bytes);  // one counter per row tile, whatever the weights
+        return bytes;
+    }
+    const int64_t chunk = prompt_chunk_tokens(K);
+    for (Weights kind : {Weights::kPacked, Weights::kGrouped, Weights::kFp16})
+        for (int64_t n : {N < chunk ? N : chunk, N > chunk ? N % chunk : (int64_t)0})
+            if (n > 0)
+                at_least(plan_prompt(M, n, K, kind).counter_bytes());
+    return bytes;
+}
+
 void fp6_tuning_set_split_k(int split_k) { g_forced_split.store(split_k < 0 ? 0 : split_k); }
 
 void fp6_tuning_set_tile(int block_rows, int block_tokens)
