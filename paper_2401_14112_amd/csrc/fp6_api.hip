@@ -335,10 +335,12 @@ double block_cost(const BlockPlan &p, int64_t K, Weights kind)
 }
 
 // Which kernel and block (us, this kernel against the tiled one in the same process):
-//   per-row packed weights: the 256 x 256 block where its tiles nearly fill the chip in no more rounds than the tiled
-//     kernel's 256 x 128 blocks, at 1.08x their rate (6 bits: 57344 x 8192, N = 4096 2774 against 3155; 28672 x 8192,
-//     N = 512 193 against 205; 8192 x 22016, N = 2048 521 against 566) - with fewer tiles it needs split-K where the
-//     smaller block needs less of it or none (8192 x 8192, N = 1024 127 against 110);
+//   per-row packed weights: the 256 x 256 block, at up to 1.17x the rate of the tiled kernel's 256 x 128 one, where its
+//     rounds of 256 blocks and its padded tokens take at most 1.1x what that block's do - which also says that it
+//     needs no split-K (57344 x 8192, N = 4096 2657 against 3106; 28672 x 8192, N = 3000 1110 against 1167; 9216 x
+//     9216, N = 1024, 144 tiles in one round against 288 in two, 172 against 206 with 6 bits, 162 against 188 with 4,
+//     202 against 219 with 5).  Beyond that it loses: 8192 x 8192, N = 1024 127 against 110, 28672 x 8192, N = 700
+//     344 against 294, 57344 x 4096, N = 300 175 against 155;
 //   group scales: always, except few rows and few tokens (8192 x 8192, N = 100: 31 against 30; 4096 x 4096 17 against
 //     13; but 28672 x 8192, N = 201 120 against 166, 16384 x 8192, N = 2048 497 against 740);
 //   fp16 weights: always (9216 x 9216, N = 256 84 against 163; 16384 x 8192, N = 2048 473 against 1176; 8192 x 8192,
@@ -367,7 +369,7 @@ PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind)
     if (kind == Weights::kPacked) {
         const int64_t tiles = row_blocks * ((N + 255) / 256), halves = row_blocks * ((N + 127) / 128);
         const int64_t rounds = (tiles + kCus - 1) / kCus, half_rounds = (halves + kCus - 1) / kCus;
-        if (tiles >= 192 && 2 * rounds * 100 <= half_rounds * 108)
+        if (20 * rounds <= 11 * half_rounds && 20 * tiles <= 11 * halves)
             p.block = block_plan_of(kBlock256x256, M, N, K);
         return p;
     }
