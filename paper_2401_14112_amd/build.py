@@ -37,7 +37,7 @@ def build_library(verbose: bool = False, extra_flags=()) -> Path:
     ]
     if verbose:
         print(" ".join(cmd), flush=True)
-    # the device assembly of the same sources, compiled alongside, for the check of the hand-issued loads
+    # the device assembly of the same sources, compiled alongside, for the checks of the hand-issued loads and copies
     asm_file = tempfile.NamedTemporaryFile(suffix=".s", delete=False)
     asm_file.close()
     asm_cmd = [c for c in cmd if c not in ("-shared", "-fPIC", "-Rpass-analysis=kernel-resource-usage")]
@@ -55,7 +55,9 @@ def build_library(verbose: bool = False, extra_flags=()) -> Path:
             raise RuntimeError("hipcc -S failed:\n" + asm_out)
         check_no_scratch(lines)
         with open(asm_file.name) as f:
-            check_loads_in_flight(f.read())
+            asm = f.read()
+        check_loads_in_flight(asm)
+        check_slot_refills(asm)
     finally:
         if asm_proc.poll() is None:
             asm_proc.kill()
@@ -162,6 +164,72 @@ def check_loads_in_flight(asm: str) -> None:
         kernel, number, line, what = problems[0]
         raise RuntimeError("%d instruction(s) touch a register with a load in flight, first in %s, line %d of the "
                            "generated assembly: `%s` (load: %s)" % (len(problems), kernel, number, line, what))
+
+
+_REFILL = "slot refill"  # the comment that linear_block.hpp leaves on copies into a weight slot
+
+
+def slot_refill_problems(asm: str) -> list:
+    """LDS reads in flight at the barrier that opens a stage in which a weight slot is requested again.  The block kernel
+    refills a slot in the stage after its last read, and its barrier does not wait for reads: a wave may pass it with
+    reads outstanding, and the copy of a faster wave could overwrite what they are about to fetch.  Every path through
+    every kernel with marked copies is followed: reads (and other requests of the counter) are outstanding until an
+    `s_waitcnt lgkmcnt(n)` leaves at most n of them, in order.  Returns (kernel, line of the read, line of the barrier,
+    line of the copy)."""
+    problems = []
+    kernel, code, labels = None, [], {}
+
+    def walk():
+        found, seen, todo = set(), set(), [(0, (), 0, ())]
+        while todo:
+            state = todo.pop()
+            if state in seen or state[0] >= len(code):
+                continue
+            seen.add(state)
+            i, queue, barrier, crossing = state
+            number, line, op, refill = code[i]
+            if op == "s_waitcnt":
+                m = re.search(r"lgkmcnt\((\d+)\)", line)
+                if m:
+                    queue = queue[max(0, len(queue) - int(m.group(1))):]
+            elif op.startswith(("ds_", "s_load", "s_buffer_load")):
+                queue = (queue + (number if op.startswith("ds_read") else 0,))[-16:]  # the counter has four bits
+            elif op == "s_barrier":
+                barrier, crossing = number, tuple(r for r in queue if r)
+            elif refill:
+                found.update((read, barrier, number) for read in crossing)
+            if op in ("s_endpgm", "s_setpc_b64"):
+                continue
+            target = labels.get(line.split()[-1]) if op.startswith(("s_branch", "s_cbranch")) else None
+            if target is not None:
+                todo.append((target, queue, barrier, crossing))
+            if op != "s_branch":
+                todo.append((i + 1, queue, barrier, crossing))
+        problems.extend((kernel,) + f for f in sorted(found))
+
+    for number, raw in enumerate(asm.splitlines(), 1):
+        line = raw.split(";")[0].strip()
+        if not line:
+            continue
+        if _LABEL.match(line):
+            if line.startswith(".L"):
+                labels[line[:-1]] = len(code)
+                continue
+            if any(refill for *_, refill in code):
+                walk()
+            kernel, code, labels = line[:-1], [], {}
+        elif not line.startswith("."):
+            code.append((number, line, line.split()[0], _REFILL in raw))
+    if any(refill for *_, refill in code):
+        walk()
+    return problems
+
+
+def check_slot_refills(asm: str) -> None:
+    problems = slot_refill_problems(asm)
+    if problems:
+        raise RuntimeError("%d LDS read(s) in flight at a barrier before the refill of a weight slot, first in %s: read in line %d "
+                           "of the generated assembly, barrier %d, copy %d" % (len(problems), *problems[0]))
 
 
 def is_stale() -> bool:

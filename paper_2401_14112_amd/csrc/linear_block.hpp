@@ -207,11 +207,14 @@ struct BlockShape {
     }
     // run during which the planes that a wave's pair l needs first are read from LDS (of the k-tile before for l = 0)
     static constexpr int read_run(int l) { return (2 * l + RUNS - (ADB ? 2 : 1)) % RUNS; }
-    // stage of a k-tile in which the slot of plane p is requested again: the one after its last read
+    // stage, counted from the k-tile's first, in which those reads are issued (-1: the last stage of the k-tile before)
+    static constexpr int read_stage(int l) { return l == 0 ? -1 : read_run(l) / SR; }
+    // stage of a k-tile in which the slot of plane p is requested again: the one after its last read is issued.  The
+    // barrier that opens such a stage comes after a wait for the wave's LDS reads, see block_barrier().
     template <class Src>
     static constexpr int request_stage(int p)
     {
-        return need_max<Src>(p) == 0 ? 0 : read_run(need_max<Src>(p)) / SR + 1;
+        return read_stage(need_max<Src>(p)) + 1;
     }
     // weight and scale copies one wave requests in stage s of a k-tile
     template <class Src>
@@ -251,17 +254,42 @@ struct BlockShape {
         }
         return true;
     }
+    // no plane is requested again in or before the stage in which a wave of some k group issues its reads of it (group
+    // scales are read with the planes of pair 0 and requested in stage 0)
+    template <class Src>
+    static constexpr bool planes_released()
+    {
+        for (int p = 0; p < Src::kPlanes; ++p)
+            for (int k = 0; k < WK; ++k)
+                if (need<Src>(p, k) >= 0 && read_stage(need<Src>(p, k)) >= request_stage<Src>(p))
+                    return false;
+        return !Src::kGroupScales || read_stage(0) < 0;
+    }
 };
 
+// Copies into the LDS slot of a weight plane or of group scales.  The comment in the statement marks them in the
+// generated assembly, where the build looks for LDS reads in flight at the barrier before them.
 template <int IMM>
-__device__ __forceinline__ void issue_load_to_lds_b32(rsrc_t rsrc, int lane_off, uint32_t lds_base)
+__device__ __forceinline__ void issue_refill_b128(rsrc_t rsrc, int lane_off, uint32_t lds_base)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen offset:%3 lds"
+    static_assert(IMM >= 0 && IMM < 4096, "the immediate offset of a buffer load is a 12-bit field");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen offset:%3 lds ; slot refill"
                  : : "s"(lds_base), "v"(lane_off), "s"(rsrc), "n"(IMM) : "memory");
 }
 
-// A bare barrier: the reads in flight across it are of LDS that nobody is about to overwrite (__syncthreads would wait
-// for them).  Everything before it in the program, the matrix instructions that consumed earlier reads included, stays
+__device__ __forceinline__ void issue_refill_b32(rsrc_t rsrc, int lane_off, uint32_t lds_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen offset:0 lds ; slot refill"
+                 : : "s"(lds_base), "v"(lane_off), "s"(rsrc) : "memory");
+}
+
+// A bare barrier: unlike __syncthreads it does not wait for LDS reads.  Those in flight across it are activation (and
+// fp16 weight) fragments of the stage that it opens, whose slots nobody requests again before the next barrier.  Where
+// the stage requests a weight slot again, the wave first waits for its LDS reads (wait_lds_reads): the words that other
+// waves' copies are about to overwrite have then arrived.  (57344 x 8192, N = 4096, 6 bits: 2717 us with that wait, 2719
+// with one for the reads of planes alone; requests one stage later, after the conversions, take the same time and spill
+// with 5 bits.)
+// Everything before the barrier in the program, the matrix instructions that consumed earlier reads included, stays
 // before it.
 __device__ __forceinline__ void block_barrier()
 {
@@ -271,6 +299,8 @@ __device__ __forceinline__ void block_barrier()
     asm volatile("" : : : "memory");
     __builtin_amdgcn_sched_barrier(0);
 }
+
+__device__ __forceinline__ void wait_lds_reads() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
 
 template <class Src, class Shape>
 __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
@@ -289,6 +319,7 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     static_assert(SR * WK * BN / 16 % WAVES == 0 && (!Src::kRunStaged || SR * WK * BM / 16 % WAVES == 0),
                   "copies of a stage must split evenly over the waves");
     static_assert(Shape::template planes_land<Src>(), "a weight plane could be read before it has landed");
+    static_assert(Shape::template planes_released<Src>(), "a weight plane could be overwritten before its reads have returned");
     static_assert(XST >= 3 && XST - 3 <= NST && RUNS % SR == 0, "bad stage");
     static_assert(!Src::kGroupScales || XST <= (RUNS * WD - (ADB ? 2 : 1)) / SR + 2, "group scales could be read before they have landed");
     static_assert(RT % 2 == 0, "pieces are converted two at a time");
@@ -407,12 +438,12 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
             if constexpr (Src::plane_bytes(p) == 1024) {
                 const int tile = (wave + WAVES * i) % (BM / 16);
                 const int half = Src::kHalfTiles && p == 0 ? ((split + t * S) & 1) * 2048 : 0;
-                issue_load_to_lds_b128<p * 1024>(w_rsrc, w_off[i < PC ? i : 0] + w_at(t) + half,
-                                                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + dst + wslot + tile * 1024)));
+                issue_refill_b128<p * 1024>(w_rsrc, w_off[i < PC ? i : 0] + w_at(t) + half,
+                                            (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + dst + wslot + tile * 1024)));
             } else {
                 const int c = (wave + WAVES * i) % (BM / 32);
-                issue_load_to_lds_b128<p * 1024>(w_rsrc, w_half_off[i < HC ? i : 0] + w_at(t),
-                                                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + dst + wslot + c * 1024)));
+                issue_refill_b128<p * 1024>(w_rsrc, w_half_off[i < HC ? i : 0] + w_at(t),
+                                            (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + dst + wslot + c * 1024)));
             }
         }
     };
@@ -429,8 +460,8 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     }
     auto s_issue = [&](int t, int wslot) {
         if constexpr (Src::kGroupScales)
-            issue_load_to_lds_b32<0>(s_rsrc, s_off + (t < n_valid ? t * S * 4 : 0),
-                                     (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + SCALES + wslot + wave % (BM / 64) * 256)));
+            issue_refill_b32(s_rsrc, s_off + (t < n_valid ? t * S * 4 : 0),
+                             (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + SCALES + wslot + wave % (BM / 64) * 256)));
     };
 
     // ---- LDS reads
@@ -548,6 +579,8 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
                         wait_loads<(XST - 3) * XCOPIES>();
                     else
                         wait_loads<Shape::template copies_after<Src>(stage)>();
+                    if constexpr (Shape::template stage_w_copies<Src>(stage) > 0)
+                        wait_lds_reads();
                     block_barrier();
                 }
                 const int next_slot = slot + WK * SLOT == RING ? 0 : slot + WK * SLOT;

@@ -1,5 +1,9 @@
-"""The build's two checks of the hand-issued loads (CPU only): no kernel may spill, and in the generated
-assembly no instruction may name a register that still has a load in flight."""
+"""The build's checks of the hand-issued loads and copies (CPU only): no kernel may spill, in the generated assembly
+no instruction may name a register that still has a load in flight, and no wave may reach the barrier before the refill
+of a weight slot with LDS reads outstanding."""
+import re
+import subprocess
+
 import pytest
 
 from paper_2401_14112_amd import build
@@ -95,3 +99,41 @@ def test_scratch_is_refused():
     build.check_no_scratch(ok)
     with pytest.raises(RuntimeError, match="spills 16 bytes"):
         build.check_no_scratch([ok[0], ok[1].replace(": 0", ": 16")])
+
+
+REFILL = "buffer_load_dwordx4 v9, s[8:11], 0 offen offset:0x400 lds ; slot refill\n"
+
+
+def test_read_in_flight_at_the_barrier_of_a_refill_is_reported():
+    stage = "ds_read_b128 v[0:3], v9 offset:1024\n ds_read_b128 v[4:7], v8\n %s\n s_barrier\n s_waitcnt lgkmcnt(0)\n"
+    late = build.slot_refill_problems(KERNEL + stage % "s_waitcnt lgkmcnt(1)" + REFILL)
+    assert late == [("_Z6kernelv", 3, 5, 7)]
+    with pytest.raises(RuntimeError, match="refill of a weight slot"):
+        build.check_slot_refills(KERNEL + stage % "s_nop 0" + REFILL)
+    assert build.slot_refill_problems(KERNEL + stage % "s_waitcnt lgkmcnt(0)" + REFILL) == []
+    # copies of activations, and stages without a refill, may cross with reads outstanding
+    assert build.slot_refill_problems(KERNEL + stage % "s_nop 0" + REFILL.split(";")[0]) == []
+    assert build.slot_refill_problems(KERNEL + stage % "s_nop 0" + "s_barrier\n" + REFILL) == []
+
+
+def test_read_in_flight_around_a_loop_is_reported():
+    # the refill comes first in the body, the read last: they meet through the back edge only
+    body = ".LBB0_1:\n %%s\n s_barrier\n %s ds_read_b128 v[0:3], v9\n s_cbranch_scc1 .LBB0_1\n s_endpgm\n" % REFILL
+    assert len(build.slot_refill_problems(KERNEL + body % "s_waitcnt vmcnt(0)")) == 1
+    assert build.slot_refill_problems(KERNEL + body % "s_waitcnt vmcnt(0) lgkmcnt(0)") == []
+
+
+@pytest.mark.parametrize("source,index", [("BlockFp6Source", 0), ("BlockFp6GroupSource", 1), ("BlockFp6GroupSource", 2)])
+def test_block_kernels_wait_for_their_reads_before_a_refill(tmp_path, source, index):
+    """The shapes of the library, compiled for themselves.  (Every build checks all of its kernels the same way.)"""
+    text = (build.CSRC / "fp6_api.hip").read_text()
+    shape = re.search(r"BlockShapeOf<false, %d> \{ typedef (BlockShape<[^>]*>)" % index, text).group(1)
+    (tmp_path / "one.hip").write_text(
+        '#include "linear_block.hpp"\nnamespace fp6 {\ntemplate __global__ void linear_block_kernel<%s, %s>(const void *, const half_t *, '
+        'const half_t *, half_t *, int, int, int, int, int, int, int, float4_t *, int *, Epilogue);\n}\n' % (source, shape))
+    subprocess.run([build.hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "--cuda-device-only", "-S", "-w",
+                    "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-I", str(build.CSRC),
+                    str(tmp_path / "one.hip"), "-o", str(tmp_path / "one.s")], check=True)
+    asm = (tmp_path / "one.s").read_text()
+    assert "s_barrier" in asm and asm.count("slot refill") >= 8    # the prologue's copies and the loop's
+    assert build.slot_refill_problems(asm) == []
