@@ -91,19 +91,22 @@ fp6_status fp6_unpack(const void *packed, const void *scales_f16, int64_t M, int
 
 /*
  * Workspace needed by fp6_linear / fp16_linear for this shape (0 when the
- * kernel chosen for it needs none).  The workspace holds split-K partial sums and
- * arrival counters.  It MUST be zero-filled once before its first use
- * (fp6_workspace_init or any device memset); the kernels leave the counters at
- * zero, so it can be reused by later calls without clearing it again.  Two calls
- * that may run concurrently (different streams) need different workspaces.
+ * kernel chosen for it needs none).  The workspace holds arrival counters, in its
+ * first fp6_workspace_zero_bytes(), and behind them split-K partial sums.  It MUST be
+ * zero-filled once before its first use (fp6_workspace_init or any device memset; the
+ * counters are enough); the kernels leave the counters at zero, so it can be reused by
+ * later calls without clearing it again: calls of any shape and any weight format of
+ * this library, as long as it has the size that the query gives for each of them.  Two
+ * calls that may run concurrently (different streams) need different workspaces.
+ * Sizes belong to the loaded library: ask for them, they change from version to version.
  */
 size_t fp6_linear_workspace_bytes(int64_t M, int64_t N, int64_t K);
 size_t fp16_linear_workspace_bytes(int64_t M, int64_t N, int64_t K);
 
 /*
- * Bytes at the start of a workspace that have to be zero before its first use: the arrival counters of every call in
- * this library for the shape (a multiple of 256; the whole workspace may be smaller).  The partial sums behind them
- * may hold anything, so a caller that makes a workspace for one call need not clear all of it.
+ * Bytes at the start of a workspace that have to be zero before its first use: the arrival counters (4096 for every
+ * supported shape; more only where a tuning hook forces the split; the whole workspace may be smaller, or none).  The
+ * partial sums behind them may hold anything, so a caller that makes a workspace for one call need not clear all of it.
  */
 size_t fp6_workspace_zero_bytes(int64_t M, int64_t N, int64_t K);
 

@@ -46,6 +46,23 @@ void fp6_tuning_set_split_k(int split_k);
  */
 void fp6_tuning_set_tile(int block_rows, int block_tokens);
 
+/*
+ * What a call would launch for the tokens around `token` (a call whose activations exceed 2 GiB is cut into launches
+ * that are planned one by one), under the tuning hooks in force.  Host arithmetic only.  weight_bits: 6, 5, 4, 3,
+ * -6 (fp6g_linear) or 16 (fp16_linear).
+ */
+enum { FP6_KERNEL_STREAM = 0, FP6_KERNEL_TILED = 1, FP6_KERNEL_BLOCK = 2 };
+typedef struct {
+    int kernel;                    /* FP6_KERNEL_* */
+    int block_rows, block_tokens;  /* output piece of a workgroup */
+    int split_k;                   /* k slices */
+    int64_t first_token, tokens;   /* of the launch */
+    size_t counter_bytes;          /* arrival counters, at the start of the workspace (0 without k slices) */
+    size_t partial_offset;         /* where its partial sums start ... */
+    size_t partial_bytes;          /* ... and their size (0 without k slices) */
+} fp6_launch_plan;
+fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, fp6_launch_plan *plan);
+
 #ifdef __cplusplus
 }
 #endif

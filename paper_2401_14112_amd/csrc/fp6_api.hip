@@ -57,10 +57,13 @@ bool packed_shape_ok(int64_t M, int64_t K)
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Where a launch keeps its split-K state: arrival counters (zero before and after every launch) and the
-// partial tiles.  A caller's workspace holds the counters first and the partial tiles right behind them, so
-// the split depends on the plan; the library's own static buffer (fp6_linear_static) keeps the counters in a
-// fixed region at its start, so that the partial tiles of one call can never be read as counters by the next.
-constexpr size_t kStaticCounterBytes = 64 * 1024;
+// partial tiles.  Both kinds of buffer hold the counters in a region of fixed size at their start, whatever the
+// plan, so that the partial tiles of one launch can never be read as counters by another: the launches of one call
+// (a call cut into chunks plans each of them for itself) and calls of other shapes and weights that share a workspace.
+// Every automatic plan with k slices has at most 128 blocks of at most eight waves, and one counter per wave or row
+// tile: 4 KB hold them.  Only a forced split factor needs more.
+constexpr size_t kCounterBytes = 4 * 1024;
+constexpr size_t kStaticCounterBytes = 64 * 1024;  // the library's static buffer (fp6_linear_static)
 
 struct SplitBuffers {
     int *counters;
@@ -70,7 +73,7 @@ struct SplitBuffers {
 struct WorkspaceRef {
     void *base;
     size_t bytes;
-    bool fixed_regions;  // the library's static buffer
+    size_t counter_region;  // its first bytes: kStaticCounterBytes or counter_region_bytes()
     // the buffers of a launch whose plan needs counter_bytes + partial_bytes; FP6_OK when they fit
     fp6_status view(size_t counter_bytes, size_t partial_bytes, SplitBuffers &out) const
     {
@@ -78,13 +81,12 @@ struct WorkspaceRef {
         out.partials = nullptr;
         if (partial_bytes == 0)
             return FP6_OK;  // no split-K: nothing is touched
-        const size_t head = fixed_regions ? kStaticCounterBytes : counter_bytes;
-        if (!base || counter_bytes > head || bytes < head || bytes - head < partial_bytes)
+        if (!base || counter_bytes > counter_region || bytes < counter_region || bytes - counter_region < partial_bytes)
             return FP6_ERR_WORKSPACE;
         if (!aligned16(base))
             return FP6_ERR_ALIGN;
         out.counters = static_cast<int *>(base);
-        out.partials = static_cast<uint8_t *>(base) + head;
+        out.partials = static_cast<uint8_t *>(base) + counter_region;
         return FP6_OK;
     }
 };
@@ -94,9 +96,7 @@ struct StreamPlan {
     int nt;          // 16-token tiles handled per launch
     int split;       // split-K factor
     int row_blocks;  // blocks along M
-    size_t counter_bytes;
-    size_t partial_bytes;
-    size_t total_bytes() const { return split > 1 ? counter_bytes + partial_bytes : 0; }
+    size_t counter_bytes, partial_bytes;  // 0 without k slices
 };
 
 // The layer is bound by memory, every block streams the same number of bytes, and one block per CU is
@@ -159,8 +159,11 @@ StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, bool packed, int tile_co
     p.nt = table[best].nt;
     p.split = (int)best_s;
     p.row_blocks = (int)((row_tiles + table[best].waves - 1) / table[best].waves);
-    p.counter_bytes = (((size_t)row_tiles * sizeof(int)) + 255) / 256 * 256;  // one arrival counter per row tile
-    p.partial_bytes = (size_t)p.split * (size_t)row_tiles * (size_t)p.nt * 64 * sizeof(float4_t);
+    p.counter_bytes = p.partial_bytes = 0;
+    if (p.split > 1) {
+        p.counter_bytes = (((size_t)row_tiles * sizeof(int)) + 255) / 256 * 256;  // one arrival counter per row tile
+        p.partial_bytes = (size_t)p.split * (size_t)row_tiles * (size_t)p.nt * 64 * sizeof(float4_t);
+    }
     return p;
 }
 
@@ -232,8 +235,7 @@ struct BlockPlan {
     int cfg;  // -1: the tiled kernel instead
     int split;
     int row_blocks, n_blocks, chunk;  // chunk: (row block, k slice) units per XCD
-    size_t counter_bytes, partial_bytes;
-    size_t total_bytes() const { return split > 1 ? counter_bytes + partial_bytes : 0; }
+    size_t counter_bytes, partial_bytes;  // 0 without k slices
 };
 
 enum class Weights { kPacked, kGrouped, kFp16 };
@@ -260,9 +262,12 @@ BlockPlan block_plan_of(int cfg, int64_t M, int64_t N, int64_t K)
     s = s > 16 ? 16 : s;
     p.split = (int)(s < 1 ? 1 : s);
     p.chunk = (int)(((int64_t)p.row_blocks * p.split + 7) / 8);
-    const size_t tiles = (size_t)p.row_blocks * p.n_blocks;
-    p.counter_bytes = (tiles * kBlockWaves * sizeof(int) + 255) / 256 * 256;  // one arrival counter per wave tile
-    p.partial_bytes = (size_t)p.split * tiles * b.rows * b.tokens * sizeof(float);
+    p.counter_bytes = p.partial_bytes = 0;
+    if (p.split > 1) {
+        const size_t tiles = (size_t)p.row_blocks * p.n_blocks;
+        p.counter_bytes = (tiles * kBlockWaves * sizeof(int) + 255) / 256 * 256;  // one arrival counter per wave tile
+        p.partial_bytes = (size_t)p.split * tiles * b.rows * b.tokens * sizeof(float);
+    }
     return p;
 }
 
@@ -270,9 +275,8 @@ struct TiledPlan {
     TileShape tile;
     int split;
     int row_blocks, n_blocks;
-    size_t counter_bytes, partial_bytes;
+    size_t counter_bytes, partial_bytes;  // 0 without k slices
     size_t lds_bytes;
-    size_t total_bytes() const { return split > 1 ? counter_bytes + partial_bytes : 0; }
 };
 
 // smallest: only the 128 x 64 block (weights with group scales)
@@ -305,8 +309,12 @@ TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, bool smallest)
         s = 1;
     p.split = (int)s;
     const int bnt = p.tile.nt * p.tile.wn;
-    p.counter_bytes = ((size_t)p.row_blocks * p.n_blocks * p.tile.wm * p.tile.wn * sizeof(int) + 255) / 256 * 256;  // one arrival counter per wave tile
-    p.partial_bytes = (size_t)p.split * (size_t)row_tiles * (size_t)p.n_blocks * bnt * 64 * sizeof(float4_t);
+    p.counter_bytes = p.partial_bytes = 0;
+    if (p.split > 1) {
+        // one arrival counter per wave tile
+        p.counter_bytes = ((size_t)p.row_blocks * p.n_blocks * p.tile.wm * p.tile.wn * sizeof(int) + 255) / 256 * 256;
+        p.partial_bytes = (size_t)p.split * (size_t)row_tiles * (size_t)p.n_blocks * bnt * 64 * sizeof(float4_t);
+    }
     p.lds_bytes = (size_t)4 * bnt * 256 * 16;  // the kernel's ring of four half tiles of activations
     return p;
 }
@@ -318,8 +326,7 @@ struct PromptPlan {
     bool is_block() const { return block.cfg >= 0; }
     int split() const { return is_block() ? block.split : tiled.split; }
     size_t counter_bytes() const { return is_block() ? block.counter_bytes : tiled.counter_bytes; }
-    size_t partial_bytes() const { return split() > 1 ? (is_block() ? block.partial_bytes : tiled.partial_bytes) : 0; }
-    size_t total_bytes() const { return split() > 1 ? counter_bytes() + partial_bytes() : 0; }
+    size_t partial_bytes() const { return is_block() ? block.partial_bytes : tiled.partial_bytes; }
 };
 
 // Estimated time of a block plan, ns: rounds of 256 blocks at the measured cost per run, a fixed part per round, and for
@@ -436,22 +443,60 @@ int64_t prompt_chunk_tokens(int64_t K)
     return fit >= 128 ? fit / 128 * 128 : fit;  // shape_ok() admits K < 2^24 only: at least 64 tokens fit
 }
 
-// Workspace of a prompt-sized call: the largest over the chunks a call is cut into (the last, shorter chunk may
-// use more k slices than the full ones).
-size_t prompt_workspace_bytes(int64_t M, int64_t N, int64_t K, Weights kind)
+// Token counts of the launches that a prompt-sized call is cut into: the full chunk and the shorter last one (0: none).
+struct PromptChunks {
+    int64_t n[2];
+    const int64_t *begin() const { return n; }
+    const int64_t *end() const { return n + 2; }
+};
+PromptChunks prompt_chunks(int64_t N, int64_t K)
 {
     const int64_t chunk = prompt_chunk_tokens(K);
-    if (chunk <= 0)
-        return 0;
-    if (N <= chunk)
-        return plan_prompt(M, N, K, kind).total_bytes();
-    size_t bytes = plan_prompt(M, chunk, K, kind).total_bytes();
-    const int64_t last = N % chunk;
-    if (last > 0) {
-        const size_t b = plan_prompt(M, last, K, kind).total_bytes();
-        bytes = b > bytes ? b : bytes;
+    return {{N < chunk ? N : chunk, N > chunk ? N % chunk : (int64_t)0}};
+}
+
+// Bytes at the start of a caller's workspace that hold arrival counters: the same for every shape, and with a forced
+// split factor for every weight format of the shape.
+size_t counter_region_bytes(int64_t M, int64_t N, int64_t K)
+{
+    size_t bytes = kCounterBytes;
+    if (g_forced_split.load(std::memory_order_relaxed) <= 0)
+        return bytes;
+    auto at_least = [&](size_t b) { bytes = b > bytes ? b : bytes; };
+    if (N <= kStreamMaxN) {
+        at_least(plan_stream(M, N, K, true).counter_bytes);
+        at_least(plan_stream(M, N, K, true, PackedFp3Source::StreamSource::kTileCols).counter_bytes);
+        at_least(plan_stream(M, N, K, false).counter_bytes);
+        return bytes;
     }
+    for (Weights kind : {Weights::kPacked, Weights::kGrouped, Weights::kFp16})
+        for (int64_t n : prompt_chunks(N, K))
+            if (n > 0)
+                at_least(plan_prompt(M, n, K, kind).counter_bytes());
     return bytes;
+}
+
+// Workspace of a call: the counters and the most partial tiles that one of its launches has (the last, shorter chunk of
+// a prompt may use more k slices than the full ones).
+size_t split_workspace_bytes(size_t partial_bytes, int64_t M, int64_t N, int64_t K)
+{
+    return partial_bytes > 0 ? counter_region_bytes(M, N, K) + partial_bytes : 0;
+}
+
+size_t stream_workspace_bytes(int64_t M, int64_t N, int64_t K, bool packed, int tile_cols = kTileK)
+{
+    return split_workspace_bytes(plan_stream(M, N, K, packed, tile_cols).partial_bytes, M, N, K);
+}
+
+size_t prompt_workspace_bytes(int64_t M, int64_t N, int64_t K, Weights kind)
+{
+    size_t partial_bytes = 0;
+    for (int64_t n : prompt_chunks(N, K))
+        if (n > 0) {
+            const size_t b = plan_prompt(M, n, K, kind).partial_bytes();
+            partial_bytes = b > partial_bytes ? b : partial_bytes;
+        }
+    return split_workspace_bytes(partial_bytes, M, N, K);
 }
 
 template <class Src>
@@ -507,8 +552,8 @@ fp6_status launch_prompt(const void *weights, const void *scales, const void *X,
     const int64_t chunk = prompt_chunk_tokens(K);
     if (chunk <= 0)
         return FP6_ERR_SHAPE;  // one token's activations exceed a 32-bit byte offset
-    // every chunk's plan must fit before anything is launched (a full chunk and the shorter last one)
-    for (int64_t n : {N < chunk ? N : chunk, N > chunk ? N % chunk : (int64_t)0}) {
+    // every chunk's plan must fit before anything is launched
+    for (int64_t n : prompt_chunks(N, K)) {
         if (n <= 0)
             continue;
         const PromptPlan p = plan_prompt(M, n, K, weights_of<Src>());
@@ -572,7 +617,7 @@ fp6_status launch_stream(const void *weights, const void *scales, const void *X,
 {
     const StreamPlan p = plan_stream(M, N, K, Src::kPackedConfigs, Src::kTileCols);
     SplitBuffers buf;
-    const fp6_status fits = workspace.view(p.counter_bytes, p.split > 1 ? p.partial_bytes : 0, buf);
+    const fp6_status fits = workspace.view(p.counter_bytes, p.partial_bytes, buf);
     if (fits != FP6_OK)
         return fits;
     int *counters = buf.counters;
@@ -649,23 +694,19 @@ fp6_status static_scratch_address(void **out)
 // the call does not fit it.  Host arithmetic only.
 fp6_status static_plan(int64_t M, int64_t N, int64_t K, size_t &counter_bytes)
 {
-    const WorkspaceRef probe{reinterpret_cast<void *>(uintptr_t(256)), FP6_STATIC_SCRATCH_BYTES, true};  // never dereferenced
+    const WorkspaceRef probe{reinterpret_cast<void *>(uintptr_t(256)), FP6_STATIC_SCRATCH_BYTES, kStaticCounterBytes};  // never dereferenced
     SplitBuffers unused;
     counter_bytes = 0;
     if (N <= kStreamMaxN) {
         const StreamPlan p = plan_stream(M, N, K, true);
-        if (p.split > 1)
-            counter_bytes = p.counter_bytes;
-        return probe.view(p.counter_bytes, p.split > 1 ? p.partial_bytes : 0, unused);
+        counter_bytes = p.counter_bytes;
+        return probe.view(p.counter_bytes, p.partial_bytes, unused);
     }
-    const int64_t chunk = prompt_chunk_tokens(K);
-    if (chunk <= 0)
-        return FP6_ERR_SHAPE;
-    for (int64_t n : {N < chunk ? N : chunk, N > chunk ? N % chunk : (int64_t)0}) {
+    for (int64_t n : prompt_chunks(N, K)) {
         if (n <= 0)
             continue;
         const PromptPlan p = plan_prompt(M, n, K, Weights::kPacked);
-        if (p.split() > 1 && p.counter_bytes() > counter_bytes)
+        if (p.counter_bytes() > counter_bytes)
             counter_bytes = p.counter_bytes();
         const fp6_status fits = probe.view(p.counter_bytes(), p.partial_bytes(), unused);
         if (fits != FP6_OK)
@@ -679,7 +720,6 @@ fp6_status packed_linear_impl(const void *packed, const void *scales_f16, const 
                               int64_t N, int64_t K, void *workspace, size_t workspace_bytes, void *stream,
                               const Epilogue &epi = Epilogue{nullptr, nullptr, 0}, bool static_buffer = false)
 {
-    const WorkspaceRef ws{workspace, workspace_bytes, static_buffer};
     if (!packed || !scales_f16 || !X_f16 || !Y_f16)
         return FP6_ERR_NULL;
     if (!packed_shape_ok(M, K) || N <= 0 || N >= (1ll << 31))
@@ -687,6 +727,7 @@ fp6_status packed_linear_impl(const void *packed, const void *scales_f16, const 
     if (!aligned16(packed) || !aligned16(scales_f16) || !aligned16(X_f16) || !aligned16(Y_f16) || !aligned16(epi.bias)
         || !aligned16(epi.residual))
         return FP6_ERR_ALIGN;
+    const WorkspaceRef ws{workspace, workspace_bytes, static_buffer ? kStaticCounterBytes : counter_region_bytes(M, N, K)};
     if (N > kStreamMaxN)
         return launch_prompt<Src>(packed, scales_f16, X_f16, Y_f16, M, N, K, ws, epi, static_cast<hipStream_t>(stream));
     return launch_stream<typename Src::StreamSource>(packed, scales_f16, X_f16, Y_f16, M, N, K, ws, epi,
@@ -719,7 +760,7 @@ size_t fp6_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
     if (!packed_shape_ok(M, K) || N <= 0)
         return 0;
     if (N <= kStreamMaxN)
-        return plan_stream(M, N, K, true).total_bytes();
+        return stream_workspace_bytes(M, N, K, true);
     // fp6g_linear asks here too
     const size_t bytes = prompt_workspace_bytes(M, N, K, Weights::kPacked), grouped = prompt_workspace_bytes(M, N, K, Weights::kGrouped);
     return bytes > grouped ? bytes : grouped;
@@ -729,26 +770,13 @@ size_t fp16_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
     if (!shape_ok(M, K) || N <= 0)
         return 0;
-    return N <= kStreamMaxN ? plan_stream(M, N, K, false).total_bytes()
+    return N <= kStreamMaxN ? stream_workspace_bytes(M, N, K, false)
                             : prompt_workspace_bytes(M, N, K, Weights::kFp16);
 }
 
 size_t fp6_workspace_zero_bytes(int64_t M, int64_t N, int64_t K)
 {
-    if (!shape_ok(M, K) || N <= 0)
-        return 0;
-    size_t bytes = 0;
-    auto at_least = [&](size_t b) { bytes = b > bytes ? b : bytes; };
-    if (N <= kStreamMaxN) {
-        at_least(plan_stream(M, N, K, true).counter_bytes);  // one counter per row tile, whatever the weights
-        return bytes;
-    }
-    const int64_t chunk = prompt_chunk_tokens(K);
-    for (Weights kind : {Weights::kPacked, Weights::kGrouped, Weights::kFp16})
-        for (int64_t n : {N < chunk ? N : chunk, N > chunk ? N % chunk : (int64_t)0})
-            if (n > 0)
-                at_least(plan_prompt(M, n, K, kind).counter_bytes());
-    return bytes;
+    return shape_ok(M, K) && N > 0 ? counter_region_bytes(M, N, K) : 0;
 }
 
 void fp6_tuning_set_split_k(int split_k) { g_forced_split.store(split_k < 0 ? 0 : split_k); }
@@ -758,6 +786,29 @@ void fp6_tuning_set_tile(int block_rows, int block_tokens)
     const bool known = ((block_rows == 128 || block_rows == 256) && (block_tokens == 64 || block_tokens == 128))
                        || (block_rows == 256 && block_tokens == 256);
     g_forced_tile.store(known ? block_rows * 1024 + block_tokens : 0);
+}
+
+fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, fp6_launch_plan *plan)
+{
+    if (!plan)
+        return FP6_ERR_NULL;
+    const bool fp16 = weight_bits == 16, grouped = weight_bits == -6;
+    if (!(fp16 ? shape_ok(M, K) : packed_shape_ok(M, K)) || token < 0 || token >= N || N >= (1ll << 31)
+        || !(fp16 || grouped || (weight_bits >= 3 && weight_bits <= 6)))
+        return FP6_ERR_SHAPE;
+    const size_t region = counter_region_bytes(M, N, K);
+    if (N <= kStreamMaxN) {
+        const StreamPlan p = plan_stream(M, N, K, !fp16, weight_bits == 3 ? PackedFp3Source::StreamSource::kTileCols : kTileK);
+        *plan = {FP6_KERNEL_STREAM, 16 * (fp16 ? kStreamCfgFp16 : kStreamCfg)[p.cfg].waves, 16 * p.nt, p.split, 0, N,
+                 p.counter_bytes, region, p.partial_bytes};
+        return FP6_OK;
+    }
+    const int64_t chunk = prompt_chunk_tokens(K), first = token / chunk * chunk, tokens = N - first < chunk ? N - first : chunk;
+    const PromptPlan p = plan_prompt(M, tokens, K, fp16 ? Weights::kFp16 : grouped ? Weights::kGrouped : Weights::kPacked);
+    *plan = {p.is_block() ? FP6_KERNEL_BLOCK : FP6_KERNEL_TILED, p.is_block() ? kBlockCfg[p.block.cfg].rows : p.tiled.tile.rows(),
+             p.is_block() ? kBlockCfg[p.block.cfg].tokens : p.tiled.tile.tokens(), p.split(), first, tokens, p.counter_bytes(),
+             region, p.partial_bytes()};
+    return FP6_OK;
 }
 
 fp6_status fp6_workspace_init(void *workspace, size_t workspace_bytes, void *stream)
@@ -916,7 +967,7 @@ size_t fp3_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
     if (!packed_shape_ok(M, K) || N <= 0)
         return 0;
-    return N <= kStreamMaxN ? plan_stream(M, N, K, true, PackedFp3Source::StreamSource::kTileCols).total_bytes()
+    return N <= kStreamMaxN ? stream_workspace_bytes(M, N, K, true, PackedFp3Source::StreamSource::kTileCols)
                             : prompt_workspace_bytes(M, N, K, Weights::kPacked);
 }
 
@@ -1003,7 +1054,7 @@ fp6_status fp16_linear(const void *W_f16, const void *X_f16, void *Y_f16, int64_
         return FP6_ERR_SHAPE;
     if (!aligned16(W_f16) || !aligned16(X_f16) || !aligned16(Y_f16))
         return FP6_ERR_ALIGN;
-    const WorkspaceRef ws{workspace, workspace_bytes, false};
+    const WorkspaceRef ws{workspace, workspace_bytes, counter_region_bytes(M, N, K)};
     if (N > kStreamMaxN)
         return launch_prompt<PlainFp16Source>(W_f16, nullptr, X_f16, Y_f16, M, N, K, ws, Epilogue{nullptr, nullptr, 0},
                                              static_cast<hipStream_t>(stream));

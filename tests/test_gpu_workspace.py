@@ -1,0 +1,71 @@
+"""One kept workspace under calls of several shapes and weight formats, and a call that is cut into chunks: the arrival
+counters lie where no launch keeps partial sums."""
+import pytest
+import torch
+
+import workloads
+from gpu_checks import check_linear
+from launch_plans import plan, workspace_bytes
+
+pytestmark = pytest.mark.gpu
+
+WIDTHS = ["fp6", "fp6g", "fp3", "fp16"]
+
+
+@pytest.fixture(scope="module")
+def pkg():
+    import paper_2401_14112_amd as p
+
+    p.load_library()
+    return p
+
+
+def _call(pkg, width, M, K, seed):
+    W = workloads.make_weights(M, K, seed, device="cuda")
+    if width == "fp16":
+        return lambda X, **kw: pkg.fp16_linear(W, X, **kw)
+    weights = getattr(pkg, width + "_quantize_pack")(W)
+    return lambda X, **kw: getattr(pkg, width + "_linear")(*weights, X, M, K, **kw)
+
+
+def test_one_workspace_for_formats_and_token_counts(pkg):
+    """Bit for bit the outputs of calls with a fresh workspace each.  What lies behind the counters is NaN at first."""
+    M, K = 8192, 2048
+    lib = pkg.load_library()
+    calls = [(w, N) for N in (200, 16, 129, 40) for w in WIDTHS]
+    linear = {w: _call(pkg, w, M, K, 3 + i) for i, w in enumerate(WIDTHS)}
+    X = {N: workloads.make_activations(N, K, N, device="cuda") for N in {n for _, n in calls}}
+    expected = {(w, N): linear[w](X[N]) for w, N in calls}
+    assert sum(plan(lib, w, M, N, K).split_k > 1 for w, N in calls) >= 12
+    workspace = torch.full((max(workspace_bytes(lib, w, M, N, K) for w, N in calls),), 0xFF, dtype=torch.uint8, device="cuda")
+    workspace[:lib.fp6_workspace_zero_bytes(M, 200, K)] = 0
+    for rounds in range(2):
+        for w, N in calls:
+            print("shared workspace %s N=%d" % (w, N), flush=True)
+            out = torch.full((N, M), float("nan"), dtype=torch.float16, device="cuda")
+            linear[w](X[N], out=out, workspace=workspace)
+            assert torch.equal(out.view(torch.int16), expected[w, N].view(torch.int16)), (w, N, rounds)
+
+
+def test_chunked_call_with_k_slices(pkg):
+    """X of 3 GiB: two launches with different blocks, both with k slices; run twice on one workspace."""
+    M, N, K = 128, 33088, 49152
+    lib = pkg.load_library()
+    first, last = plan(lib, "fp16", M, N, K), plan(lib, "fp16", M, N, K, N - 1)
+    assert first.first_token < last.first_token and first.split_k > 1 and last.split_k > 1
+    assert (first.block_rows, first.block_tokens) != (last.block_rows, last.block_tokens)
+    print("chunked call M=%d N=%d K=%d" % (M, N, K), flush=True)
+    W = workloads.make_weights(M, K, 1, device="cuda")
+    X = torch.empty((N, K), dtype=torch.float16, device="cuda")
+    for n in range(0, N, 4136):
+        X[n:n + 4136] = workloads.make_activations(4136, K, n, device="cuda")
+    workspace = torch.zeros(pkg.fp16_linear_workspace_bytes(M, N, K), dtype=torch.uint8, device="cuda")
+    outs = []
+    for _ in range(2):
+        out = torch.full((N, M), float("nan"), dtype=torch.float16, device="cuda")
+        outs.append(pkg.fp16_linear(W, X, out=out, workspace=workspace))
+    Wt = W.float().t().contiguous()
+    ref = torch.cat([X[n:n + 4136].float() @ Wt for n in range(0, N, 4136)]).cpu().numpy().astype("float64")
+    for out in outs:
+        check_linear(out.cpu().numpy(), ref, "chunked call")
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))

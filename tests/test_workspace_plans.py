@@ -1,0 +1,77 @@
+"""Where the launches of a call keep their split-K state (CPU only: the plans are host arithmetic).  Every launch counts
+arrivals in the counters that the launches before it left at zero, so no launch may keep partial sums where another one
+that uses the workspace, in the same call or a later one, counts."""
+import random
+
+import pytest
+
+from launch_plans import BITS, plan, workspace_bytes
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2401_14112_amd as pkg
+
+    return pkg.load_library()
+
+
+def _launches(lib, width, M, N, K):
+    first = plan(lib, width, M, N, K)
+    assert first.first_token == 0
+    last = plan(lib, width, M, N, K, N - 1)
+    assert last.first_token + last.tokens == N and last.tokens <= first.tokens
+    return [first, last]
+
+
+def _check(lib, shapes):
+    """All launches of all calls in `shapes` on one workspace of the largest size queried."""
+    launches = []
+    for width, M, N, K in shapes:
+        need = workspace_bytes(lib, width, M, N, K)
+        for p in _launches(lib, width, M, N, K):
+            assert (p.partial_bytes == 0) == (p.counter_bytes == 0) == (p.split_k == 1)
+            if p.split_k > 1:
+                assert p.partial_offset + p.partial_bytes <= need, (width, M, N, K)
+                assert p.partial_offset % 16 == 0
+                assert p.counter_bytes <= lib.fp6_workspace_zero_bytes(M, N, K)
+                launches.append(((width, M, N, K), p))
+    for a, p in launches:
+        for b, q in launches:
+            assert q.counter_bytes <= p.partial_offset, "counters of %s lie in the partial sums of %s" % (b, a)
+    return launches
+
+
+@pytest.mark.parametrize("width,M,N,K", [
+    # X beyond 2 GiB: a full chunk and a shorter last one with different blocks and more counters ...
+    ("fp16", 128, 33088, 49152), ("fp6g", 384, 12864, 139264),
+    # ... or fewer, so that the last launch of one call could write where the first of the next one counts
+    ("fp16", 2048, 1200, 1 << 20), ("fp6", 16, 400, (1 << 23) - 256), ("fp6g", 1024, 6000, 1 << 18)])
+def test_launches_of_a_chunked_call(lib, width, M, N, K):
+    a, b = _launches(lib, width, M, N, K)
+    assert a.first_token != b.first_token, "the case is meant to be cut into chunks"
+    assert _check(lib, [(width, M, N, K)])
+
+
+@pytest.mark.parametrize("N", [1, 16, 17, 33, 64, 65, 100, 200, 512])
+def test_formats_share_the_workspace_of_a_shape(lib, N):
+    assert _check(lib, [(w, 8192, N, 8192) for w in BITS])
+
+
+def test_any_calls_share_a_workspace(lib):
+    rng = random.Random(0)
+    for _ in range(200):
+        shapes = []
+        for _ in range(6):
+            M, K = 16 * rng.randint(1, 1 << rng.randint(0, 11)), 256 * rng.randint(1, 1 << rng.randint(0, 7))
+            shapes.append((rng.choice(list(BITS)), M, rng.randint(1, 1 << rng.randint(0, 12)), K))
+        _check(lib, shapes)
+
+
+@pytest.mark.parametrize("split", [2, 5, 16])
+def test_forced_split_factors_on_one_shape(lib, split):
+    lib.fp6_tuning_set_split_k(split)
+    try:
+        for M, N, K in [(8192, 16, 8192), (28672, 200, 4096), (57344, 700, 4096), (128, 33088, 49152)]:
+            assert _check(lib, [(w, M, N, K) for w in BITS])
+    finally:
+        lib.fp6_tuning_set_split_k(0)
