@@ -48,8 +48,8 @@ void fp6_tuning_set_tile(int block_rows, int block_tokens);
 
 /*
  * What a call would launch for the tokens around `token` (a call whose activations exceed 2 GiB is cut into launches
- * that are planned one by one), under the tuning hooks in force.  Host arithmetic only.  weight_bits: 6, 5, 4, 3,
- * -6 (fp6g_linear) or 16 (fp16_linear).
+ * that are planned one by one), under the tuning hooks in force, given a workspace of workspace_bytes (refused with
+ * FP6_ERR_WORKSPACE like the call).  Host arithmetic only.  weight_bits: 6, 5, 4, 3, -6 (fp6g_linear) or 16 (fp16_linear).
  */
 enum { FP6_KERNEL_STREAM = 0, FP6_KERNEL_TILED = 1, FP6_KERNEL_BLOCK = 2 };
 typedef struct {
@@ -61,7 +61,8 @@ typedef struct {
     size_t partial_offset;         /* where its partial sums start ... */
     size_t partial_bytes;          /* ... and their size (0 without k slices) */
 } fp6_launch_plan;
-fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, fp6_launch_plan *plan);
+fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes,
+                           fp6_launch_plan *plan);
 
 #ifdef __cplusplus
 }

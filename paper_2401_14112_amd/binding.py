@@ -122,7 +122,7 @@ def load_library():
     L.fp6_tuning_set_tile.restype = None
     L.fp6_tuning_set_tile.argtypes = [ci, ci]
     L.fp6_tuning_plan.restype = ci
-    L.fp6_tuning_plan.argtypes = [ci, i64, i64, i64, i64, vp]
+    L.fp6_tuning_plan.argtypes = [ci, i64, i64, i64, i64, sz, vp]
     _lib = L
     return L
 

@@ -246,7 +246,8 @@ constexpr Weights weights_of()
                                                 : std::is_same_v<Src, PackedFp6GroupSource> ? Weights::kGrouped : Weights::kPacked;
 }
 
-BlockPlan block_plan_of(int cfg, int64_t M, int64_t N, int64_t K)
+// partial_limit: bytes that the partial tiles may take
+BlockPlan block_plan_of(int cfg, int64_t M, int64_t N, int64_t K, size_t partial_limit = SIZE_MAX)
 {
     BlockPlan p;
     p.cfg = cfg;
@@ -260,13 +261,15 @@ BlockPlan block_plan_of(int cfg, int64_t M, int64_t N, int64_t K)
     const int64_t max_split = KT >= 8 ? KT / 4 : 1;  // at least four k-tiles per slice
     s = s > max_split ? max_split : s;
     s = s > 16 ? 16 : s;
+    const size_t tiles = (size_t)p.row_blocks * p.n_blocks, slice_bytes = tiles * b.rows * b.tokens * sizeof(float);
+    if (s > 1 && slice_bytes * (size_t)s > partial_limit)
+        s = (int64_t)(partial_limit / slice_bytes);
     p.split = (int)(s < 1 ? 1 : s);
     p.chunk = (int)(((int64_t)p.row_blocks * p.split + 7) / 8);
     p.counter_bytes = p.partial_bytes = 0;
     if (p.split > 1) {
-        const size_t tiles = (size_t)p.row_blocks * p.n_blocks;
         p.counter_bytes = (tiles * kBlockWaves * sizeof(int) + 255) / 256 * 256;  // one arrival counter per wave tile
-        p.partial_bytes = (size_t)p.split * tiles * b.rows * b.tokens * sizeof(float);
+        p.partial_bytes = (size_t)p.split * slice_bytes;
     }
     return p;
 }
@@ -279,22 +282,15 @@ struct TiledPlan {
     size_t lds_bytes;
 };
 
-// smallest: only the 128 x 64 block (weights with group scales)
-TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, bool smallest)
+// few row blocks and a short prompt: small blocks and little split-K (measured on 8192-row layers)
+bool few_blocks(int64_t M, int64_t N) { return N <= 128 && (M + 255) / 256 < 64; }
+
+TiledPlan tiled_plan_of(const TileShape &tile, int64_t M, int64_t N, int64_t K)
 {
     TiledPlan p;
     const int64_t row_tiles = M / kTileRows;
     const int64_t KT = K / kTileK;
-    const int forced = g_forced_tile.load(std::memory_order_relaxed);
-    const int rows = forced / 1024, tokens = forced % 1024;
-    if (forced > 0)
-        p.tile = rows == 256 ? (tokens == 128 ? kTile256x128 : kTile256x64) : (tokens == 128 ? kTile128x128 : kTile128x64);
-    else if (N <= 128 && (M + 255) / 256 < 64)
-        p.tile = kTile128x64;  // few row blocks: small blocks and little split-K (measured on 8192-row layers)
-    else
-        p.tile = kTile256x128;  // the shape that moves the fewest bytes per MFMA
-    if (smallest)
-        p.tile = kTile128x64;
+    p.tile = tile;
     p.row_blocks = (int)((M + p.tile.rows() - 1) / p.tile.rows());
     p.n_blocks = (int)((N + p.tile.tokens() - 1) / p.tile.tokens());
     int64_t s = g_forced_split.load(std::memory_order_relaxed);
@@ -317,6 +313,17 @@ TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, bool smallest)
     }
     p.lds_bytes = (size_t)4 * bnt * 256 * 16;  // the kernel's ring of four half tiles of activations
     return p;
+}
+
+// smallest: only the 128 x 64 block (weights with group scales)
+TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, bool smallest)
+{
+    const int forced = g_forced_tile.load(std::memory_order_relaxed);
+    const int rows = forced / 1024, tokens = forced % 1024;
+    TileShape tile = few_blocks(M, N) ? kTile128x64 : kTile256x128;  // the latter moves the fewest bytes per MFMA
+    if (forced > 0)
+        tile = rows == 256 ? (tokens == 128 ? kTile256x128 : kTile256x64) : (tokens == 128 ? kTile128x128 : kTile128x64);
+    return tiled_plan_of(smallest ? kTile128x64 : tile, M, N, K);
 }
 
 // What a call of more than kStreamMaxN tokens launches: the block kernel where `block.cfg` is set, else the tiled one.
@@ -353,7 +360,7 @@ double block_cost(const BlockPlan &p, int64_t K, Weights kind)
 //   fp16 weights: always (9216 x 9216, N = 256 84 against 163; 16384 x 8192, N = 2048 473 against 1176; 8192 x 8192,
 //     N = 100 44 against 49).
 // Among its blocks the cheapest by block_cost().
-PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind)
+PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind, size_t partial_limit = SIZE_MAX)
 {
     PromptPlan p;
     p.block.cfg = -1;
@@ -380,13 +387,13 @@ PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind)
             p.block = block_plan_of(kBlock256x256, M, N, K);
         return p;
     }
-    if (kind == Weights::kGrouped && N <= 128 && row_blocks < 64)
+    if (kind == Weights::kGrouped && few_blocks(M, N))
         return p;
     double best = 0.0;
     // with group scales the 256 x 256 block does not fit the registers, the 128 x 64 one loses to the tiled kernel
     const bool fp16 = kind == Weights::kFp16;
     for (int c = fp16 ? 0 : 1; c < (fp16 ? kBlockCfgs : kBlockCfgs - 1); ++c) {
-        const BlockPlan b = block_plan_of(c, M, N, K);
+        const BlockPlan b = block_plan_of(c, M, N, K, partial_limit);
         const double cost = block_cost(b, K, kind);
         if (p.block.cfg < 0 || cost < best) {
             p.block = b;
@@ -499,13 +506,32 @@ size_t prompt_workspace_bytes(int64_t M, int64_t N, int64_t K, Weights kind)
     return split_workspace_bytes(partial_bytes, M, N, K);
 }
 
+// The plan of a launch on the workspace that the caller brought.  The queried size holds the k slices of the best plan.
+// A smaller one, or none, is refused - unless it holds what 128 x 128 blocks need (128 x 64 on few row blocks): they
+// need no k slices where more than half of the CUs have a block, and callers of fp16_linear and fp6g_linear may rely on
+// that.  The call then runs with as many slices as fit (8192 x 22016, N = 512, fp16: 67 MB and 256 x 256 blocks in 4
+// slices as queried, 128 x 128 blocks without a workspace).
+fp6_status plan_prompt_within(int64_t M, int64_t N, int64_t K, Weights kind, const WorkspaceRef &workspace, PromptPlan &p, SplitBuffers &buf)
+{
+    p = plan_prompt(M, N, K, kind);
+    const fp6_status fits = workspace.view(p.counter_bytes(), p.partial_bytes(), buf);
+    if (fits != FP6_ERR_WORKSPACE || !p.is_block() || g_forced_split.load(std::memory_order_relaxed) > 0)
+        return fits;
+    const TiledPlan least = tiled_plan_of(few_blocks(M, N) ? kTile128x64 : kTile128x128, M, N, K);
+    const size_t bytes = workspace.base ? workspace.bytes : 0, region = workspace.counter_region;
+    if (least.split > 1 && bytes < region + least.partial_bytes)
+        return fits;
+    p = plan_prompt(M, N, K, kind, bytes > region ? bytes - region : 0);
+    return workspace.view(p.counter_bytes(), p.partial_bytes(), buf);
+}
+
 template <class Src>
 fp6_status launch_prompt_chunk(const void *weights, const void *scales, const void *X, void *Y, int64_t M, int64_t N,
                               int64_t K, const WorkspaceRef &workspace, const Epilogue &epi, hipStream_t stream)
 {
-    const PromptPlan p = plan_prompt(M, N, K, weights_of<Src>());
+    PromptPlan p;
     SplitBuffers buf;
-    const fp6_status fits = workspace.view(p.counter_bytes(), p.partial_bytes(), buf);
+    const fp6_status fits = plan_prompt_within(M, N, K, weights_of<Src>(), workspace, p, buf);
     if (fits != FP6_OK)
         return fits;
     int *counters = buf.counters;
@@ -556,9 +582,9 @@ fp6_status launch_prompt(const void *weights, const void *scales, const void *X,
     for (int64_t n : prompt_chunks(N, K)) {
         if (n <= 0)
             continue;
-        const PromptPlan p = plan_prompt(M, n, K, weights_of<Src>());
+        PromptPlan p;
         SplitBuffers unused;
-        const fp6_status fits = workspace.view(p.counter_bytes(), p.partial_bytes(), unused);
+        const fp6_status fits = plan_prompt_within(M, n, K, weights_of<Src>(), workspace, p, unused);
         if (fits != FP6_OK)
             return fits;
     }
@@ -788,7 +814,8 @@ void fp6_tuning_set_tile(int block_rows, int block_tokens)
     g_forced_tile.store(known ? block_rows * 1024 + block_tokens : 0);
 }
 
-fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, fp6_launch_plan *plan)
+fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes,
+                           fp6_launch_plan *plan)
 {
     if (!plan)
         return FP6_ERR_NULL;
@@ -797,14 +824,23 @@ fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int
         || !(fp16 || grouped || (weight_bits >= 3 && weight_bits <= 6)))
         return FP6_ERR_SHAPE;
     const size_t region = counter_region_bytes(M, N, K);
+    const WorkspaceRef ws{reinterpret_cast<void *>(uintptr_t(256)), workspace_bytes, region};  // never dereferenced
+    SplitBuffers unused;
     if (N <= kStreamMaxN) {
         const StreamPlan p = plan_stream(M, N, K, !fp16, weight_bits == 3 ? PackedFp3Source::StreamSource::kTileCols : kTileK);
+        const fp6_status fits = ws.view(p.counter_bytes, p.partial_bytes, unused);
+        if (fits != FP6_OK)
+            return fits;
         *plan = {FP6_KERNEL_STREAM, 16 * (fp16 ? kStreamCfgFp16 : kStreamCfg)[p.cfg].waves, 16 * p.nt, p.split, 0, N,
                  p.counter_bytes, region, p.partial_bytes};
         return FP6_OK;
     }
     const int64_t chunk = prompt_chunk_tokens(K), first = token / chunk * chunk, tokens = N - first < chunk ? N - first : chunk;
-    const PromptPlan p = plan_prompt(M, tokens, K, fp16 ? Weights::kFp16 : grouped ? Weights::kGrouped : Weights::kPacked);
+    PromptPlan p;
+    const fp6_status fits = plan_prompt_within(M, tokens, K, fp16 ? Weights::kFp16 : grouped ? Weights::kGrouped : Weights::kPacked,
+                                               ws, p, unused);
+    if (fits != FP6_OK)
+        return fits;
     *plan = {p.is_block() ? FP6_KERNEL_BLOCK : FP6_KERNEL_TILED, p.is_block() ? kBlockCfg[p.block.cfg].rows : p.tiled.tile.rows(),
              p.is_block() ? kBlockCfg[p.block.cfg].tokens : p.tiled.tile.tokens(), p.split(), first, tokens, p.counter_bytes(),
              region, p.partial_bytes()};

@@ -11,11 +11,11 @@ class LaunchPlan(ctypes.Structure):
                 ("partial_offset", ctypes.c_size_t), ("partial_bytes", ctypes.c_size_t)]
 
 
-def plan(lib, width, M, N, K, token=0):
+def plan(lib, width, M, N, K, token=0, workspace_bytes=2 ** 64 - 1):
+    """The plan, or the status of a refusal."""
     p = LaunchPlan()
-    status = lib.fp6_tuning_plan(BITS[width], M, N, K, token, ctypes.byref(p))
-    assert status == 0, (status, width, M, N, K, token)
-    return p
+    status = lib.fp6_tuning_plan(BITS[width], M, N, K, token, workspace_bytes, ctypes.byref(p))
+    return p if status == 0 else status
 
 
 def workspace_bytes(lib, width, M, N, K):

@@ -69,3 +69,27 @@ def test_chunked_call_with_k_slices(pkg):
     for out in outs:
         check_linear(out.cpu().numpy(), ref, "chunked call")
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
+@pytest.mark.parametrize("width,M,N,K", [("fp16", 8288, 68, 2048), ("fp6g", 4096, 640, 8192)])
+def test_less_workspace_than_queried(pkg, width, M, N, K):
+    """None at all and room for fewer k slices, through the C entry points."""
+    lib = pkg.load_library()
+    W, X = workloads.make_weights(M, K, 7, device="cuda"), workloads.make_activations(N, K, 8, device="cuda")
+    queried = workspace_bytes(lib, width, M, N, K)
+    if width == "fp16":
+        dense, head, tail = W, (W.data_ptr(),), ()
+    else:
+        packed, scales = pkg.fp6g_quantize_pack(W)
+        dense, head, tail = pkg.fp6g_unpack(packed, scales, M, K), (packed.data_ptr(), scales.data_ptr()), (128,)
+    ref = (X.float() @ dense.float().t()).cpu().numpy().astype("float64")
+    for have in (queried, queried * 2 // 3, 0):
+        p = plan(lib, width, M, N, K, workspace_bytes=have)
+        print("%s M=%d N=%d K=%d workspace %d: split %d" % (width, M, N, K, have, p.split_k), flush=True)
+        assert (p.split_k > 1) == (have == queried) or have == queried * 2 // 3
+        workspace = torch.zeros(max(have, 16), dtype=torch.uint8, device="cuda")
+        out = torch.full((N, M), float("nan"), dtype=torch.float16, device="cuda")
+        status = getattr(lib, width + "_linear")(*head, X.data_ptr(), out.data_ptr(), M, N, K, *tail,
+                                                 workspace.data_ptr() if have else None, have, torch.cuda.current_stream().cuda_stream)
+        assert status == 0
+        check_linear(out.cpu().numpy(), ref, "%s with %d bytes" % (width, have))

@@ -75,3 +75,45 @@ def test_forced_split_factors_on_one_shape(lib, split):
             assert _check(lib, [(w, M, N, K) for w in BITS])
     finally:
         lib.fp6_tuning_set_split_k(0)
+
+
+REFUSED = 3  # FP6_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("width,M,N,K", [("fp16", 8192, 512, 22016), ("fp16", 8288, 68, 2048), ("fp6g", 4096, 640, 8192),
+                                         ("fp6g", 16640, 100, 4096)])
+def test_calls_whose_small_blocks_fill_the_chip_need_no_workspace(lib, width, M, N, K):
+    """More than 128 blocks of 128 x 128 (128 x 64) outputs: no k slices needed, though the best plan has some."""
+    queried = workspace_bytes(lib, width, M, N, K)
+    best = plan(lib, width, M, N, K, workspace_bytes=queried)
+    assert best.split_k > 1
+    assert plan(lib, width, M, N, K, workspace_bytes=0).split_k == 1
+    for have in range(0, queried, queried // 7):
+        p = plan(lib, width, M, N, K, workspace_bytes=have)
+        assert p.split_k == 1 or p.partial_offset + p.partial_bytes <= have
+
+
+def test_smaller_workspaces_are_refused_otherwise(lib):
+    rng = random.Random(1)
+    refused = 0
+    for _ in range(400):
+        width = rng.choice(list(BITS))
+        M, K = 16 * rng.randint(1, 1 << rng.randint(0, 11)), 256 * rng.randint(8, 64)
+        N = rng.randint(1, 1 << rng.randint(0, 10))
+        best = plan(lib, width, M, N, K)
+        if best.split_k == 1:
+            continue
+        need = best.partial_offset + best.partial_bytes
+        assert plan(lib, width, M, N, K, workspace_bytes=need).split_k == best.split_k
+        less = plan(lib, width, M, N, K, workspace_bytes=need - 16)
+        tokens = 64 if N <= 128 and (M + 255) // 256 < 64 else 128
+        blocks = (M + 127) // 128 * ((N + tokens - 1) // tokens)
+        if N <= 64 or width not in ("fp6g", "fp16"):
+            assert less == REFUSED, (width, M, N, K)
+            refused += 1
+        elif blocks <= 128:
+            assert plan(lib, width, M, N, K, workspace_bytes=0) == REFUSED, (width, M, N, K)
+            refused += 1
+        if less != REFUSED:
+            assert less.split_k == 1 or less.partial_offset + less.partial_bytes <= need - 16
+    assert refused > 50
