@@ -523,6 +523,8 @@ def fp16_linear(W: torch.Tensor, X: torch.Tensor, out: Optional[torch.Tensor] = 
     if out is None:
         out = torch.empty((N, M), dtype=torch.float16, device=X.device)
     _dev(out, torch.float16, "out")
+    if out.numel() != N * M:
+        raise Fp6Error("out has the wrong size")
     if workspace is None:
         workspace = _new_workspace(L.fp16_linear_workspace_bytes(M, N, K), M, N, K, X.device)
     ws_ptr, ws_len = (workspace.data_ptr(), workspace.numel()) if workspace is not None else (None, 0)

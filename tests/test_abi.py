@@ -141,3 +141,34 @@ def test_binding_refuses_cpu_tensors():
     with pytest.raises(pkg.Fp6Error):
         pkg.fp6_linear(torch.zeros(3072, dtype=torch.uint8), torch.zeros(16, dtype=torch.float16),
                        torch.zeros((1, 256), dtype=torch.float16), 16, 256)
+
+
+@pytest.mark.parametrize("name", ["fp6_linear", "fp3_linear", "fp6g_linear", "fp6_linear_fused", "fp16_linear", "fp6_linear_static"])
+@pytest.mark.parametrize("shape", [(1, 32), (2, 16), (4, 32)])
+def test_binding_refuses_outputs_of_the_wrong_size(name, shape, monkeypatch):
+    """Before anything is launched: a smaller output would be written past its end."""
+    import torch
+
+    from paper_2401_14112_amd import binding
+
+    N, M, K = 2, 32, 256
+    lib = binding.load_library()
+
+    def forbidden(*a):
+        raise AssertionError("launched with an output of the wrong size")
+
+    class Host:
+        def __getattr__(self, n):
+            return getattr(lib, n) if n.endswith("_bytes") else forbidden
+
+    monkeypatch.setattr(binding, "load_library", Host)
+    monkeypatch.setattr(binding, "_entry", lambda n: getattr(Host(), n))
+    monkeypatch.setattr(binding, "_dev", lambda t, dtype, what: t)
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
+    X, out = torch.zeros((N, K), dtype=torch.float16), torch.zeros(shape, dtype=torch.float16)
+    weights = (torch.zeros((M, K), dtype=torch.float16),) if name == "fp16_linear" else (
+        torch.zeros(lib.fp3_packed_bytes(M, K) if name == "fp3_linear" else lib.fp6_packed_bytes(M, K), dtype=torch.uint8),
+        torch.zeros((M, K // 128) if name == "fp6g_linear" else M, dtype=torch.float16))
+    size = () if name == "fp16_linear" else (M, K)
+    with pytest.raises(binding.Fp6Error, match="out"):
+        getattr(binding, name)(*weights, X, *size, out=out)
