@@ -234,7 +234,7 @@ template <> struct BlockSourceOf<PlainFp16Source> { typedef BlockFp16Source type
 struct BlockPlan {
     int cfg;  // -1: the tiled kernel instead
     int split;
-    int row_blocks, n_blocks, chunk;  // chunk: (row block, k slice) units per XCD
+    int row_blocks, n_blocks, chunk;  // chunk: output pieces per XCD
     size_t counter_bytes, partial_bytes;  // 0 without k slices
 };
 
@@ -265,7 +265,7 @@ BlockPlan block_plan_of(int cfg, int64_t M, int64_t N, int64_t K, size_t partial
     if (s > 1 && slice_bytes * (size_t)s > partial_limit)
         s = (int64_t)(partial_limit / slice_bytes);
     p.split = (int)(s < 1 ? 1 : s);
-    p.chunk = (int)(((int64_t)p.row_blocks * p.split + 7) / 8);
+    p.chunk = pieces_per_xcd(p.row_blocks * p.split, p.n_blocks);
     p.counter_bytes = p.partial_bytes = 0;
     if (p.split > 1) {
         p.counter_bytes = (tiles * kBlockWaves * sizeof(int) + 255) / 256 * 256;  // one arrival counter per wave tile
@@ -417,7 +417,7 @@ fp6_status launch_block_cfg(const BlockPlan &p, const void *weights, const void 
     static std::atomic<uint64_t> lds_done{0};  // per instantiation
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds, lds_done))
         return FP6_ERR_HIP;
-    const dim3 grid((unsigned)(8 * p.chunk * p.n_blocks)), block(Shape::kThreads);
+    const dim3 grid((unsigned)(kXcds * p.chunk)), block(Shape::kThreads);
     hipLaunchKernelGGL(kernel, grid, block, lds, stream, weights, static_cast<const half_t *>(scales),
                        static_cast<const half_t *>(X), static_cast<half_t *>(Y), (int)M, (int)N, (int)K, p.split,
                        p.n_blocks, p.row_blocks, p.chunk, partials, counters, epi);

@@ -267,6 +267,38 @@ struct BlockShape {
     }
 };
 
+// Which piece a block works on: unit (row block and k slice) and token block; unit = units: none.  Consecutive block ids
+// land on consecutive XCDs.  Each XCD takes `chunk` consecutive pieces, an eighth of them all.  The pieces are ordered by
+// eighths of the units (slice-major, so that an eighth shares the activations of few slices), each walked in groups of
+// eight units x all token blocks, units fastest.  Dealing pieces and not whole units keeps the XCDs even: 20 units x 11
+// token blocks give each 27 or 28 blocks for its 32 CUs, where whole units gave six of them 33 and the launch a second
+// round (5104 x 1024, N = 2571, 3 bits 54.5 -> 36.1 us; 6992 x 11008, N = 301, group scales 110.8 -> 71.4).
+struct BlockPiece {
+    int unit, n_block;
+};
+constexpr int kXcds = 8;
+__host__ __device__ constexpr int pieces_per_xcd(int units, int n_blocks)
+{
+    return (int)(((int64_t)units * n_blocks + kXcds - 1) / kXcds);
+}
+__host__ __device__ constexpr BlockPiece piece_of_block(int id, int units, int n_blocks, int chunk)
+{
+    constexpr int kGroup = 8;
+    const int eighth = (units + kXcds - 1) / kXcds;
+    int rest = id % kXcds * chunk + id / kXcds;
+    const int first = rest / (eighth * n_blocks) * eighth;
+    if (first >= units)
+        return {units, 0};  // the grid is padded to a multiple of eight
+    rest -= first * n_blocks;
+    const int here = units - first < eighth ? units - first : eighth;
+    const int group = rest / (kGroup * n_blocks) * kGroup;
+    if (group >= here)
+        return {units, 0};
+    rest -= group * n_blocks;
+    const int in_group = here - group < kGroup ? here - group : kGroup;
+    return rest < in_group * n_blocks ? BlockPiece{first + group + rest % in_group, rest / in_group} : BlockPiece{units, 0};
+}
+
 // Copies into the LDS slot of a weight plane or of group scales.  The comment in the statement marks them in the
 // generated assembly, where the build looks for LDS reads in flight at the barrier before them.
 template <int IMM>
@@ -334,18 +366,10 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     const int KT = K / kTileK;
     const int n_row_tiles = M / kTileRows;
 
-    // block -> (unit = row block and k slice, token block).  Consecutive block ids land on consecutive XCDs; each XCD
-    // takes a contiguous range of `chunk` units (slice-major, so its blocks share the activations of few slices) and
-    // walks it in groups of eight units x all token blocks, units fastest.
-    constexpr int kXcds = 8, kGroup = 8;
-    const int xcd = blockIdx.x % kXcds, index = blockIdx.x / kXcds;
-    const int group = index / (kGroup * n_blocks);
-    const int in_group = chunk - group * kGroup < kGroup ? chunk - group * kGroup : kGroup;
-    const int rest = index - group * (kGroup * n_blocks);
-    const int unit = xcd * chunk + group * kGroup + rest % in_group;
-    const int n_block = rest / in_group;
-    if (unit >= row_blocks * S)
-        return;  // the ranges of the last XCDs may be shorter (whole block, before any barrier)
+    const BlockPiece at = piece_of_block(blockIdx.x, row_blocks * S, n_blocks, chunk);
+    if (at.unit >= row_blocks * S)
+        return;  // padding (whole block, before any barrier)
+    const int unit = at.unit, n_block = at.n_block;
     const int split = unit / row_blocks, row_block = unit - split * row_blocks;
     const int row0 = row_block * BM, col0 = n_block * BN;
     // k-tiles split, split + S, ... of the row block

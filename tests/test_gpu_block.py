@@ -10,6 +10,7 @@ import torch
 
 import workloads
 from gpu_checks import check_linear
+from launch_plans import BLOCK, TILED, plan
 
 pytestmark = pytest.mark.gpu
 
@@ -94,9 +95,35 @@ def test_block_fused_steps(pkg, width, block, split):
     check_linear(Y.cpu().numpy(), Y_ref, "fused %s %dx%d" % (width, *block))
 
 
+@pytest.mark.parametrize("width,block,M,K,N", [("fp16", (128, 64), 9616, 256, 130), ("fp6", (256, 256), 5104, 512, 1300),
+                                               ("fp6g", (256, 128), 18448, 256, 200)])
+def test_block_order_over_several_groups(pkg, width, block, M, K, N):
+    """More than eight units per XCD, or numbers of them that eight does not divide: 76 x 3, 20 x 6 and 73 x 2 pieces."""
+    print("order %s M=%d K=%d N=%d" % (width, M, K, N), flush=True)
+    W, X = workloads.make_weights(M, K, 1, device="cuda"), workloads.make_activations(N, K, 2, device="cuda")
+    weights = (W,) if width == "fp16" else getattr(pkg, width + "_quantize_pack")(W)
+    dense = W if width == "fp16" else getattr(pkg, width + "_unpack")(*weights, M, K)
+    out = torch.full((N, M), float("nan"), dtype=torch.float16, device="cuda")
+    pkg.fp6_tuning_set_tile(*block)
+    pkg.fp6_tuning_set_split_k(1)
+    try:
+        p = plan(pkg.load_library(), width, M, N, K)
+        assert (p.kernel, p.block_rows, p.block_tokens) == (BLOCK, *block)
+        if width == "fp16":
+            pkg.fp16_linear(W, X, out=out)
+        else:
+            getattr(pkg, width + "_linear")(*weights, X, M, K, out=out)
+    finally:
+        pkg.fp6_tuning_set_tile(0, 0)
+        pkg.fp6_tuning_set_split_k(0)
+    check_linear(out.cpu().numpy(), (X.float() @ dense.float().t()).cpu().numpy().astype(np.float64), "order %s" % width)
+
+
 def test_plan_reaches_the_block_kernel_unforced(pkg):
     """6-bit weights: the automatic plan's largest block against the other kernel on the same call."""
     M, K, N = 4096, 512, 3100      # 16 x 13 tiles of 256 x 256 (the last one ragged) against 16 x 25 of 256 x 128
+    p = plan(pkg.load_library(), "fp6", M, N, K)
+    assert (p.kernel, p.block_rows, p.block_tokens) == (BLOCK, 256, 256)
     print("automatic plan M=%d K=%d N=%d" % (M, K, N), flush=True)
     W = workloads.make_weights(M, K, 1, device="cuda")
     X = workloads.make_activations(N, K, 2, device="cuda")
@@ -104,6 +131,7 @@ def test_plan_reaches_the_block_kernel_unforced(pkg):
     auto = pkg.fp6_linear(packed, scales, X, M, K)
     pkg.fp6_tuning_set_tile(256, 128)
     try:
+        assert plan(pkg.load_library(), "fp6", M, N, K).kernel == TILED
         other = pkg.fp6_linear(packed, scales, X, M, K)
     finally:
         pkg.fp6_tuning_set_tile(0, 0)

@@ -5,6 +5,8 @@ The quantizer kernel does not divide: it multiplies by a reciprocal, applies one
 and rounds the fp32 quotient onto the e3m2 grid with integer bit tricks.  That this equals the exact
 round-to-nearest-even of |w|/scale (ties included) is an argument about fp32 arithmetic; here it is tested.
 """
+import subprocess
+
 import numpy as np
 
 
@@ -74,3 +76,36 @@ def test_quantizer_shortcut_on_exact_ties(oracle):
         assert np.array_equal(_gpu_style_codes(wb, sb[idx]), _oracle_codes(oracle, wb, sb[idx]))
     # and the oracle agrees on the ties themselves (sample)
     assert np.array_equal(_oracle_codes(oracle, w_bits[idx], sb[idx]), want[idx])
+
+
+def test_block_order_is_a_bijection_that_fills_the_xcds_evenly(tmp_path):
+    """The block kernel's own map from block ids to output pieces, evaluated by the compiler: every piece once, no XCD
+    with more than an eighth of them (rounded up), for even and uneven numbers of units and short last groups."""
+    from paper_2401_14112_amd import build
+
+    (tmp_path / "order.hip").write_text("""
+#include "linear_block.hpp"
+template <int UNITS, int NB> struct Order {
+    static constexpr bool covers() {
+        const int chunk = fp6::pieces_per_xcd(UNITS, NB);
+        if (chunk != (UNITS * NB + 7) / 8) return false;
+        bool seen[UNITS * NB] = {};
+        int found = 0;
+        for (int id = 0; id < 8 * chunk; ++id) {
+            const fp6::BlockPiece p = fp6::piece_of_block(id, UNITS, NB, chunk);
+            if (p.unit == UNITS) continue;
+            if (p.unit < 0 || p.unit > UNITS || p.n_block < 0 || p.n_block >= NB || seen[p.n_block * UNITS + p.unit]) return false;
+            seen[p.n_block * UNITS + p.unit] = true;
+            ++found;
+        }
+        return found == UNITS * NB;
+    }
+};
+template <int... UNITS> constexpr bool all() {
+    return ((Order<UNITS, 1>::covers() && Order<UNITS, 2>::covers() && Order<UNITS, 3>::covers() && Order<UNITS, 11>::covers()
+             && Order<UNITS, 16>::covers()) && ...);
+}
+static_assert(all<1, 2, 7, 8, 9, 19, 20, 25, 63, 64, 65, 72, 76, 84, 128, 224, 257>(), "a piece is missed or dealt twice");
+""")
+    subprocess.run([build.hipcc(), "--offload-arch=gfx950", "-std=c++17", "--cuda-host-only", "-fsyntax-only", "-w",
+                    "-fconstexpr-steps=100000000", "-I", str(build.CSRC), str(tmp_path / "order.hip")], check=True)
