@@ -70,6 +70,20 @@ struct SplitBuffers {
     uint8_t *partials;
 };
 
+// Distance, in counters, of the arrival counters of a prompt-sized launch: as far apart as the region allows, up to 128
+// bytes.  Arrivals at one cache line queue up: with 12 slices and 16 counters per line the queue costs 1.2 us
+// (256 x 12544, N = 96, 6 bits 16.7 -> 15.2 us, 1232 x 7168, N = 80 14.5 -> 13.1; fp16, 816 x 5632, N = 418 31.1 -> 18.7);
+// spread, no 64 bytes see more than 64 of them, where they could see 256.
+int counter_step(size_t counters)
+{
+    int step = 1;
+    while (step < 32 && counters * (size_t)step * 2 * sizeof(int) <= kCounterBytes)
+        step *= 2;
+    return step;
+}
+
+size_t counter_bytes_of(size_t counters, int step) { return (counters * (size_t)step * sizeof(int) + 255) / 256 * 256; }
+
 struct WorkspaceRef {
     void *base;
     size_t bytes;
@@ -235,6 +249,7 @@ struct BlockPlan {
     int cfg;  // -1: the tiled kernel instead
     int split;
     int row_blocks, n_blocks, chunk;  // chunk: output pieces per XCD
+    int counter_step;
     size_t counter_bytes, partial_bytes;  // 0 without k slices
 };
 
@@ -267,8 +282,9 @@ BlockPlan block_plan_of(int cfg, int64_t M, int64_t N, int64_t K, size_t partial
     p.split = (int)(s < 1 ? 1 : s);
     p.chunk = pieces_per_xcd(p.row_blocks * p.split, p.n_blocks);
     p.counter_bytes = p.partial_bytes = 0;
+    p.counter_step = counter_step(tiles * kBlockWaves);  // one arrival counter per wave tile
     if (p.split > 1) {
-        p.counter_bytes = (tiles * kBlockWaves * sizeof(int) + 255) / 256 * 256;  // one arrival counter per wave tile
+        p.counter_bytes = counter_bytes_of(tiles * kBlockWaves, p.counter_step);
         p.partial_bytes = (size_t)p.split * slice_bytes;
     }
     return p;
@@ -278,6 +294,7 @@ struct TiledPlan {
     TileShape tile;
     int split;
     int row_blocks, n_blocks;
+    int counter_step;
     size_t counter_bytes, partial_bytes;  // 0 without k slices
     size_t lds_bytes;
 };
@@ -305,10 +322,11 @@ TiledPlan tiled_plan_of(const TileShape &tile, int64_t M, int64_t N, int64_t K)
         s = 1;
     p.split = (int)s;
     const int bnt = p.tile.nt * p.tile.wn;
+    const size_t counters = (size_t)p.row_blocks * p.n_blocks * p.tile.wm * p.tile.wn;  // one per wave tile
     p.counter_bytes = p.partial_bytes = 0;
+    p.counter_step = counter_step(counters);
     if (p.split > 1) {
-        // one arrival counter per wave tile
-        p.counter_bytes = ((size_t)p.row_blocks * p.n_blocks * p.tile.wm * p.tile.wn * sizeof(int) + 255) / 256 * 256;
+        p.counter_bytes = counter_bytes_of(counters, p.counter_step);
         p.partial_bytes = (size_t)p.split * (size_t)row_tiles * (size_t)p.n_blocks * bnt * 64 * sizeof(float4_t);
     }
     p.lds_bytes = (size_t)4 * bnt * 256 * 16;  // the kernel's ring of four half tiles of activations
@@ -420,7 +438,7 @@ fp6_status launch_block_cfg(const BlockPlan &p, const void *weights, const void 
     const dim3 grid((unsigned)(kXcds * p.chunk)), block(Shape::kThreads);
     hipLaunchKernelGGL(kernel, grid, block, lds, stream, weights, static_cast<const half_t *>(scales),
                        static_cast<const half_t *>(X), static_cast<half_t *>(Y), (int)M, (int)N, (int)K, p.split,
-                       p.n_blocks, p.row_blocks, p.chunk, partials, counters, epi);
+                       p.n_blocks, p.row_blocks, p.chunk, partials, counters, p.counter_step, epi);
     return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
 }
 
@@ -438,7 +456,7 @@ fp6_status launch_tiled_cfg(const TiledPlan &p, const void *weights, const void 
     const dim3 grid((unsigned)(padded_row_blocks * p.n_blocks * p.split)), block(WM * WN * 64);
     hipLaunchKernelGGL(kernel, grid, block, p.lds_bytes, stream, weights, static_cast<const half_t *>(scales),
                        static_cast<const half_t *>(X), static_cast<half_t *>(Y), (int)M, (int)N, (int)K, p.split,
-                       p.n_blocks, partials, counters, epi);
+                       p.n_blocks, partials, counters, p.counter_step, epi);
     return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
 }
 

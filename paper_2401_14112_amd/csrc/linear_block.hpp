@@ -338,7 +338,7 @@ template <class Src, class Shape>
 __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     const void *__restrict__ weights, const half_t *__restrict__ scales, const half_t *__restrict__ X, half_t *Y, int M,
     int N, int K, int S, int n_blocks, int row_blocks, int chunk, float4_t *__restrict__ partials,
-    int *__restrict__ counters, Epilogue epi)
+    int *__restrict__ counters, int counter_step, Epilogue epi)
 {
     constexpr int RT = Shape::RT, NT = Shape::NT, WM = Shape::WM, WN = Shape::WN, WK = Shape::WK;
     constexpr int SR = Shape::SR, XST = Shape::XST, WD = Shape::WD, WAVES = Shape::WAVES;
@@ -725,7 +725,7 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's partial stores are done
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     int arrived = 0;
-    int *counter = counters + tile_id * WAVES + wave;
+    int *counter = counters + (tile_id * WAVES + wave) * counter_step;
     if (lane == 0)
         arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     arrived = __builtin_amdgcn_readfirstlane(arrived);

@@ -23,7 +23,7 @@ template <class Src, int RT, int NT, int WM, int WN>
 __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
     const void *__restrict__ weights, const half_t *__restrict__ scales, const half_t *__restrict__ X,
     half_t *Y, int M, int N, int K, int S, int n_blocks, float4_t *__restrict__ partials,
-    int *__restrict__ counters, Epilogue epi)
+    int *__restrict__ counters, int counter_step, Epilogue epi)
 {
     constexpr int WAVES = WM * WN;
     constexpr int BNT = WN * NT;             // 16-token tiles of the block
@@ -273,7 +273,7 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's partial stores are done
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    int *counter = counters + ((int64_t)row_block * n_blocks + n_block) * WAVES + wave;
+    int *counter = counters + (((int64_t)row_block * n_blocks + n_block) * WAVES + wave) * counter_step;
     int arrived = 0;
     if (lane == 0)
         arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

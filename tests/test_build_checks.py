@@ -130,7 +130,7 @@ def test_block_kernels_wait_for_their_reads_before_a_refill(tmp_path, source, in
     shape = re.search(r"BlockShapeOf<false, %d> \{ typedef (BlockShape<[^>]*>)" % index, text).group(1)
     (tmp_path / "one.hip").write_text(
         '#include "linear_block.hpp"\nnamespace fp6 {\ntemplate __global__ void linear_block_kernel<%s, %s>(const void *, const half_t *, '
-        'const half_t *, half_t *, int, int, int, int, int, int, int, float4_t *, int *, Epilogue);\n}\n' % (source, shape))
+        'const half_t *, half_t *, int, int, int, int, int, int, int, float4_t *, int *, int, Epilogue);\n}\n' % (source, shape))
     subprocess.run([build.hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "--cuda-device-only", "-S", "-w",
                     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-I", str(build.CSRC),
                     str(tmp_path / "one.hip"), "-o", str(tmp_path / "one.s")], check=True)
