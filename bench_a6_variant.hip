@@ -172,7 +172,7 @@ int launch_tiled(const void *w, const void *sc, const void *X, void *Y, int64_t 
     float4_t *partials = reinterpret_cast<float4_t *>(static_cast<char *>(ws) + 65536);
     hipLaunchKernelGGL(kernel, dim3((unsigned)((rb + 7) / 8 * 8 * nb * S)), dim3(WM * WN * 64), lds, st, w,
                        static_cast<const half_t *>(sc), static_cast<const half_t *>(X), static_cast<half_t *>(Y), (int)M,
-                       (int)N, (int)K, S, nb, partials, counters, Epilogue{nullptr, nullptr, 0});
+                       (int)N, (int)K, S, nb, partials, counters, 1, Epilogue{nullptr, nullptr, 0});
     return hipGetLastError() == hipSuccess ? 0 : 5;
 }
 

@@ -137,3 +137,12 @@ def test_block_kernels_wait_for_their_reads_before_a_refill(tmp_path, source, in
     asm = (tmp_path / "one.s").read_text()
     assert "s_barrier" in asm and asm.count("slot refill") >= 8    # the prologue's copies and the loop's
     assert build.slot_refill_problems(asm) == []
+
+
+def test_bench_only_kernels_follow_the_headers():
+    """bench_a6_variant.hip instantiates and launches the library's kernel templates itself."""
+    root = build.PKG.parent
+    r = subprocess.run([build.hipcc(), "--offload-arch=gfx950", "-std=c++17", "--cuda-host-only", "-fsyntax-only", "-w",
+                        "-I", str(root / "include"), "-I", str(root), str(root / "bench_a6_variant.hip")],
+                       stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert r.returncode == 0, r.stdout
