@@ -333,7 +333,7 @@ TiledPlan tiled_plan_of(const TileShape &tile, int64_t M, int64_t N, int64_t K)
     return p;
 }
 
-// smallest: only the 128 x 64 block (weights with group scales)
+// smallest: the 128 x 64 block (weights with group scales; their 128 x 128 one is chosen in plan_prompt)
 TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, bool smallest)
 {
     const int forced = g_forced_tile.load(std::memory_order_relaxed);
@@ -366,6 +366,35 @@ double block_cost(const BlockPlan &p, int64_t K, Weights kind)
     return p.split == 1 ? ns : ns + (double)p.split * b.rows * b.tokens * 4.0 / 50.0 + (double)p.partial_bytes * 1.5e-4;
 }
 
+// Whether the cheapest block plan for group scales has so few k-tiles per block that the tiled kernel's 128 x 128 blocks
+// are faster: the block kernel pays more before and after its k loop (its rings fill, two waves meet in LDS, the last
+// slice reads its own partial tiles back).  The tiled kernel deals whole row blocks to the XCDs, so it has to be done in one
+// round on the fullest of them (in two it takes 1.3 to 2 times as long), and it gains less where few XCDs hold most blocks.
+// Median time of the block kernel over the tiled one's, 5400 calls of 256 to 57344 rows and 129 to 1200 tokens, by k-tiles
+// per block:
+//   no k slices, up to 8 blocks on an XCD     2 1.06, 3 1.04, 4 1.03, 5 1.01, 6 1.00
+//   no k slices, more blocks                  2 1.04, 3 1.01, 4 0.98, 5 0.97
+//   2 or 3 slices                             4 1.17, 5 1.12, 6 1.08, 7 1.06
+//   4 to 7 slices                             4 1.15, 5 1.07, 6 1.05, 7 1.01
+//   8 to 16 slices                            4 1.10, 5 1.02, 6 0.96
+//   slices, more than 16 blocks on an XCD and 1.6 times the average   4 1.04, 5 1.00, 6 0.97
+//   256 x 128 blocks in slices                4 1.03, 5 0.96
+// (2048 x 4096, N = 265: 21.4 us against 17.9; 784 x 512, N = 636: 8.3 against 7.7.)
+bool short_blocks(const BlockPlan &b, const TiledPlan &tiled, int64_t K)
+{
+    const int64_t blocks = (int64_t)tiled.row_blocks * tiled.n_blocks * tiled.split;
+    const int64_t fullest = (int64_t)((tiled.row_blocks + kXcds - 1) / kXcds) * tiled.n_blocks * tiled.split;
+    if (fullest > kCus / kXcds)
+        return false;
+    const int64_t k_tiles = (K / kTileK + b.split - 1) / b.split;
+    if (b.split == 1)
+        return kBlockCfg[b.cfg].rows == 128 && k_tiles <= (fullest <= 8 ? 5 : 3);
+    const bool uneven = fullest > 16 && 5 * fullest >= 8 * ((blocks + kXcds - 1) / kXcds);
+    if (uneven || kBlockCfg[b.cfg].rows == 256)
+        return k_tiles <= 4;
+    return k_tiles <= (b.split < 4 ? 7 : b.split < 8 ? 6 : 5);
+}
+
 // Which kernel and block (us, this kernel against the tiled one in the same process):
 //   per-row packed weights: the 256 x 256 block, at up to 1.17x the rate of the tiled kernel's 256 x 128 one, where its
 //     rounds of 256 blocks and its padded tokens take at most 1.1x what that block's do - which also says that it
@@ -374,7 +403,8 @@ double block_cost(const BlockPlan &p, int64_t K, Weights kind)
 //     202 against 219 with 5).  Beyond that it loses: 8192 x 8192, N = 1024 127 against 110, 28672 x 8192, N = 700
 //     344 against 294, 57344 x 4096, N = 300 175 against 155;
 //   group scales: always, except few rows and few tokens (8192 x 8192, N = 100: 31 against 30; 4096 x 4096 17 against
-//     13; but 28672 x 8192, N = 201 120 against 166, 16384 x 8192, N = 2048 497 against 740);
+//     13; but 28672 x 8192, N = 201 120 against 166, 16384 x 8192, N = 2048 497 against 740) and short blocks, see
+//     short_blocks();
 //   fp16 weights: always (9216 x 9216, N = 256 84 against 163; 16384 x 8192, N = 2048 473 against 1176; 8192 x 8192,
 //     N = 100 44 against 49).
 // Among its blocks the cheapest by block_cost().
@@ -416,6 +446,13 @@ PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind, size_t par
         if (p.block.cfg < 0 || cost < best) {
             p.block = b;
             best = cost;
+        }
+    }
+    if (kind == Weights::kGrouped) {
+        const TiledPlan tiled = tiled_plan_of(kTile128x128, M, N, K);
+        if (tiled.partial_bytes <= partial_limit && short_blocks(p.block, tiled, K)) {
+            p.tiled = tiled;
+            p.block.cfg = -1;
         }
     }
     return p;
@@ -579,9 +616,9 @@ fp6_status launch_prompt_chunk(const void *weights, const void *scales, const vo
                                                          stream);
     if constexpr (weights_of<Src>() != Weights::kFp16) {
         FP6_TILED_CASE(2, 4, 4, 1)
+        FP6_TILED_CASE(2, 4, 4, 2)
     }
     if constexpr (weights_of<Src>() == Weights::kPacked) {
-        FP6_TILED_CASE(2, 4, 4, 2)
         FP6_TILED_CASE(2, 4, 8, 1)
         FP6_TILED_CASE(2, 8, 8, 1)
     }

@@ -139,3 +139,22 @@ def test_plan_reaches_the_block_kernel_unforced(pkg):
     # both against fp32 products of the de-quantized weights (rounded to fp16 once: another 2^-11)
     check_linear(auto.cpu().numpy(), ref, "automatic")
     check_linear(other.cpu().numpy(), ref, "256x128")
+
+
+@pytest.mark.parametrize("M,K,N,kernel,split", [
+    (560, 512, 385, TILED, 1), (528, 1280, 130, TILED, 1), (528, 1536, 130, BLOCK, 1),            # up to 128 blocks
+    (4112, 512, 513, TILED, 1), (4112, 1024, 513, BLOCK, 1),                                        # more of them
+    (9232, 512, 385, BLOCK, 1),                                                                    # two rounds of the tiled kernel
+    (560, 2048, 150, TILED, 2), (16, 6656, 129, TILED, 6), (2064, 3584, 385, BLOCK, 3),            # k slices
+    (16, 16384, 129, TILED, 16), (16, 20480, 129, BLOCK, 16), (20464, 3072, 118, TILED, 1)])
+def test_group_scales_with_few_k_tiles_per_block(pkg, M, K, N, kernel, split):
+    """Either side of the rule that gives short blocks to the tiled kernel, as the automatic plan chooses."""
+    print("group scales M=%d K=%d N=%d" % (M, K, N), flush=True)
+    p = plan(pkg.load_library(), "fp6g", M, N, K)
+    assert (p.kernel, p.split_k) == (kernel, split)
+    W, X = workloads.make_weights(M, K, 1, device="cuda"), workloads.make_activations(N, K, 2, device="cuda")
+    weights = pkg.fp6g_quantize_pack(W)
+    outs = [pkg.fp6g_linear(*weights, X, M, K) for _ in range(2)]
+    assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+    dense = pkg.fp6g_unpack(*weights, M, K)
+    check_linear(outs[0].cpu().numpy(), (X.float() @ dense.float().t()).cpu().numpy().astype(np.float64), "group scales")
