@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 from functools import lru_cache
+from operator import index
 from pathlib import Path
 from typing import Optional, Tuple
 
@@ -155,6 +156,7 @@ def _entry(name: str):
 
 @lru_cache(maxsize=4096)
 def _packed_bytes(prefix: str, M: int, K: int) -> int:
+    """Kept by value, so callers pass index(M), index(K): a size may come as a tensor that changes between calls."""
     return int(_entry(prefix + "_packed_bytes")(M, K))
 
 
@@ -244,7 +246,7 @@ def _linear(prefix: str, packed, scales, X, M, K, out, workspace):
     if X.dim() != 2 or X.shape[1] != K:
         raise Fp6Error("X must be [N][K]")
     N = X.shape[0]
-    nbytes = _packed_bytes(prefix, M, K)
+    nbytes = _packed_bytes(prefix, index(M), index(K))
     if nbytes == 0 or N == 0:
         _check(2)
     if packed.numel() != nbytes or scales.numel() != M:
@@ -309,7 +311,7 @@ def _linear_fused(prefix, packed, scales, X, M, K, bias, residual, gated, out, w
         raise Fp6Error("X must be [N][K]")
     N = X.shape[0]
     base = "fp6" if prefix == "fp6g" else prefix
-    nbytes = _packed_bytes(base, M, K)
+    nbytes = _packed_bytes(base, index(M), index(K))
     if nbytes == 0 or N == 0 or (prefix == "fp6g" and (group <= 0 or K % group)):
         _check(2)
     n_scales = M * (K // group) if prefix == "fp6g" else M

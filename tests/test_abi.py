@@ -173,3 +173,29 @@ def test_binding_refuses_outputs_of_the_wrong_size(name, shape, monkeypatch):
     size = () if name == "fp16_linear" else (M, K)
     with pytest.raises(binding.Fp6Error, match="out"):
         getattr(binding, name)(*weights, X, *size, out=out)
+
+
+@pytest.mark.parametrize("name", ["fp6_linear", "fp6_linear_fused"])
+def test_binding_takes_sizes_of_any_integer_type(name, monkeypatch):
+    """Sizes are looked up once per value, not per object: a 0-d tensor may change, an array cannot be a key."""
+    import numpy as np
+    import torch
+
+    from paper_2401_14112_amd import binding
+
+    lib = binding.load_library()
+    entry, launches = lambda n: getattr(lib, n) if n.endswith("_bytes") else lambda *a: launches.append(n) or 0, []
+    monkeypatch.setattr(binding, "_entry", entry)
+    monkeypatch.setattr(binding, "_dev", lambda t, dtype, what: t)
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
+    K = np.array(256)
+
+    def call(M, rows):
+        getattr(binding, name)(torch.zeros(lib.fp6_packed_bytes(rows, 256), dtype=torch.uint8), torch.zeros(rows, dtype=torch.float16),
+                               torch.zeros((2, 256), dtype=torch.float16), M, K, out=torch.zeros((2, rows), dtype=torch.float16))
+
+    M = torch.tensor(64)
+    call(M, 64)
+    M.fill_(128)
+    call(M, 128)
+    assert launches.count(name) == 2
