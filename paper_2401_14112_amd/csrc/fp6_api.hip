@@ -228,7 +228,6 @@ struct BlockShapeOf;
 template <> struct BlockShapeOf<false, 0> { typedef BlockShape<4, 8, 4, 2, 1, 1, 6, 1, false> type; };
 template <> struct BlockShapeOf<false, 1> { typedef BlockShape<4, 4, 4, 2, 1, 2, 5, 1, true> type; };
 template <> struct BlockShapeOf<false, 2> { typedef BlockShape<4, 4, 2, 2, 2, 1, 5, 2, true> type; };
-template <> struct BlockShapeOf<false, 3> { typedef BlockShape<4, 2, 2, 2, 2, 1, 6, 2, true> type; };
 template <> struct BlockShapeOf<true, 0> { typedef BlockShape<4, 8, 4, 2, 1, 1, 4, 1, true> type; };
 template <> struct BlockShapeOf<true, 1> { typedef BlockShape<4, 4, 4, 2, 1, 1, 6, 1, true> type; };
 template <> struct BlockShapeOf<true, 2> { typedef BlockShape<4, 4, 2, 2, 2, 1, 4, 1, true> type; };
@@ -379,7 +378,7 @@ double block_cost(const BlockPlan &p, int64_t K, Weights kind)
 //   8 to 16 slices                            4 1.10, 5 1.02, 6 0.96
 //   slices, more than 16 blocks on an XCD and 1.6 times the average   4 1.04, 5 1.00, 6 0.97
 //   256 x 128 blocks in slices                4 1.03, 5 0.96
-// (2048 x 4096, N = 265: 21.4 us against 17.9; 784 x 512, N = 636: 8.3 against 7.7.)
+// (2048 x 4096, N = 265: 21.2 us against 18.0; 784 x 512, N = 636: 8.2 against 7.7; 6448 x 2048, N = 245: 20.5 against 16.6.)
 bool short_blocks(const BlockPlan &b, const TiledPlan &tiled, int64_t K)
 {
     const int64_t blocks = (int64_t)tiled.row_blocks * tiled.n_blocks * tiled.split;
@@ -398,15 +397,18 @@ bool short_blocks(const BlockPlan &b, const TiledPlan &tiled, int64_t K)
 // Which kernel and block (us, this kernel against the tiled one in the same process):
 //   per-row packed weights: the 256 x 256 block, at up to 1.17x the rate of the tiled kernel's 256 x 128 one, where its
 //     rounds of 256 blocks and its padded tokens take at most 1.1x what that block's do - which also says that it
-//     needs no split-K (57344 x 8192, N = 4096 2657 against 3106; 28672 x 8192, N = 3000 1110 against 1167; 9216 x
+//     needs no split-K (57344 x 8192, N = 4096 2764 against 3186; 28672 x 8192, N = 3000 1110 against 1167; 9216 x
 //     9216, N = 1024, 144 tiles in one round against 288 in two, 172 against 206 with 6 bits, 162 against 188 with 4,
-//     202 against 219 with 5).  Beyond that it loses: 8192 x 8192, N = 1024 127 against 110, 28672 x 8192, N = 700
-//     344 against 294, 57344 x 4096, N = 300 175 against 155;
+//     202 against 219 with 5, 168 against 193 with 3).  Drawn calls of 256 to 57344 rows and 65 to 4096 tokens, time over
+//     that without it, median and largest: 6 bits 0.87, 0.98; 5 bits 0.93, 1.02; 4 bits 0.88, 0.98; 3 bits 0.90, 1.03 (800
+//     in all).  Beyond that rule it loses: 8192 x 8192, N = 1024 127 against 110, 28672 x 8192, N = 700 344 against 294,
+//     57344 x 4096, N = 300 175 against 155;
 //   group scales: always, except few rows and few tokens (8192 x 8192, N = 100: 31 against 30; 4096 x 4096 17 against
-//     13; but 28672 x 8192, N = 201 120 against 166, 16384 x 8192, N = 2048 497 against 740) and short blocks, see
+//     13; but 28672 x 8192, N = 201 107 against 160, 16384 x 8192, N = 2048 497 against 740) and short blocks, see
 //     short_blocks();
-//   fp16 weights: always (9216 x 9216, N = 256 84 against 163; 16384 x 8192, N = 2048 473 against 1176; 8192 x 8192,
-//     N = 100 44 against 49).
+//   fp16 weights: always (9216 x 9216, N = 256 64 against 155; 16384 x 8192, N = 2048 473 against 1176; 8192 x 8192,
+//     N = 100 38 against 43; 1536 x 4864, N = 241 16.4 against 32.8; 608 x 1024, N = 106 6.8 against 12.8; 3684 drawn
+//     calls of the range above: median 0.46, largest 0.93).
 // Among its blocks the cheapest by block_cost().
 PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind, size_t partial_limit = SIZE_MAX)
 {
@@ -498,7 +500,8 @@ fp6_status launch_tiled_cfg(const TiledPlan &p, const void *weights, const void 
 }
 
 // Both kernels address the activations with 32-bit byte offsets, so one launch takes at most this many
-// tokens (a multiple of the widest block); longer inputs are processed in chunks on the same stream.
+// tokens (a multiple of 128, so that a full chunk ends with whole tiled blocks and at most half a 256-token one);
+// longer inputs are processed in chunks on the same stream.
 int64_t prompt_chunk_tokens(int64_t K)
 {
     const int64_t fit = ((1ll << 31) - 1) / (2 * K);

@@ -9,13 +9,15 @@
 // What bounds it, measured: with every CU busy the chip is limited by power, not by issue slots.  A loop of nothing but
 // matrix instructions on random fp16 activations and e3m2 weights in registers reaches 2060-2130 TFLOP/s with the
 // 16 x 16 x 32 form (1700 with 32 x 32 x 16: hence the former); one 128-bit LDS read per four of them costs 7 %, one
-// per two 25 %; the engine clock falls to 1.6 GHz under the 256 x 256 block.  So a wave tile is tall (RT = 4: an
-// activation fragment read from LDS serves four matrix instructions) and the block is as large as the accumulators
-// allow (fewer copies from L2 per product: in an ablation the copies of activations cost 14 % and those of weights 8 %
-// of the 256 x 256 block's time).  The 6-bit conversion occupies the SIMD for 65 clk and is paid once per row tile and
-// token half: 1/NT of the matrix time.  Measured (57344 x 8192, N = 4096, 6 bits, gated): 3106 -> 2657 us = 1450
-// TFLOP/s; 9216 x 9216, N = 256, fp16: 169 -> 83 us (its weights no longer cross the L1 as half lines into
-// registers); 28672 x 8192, N = 201, group scales: 159 -> 116 us.
+// per two 25 %; under the 256 x 256 block the engine runs at 1.87 GHz with the matrix pipes 0.70 busy (57344 x 8192,
+// N = 4096, 6 bits).  So a wave tile is tall (RT = 4: an activation fragment read from LDS serves four matrix
+// instructions) and the block is as large as the accumulators allow (fewer copies from L2 per product).  The 6-bit
+// conversion occupies the SIMD for 65 clk and is paid once per row tile and token half: 1/NT of the matrix time.
+// Measured, before this kernel and with it, in one process each: 57344 x 8192, N = 4096, 6 bits 3186 -> 2764 us = 1392
+// TFLOP/s; 9216 x 9216, N = 256, fp16 155 -> 64 us (weights in the last-level cache); 28672 x 8192, N = 201, group scales
+// 160 -> 107 us.  Both operands of fp16 weights, and the activations of every format, are copied in pieces of 64 bytes per
+// row, so each 128-byte line is requested twice (fp16, 8192 x 22016, N = 512: 23.4 M requests from the L1 for 1.44 GB of
+// copies, the waves waiting 0.54 of their cycles and the matrix pipes 0.39 busy).
 // Tried and not kept: four more waves that only copy (two for activations, two for weights, each with a counter of its
 // own): -7 to +5 %; four waves of 128 x 64 (one per SIMD): equal; ring depths of 4 to 8 stages: within 3 %; the last
 // step as loops over tiles staged in LDS (a fifth of the code): 1-2 us slower per launch.
@@ -378,8 +380,7 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     // ---- requests.  Copy c of a stage of activations serves ring slot e = c / (BN/16) of the stage and token tile
     // c % (BN/16); slot e holds run e / WK of k group e % WK, which starts at run RUNS * (e % WK) of the k-tile.
     const rsrc_t x_rsrc = make_rsrc(X, (uint32_t)N * (uint32_t)K * 2u);
-    constexpr int XC = SR * WK * BN / 16 / WAVES;   // of activations, per wave
-    constexpr int AC = Src::kRunStaged ? SR * WK * BM / 16 / WAVES : 0;  // of run-staged weights, per wave
+    constexpr int XC = SR * WK * BN / 16 / WAVES;  // of activations, per wave
     uint32_t x_off[XC];
     int x_dst[XC];
     {
@@ -411,7 +412,7 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
         issue_load_to_lds_b128<0>(r, a_off + t * x_step + (run + e / WK + e % WK * RUNS) * 64,
                                   (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + slot + e * SLOT + BN * 64 + tile * 1024)));
     };
-    auto x_issue_one = [&](int t, int run, int i, int slot) {  // of both, for waves that copy everything
+    auto x_issue_one = [&](int t, int run, int i, int slot) {  // copy i of both: activations first, then run-staged weights
         if (i < XC)
             x_issue(t, run, i < XC ? i : 0, slot);
         else

@@ -477,6 +477,7 @@ __global__ __launch_bounds__(256) void probe_read_kernel(const uint8_t *__restri
 }
 
 // probe_mfma_kernel: every wave issues iters x 4 independent v_mfma_f32_32x32x16_f16 on register operands.
+typedef float float16_t __attribute__((ext_vector_type(16)));
 __global__ __launch_bounds__(256) void probe_mfma_kernel(int iters, float *__restrict__ sink)
 {
     const half_t one = (half_t)1.0f, tiny = (half_t)0.0009765625f;
