@@ -38,7 +38,7 @@ struct StreamShapeOf {
     typedef StreamShape<c.nt, c.waves, c.depth, c.stage, c.spread, c.deal> type;
 };
 constexpr int kStreamMaxN = 64;  // token counts up to this use the streaming kernel
-constexpr int kCus = 256;
+constexpr int kCus = kXcds * kCusPerXcd;
 
 std::atomic<int> g_forced_split{0};
 
@@ -383,7 +383,7 @@ bool short_blocks(const BlockPlan &b, const TiledPlan &tiled, int64_t K)
 {
     const int64_t blocks = (int64_t)tiled.row_blocks * tiled.n_blocks * tiled.split;
     const int64_t fullest = (int64_t)((tiled.row_blocks + kXcds - 1) / kXcds) * tiled.n_blocks * tiled.split;
-    if (fullest > kCus / kXcds)
+    if (fullest > kCusPerXcd)
         return false;
     const int64_t k_tiles = (K / kTileK + b.split - 1) / b.split;
     if (b.split == 1)
