@@ -180,11 +180,11 @@ template <class Src>
 int launch(const void *w, const void *sc, const void *X, void *Y, int64_t M, int64_t N, int64_t K, void *ws, hipStream_t st)
 {
     if (N <= 16)
-        return launch_stream<Src, StreamShape<1, 8, 2, 1, 1, true>>(w, sc, X, Y, M, N, K, ws, st);
+        return launch_stream<Src, StreamShape<1, 8, 1, 2>>(w, sc, X, Y, M, N, K, ws, st);
     if (N <= 32)
-        return launch_stream<Src, StreamShape<2, 8, 2, 1, 1, true>>(w, sc, X, Y, M, N, K, ws, st);
+        return launch_stream<Src, StreamShape<2, 8, 1, 2>>(w, sc, X, Y, M, N, K, ws, st);
     if (N <= 64)
-        return launch_stream<Src, StreamShape<4, 8, 2, 1, 1, true>>(w, sc, X, Y, M, N, K, ws, st);
+        return launch_stream<Src, StreamShape<4, 8, 1, 2>>(w, sc, X, Y, M, N, K, ws, st);
     return launch_tiled<Src>(w, sc, X, Y, M, N, K, ws, st);
 }
 

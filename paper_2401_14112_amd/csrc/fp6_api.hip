@@ -4,6 +4,7 @@
 #include "../../include/fp6_bench.h"
 
 #include <atomic>
+#include <initializer_list>
 
 #include "fp6_device.hpp"
 #include "linear_stream.hpp"
@@ -16,27 +17,36 @@ namespace {
 using namespace fp6;
 
 constexpr int kLayoutVersion = 4;  // 4: 3-bit tiles of 512 columns (6-, 5-, 4-bit streams as in 3)
-// Configurations of the streaming kernel: {token tiles per wave, waves per block, weight tiles in flight per
-// wave, k-tiles per activation stage, iterations over which the activation copies of a stage are spread,
-// k-tiles dealt round-robin to the split-K slices}.
-// For N <= 16 there are two block heights; the plan takes the one that fills the chip best for the shape.
+// Configurations of the streaming kernel: {token tiles per wave, row tiles per block, groups of k-tiles per block (one wave
+// each), weight tiles in flight per wave, tokens of a token tile that are staged}.
 struct StreamCfg {
-    int nt, waves, depth, stage, spread;
-    bool deal;
+    int nt, wm, wk, depth, xr;
 };
-constexpr int kStreamCfgs = 4;
-constexpr StreamCfg kStreamCfg[kStreamCfgs] = {{1, 4, 4, 4, 1, true}, {1, 8, 2, 1, 1, true}, {2, 8, 2, 1, 1, true},
-                                               {4, 8, 2, 1, 1, true}};
+// Packed weights.  First of each kind the one that the tuning hook for the split factor pins and that layers with more row
+// blocks than CUs take.
+constexpr StreamCfg kStreamCfg[] = {{1, 8, 1, 2, 2},  {1, 4, 2, 2, 2},  {1, 2, 4, 2, 2},  {1, 1, 8, 2, 2},
+                                    {1, 8, 1, 2, 8},  {1, 4, 2, 2, 8},  {1, 2, 4, 2, 8},  {1, 1, 8, 2, 8},
+                                    {1, 8, 1, 2, 16}, {1, 4, 2, 2, 16}, {1, 2, 4, 2, 16}, {1, 1, 8, 2, 16},
+                                    {2, 8, 1, 2, 16}, {2, 6, 1, 2, 16}, {2, 4, 2, 2, 16}, {2, 2, 4, 2, 16},
+                                    {3, 8, 1, 2, 16}, {3, 6, 1, 2, 16}, {3, 4, 2, 2, 16},
+                                    {4, 8, 1, 2, 16}, {4, 6, 1, 2, 16}, {4, 4, 2, 2, 16}};
 // fp16 weights (staged through LDS, 8 KB per tile in flight): depths and block heights that fit the LDS of a
-// CU beside the activation stages.  Measured on 8192x22016: all shapes of a token count within 2 us of each
-// other, dealt slices 1-2 us ahead of contiguous ones.
-constexpr StreamCfg kStreamCfgFp16[kStreamCfgs] = {{1, 4, 4, 1, 1, true}, {1, 8, 2, 2, 1, true}, {2, 8, 2, 1, 1, true},
-                                                   {4, 4, 2, 1, 1, true}};
+// CU beside the activation stages.
+constexpr StreamCfg kStreamCfgFp16[] = {{1, 8, 1, 2, 16}, {1, 4, 1, 4, 16}, {1, 4, 2, 2, 16}, {1, 1, 4, 2, 16},
+                                        {2, 8, 1, 2, 16}, {2, 6, 1, 2, 16}, {2, 2, 2, 2, 16},
+                                        {3, 4, 1, 2, 16}, {3, 6, 1, 2, 16},
+                                        {4, 4, 1, 2, 16}, {4, 6, 1, 2, 16}};
+constexpr int kStreamCfgs = sizeof(kStreamCfg) / sizeof(kStreamCfg[0]), kStreamCfgsFp16 = sizeof(kStreamCfgFp16) / sizeof(kStreamCfgFp16[0]);
 template <bool PACKED, int C>
 struct StreamShapeOf {
     static constexpr StreamCfg c = PACKED ? kStreamCfg[C] : kStreamCfgFp16[C];
-    typedef StreamShape<c.nt, c.waves, c.depth, c.stage, c.spread, c.deal> type;
+    typedef StreamShape<c.nt, c.wm, c.wk, c.depth, c.xr> type;
 };
+constexpr int kMaxLds = 160 * 1024;
+constexpr int stream_lds_bytes(const StreamCfg &c, int tile_cols, int lds_tile)
+{
+    return 2 * c.wk * c.nt * (tile_cols / 32) * c.xr / 16 * 1024 + c.wm * c.wk * c.depth * lds_tile;
+}
 constexpr int kStreamMaxN = 64;  // token counts up to this use the streaming kernel
 constexpr int kCus = kXcds * kCusPerXcd;
 
@@ -88,6 +98,7 @@ struct WorkspaceRef {
     void *base;
     size_t bytes;
     size_t counter_region;  // its first bytes: kStaticCounterBytes or counter_region_bytes()
+    bool own = false;       // the library's buffer
     // the buffers of a launch whose plan needs counter_bytes + partial_bytes; FP6_OK when they fit
     fp6_status view(size_t counter_bytes, size_t partial_bytes, SplitBuffers &out) const
     {
@@ -105,78 +116,150 @@ struct WorkspaceRef {
     }
 };
 
+// The weights a launch reads, as the plan sees them.
+struct StreamWeights {
+    bool packed, grouped;
+    int bits;       // per weight
+    int tile_cols;  // columns of a weight tile in the streaming kernel
+    int lds_tile;   // bytes of LDS that a tile in flight takes
+};
+// Configurations that exist for a format: those that fit the LDS.  Group scales beyond 8 tokens go without the block of two row
+// tiles and keep their k slices (8192 x 2048, N = 16 6.4 us with two slices of four row tiles, 5.7 with that block).
+constexpr bool stream_cfg_built(const StreamCfg &c, const StreamWeights &w)
+{
+    return stream_lds_bytes(c, w.tile_cols, w.lds_tile) <= kMaxLds && !(w.grouped && c.nt == 1 && c.wm == 2 && c.xr == 16);
+}
+template <class Src>  // the source of a format, as the entry points name it
+constexpr StreamWeights stream_weights_of()
+{
+    typedef typename Src::StreamSource S;
+    return {S::kPackedConfigs, std::is_same_v<S, PackedFp6GroupSource>, S::kBits, S::kTileCols, S::kLdsTileBytes};
+}
+
 struct StreamPlan {
     int cfg;         // index into kStreamCfg / kStreamCfgFp16
-    int nt;          // 16-token tiles handled per launch
     int split;       // split-K factor
     int row_blocks;  // blocks along M
     size_t counter_bytes, partial_bytes;  // 0 without k slices
+    // What the call asks its caller for.  A call is refused without the workspace that the size query names, and the query
+    // does not depend on the block chosen: a shape whose blocks of eight row tiles would take k slices asks for those also
+    // where its block needs none.
+    size_t required_counters, required_partials;
 };
 
-// The layer is bound by memory, every block streams the same number of bytes, and one block per CU is
-// resident: the launch should be ONE round of at most 256 blocks, as many as possible.  Measured on the
-// 70B-class shapes at N = 16: 240 blocks of 8 waves beat 320 or 480 blocks of 4 waves by 15-20 %, and 172
-// blocks in one round beat 344 blocks in two.  So: for every available block height, the largest split-K
-// factor that keeps row blocks x S <= 256 (at least two k-tiles per slice); take the candidate with the
-// most blocks, on a tie the one with the taller blocks (more rows share each copy of the activations; with
-// the k-tiles dealt to the slices a larger S no longer costs a sweeping front of its own).
-StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, bool packed, int tile_cols = kTileK)
+// k slices and token tiles of the blocks of eight (four) row tiles for whose partial sums a caller's workspace is sized.
+struct StreamSlices {
+    int64_t split, nt;
+};
+StreamSlices stream_slices_of_shape(int64_t M, int64_t N, int64_t KT, bool packed)
 {
-    const StreamCfg *table = packed ? kStreamCfg : kStreamCfgFp16;
-    const int64_t row_tiles = M / kTileRows;
-    const int64_t KT = (K + tile_cols - 1) / tile_cols;  // steps of the streaming kernel for this source
-    const int first = N <= 16 ? 0 : (N <= 32 ? 2 : 3);
-    const int last = N <= 16 ? 1 : first;
-    const int64_t forced = g_forced_split.load(std::memory_order_relaxed);
-    const int64_t max_split = KT >= 4 ? KT / 2 : 1;  // at least two k-tiles per slice
-    int best = first;
-    int64_t best_s = 1, best_blocks = -1;
-    bool best_single = false;
-    for (int c = first; c <= last; ++c) {
-        const int64_t rb = (row_tiles + table[c].waves - 1) / table[c].waves;
-        int64_t s = forced > 0 ? forced : kCus / rb;
-        if (s > max_split)
-            s = max_split;
-        if (s > 64)
-            s = 64;
-        if (s < 1)
-            s = 1;
-        // the kernel addresses the partial tiles with 32-bit byte offsets
-        while (s > 1 && (uint64_t)s * (uint64_t)row_tiles * (uint64_t)table[c].nt * 1024u >= (1ull << 31))
+    const int64_t row_tiles = M / kTileRows, max_split = KT >= 4 ? KT / 2 : 1;
+    const bool four = !packed && N > 32;
+    StreamSlices best{1, N <= 16 ? 1 : N <= 32 ? 2 : 4};
+    int64_t best_blocks = -1;
+    for (int waves = N <= 16 || four ? 4 : 8; waves <= (four ? 4 : 8); waves += 4) {
+        const int64_t rb = (row_tiles + waves - 1) / waves;
+        int64_t s = kCus / rb;
+        s = s > max_split ? max_split : s;
+        s = s > 64 ? 64 : s < 1 ? 1 : s;
+        while (s > 1 && (uint64_t)s * (uint64_t)row_tiles * (uint64_t)best.nt * 1024u >= (1ull << 31))
             s /= 2;
-        // ... and, with the k-tiles dealt to the slices, the weights with 32-bit offsets that step by s k-tiles
-        // and run up to 20 steps past the end of a slice (look-ahead of the pipeline; those read as zeros)
-        while (s > 1 && table[c].deal && (uint64_t)(KT + 20 * s) * (uint64_t)row_tiles * kTileBytes >= (1ull << 31))
+        while (s > 1 && (uint64_t)(KT + 20 * s) * (uint64_t)row_tiles * kTileBytes >= (1ull << 31))
             s /= 2;
         const int64_t blocks = rb * s;
         const bool single = blocks <= kCus;
-        bool better;
-        if (best_blocks < 0)
-            better = true;
-        else if (single != best_single)
-            better = single;
-        else if (single)
-            better = blocks > best_blocks || (blocks == best_blocks && (table[c].deal ? s > best_s : s < best_s));
-        else
-            better = blocks < best_blocks;  // several rounds either way: the fewer, taller blocks
-        if (better) {
-            best = c;
-            best_s = s;
+        if (best_blocks < 0
+            || (single ? best_blocks > kCus || blocks > best_blocks || (blocks == best_blocks && s > best.split)
+                       : best_blocks > kCus && blocks < best_blocks)) {
+            best.split = s;
             best_blocks = blocks;
-            best_single = single;
+        }
+    }
+    return best;
+}
+
+// The launch's buffers in a caller's workspace, which is refused unless it holds what the call asks for; the library's own
+// buffer has no such promise to keep.
+fp6_status stream_buffers(const StreamPlan &p, const WorkspaceRef &workspace, SplitBuffers &buf)
+{
+    return workspace.own ? workspace.view(p.counter_bytes, p.partial_bytes, buf) : workspace.view(p.required_counters, p.required_partials, buf);
+}
+
+// Estimated time of a launch, us.  A stage (one k-tile per wave) of a block takes 0.38 us and 5 ns per KB of weights,
+// 9.5 ns per KB of activations and from three token tiles on 80 ns for each, on a CU that does not wait for memory; the
+// launch as a whole is no faster than 6.9 TB/s, and then half of the activation time still shows; a launch with k slices
+// hands them over, one with groups of k-tiles adds them up in LDS.
+double stream_cost(const StreamCfg &c, int64_t M, int64_t K, int64_t s, const StreamWeights &w)
+{
+    const int64_t KT = (K + w.tile_cols - 1) / w.tile_cols;
+    const double blocks = (double)((M / kTileRows + c.wm - 1) / c.wm * s), rounds = blocks > kCus ? blocks / kCus : 1.0;
+    const double stages = rounds * (double)(((KT + s - 1) / s + c.wk - 1) / c.wk);
+    const double tile_kb = w.tile_cols / 512.0;  // of one bit per weight
+    const double weight_kb = tile_kb * c.wm * c.wk * w.bits, x_kb = tile_kb * 16.0 * c.wk * c.nt * c.xr / 16.0;
+    const double x_us = 0.0095 * x_kb + (c.nt > 2 ? 0.08 * c.nt * w.tile_cols / kTileK : 0.0);
+    const double handover = s > 1 ? 0.5 + (double)s * (0.17 + 0.15 * c.nt) : 0.0, groups = c.wk > 1 ? 0.1 + 0.05 * c.wk * c.nt : 0.0;
+    const double alone = stages * (0.38 + (w.packed ? 0.005 : 0.016) * weight_kb + x_us) + handover;
+    const double memory = (double)M * (double)K * w.bits / 8.0 / (w.packed ? 6.9e6 : 5.4e6) + stages * 0.5 * x_us + 0.3 * handover;
+    return (alone > memory ? alone : memory) + groups;
+}
+
+// The block and the split-K factor with the least estimated time, with no more partial sums than the caller's workspace
+// holds.  Few row tiles: fewer of them per block and more groups of k-tiles, so that the chip is full without k slices
+// (4096 x 4096, N = 1 8.4 us with S = 8 and eight row tiles, 4.7 with one; 2048 x 16384, N = 1 13.2 -> 7.8; 8192 x 8192,
+// N = 1 11.6 -> 10.2); more tokens: more row tiles, which share the copies of the activations (8192 x 22016, N = 16 23.0 us
+// with eight, 26.0 with two).  Six row tiles where eight leave CUs idle (12288 x 12288, N = 45 28.4 -> 25.6).
+StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, const StreamWeights &w)
+{
+    const StreamCfg *table = w.packed ? kStreamCfg : kStreamCfgFp16;
+    const int64_t row_tiles = M / kTileRows;
+    const int64_t KT = (K + w.tile_cols - 1) / w.tile_cols;  // steps of the streaming kernel for this source
+    const int64_t forced = g_forced_split.load(std::memory_order_relaxed);
+    const int64_t max_split = KT >= 4 ? KT / 2 : 1;  // at least two k-tiles per slice
+    const int nt = (int)((N + 15) / 16), xr = !w.packed || N > 8 ? 16 : N > 2 ? 8 : 2;
+    const StreamSlices shape = stream_slices_of_shape(M, N, KT, w.packed);
+    StreamPlan p{-1, 1, 0, 0, 0, 0, 0};
+    double best = 0.0;
+    for (int i = 0; i < (w.packed ? kStreamCfgs : kStreamCfgsFp16); ++i) {
+        const StreamCfg &c = table[i];
+        if (c.nt != nt || c.xr != xr || !stream_cfg_built(c, w))
+            continue;
+        const int64_t rb = (row_tiles + c.wm - 1) / c.wm;
+        if (p.cfg >= 0 && rb > kCus)
+            continue;  // a second round, most of it idle: one row of blocks more than CUs costs up to half as much again
+        int64_t s = forced > 0 ? forced : kCus / rb;
+        s = s > max_split ? max_split : s;
+        if (forced <= 0 && s * nt > shape.split * shape.nt)
+            s = shape.split * shape.nt / nt;
+        s = s > 64 ? 64 : s < 1 ? 1 : s;
+        // the kernel addresses the partial tiles with 32-bit byte offsets
+        while (s > 1 && (uint64_t)s * (uint64_t)row_tiles * (uint64_t)nt * 1024u >= (1ull << 31))
+            s /= 2;
+        // ... and, with the k-tiles dealt to slices and groups, the weights with 32-bit offsets that step by s * wk k-tiles
+        // and run up to five such steps past the end of a slice (look-ahead of the pipeline; those read as zeros)
+        while (s > 1 && (uint64_t)(KT + (c.wk > 4 ? 5 * c.wk : 20) * s) * (uint64_t)row_tiles * kTileBytes >= (1ull << 31))
+            s /= 2;
+        for (;; s /= 2) {  // the most slices, then halves
+            const double cost = stream_cost(c, M, K, s, w);
+            if (p.cfg < 0 || cost < best) {
+                p.cfg = i;
+                p.split = (int)s;
+                p.row_blocks = (int)rb;
+                best = cost;
+            }
+            if (forced > 0 || s == 1)
+                break;
         }
         if (forced > 0)
             break;  // the tuning hook pins the first candidate, so that tests reach every split factor
     }
-    StreamPlan p;
-    p.cfg = best;
-    p.nt = table[best].nt;
-    p.split = (int)best_s;
-    p.row_blocks = (int)((row_tiles + table[best].waves - 1) / table[best].waves);
-    p.counter_bytes = p.partial_bytes = 0;
+    const auto counters = [&] { return ((size_t)row_tiles * sizeof(int) + 255) / 256 * 256; };  // one per row tile
+    const auto partials = [&](int64_t s, int64_t n) { return (size_t)s * (size_t)row_tiles * (size_t)n * 64 * sizeof(float4_t); };
     if (p.split > 1) {
-        p.counter_bytes = (((size_t)row_tiles * sizeof(int)) + 255) / 256 * 256;  // one arrival counter per row tile
-        p.partial_bytes = (size_t)p.split * (size_t)row_tiles * (size_t)p.nt * 64 * sizeof(float4_t);
+        p.counter_bytes = p.required_counters = counters();
+        p.partial_bytes = p.required_partials = partials(p.split, nt);
+    } else if (forced <= 0 && shape.split > 1) {
+        p.required_counters = counters();
+        p.required_partials = partials(shape.split, shape.nt);
     }
     return p;
 }
@@ -529,9 +612,9 @@ size_t counter_region_bytes(int64_t M, int64_t N, int64_t K)
         return bytes;
     auto at_least = [&](size_t b) { bytes = b > bytes ? b : bytes; };
     if (N <= kStreamMaxN) {
-        at_least(plan_stream(M, N, K, true).counter_bytes);
-        at_least(plan_stream(M, N, K, true, PackedFp3Source::StreamSource::kTileCols).counter_bytes);
-        at_least(plan_stream(M, N, K, false).counter_bytes);
+        at_least(plan_stream(M, N, K, stream_weights_of<PackedFp6Source>()).counter_bytes);
+        at_least(plan_stream(M, N, K, stream_weights_of<PackedFp3Source>()).counter_bytes);
+        at_least(plan_stream(M, N, K, stream_weights_of<PlainFp16Source>()).counter_bytes);
         return bytes;
     }
     for (Weights kind : {Weights::kPacked, Weights::kGrouped, Weights::kFp16})
@@ -548,9 +631,15 @@ size_t split_workspace_bytes(size_t partial_bytes, int64_t M, int64_t N, int64_t
     return partial_bytes > 0 ? counter_region_bytes(M, N, K) + partial_bytes : 0;
 }
 
-size_t stream_workspace_bytes(int64_t M, int64_t N, int64_t K, bool packed, int tile_cols = kTileK)
+// The largest of the given weights (formats that share a size query).
+size_t stream_workspace_bytes(int64_t M, int64_t N, int64_t K, std::initializer_list<StreamWeights> weights)
 {
-    return split_workspace_bytes(plan_stream(M, N, K, packed, tile_cols).partial_bytes, M, N, K);
+    size_t bytes = 0;
+    for (const StreamWeights &w : weights) {
+        const size_t b = plan_stream(M, N, K, w).required_partials;
+        bytes = b > bytes ? b : bytes;
+    }
+    return split_workspace_bytes(bytes, M, N, K);
 }
 
 size_t prompt_workspace_bytes(int64_t M, int64_t N, int64_t K, Weights kind)
@@ -669,13 +758,14 @@ fp6_status launch_stream_cfg(const StreamPlan &p, const void *weights, const voi
 {
     typedef typename StreamShapeOf<Src::kPackedConfigs, C>::type Shape;
     constexpr StreamCfg c = StreamShapeOf<Src::kPackedConfigs, C>::c;
+    static_assert(Shape::template lds_bytes<Src>() == stream_lds_bytes(c, Src::kTileCols, Src::kLdsTileBytes), "the plan's LDS");
     auto kernel = linear_stream_kernel<Src, Shape>;
     constexpr size_t lds = Shape::template lds_bytes<Src>();
     static_assert(lds <= 160 * 1024, "activation stages and staged weight tiles exceed the LDS of a CU");
     static std::atomic<uint64_t> lds_done{0};  // per instantiation
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds, lds_done))
         return FP6_ERR_HIP;
-    const dim3 grid((unsigned)p.row_blocks, (unsigned)p.split), block(c.waves * 64);  // x runs fastest: row blocks of one k slice
+    const dim3 grid((unsigned)p.row_blocks, (unsigned)p.split), block(Shape::kThreads);  // x runs fastest: row blocks of one k slice
     // tokens are processed 16*nt at a time; each pass re-streams the weights
     const int64_t step = 16 * c.nt;
     const int64_t Mout = epi.gated ? M / 2 : M;
@@ -695,23 +785,30 @@ fp6_status launch_stream_cfg(const StreamPlan &p, const void *weights, const voi
     return FP6_OK;
 }
 
-template <class Src>
+template <class Src, int C = 0>
+fp6_status launch_stream_plan(const StreamPlan &p, const void *weights, const void *scales, const void *X, void *Y, int64_t M,
+                              int64_t N, int64_t K, float4_t *partials, int *counters, const Epilogue &epi, hipStream_t stream)
+{
+    if constexpr (C < (Src::kPackedConfigs ? kStreamCfgs : kStreamCfgsFp16)) {
+        if constexpr (stream_cfg_built(StreamShapeOf<Src::kPackedConfigs, C>::c, stream_weights_of<Src>()))
+            if (p.cfg == C)
+                return launch_stream_cfg<Src, C>(p, weights, scales, X, Y, M, N, K, partials, counters, epi, stream);
+        return launch_stream_plan<Src, C + 1>(p, weights, scales, X, Y, M, N, K, partials, counters, epi, stream);
+    }
+    return FP6_ERR_SHAPE;  // not reached: plan_stream only picks the configurations above
+}
+
+template <class Src>  // the source of a format, as the entry points name it
 fp6_status launch_stream(const void *weights, const void *scales, const void *X, void *Y, int64_t M, int64_t N,
                          int64_t K, const WorkspaceRef &workspace, const Epilogue &epi, hipStream_t stream)
 {
-    const StreamPlan p = plan_stream(M, N, K, Src::kPackedConfigs, Src::kTileCols);
+    const StreamPlan p = plan_stream(M, N, K, stream_weights_of<Src>());
     SplitBuffers buf;
-    const fp6_status fits = workspace.view(p.counter_bytes, p.partial_bytes, buf);
+    const fp6_status fits = stream_buffers(p, workspace, buf);
     if (fits != FP6_OK)
         return fits;
-    int *counters = buf.counters;
-    float4_t *partials = reinterpret_cast<float4_t *>(buf.partials);
-    switch (p.cfg) {
-    case 0: return launch_stream_cfg<Src, 0>(p, weights, scales, X, Y, M, N, K, partials, counters, epi, stream);
-    case 1: return launch_stream_cfg<Src, 1>(p, weights, scales, X, Y, M, N, K, partials, counters, epi, stream);
-    case 2: return launch_stream_cfg<Src, 2>(p, weights, scales, X, Y, M, N, K, partials, counters, epi, stream);
-    default: return launch_stream_cfg<Src, 3>(p, weights, scales, X, Y, M, N, K, partials, counters, epi, stream);
-    }
+    return launch_stream_plan<typename Src::StreamSource>(p, weights, scales, X, Y, M, N, K,
+                                                          reinterpret_cast<float4_t *>(buf.partials), buf.counters, epi, stream);
 }
 
 template <class Fmt>
@@ -778,11 +875,11 @@ fp6_status static_scratch_address(void **out)
 // the call does not fit it.  Host arithmetic only.
 fp6_status static_plan(int64_t M, int64_t N, int64_t K, size_t &counter_bytes)
 {
-    const WorkspaceRef probe{reinterpret_cast<void *>(uintptr_t(256)), FP6_STATIC_SCRATCH_BYTES, kStaticCounterBytes};  // never dereferenced
+    const WorkspaceRef probe{reinterpret_cast<void *>(uintptr_t(256)), FP6_STATIC_SCRATCH_BYTES, kStaticCounterBytes, true};  // never dereferenced
     SplitBuffers unused;
     counter_bytes = 0;
     if (N <= kStreamMaxN) {
-        const StreamPlan p = plan_stream(M, N, K, true);
+        const StreamPlan p = plan_stream(M, N, K, stream_weights_of<PackedFp6Source>());
         counter_bytes = p.counter_bytes;
         return probe.view(p.counter_bytes, p.partial_bytes, unused);
     }
@@ -811,11 +908,10 @@ fp6_status packed_linear_impl(const void *packed, const void *scales_f16, const 
     if (!aligned16(packed) || !aligned16(scales_f16) || !aligned16(X_f16) || !aligned16(Y_f16) || !aligned16(epi.bias)
         || !aligned16(epi.residual))
         return FP6_ERR_ALIGN;
-    const WorkspaceRef ws{workspace, workspace_bytes, static_buffer ? kStaticCounterBytes : counter_region_bytes(M, N, K)};
+    const WorkspaceRef ws{workspace, workspace_bytes, static_buffer ? kStaticCounterBytes : counter_region_bytes(M, N, K), static_buffer};
     if (N > kStreamMaxN)
         return launch_prompt<Src>(packed, scales_f16, X_f16, Y_f16, M, N, K, ws, epi, static_cast<hipStream_t>(stream));
-    return launch_stream<typename Src::StreamSource>(packed, scales_f16, X_f16, Y_f16, M, N, K, ws, epi,
-                                                     static_cast<hipStream_t>(stream));
+    return launch_stream<Src>(packed, scales_f16, X_f16, Y_f16, M, N, K, ws, epi, static_cast<hipStream_t>(stream));
 }
 
 }  // namespace
@@ -844,7 +940,9 @@ size_t fp6_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
     if (!packed_shape_ok(M, K) || N <= 0)
         return 0;
     if (N <= kStreamMaxN)
-        return stream_workspace_bytes(M, N, K, true);
+        // fp5, fp4 and fp6g ask here too
+        return stream_workspace_bytes(M, N, K, {stream_weights_of<PackedFp6Source>(), stream_weights_of<PackedFp6GroupSource>(),
+                                                stream_weights_of<PackedFp5Source>(), stream_weights_of<PackedFp4Source>()});
     // fp6g_linear asks here too
     const size_t bytes = prompt_workspace_bytes(M, N, K, Weights::kPacked), grouped = prompt_workspace_bytes(M, N, K, Weights::kGrouped);
     return bytes > grouped ? bytes : grouped;
@@ -854,7 +952,7 @@ size_t fp16_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
     if (!shape_ok(M, K) || N <= 0)
         return 0;
-    return N <= kStreamMaxN ? stream_workspace_bytes(M, N, K, false)
+    return N <= kStreamMaxN ? stream_workspace_bytes(M, N, K, {stream_weights_of<PlainFp16Source>()})
                             : prompt_workspace_bytes(M, N, K, Weights::kFp16);
 }
 
@@ -885,12 +983,17 @@ fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int
     const WorkspaceRef ws{reinterpret_cast<void *>(uintptr_t(256)), workspace_bytes, region};  // never dereferenced
     SplitBuffers unused;
     if (N <= kStreamMaxN) {
-        const StreamPlan p = plan_stream(M, N, K, !fp16, weight_bits == 3 ? PackedFp3Source::StreamSource::kTileCols : kTileK);
-        const fp6_status fits = ws.view(p.counter_bytes, p.partial_bytes, unused);
+        const StreamWeights w = fp16               ? stream_weights_of<PlainFp16Source>()
+                                : weight_bits == 3 ? stream_weights_of<PackedFp3Source>()
+                                : weight_bits == 4 ? stream_weights_of<PackedFp4Source>()
+                                : weight_bits == 5 ? stream_weights_of<PackedFp5Source>()
+                                : grouped          ? stream_weights_of<PackedFp6GroupSource>() : stream_weights_of<PackedFp6Source>();
+        const StreamPlan p = plan_stream(M, N, K, w);
+        const fp6_status fits = stream_buffers(p, ws, unused);
         if (fits != FP6_OK)
             return fits;
-        *plan = {FP6_KERNEL_STREAM, 16 * (fp16 ? kStreamCfgFp16 : kStreamCfg)[p.cfg].waves, 16 * p.nt, p.split, 0, N,
-                 p.counter_bytes, region, p.partial_bytes};
+        const StreamCfg &c = (fp16 ? kStreamCfgFp16 : kStreamCfg)[p.cfg];
+        *plan = {FP6_KERNEL_STREAM, kTileRows * c.wm, 16 * c.nt, p.split, 0, N, p.counter_bytes, region, p.partial_bytes};
         return FP6_OK;
     }
     const int64_t chunk = prompt_chunk_tokens(K), first = token / chunk * chunk, tokens = N - first < chunk ? N - first : chunk;
@@ -1061,7 +1164,7 @@ size_t fp3_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
     if (!packed_shape_ok(M, K) || N <= 0)
         return 0;
-    return N <= kStreamMaxN ? stream_workspace_bytes(M, N, K, true, PackedFp3Source::StreamSource::kTileCols)
+    return N <= kStreamMaxN ? stream_workspace_bytes(M, N, K, {stream_weights_of<PackedFp3Source>()})
                             : prompt_workspace_bytes(M, N, K, Weights::kPacked);
 }
 
@@ -1152,7 +1255,7 @@ fp6_status fp16_linear(const void *W_f16, const void *X_f16, void *Y_f16, int64_
     if (N > kStreamMaxN)
         return launch_prompt<PlainFp16Source>(W_f16, nullptr, X_f16, Y_f16, M, N, K, ws, Epilogue{nullptr, nullptr, 0},
                                              static_cast<hipStream_t>(stream));
-    return launch_stream<PlainFp16Source::StreamSource>(W_f16, nullptr, X_f16, Y_f16, M, N, K, ws, Epilogue{nullptr, nullptr, 0},
+    return launch_stream<PlainFp16Source>(W_f16, nullptr, X_f16, Y_f16, M, N, K, ws, Epilogue{nullptr, nullptr, 0},
                                           static_cast<hipStream_t>(stream));
 }
 

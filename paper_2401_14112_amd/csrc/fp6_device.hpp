@@ -267,6 +267,7 @@ struct PackedFp6Source {
     static constexpr int kLdsTileBytes = 0;  // tiles in flight live in registers
     static constexpr int kTileCols = kTileK;  // columns of one weight tile in the streaming kernel
     static constexpr bool kHasScale = true;
+    static constexpr int kBits = 6;  // per weight
     static constexpr int kLoads = 3;
     // bytes from one k-tile of the slice to the next
     __device__ static __forceinline__ int tile_stride(int64_t RT) { return (int)(RT * kTileBytes); }
@@ -318,6 +319,7 @@ struct PackedFp6GroupSource {
     static constexpr int kLdsTileBytes = 0;  // tiles in flight live in registers
     static constexpr int kTileCols = kTileK;  // columns of one weight tile in the streaming kernel
     static constexpr bool kHasScale = false;  // no per-row factor in the epilogue
+    static constexpr int kBits = 6;  // per weight
     static constexpr int kLoads = 4;
     struct Tile {
         u32x4 p0, p1, p2;
@@ -411,6 +413,7 @@ struct PackedFp5Source {
     static constexpr int kLdsTileBytes = 0;  // tiles in flight live in registers
     static constexpr int kTileCols = kTileK;  // columns of one weight tile in the streaming kernel
     static constexpr bool kHasScale = true;
+    static constexpr int kBits = 5;  // per weight
     static constexpr int kLoads = 3;
     static constexpr int kTileBytes5 = 2560;
     __device__ static __forceinline__ int tile_stride(int64_t RT) { return (int)(RT * kTileBytes5); }
@@ -485,6 +488,7 @@ struct PackedFp4Source {
     static constexpr int kLdsTileBytes = 0;  // tiles in flight live in registers
     static constexpr int kTileCols = kTileK;  // columns of one weight tile in the streaming kernel
     static constexpr bool kHasScale = true;
+    static constexpr int kBits = 4;  // per weight
     static constexpr int kLoads = 2;
     static constexpr int kTileBytes4 = 2048;
     __device__ static __forceinline__ int tile_stride(int64_t RT) { return (int)(RT * kTileBytes4); }
@@ -555,6 +559,7 @@ struct PackedFp3WideSource {
     static constexpr int kLdsTileBytes = 0;  // tiles in flight live in registers
     static constexpr int kTileCols = 512;
     static constexpr bool kHasScale = true;
+    static constexpr int kBits = 3;  // per weight
     static constexpr int kLoads = 3;
     __device__ static __forceinline__ int tile_stride(int64_t RT) { return (int)(RT * kTileBytes3); }
     __device__ static __forceinline__ int k_offset(int f, int q) { return f * 32 + q * 8; }
@@ -600,6 +605,7 @@ struct PackedFp3Source {
     static constexpr int kLdsTileBytes = 0;
     static constexpr int kTileCols = kTileK;
     static constexpr bool kHasScale = true;
+    static constexpr int kBits = 3;  // per weight
     static constexpr int kLoads = 2;
     __device__ static __forceinline__ int k_offset(int f, int q) { return f * 32 + q * 8; }
     struct Stream {
@@ -671,6 +677,7 @@ struct StagedFp16Source {
     typedef StagedFp16Source StreamSource;  // the source the streaming kernel uses for this format
     static constexpr bool kPackedConfigs = false;
     static constexpr bool kHasScale = false;
+    static constexpr int kBits = 16;  // per weight
     static constexpr int kLoads = 8;
     static constexpr int kLdsTileBytes = 8192;
     static constexpr int kTileCols = kTileK;
@@ -752,7 +759,76 @@ struct Epilogue {
     int gated;               // nonzero: weight rows 2i (gate), 2i+1 (up) give output row i of M/2
 };
 
-// Rows m0 .. m0+3 (m0 % 4 == 0) of token column `col`: the four sums one lane holds after the MFMAs.
+// What the steps read, for rows m0 .. m0+3 (m0 % 4 == 0), requested on its own: in front of the arithmetic the loads are in
+// flight together, inside it each waits for the one before.
+struct RowTerms {
+    half4_t scale, bias;
+};
+template <bool kHasScale>
+__device__ __forceinline__ RowTerms row_terms(const Epilogue &e, const half_t *__restrict__ scales, int m0)
+{
+    RowTerms t = {};
+    if (kHasScale)
+        t.scale = *reinterpret_cast<const half4_t *>(scales + m0);
+    if (e.bias)
+        t.bias = *reinterpret_cast<const half4_t *>(e.bias + m0);
+    return t;
+}
+// ... of token column `col`: four rows, when gated the two output rows (the call has a residual).  No branch: the loads of two
+// branches would share registers, which the build's check of loads in flight reads as a late write.
+__device__ __forceinline__ half4_t residual_rows(const Epilogue &e, int col, int m0, int M)
+{
+    const half_t *p = e.residual + (e.gated ? (int64_t)col * (M >> 1) + (m0 >> 1) : (int64_t)col * M + m0);
+    const half2_t a = *reinterpret_cast<const half2_t *>(p), b = *reinterpret_cast<const half2_t *>(p + (e.gated ? 0 : 2));
+    return (half4_t){a[0], a[1], b[0], b[1]};
+}
+
+// Rows m0 .. m0+3 of token column `col`: the four sums one lane holds after the MFMAs.
+// Y and the residual are [tokens][M] (or [tokens][M/2] when gated).
+template <bool kHasScale>
+__device__ __forceinline__ void finish_rows(const Epilogue &e, const RowTerms &t, const half4_t &residual, const float4_t &sum,
+                                            int col, int m0, int M, half_t *Y)
+{
+    float v[4] = {sum[0], sum[1], sum[2], sum[3]};
+    if (kHasScale) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v[i] *= (float)t.scale[i];
+    }
+    if (e.bias) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v[i] += (float)t.bias[i];
+    }
+    if (!e.gated) {
+        if (e.residual) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                v[i] += (float)residual[i];
+        }
+        half4_t y;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            y[i] = (half_t)v[i];
+        *reinterpret_cast<half4_t *>(Y + (int64_t)col * M + m0) = y;
+    } else {
+        float o[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            o[i] = v[2 * i] / (1.0f + __expf(-v[2 * i])) * v[2 * i + 1];
+        if (e.residual) {
+            o[0] += (float)residual[0];
+            o[1] += (float)residual[1];
+        }
+        half2_t y;
+        y[0] = (half_t)o[0];
+        y[1] = (half_t)o[1];
+        *reinterpret_cast<half2_t *>(Y + (int64_t)col * (M >> 1) + (m0 >> 1)) = y;
+    }
+}
+// The same with the reads in place, one after the other: the form of the prompt-sized kernels, whose last step is a small part
+// of a launch and whose loops lose more by the registers of the other form (group scales, 118.0 -> 120.7 us on 28672 x 8192,
+// N = 201).
 // Y and the residual are [tokens][M] (or [tokens][M/2] when gated).
 template <bool kHasScale>
 __device__ __forceinline__ void finish_rows(const Epilogue &e, const half_t *__restrict__ scales, const float4_t &sum,

@@ -1,0 +1,44 @@
+"""The streaming kernel's plans (CPU only): what a call asks its caller for depends on the shape, not on the block chosen."""
+import random
+
+from launch_plans import BITS, STREAM, plan, workspace_bytes
+
+REFUSED = 3  # FP6_ERR_WORKSPACE
+REGION = 4096
+
+
+def _slices(width, M, N, K):
+    """k slices and token tiles of blocks of eight (four) row tiles, which the workspace is sized for."""
+    row_tiles, cols = M // 16, 512 if width == "fp3" else 256
+    k_tiles = -(-K // cols)
+    most = k_tiles // 2 if k_tiles >= 4 else 1
+    best = None
+    for waves in ([4] if width == "fp16" and N > 32 else [4, 8] if N <= 16 else [8]):
+        rb = -(-row_tiles // waves)
+        s = max(1, min(256 // rb, most, 64))
+        key = (rb * s <= 256, rb * s if rb * s <= 256 else -rb * s, s)
+        best = max(best, key) if best else key
+    return best[2], 1 if N <= 16 else 2 if N <= 32 else 4
+
+
+def test_what_a_call_asks_for():
+    import paper_2401_14112_amd as pkg
+
+    lib = pkg.load_library()
+    rng = random.Random(2)
+    without = with_slices = 0
+    for _ in range(3000):
+        width = rng.choice(list(BITS))
+        M, K = 16 * round(2 ** rng.uniform(0, 11.8)), 256 * round(2 ** rng.uniform(0, 6.8))
+        N = rng.randint(1, 1 << rng.randint(0, 6))
+        s, tiles = _slices(width, M, N, K)
+        most = REGION + s * (M // 16) * tiles * 1024 if s > 1 else 0
+        p = plan(lib, width, M, N, K)
+        assert p.kernel == STREAM and p.block_tokens >= N and p.split_k <= s * tiles
+        assert workspace_bytes(lib, width, M, N, K) <= most or width in ("fp6", "fp5", "fp4", "fp6g") and s > 1
+        # what was enough for eight row tiles is enough, and without any the call runs where those took no slices
+        assert plan(lib, width, M, N, K, workspace_bytes=most) != REFUSED, (width, M, N, K)
+        assert (plan(lib, width, M, N, K, workspace_bytes=0) == REFUSED) == (s > 1), (width, M, N, K)
+        with_slices += p.split_k > 1
+        without += p.split_k == 1 and s > 1
+    assert with_slices > 300 and without > 300
