@@ -297,19 +297,19 @@ std::atomic<int> g_forced_tile{0};  // 0 = automatic, else rows * 1024 + tokens 
 
 // ---- block kernel (prompt-sized N: fp16 weights, group-wise scales, and large products) -----------------------
 
-// Block shapes: {rows, tokens}.  Costs are ns per run of 32 columns with every CU busy (K = 8192, 16384 x 2048 outputs),
+// Block shapes: {rows, tokens}.  Costs are ns per run of 32 columns with most CUs busy (median of 2000 drawn calls, K >= 4096),
 // for fp16 weights and for 6-bit weights with group scales.
 struct BlockCfg {
     int rows, tokens;
     double fp16_ns, group_ns;
 };
 constexpr int kBlockCfgs = 4, kBlock256x256 = 0;
-constexpr BlockCfg kBlockCfg[kBlockCfgs] = {{256, 256, 924, 0}, {256, 128, 632, 485}, {128, 128, 333, 293}, {128, 64, 228, 0}};
+constexpr BlockCfg kBlockCfg[kBlockCfgs] = {{256, 256, 805, 0}, {256, 128, 590, 480}, {128, 128, 258, 293}, {128, 64, 198, 0}};
 // BlockShape<RT, NT, WM, WN, WK, SR, XST, WD, ADB> of each, for run-staged (fp16) and packed weights
 template <bool RUN_STAGED, int C>
 struct BlockShapeOf;
 template <> struct BlockShapeOf<false, 0> { typedef BlockShape<4, 8, 4, 2, 1, 1, 6, 1, false> type; };
-template <> struct BlockShapeOf<false, 1> { typedef BlockShape<4, 4, 4, 2, 1, 2, 5, 1, true> type; };
+template <> struct BlockShapeOf<false, 1> { typedef BlockShape<4, 4, 4, 2, 1, 2, 4, 1, true> type; };
 template <> struct BlockShapeOf<false, 2> { typedef BlockShape<4, 4, 2, 2, 2, 1, 5, 2, true> type; };
 template <> struct BlockShapeOf<true, 0> { typedef BlockShape<4, 8, 4, 2, 1, 1, 4, 1, true> type; };
 template <> struct BlockShapeOf<true, 1> { typedef BlockShape<4, 4, 4, 2, 1, 1, 6, 1, true> type; };
@@ -444,7 +444,10 @@ double block_cost(const BlockPlan &p, int64_t K, Weights kind)
     const double blocks = (double)p.row_blocks * p.n_blocks * p.split;
     const double rounds = (double)(((int64_t)blocks + kCus - 1) / kCus);
     const double runs = 8.0 * (double)((K / kTileK + p.split - 1) / p.split);
-    const double ns = rounds * (runs * (kind == Weights::kFp16 ? b.fp16_ns : b.group_ns) + 8000.0);
+    // 128-row blocks of fp16 weights fetch twice the bytes per product, and long rows of both operands share fewer L2 sets
+    // (258 ns up to K = 12288, 300 to 340 beyond 20000)
+    const double long_rows = b.rows == 128 && K > 12288 ? 1.0 + 0.25 * (double)((K < 28672 ? K : 28672) - 12288) / 12288.0 : 1.0;
+    const double ns = rounds * (runs * (kind == Weights::kFp16 ? b.fp16_ns * long_rows : b.group_ns) + 8000.0);
     return p.split == 1 ? ns : ns + (double)p.split * b.rows * b.tokens * 4.0 / 50.0 + (double)p.partial_bytes * 1.5e-4;
 }
 

@@ -15,9 +15,13 @@
 // conversion occupies the SIMD for 65 clk and is paid once per row tile and token half: 1/NT of the matrix time.
 // Measured, before this kernel and with it, in one process each: 57344 x 8192, N = 4096, 6 bits 3186 -> 2764 us = 1392
 // TFLOP/s; 9216 x 9216, N = 256, fp16 155 -> 64 us (weights in the last-level cache); 28672 x 8192, N = 201, group scales
-// 160 -> 107 us.  Both operands of fp16 weights, and the activations of every format, are copied in pieces of 64 bytes per
-// row, so each 128-byte line is requested twice (fp16, 8192 x 22016, N = 512: 23.4 M requests from the L1 for 1.44 GB of
-// copies, the waves waiting 0.54 of their cycles and the matrix pipes 0.39 busy).
+// 160 -> 107 us.  Where a stage is one run per k group, both operands of fp16 weights, and the activations of every format, are
+// copied in pieces of 64 bytes per row, so each 128-byte line is requested twice (fp16, 8192 x 22016, N = 512, 256 x 256: 23.4 M
+// requests from the L1 for 1.44 GB of copies, the waves waiting 0.54 of their cycles and the matrix pipes 0.39 busy).  Where it
+// is a pair of neighbouring runs they are copied in whole lines: fp16, 128 x 128 blocks, 4096 x 8192, N = 1024 80.3 -> 60.3 us, 8192 x
+// 8192, N = 128 45.6 -> 40.5; 128 x 64, 1536 x 4864, N = 241 16.6 -> 13.4; group scales, 256 x 128 with four stages instead of
+// five, 8192 x 22016, N = 512 179.1 -> 175.1.  It takes rings of four stages: with three, which is what the LDS holds of 256 x 128
+// fp16 blocks, each wait is for the copies just requested (82.9 -> 83.9 on 9216 x 9216, N = 256; 128 x 128 with three 83).
 // Tried and not kept: four more waves that only copy (two for activations, two for weights, each with a counter of its
 // own): -7 to +5 %; four waves of 128 x 64 (one per SIMD): equal; ring depths of 4 to 8 stages: within 3 %; the last
 // step as loops over tiles staged in LDS (a fifth of the code): 1-2 us slower per launch.
@@ -228,6 +232,13 @@ struct BlockShape {
         return n;
     }
     static constexpr int kStagesPerTile = RUNS / SR;
+    // A stage is two neighbouring runs: what is staged run by run is copied and stored as 64 columns, in whole 128-byte lines.
+    // (With two k groups that makes them take the even and the odd runs, which only run-staged weights can do.)
+    template <class Src>
+    static constexpr bool paired()
+    {
+        return SR * WK == 2 && (WK == 1 || Src::kRunStaged);
+    }
     template <class Src>
     static constexpr int x_copies()
     {
@@ -358,6 +369,7 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     constexpr int WTILE = Shape::template wtile_bytes<Src>();
     constexpr int XCOPIES = Shape::template x_copies<Src>();
     constexpr int NST = Shape::kStagesPerTile;
+    constexpr bool PAIR = Shape::template paired<Src>();
     static_assert(SR * WK * BN / 16 % WAVES == 0 && (!Src::kRunStaged || SR * WK * BM / 16 % WAVES == 0),
                   "copies of a stage must split evenly over the waves");
     static_assert(Shape::template planes_land<Src>(), "a weight plane could be read before it has landed");
@@ -392,33 +404,36 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     uint32_t x_off[XC];
     int x_dst[XC];
     {
-        const int n = lane >> 2;
+        const int n = lane >> 2, rho = lane >> 3;
 #pragma unroll
         for (int i = 0; i < XC; ++i) {
             const int c = wave + WAVES * i, e = c / (BN / 16), tile = c % (BN / 16);
             const int q = (lane & 3) ^ x_swizzle(n), run = e / WK + e % WK * RUNS;
-            const int col = col0 + tile * 16 + n;
-            x_off[i] = col < N ? (uint32_t)(col * K + split * kTileK + run * 32 + q * 8) * 2u : (uint32_t)kOutOfRange;
-            x_dst[i] = e * SLOT + tile * 1024;
+            const int col = col0 + (PAIR ? c * 8 + rho : tile * 16 + n);
+            const int k = split * kTileK + (PAIR ? ((lane & 7) ^ w_swizzle(rho)) * 8 : run * 32 + q * 8);
+            x_off[i] = col < N ? (uint32_t)(col * K + k) * 2u : (uint32_t)kOutOfRange;
+            x_dst[i] = PAIR ? c * 1024 : e * SLOT + tile * 1024;
         }
     }
     int a_off = 0;  // lane offset in a row tile of run-staged weights
     if constexpr (Src::kRunStaged) {
-        const int n = lane >> 2;
-        a_off = (n * K + split * kTileK + ((lane & 3) ^ x_swizzle(n)) * 8) * 2;
+        const int n = PAIR ? lane >> 3 : lane >> 2;
+        a_off = (n * K + split * kTileK + (PAIR ? (lane & 7) ^ w_swizzle(n) : (lane & 3) ^ x_swizzle(n)) * 8) * 2;
     }
     const int x_step = S * kTileK * 2;  // bytes of activations (or of row-major weights) from one k-tile to the next
     // copy i of the stage that starts at run `run` of k-tile t, into the ring slots at `slot`
     auto x_issue = [&](int t, int run, int i, int slot) {
-        issue_load_to_lds_b128<0>(x_rsrc, (int)(x_off[i] + (uint32_t)(t * x_step + run * 64)),
+        issue_load_to_lds_b128<0>(x_rsrc, (int)(x_off[i] + (uint32_t)(t * x_step + run * (PAIR ? WK * 64 : 64))),
                                   (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + slot + x_dst[i])));
     };
     auto a_issue = [&](int t, int run, int i, int slot) {
-        const int c = wave + WAVES * i, e = c / (BM / 16), tile = c % (BM / 16);
+        const int c = wave + WAVES * i, e = c / (BM / 16), tile = PAIR ? c / 2 : c % (BM / 16);
         const int rt = row0 / 16 + tile < n_row_tiles ? row0 / 16 + tile : n_row_tiles - 1;
-        const rsrc_t r = make_rsrc(static_cast<const half_t *>(weights) + (int64_t)rt * kTileRows * K, (uint32_t)(kTileRows * K * 2));
-        issue_load_to_lds_b128<0>(r, a_off + t * x_step + (run + e / WK + e % WK * RUNS) * 64,
-                                  (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + slot + e * SLOT + BN * 64 + tile * 1024)));
+        const rsrc_t r = make_rsrc(static_cast<const half_t *>(weights) + ((int64_t)rt * kTileRows + (PAIR ? c % 2 * 8 : 0)) * K,
+                                   (uint32_t)((PAIR ? 8 : kTileRows) * K * 2));
+        const int k_bytes = (PAIR ? run * WK : run + e / WK + e % WK * RUNS) * 64;
+        issue_load_to_lds_b128<0>(r, a_off + t * x_step + k_bytes,
+                                  (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + slot + (PAIR ? BN * 128 + c * 1024 : e * SLOT + BN * 64 + tile * 1024))));
     };
     auto x_issue_one = [&](int t, int run, int i, int slot) {  // copy i of both: activations first, then run-staged weights
         if (i < XC)
@@ -498,10 +513,14 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     };
 
     // ---- LDS reads
-    const int piece = x_piece_of_lane(lane) * 16;
-    const int b_base = wk * SLOT + wn * NT * 1024 + piece, a_base = wk * SLOT + BN * 64 + wm * RT * 1024 + piece;
-    auto ldb = [&](int slot, int nt) { return bit_cast<half8_t>(*reinterpret_cast<const u32x4 *>(lds + (slot + b_base) + nt * 1024)); };
-    auto lda = [&](int slot, int g) { return bit_cast<half8_t>(*reinterpret_cast<const u32x4 *>(lds + (slot + a_base) + g * 1024)); };
+    // a run's 16 rows x 32 columns (unpaired: 1 KB), or its half of 16 rows x 64 columns (paired: chunk 4 * odd + q of each row)
+    const int piece_row = lane & 15;
+    const int piece = PAIR ? ((piece_row >> 3) * 64 + 8 * (piece_row & 7) + ((lane >> 4) ^ w_swizzle(piece_row))) * 16 : x_piece_of_lane(lane) * 16;
+    constexpr int TILE = PAIR ? 2048 : 1024;
+    const int b_base = (PAIR ? 0 : wk * SLOT) + wn * NT * TILE, a_base = (PAIR ? BN * 128 : wk * SLOT + BN * 64) + wm * RT * TILE;
+    const int b_even = b_base + piece, b_odd = b_base + (piece ^ 64), a_even = a_base + piece, a_odd = a_base + (piece ^ 64);
+    auto ldb = [&](int slot, int nt, bool odd) { return bit_cast<half8_t>(*reinterpret_cast<const u32x4 *>(lds + (slot + (odd ? b_odd : b_even)) + nt * TILE)); };
+    auto lda = [&](int slot, int g, bool odd) { return bit_cast<half8_t>(*reinterpret_cast<const u32x4 *>(lds + (slot + (odd ? a_odd : a_even)) + g * TILE)); };
     typename Src::Piece pieces[RT];
     half2_t group_scale[RT];
     // planes that first serve the wave's pair l of k-tile t, row tile g
@@ -590,11 +609,13 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     static_assert(NT % LOOK == 0, "ring of B fragments");
     auto k_loop = [&](auto wk_c) {
         half8_t bq[LOOK];
-        static_for<LOOK>([&](auto ic) { bq[decltype(ic)::value] = ldb(0, decltype(ic)::value); });
+        // whether a run of the wave is the odd one of its pair
+        constexpr auto odd = [](int run) { return PAIR && (WK == 2 ? decltype(wk_c)::value == 1 : run % 2 == 1); };
+        static_for<LOOK>([&](auto ic) { bq[decltype(ic)::value] = ldb(0, decltype(ic)::value, odd(0)); });
         static_for<RT>([&](auto uc) {
             read_planes(wk_c, std::integral_constant<int, 0>{}, uc, 0, 0);
             if constexpr (Src::kRunStaged)
-                a[0][0][decltype(uc)::value] = lda(0, decltype(uc)::value);
+                a[0][0][decltype(uc)::value] = lda(0, decltype(uc)::value, odd(0));
         });
         if constexpr (!Src::kRunStaged && ADB)
             static_for<RT / 2>([&](auto uc) { convert(wk_c, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{}, uc); });
@@ -616,7 +637,8 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
                         wait_lds_reads();
                     block_barrier();
                 }
-                const int next_slot = slot + WK * SLOT == RING ? 0 : slot + WK * SLOT;
+                constexpr int STEP = !PAIR ? WK * SLOT : WK == 2 || run % 2 == 1 ? 2 * SLOT : 0;
+                const int next_slot = slot + STEP == RING ? 0 : slot + STEP;
                 if constexpr (!Src::kRunStaged && !ADB && e == 0)
                     static_for<RT / 2>([&](auto uc) { convert(wk_c, std::integral_constant<int, pair>{}, std::integral_constant<int, 0>{}, uc); });
                 static_for<NT>([&](auto ic) {
@@ -627,7 +649,7 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
                         static_for<RT>([&](auto uc) {
                             constexpr int u = decltype(uc)::value;
                             if constexpr (u * NT / RT == i)
-                                a[(run + 1) & 1][0][u] = lda(next_slot, u);
+                                a[(run + 1) & 1][0][u] = lda(next_slot, u, odd(run + 1));
                         });
                     } else {
                         if constexpr (e == (ADB ? 0 : 1))
@@ -641,7 +663,7 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
                                     convert(wk_c, NextPair{}, std::integral_constant<int, (pair + 1) & 1>{}, uc);
                             });
                     }
-                    bq[i % LOOK] = i + LOOK < NT ? ldb(slot, i + LOOK) : ldb(next_slot, i + LOOK - NT);
+                    bq[i % LOOK] = i + LOOK < NT ? ldb(slot, i + LOOK, odd(run)) : ldb(next_slot, i + LOOK - NT, odd(run + 1));
 #pragma unroll
                     for (int g = 0; g < RT; ++g) {
                         const half8_t &af = Src::kRunStaged ? a[ADB ? run & 1 : 0][0][g] : a[ADB ? pair & 1 : 0][e][g];
