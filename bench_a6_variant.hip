@@ -153,7 +153,7 @@ int launch_tiled(const void *w, const void *sc, const void *X, void *Y, int64_t 
                  hipStream_t st)
 {
     constexpr int RT = 2, NT = 8, WM = 8, WN = 1;
-    auto kernel = linear_tiled_kernel<Src, RT, NT, WM, WN>;
+    auto kernel = linear_tiled_kernel<Src, RT, NT, WM, WN, 1>;
     const size_t lds = (size_t)4 * NT * WN * 256 * 16;
     static bool done = false;
     if (!done) {

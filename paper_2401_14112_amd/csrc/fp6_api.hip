@@ -266,16 +266,17 @@ StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, const StreamWeights &w)
 
 // ---- tiled kernel (prefill-sized N) -----------------------------------------
 
-// Block shapes offered by the tiled kernel: {RT, NT, WM, WN}; block = (16*RT*WM) rows x (16*NT*WN) tokens.
+// Block shapes offered by the tiled kernel: {RT, NT, WM, WN, WK}; block = (16*RT*WM) rows x (16*NT*WN) tokens.  WK: the most k
+// groups it is launched with, see two_k_groups().
 struct TileShape {
-    int rt, nt, wm, wn;
+    int rt, nt, wm, wn, wk;
     int rows() const { return 16 * rt * wm; }
     int tokens() const { return 16 * nt * wn; }
 };
-constexpr TileShape kTile256x128{2, 8, 8, 1};
-constexpr TileShape kTile128x128{2, 4, 4, 2};
-constexpr TileShape kTile256x64{2, 4, 8, 1};
-constexpr TileShape kTile128x64{2, 4, 4, 1};
+constexpr TileShape kTile256x128{2, 8, 8, 1, 1};
+constexpr TileShape kTile128x128{2, 4, 4, 2, 1};
+constexpr TileShape kTile256x64{2, 4, 8, 1, 1};
+constexpr TileShape kTile128x64{2, 4, 4, 1, 2};
 
 // A kernel that uses more than 64 KB of dynamic LDS has to be told so once per device.  `done` holds one
 // bit per device ordinal (mod 64); safe to call from several host threads.
@@ -378,7 +379,6 @@ struct TiledPlan {
     int row_blocks, n_blocks;
     int counter_step;
     size_t counter_bytes, partial_bytes;  // 0 without k slices
-    size_t lds_bytes;
 };
 
 // few row blocks and a short prompt: small blocks and little split-K (measured on 8192-row layers)
@@ -404,14 +404,13 @@ TiledPlan tiled_plan_of(const TileShape &tile, int64_t M, int64_t N, int64_t K)
         s = 1;
     p.split = (int)s;
     const int bnt = p.tile.nt * p.tile.wn;
-    const size_t counters = (size_t)p.row_blocks * p.n_blocks * p.tile.wm * p.tile.wn;  // one per wave tile
+    const size_t counters = (size_t)p.row_blocks * p.n_blocks * p.tile.wm * p.tile.wn * p.tile.wk;  // one per wave
     p.counter_bytes = p.partial_bytes = 0;
     p.counter_step = counter_step(counters);
     if (p.split > 1) {
         p.counter_bytes = counter_bytes_of(counters, p.counter_step);
         p.partial_bytes = (size_t)p.split * (size_t)row_tiles * (size_t)p.n_blocks * bnt * 64 * sizeof(float4_t);
     }
-    p.lds_bytes = (size_t)4 * bnt * 256 * 16;  // the kernel's ring of four half tiles of activations
     return p;
 }
 
@@ -567,19 +566,38 @@ fp6_status launch_block_cfg(const BlockPlan &p, const void *weights, const void 
     return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
 }
 
-template <class Src, int RT, int NT, int WM, int WN>
+// Whether the 128 x 64 block of the tiled kernel takes two groups of k-tiles (eight waves) instead of one (four).  Worth it where
+// the conversions are long beside the matrix work and a slice is long enough for the second pipeline fill and the meeting in LDS.
+// Median time with two over one, 1166 calls of 256 to 57344 rows and 65 to 128 tokens, by k-tiles per slice:
+//                  < 8    8-12   12-20  20-40  > 40
+//   3 bits         0.95   0.93   0.91   0.89   0.85    (largest 1.15, 0.96, 0.96, 1.03, 0.88)
+//   4 bits         0.97   0.96   0.95   0.91   0.91    (1.16, 1.09, 0.99, 0.97, 0.94)
+//   5 bits         1.00   0.99   0.98   0.96   0.93    (1.22, 1.04, 1.17, 1.00, 0.95)
+//   6 bits         1.03   1.03   1.02   1.00   1.00
+//   group scales   1.08   1.04   1.01   0.98   0.97    (1.25, 1.14, 1.09, 0.99, 0.99)
+template <class Src>
+bool two_k_groups(int64_t K, int split)
+{
+    const int64_t k_tiles = K / kTileK / split;
+    if (weights_of<Src>() == Weights::kPacked && Src::kBits == 6)
+        return false;
+    return k_tiles >= (weights_of<Src>() == Weights::kPacked && Src::kBits < 5 ? 12 : 20);
+}
+
+template <class Src, int RT, int NT, int WM, int WN, int WK>
 fp6_status launch_tiled_cfg(const TiledPlan &p, const void *weights, const void *scales, const void *X, void *Y,
                             int64_t M, int64_t N, int64_t K, float4_t *partials, int *counters, const Epilogue &epi,
                             hipStream_t stream)
 {
-    auto kernel = linear_tiled_kernel<Src, RT, NT, WM, WN>;
+    auto kernel = linear_tiled_kernel<Src, RT, NT, WM, WN, WK>;
+    constexpr size_t lds = (size_t)4 * WK * WN * NT * 256 * 16;  // a ring of four half tiles of activations per k group
     static std::atomic<uint64_t> lds_done{0};  // per instantiation
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(kernel), p.lds_bytes, lds_done))
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds, lds_done))
         return FP6_ERR_HIP;
     // row blocks are dealt to the 8 XCDs round-robin: the grid is padded to a multiple of 8 row blocks
     const int padded_row_blocks = (p.row_blocks + 7) / 8 * 8;
-    const dim3 grid((unsigned)(padded_row_blocks * p.n_blocks * p.split)), block(WM * WN * 64);
-    hipLaunchKernelGGL(kernel, grid, block, p.lds_bytes, stream, weights, static_cast<const half_t *>(scales),
+    const dim3 grid((unsigned)(padded_row_blocks * p.n_blocks * p.split)), block(WM * WN * WK * 64);
+    hipLaunchKernelGGL(kernel, grid, block, lds, stream, weights, static_cast<const half_t *>(scales),
                        static_cast<const half_t *>(X), static_cast<half_t *>(Y), (int)M, (int)N, (int)K, p.split,
                        p.n_blocks, partials, counters, p.counter_step, epi);
     return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
@@ -705,17 +723,20 @@ fp6_status launch_prompt_chunk(const void *weights, const void *scales, const vo
         return FP6_ERR_SHAPE;  // not reached: plan_prompt only picks the blocks above
     }
     const TileShape &t = p.tiled.tile;
-#define FP6_TILED_CASE(RT_, NT_, WM_, WN_)                                                                        \
-    if (t.rt == RT_ && t.nt == NT_ && t.wm == WM_ && t.wn == WN_)                                                 \
-        return launch_tiled_cfg<Src, RT_, NT_, WM_, WN_>(p.tiled, weights, scales, X, Y, M, N, K, partials, counters, epi, \
+#define FP6_TILED_CASE(RT_, NT_, WM_, WN_, WK_)                                                                        \
+    if (t.rt == RT_ && t.nt == NT_ && t.wm == WM_ && t.wn == WN_ && t.wk >= WK_)                                                 \
+        return launch_tiled_cfg<Src, RT_, NT_, WM_, WN_, WK_>(p.tiled, weights, scales, X, Y, M, N, K, partials, counters, epi, \
                                                          stream);
     if constexpr (weights_of<Src>() != Weights::kFp16) {
-        FP6_TILED_CASE(2, 4, 4, 1)
-        FP6_TILED_CASE(2, 4, 4, 2)
+        if (two_k_groups<Src>(K, p.tiled.split)) {
+            FP6_TILED_CASE(2, 4, 4, 1, 2)
+        }
+        FP6_TILED_CASE(2, 4, 4, 1, 1)
+        FP6_TILED_CASE(2, 4, 4, 2, 1)
     }
     if constexpr (weights_of<Src>() == Weights::kPacked) {
-        FP6_TILED_CASE(2, 4, 8, 1)
-        FP6_TILED_CASE(2, 8, 8, 1)
+        FP6_TILED_CASE(2, 4, 8, 1, 1)
+        FP6_TILED_CASE(2, 8, 8, 1, 1)
     }
 #undef FP6_TILED_CASE
     return FP6_ERR_SHAPE;  // not reached: plan_prompt only picks the shapes above

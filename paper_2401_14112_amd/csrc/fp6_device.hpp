@@ -610,12 +610,13 @@ struct PackedFp3Source {
     __device__ static __forceinline__ int k_offset(int f, int q) { return f * 32 + q * 8; }
     struct Stream {
         rsrc_t rsrc;
-        int off, first, stride;  // lane offset, first k-tile, bytes from one tile of a row tile to the next
-        // k-tiles kt_first .. kt_first + n_tiles - 1 of one row tile (contiguous: kt_step is 1 for every user)
+        int off, first, step, last, stride;  // lane offset, k-tiles, bytes from one tile of a row tile to the next
         __device__ __forceinline__ void init(const void *weights, const half_t * /*scales*/, int64_t row_tile, int kt_first,
-                                             int /*kt_step*/, int n_tiles, int64_t RT, int64_t /*K*/, int lane)
+                                             int kt_step, int n_tiles, int64_t RT, int64_t /*K*/, int lane)
         {
-            const int t0 = kt_first >> 1, t1 = (kt_first + n_tiles - 1) >> 1;  // first and last tile touched
+            step = kt_step;
+            last = kt_first + (n_tiles - 1) * kt_step;
+            const int t0 = kt_first >> 1, t1 = last >> 1;  // first and last tile touched
             rsrc = make_rsrc(static_cast<const uint8_t *>(weights) + ((int64_t)t0 * RT + row_tile) * kTileBytes3,
                              (uint32_t)(((int64_t)(t1 - t0) * RT + 1) * kTileBytes3));
             off = lane * 16;
@@ -624,8 +625,8 @@ struct PackedFp3Source {
         }
         __device__ __forceinline__ void issue(Tile &tile, int t) const
         {
-            const int kt = first + t, half = kt & 1;
-            const int o = off + ((kt >> 1) - (first >> 1)) * stride;
+            const int kt = first + t * step, half = kt & 1;
+            const int o = kt > last ? kOutOfRange : off + ((kt >> 1) - (first >> 1)) * stride;
             tile.p0 = issue_load_b128<0, true>(rsrc, o + half * 2048);
             tile.p1 = issue_load_b64<1024>(rsrc, o + half * 8);
         }

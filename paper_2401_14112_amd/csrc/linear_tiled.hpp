@@ -2,7 +2,7 @@
 // the block kernel's 256 x 256 pieces (linear_block.hpp), where the layer is bound by
 // the matrix cores (Section 7.1 of the paper: all kernels become compute-bound beyond batch 128).
 //
-// A block is WM x WN waves; wave (wm, wn) owns RT 16-row tiles and NT 16-token tiles, i.e. a
+// A block is WM x WN x WK waves; wave (wm, wn) owns RT 16-row tiles and NT 16-token tiles, i.e. a
 // (16*RT) x (16*NT) piece of Y held in fp32 accumulators; the block covers (16*RT*WM) rows and
 // (16*NT*WN) tokens.  Per 256-column k-tile a wave fetches its RT packed weight tiles straight into
 // registers, de-quantizes four runs of 32 columns with one conversion and feeds every run to NT MFMAs (the
@@ -11,7 +11,11 @@
 // global -> LDS without passing through registers, already in B-fragment order (the 64 lanes of one
 // copy instruction fetch the 64 pieces that the 64 lanes of one MFMA will read), half a k-tile (128
 // columns) at a time into a ring of four buffers, requested three half tiles ahead and made visible one
-// half tile ahead; weights are double-buffered in registers, one k-tile ahead.
+// half tile ahead; weights are double-buffered in registers, one k-tile ahead.  With WK = 2 two waves share such a piece, one
+// takes the even and one the odd k-tiles of the slice, and their sums meet in LDS: two waves per SIMD instead of one for the
+// blocks of 128 x 64, whose conversions and LDS reads then run under each other's matrix instructions (6656 x 17920, N = 100,
+// 3 bits 38.6 -> 34.9 us, 12288 x 12288, N = 96, 5 bits 58.3 -> 54.5, 10240 x 8192, N = 96, 4 bits 33.0 -> 30.1; 6 bits, whose
+// conversion is short, gain nothing).  Copying the activations in whole 128-byte lines changed none of them, nor the other blocks.
 //
 // Split-K and the epilogue are those of the streaming kernel (linear_stream.hpp).
 #pragma once
@@ -19,20 +23,21 @@
 
 namespace fp6 {
 
-template <class Src, int RT, int NT, int WM, int WN>
-__global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
+template <class Src, int RT, int NT, int WM, int WN, int WK>
+__global__ __launch_bounds__(WM * WN * WK * 64) void linear_tiled_kernel(
     const void *__restrict__ weights, const half_t *__restrict__ scales, const half_t *__restrict__ X,
     half_t *Y, int M, int N, int K, int S, int n_blocks, float4_t *__restrict__ partials,
     int *__restrict__ counters, int counter_step, Epilogue epi)
 {
-    constexpr int WAVES = WM * WN;
+    constexpr int WAVES = WM * WN * WK;
+    static_assert(WK == 1 || (WK == 2 && RT == 2), "two k groups share two row tiles");
     constexpr int BNT = WN * NT;             // 16-token tiles of the block
     // Activations are staged half a k-tile (128 columns = runs 0..3 or 4..7) at a time in a ring of XS
     // buffers; weights are double-buffered in registers (whole k-tiles).
     constexpr int XS = 4;
-    constexpr int XHPIECES = BNT * 256;      // 16-byte pieces of one half tile of activations
+    constexpr int XHPIECES = WK * BNT * 256; // 16-byte pieces of one half tile of activations (of every k group)
     constexpr int XHBYTES = XHPIECES * 16;
-    constexpr int HCOPIES = BNT * 4;         // copy instructions per half tile (one per token tile and run)
+    constexpr int HCOPIES = WK * BNT * 4;    // copy instructions per half tile (one per token tile and run)
     static_assert(HCOPIES % WAVES == 0, "activation copies must split evenly over the waves");
     constexpr int XPERH = HCOPIES / WAVES;
     constexpr int WLOADS = RT * Src::kLoads; // weight loads of one wave per k-tile
@@ -42,7 +47,7 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave % WM, wn = wave / WM;
+    const int wm = wave % WM, wn = wave / WM % WN, wk = wave / (WM * WN);
     const int KT = K / kTileK;
     const int n_row_tiles = M / kTileRows;
     // block -> (row block, token block, k slice).  Consecutive block ids land on consecutive XCDs (8 of
@@ -66,12 +71,15 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
     const int kt0 = (int)(((unsigned)KT * (unsigned)split) / (unsigned)S);
     const int kt1 = (int)(((unsigned)KT * (unsigned)(split + 1)) / (unsigned)S);
     const int n_valid = kt1 - kt0;
+    // k group wk takes k-tiles wk, wk + WK, ... of the slice ("k-tile t" below is the wave's t-th); a group that has one less, or
+    // none, multiplies zero activations
+    const int n_steps = (n_valid + WK - 1) / WK, n_own = (n_valid - wk + WK - 1) / WK;
 
     typename Src::Stream w_stream[RT];
 #pragma unroll
     for (int r = 0; r < RT; ++r) {
         const int rt = row_tile0 + r;
-        w_stream[r].init(weights, scales, rt < n_row_tiles ? rt : n_row_tiles - 1, kt0, 1, n_valid, n_row_tiles, K, lane);
+        w_stream[r].init(weights, scales, rt < n_row_tiles ? rt : n_row_tiles - 1, n_own > 0 ? kt0 + wk : kt0, WK, n_own > 0 ? n_own : 1, n_row_tiles, K, lane);
     }
     const rsrc_t x_rsrc = make_rsrc(X, (uint32_t)N * (uint32_t)K * 2u);
 
@@ -87,9 +95,9 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
     const uint32_t xs_lds = (uint32_t)reinterpret_cast<uintptr_t>(xs_dyn);
     // copy i (of the XPERH this wave contributes) of half tile h into ring buffer buf
     auto x_issue_one = [&](int h, int buf, int i) {
-        const int t = h >> 1;
         const int j = wave + WAVES * i;
-        const int nt = j >> 2, f = (j & 3) + 4 * (h & 1);
+        const int t = WK * (h >> 1) + (WK == 1 ? 0 : j / (BNT * 4));
+        const int nt = (WK == 1 ? j : j % (BNT * 4)) >> 2, f = (j & 3) + 4 * (h & 1);
         const int col = block_col0 + nt * 16 + xn;
         const int off = (t < n_valid && col < N)
                             ? (col * K + (kt0 + t) * kTileK + Src::k_offset(f, xq)) * 2
@@ -124,7 +132,7 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
     half8_t a[2][2][RT];  // [group parity][even/odd run][row tile]
     half8_t bq[LOOK];
     auto ldb = [&](const u32x4 *xbuf, int st) {
-        return bit_cast<half8_t>(xbuf[((wn * NT + (st % NT)) * 4 + st / NT) * 64 + b_piece]);
+        return bit_cast<half8_t>(xbuf[(((wk * WN + wn) * NT + (st % NT)) * 4 + st / NT) * 64 + b_piece]);
     };
     // HP: which half of the k-tile t; xbuf: its activations; xnext: those of the following half tile;
     // request(step): called after each of the 4*NT steps of the half tile, issues the memory requests that the
@@ -192,7 +200,7 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
 #pragma unroll
     for (int i = 0; i < LOOK; ++i)
         bq[i] = ldb(xs_dyn, i);
-    const int n_half = 2 * n_valid;
+    const int n_half = 2 * n_steps;
     for (int h0 = 0; h0 < n_half; h0 += XS) {
         static_for<XS>([&](auto uc) {
             constexpr int u = decltype(uc)::value;
@@ -234,11 +242,35 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
     pin_tiles(w[0]);
     pin_tiles(w[1]);
 
+    // ---- two k groups meet in LDS: group wk keeps row tile wk of the two
+    constexpr int OWN = RT / WK;  // row tiles from here on
+    float4_t own[OWN][NT];
+    const int row_own = row_tile0 + (WK == 1 ? 0 : wk);
+    if constexpr (WK == 2) {
+        static_assert(WAVES * NT * 1024 <= XS * XHBYTES, "exchange buffer");
+        float4_t *ex = reinterpret_cast<float4_t *>(xs_dyn);
+        __syncthreads();
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            ex[(wave * NT + nt) * 64 + lane] = wk == 0 ? acc[1][nt] : acc[0][nt];
+        __syncthreads();
+        const int partner = wk == 0 ? wave + WM * WN : wave - WM * WN;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+            own[0][nt] = (wk == 0 ? acc[0][nt] : acc[1][nt]) + ex[(partner * NT + nt) * 64 + lane];
+    } else {
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                own[r][nt] = acc[r][nt];
+    }
+
     // ---- epilogue.  Lane L holds, per (row tile, token tile), rows 4*(L/16)+i of token column L%16.
     const int n_in_tile = lane & 15;
     const int n_tiles_total = n_blocks * BNT;
     auto finish = [&](const float4_t (&sum)[NT], int r) {
-        const int m0 = (row_tile0 + r) * kTileRows + 4 * (lane >> 4);
+        const int m0 = (row_own + r) * kTileRows + 4 * (lane >> 4);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             const int col = col0 + nt * 16 + n_in_tile;
@@ -249,9 +281,9 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
 
     if (S == 1) {
 #pragma unroll
-        for (int r = 0; r < RT; ++r)
-            if (row_tile0 + r < n_row_tiles)
-                finish(acc[r], r);
+        for (int r = 0; r < OWN; ++r)
+            if (row_own + r < n_row_tiles)
+                finish(own[r], r);
         return;
     }
 
@@ -259,16 +291,16 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
     // and access and one arrival counter per wave, so that no wave waits for its block before the hand-over
     // (8192 x 22016, N = 512 151.0 -> 148.4 us, N = 256 87.2 -> 85.9, 28672 x 8192, N = 128 66.1 -> 64.8)
     auto slice = [&](int s, int r) {  // the wave's NT tiles of row tile r
-        return partial_buffer(partials + (((int64_t)s * n_row_tiles + (row_tile0 + r)) * n_tiles_total + (n_block * WN + wn) * NT) * 64, NT * 1024);
+        return partial_buffer(partials + (((int64_t)s * n_row_tiles + (row_own + r)) * n_tiles_total + (n_block * WN + wn) * NT) * 64, NT * 1024);
     };
 #pragma unroll
-    for (int r = 0; r < RT; ++r)
-        if (row_tile0 + r < n_row_tiles) {
+    for (int r = 0; r < OWN; ++r)
+        if (row_own + r < n_row_tiles) {
             const partial_rsrc_t dst = slice(split, r);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
                 if (col0 + nt * 16 + n_in_tile < N)
-                    agent_store(dst, nt * 1024 + lane * 16, acc[r][nt]);
+                    agent_store(dst, nt * 1024 + lane * 16, own[r][nt]);
         }
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's partial stores are done
@@ -282,8 +314,8 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
     if (arrived != S - 1)
         return;
 #pragma unroll
-    for (int r = 0; r < RT; ++r) {
-        if (row_tile0 + r >= n_row_tiles)
+    for (int r = 0; r < OWN; ++r) {
+        if (row_own + r >= n_row_tiles)
             continue;
         float4_t sum[NT];
 #pragma unroll
@@ -307,7 +339,7 @@ __global__ __launch_bounds__(WM * WN * 64) void linear_tiled_kernel(
                 if (s0 + u < S) {
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt)
-                        sum[nt] += s0 + u == split ? acc[r][nt] : part[u][nt];
+                        sum[nt] += s0 + u == split ? own[r][nt] : part[u][nt];
                 }
         }
         finish(sum, r);
