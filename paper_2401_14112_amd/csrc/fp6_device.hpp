@@ -735,8 +735,6 @@ struct StagedFp16Source {
     }
 };
 
-constexpr int stream_gcd(int a, int b) { return b == 0 ? a : stream_gcd(b, a % b); }
-
 template <class F, int... I>
 __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
 {
