@@ -100,7 +100,8 @@ fp6_status fp6_unpack(const void *packed, const void *scales_f16, int64_t M, int
  * calls that may run concurrently (different streams) need different workspaces.
  * A smaller workspace is refused; only fp16_linear and fp6g_linear on more than 64 tokens
  * also run, slower, with one that holds the k slices of 128 x 128 output blocks, hence with
- * none where there are more than 128 such blocks.
+ * none where there are more than 128 such blocks, and fp16_linear in some other cases too
+ * (whatever was enough for it in an earlier version is still enough).
  * Sizes belong to the loaded library: ask for them, they change from version to version.
  */
 size_t fp6_linear_workspace_bytes(int64_t M, int64_t N, int64_t K);

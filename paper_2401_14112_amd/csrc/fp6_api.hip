@@ -437,17 +437,40 @@ struct PromptPlan {
 
 // Estimated time of a block plan, ns: rounds of 256 blocks at the measured cost per run, a fixed part per round, and for
 // split-K what the last arrival reads (its tile of every slice, at the ~50 GB/s one CU gets) and what all slices write.
-double block_cost(const BlockPlan &p, int64_t K, Weights kind)
+double block_cost(const BlockPlan &p, int64_t K, double run_ns)
 {
     const BlockCfg &b = kBlockCfg[p.cfg];
     const double blocks = (double)p.row_blocks * p.n_blocks * p.split;
     const double rounds = (double)(((int64_t)blocks + kCus - 1) / kCus);
     const double runs = 8.0 * (double)((K / kTileK + p.split - 1) / p.split);
+    const double ns = rounds * (runs * run_ns + 8000.0);
+    return p.split == 1 ? ns : ns + (double)p.split * b.rows * b.tokens * 4.0 / 50.0 + (double)p.partial_bytes * 1.5e-4;
+}
+double block_cost(const BlockPlan &p, int64_t K, Weights kind)
+{
+    const BlockCfg &b = kBlockCfg[p.cfg];
     // 128-row blocks of fp16 weights fetch twice the bytes per product, and long rows of both operands share fewer L2 sets
     // (258 ns up to K = 12288, 300 to 340 beyond 20000)
     const double long_rows = b.rows == 128 && K > 12288 ? 1.0 + 0.25 * (double)((K < 28672 ? K : 28672) - 12288) / 12288.0 : 1.0;
-    const double ns = rounds * (runs * (kind == Weights::kFp16 ? b.fp16_ns * long_rows : b.group_ns) + 8000.0);
-    return p.split == 1 ? ns : ns + (double)p.split * b.rows * b.tokens * 4.0 / 50.0 + (double)p.partial_bytes * 1.5e-4;
+    return block_cost(p, K, kind == Weights::kFp16 ? b.fp16_ns * long_rows : b.group_ns);
+}
+
+// Partial sums with which fp16_linear runs at any rate: those of the block that kFp16AcceptedNs chooses.  These figures are not
+// for speed and stay as they are when the ones above are measured anew: a caller that had enough has enough.
+constexpr double kFp16AcceptedNs[kBlockCfgs] = {924, 632, 333, 228};
+size_t fp16_accepted_partials(int64_t M, int64_t N, int64_t K)
+{
+    size_t bytes = 0;
+    double best = 0.0;
+    for (int c = 0; c < kBlockCfgs; ++c) {
+        const BlockPlan b = block_plan_of(c, M, N, K);
+        const double cost = block_cost(b, K, kFp16AcceptedNs[c]);
+        if (c == 0 || cost < best) {
+            bytes = b.partial_bytes;
+            best = cost;
+        }
+    }
+    return bytes;
 }
 
 // Whether the cheapest block plan for group scales has so few k-tiles per block that the tiled kernel's 128 x 128 blocks
@@ -677,8 +700,8 @@ size_t prompt_workspace_bytes(int64_t M, int64_t N, int64_t K, Weights kind)
 // The plan of a launch on the workspace that the caller brought.  The queried size holds the k slices of the best plan.
 // A smaller one, or none, is refused - unless it holds what 128 x 128 blocks need (128 x 64 on few row blocks): they
 // need no k slices where more than half of the CUs have a block, and callers of fp16_linear and fp6g_linear may rely on
-// that.  The call then runs with as many slices as fit (8192 x 22016, N = 512, fp16: 67 MB and 256 x 256 blocks in 4
-// slices as queried, 128 x 128 blocks without a workspace).
+// that; or, fp16_linear, what fp16_accepted_partials() says.  The call then runs with as many slices as fit (8192 x 22016,
+// N = 512, fp16: 67 MB and 256 x 256 blocks in 4 slices as queried, 128 x 128 blocks without a workspace).
 fp6_status plan_prompt_within(int64_t M, int64_t N, int64_t K, Weights kind, const WorkspaceRef &workspace, PromptPlan &p, SplitBuffers &buf)
 {
     p = plan_prompt(M, N, K, kind);
@@ -687,7 +710,10 @@ fp6_status plan_prompt_within(int64_t M, int64_t N, int64_t K, Weights kind, con
         return fits;
     const TiledPlan least = tiled_plan_of(few_blocks(M, N) ? kTile128x64 : kTile128x128, M, N, K);
     const size_t bytes = workspace.base ? workspace.bytes : 0, region = workspace.counter_region;
-    if (least.split > 1 && bytes < region + least.partial_bytes)
+    size_t enough = least.partial_bytes;
+    if (kind == Weights::kFp16 && fp16_accepted_partials(M, N, K) < enough)
+        enough = fp16_accepted_partials(M, N, K);
+    if (enough > 0 && bytes < region + enough)
         return fits;
     p = plan_prompt(M, N, K, kind, bytes > region ? bytes - region : 0);
     return workspace.view(p.counter_bytes(), p.partial_bytes(), buf);

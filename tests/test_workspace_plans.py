@@ -117,3 +117,42 @@ def test_smaller_workspaces_are_refused_otherwise(lib):
         if less != REFUSED:
             assert less.split_k == 1 or less.partial_offset + less.partial_bytes <= need - 16
     assert refused > 50
+
+
+# {rows, tokens}: figures by which the block of fp16_linear was chosen before they were measured anew, ns per run of 32 columns
+FP16_ACCEPTED = {(256, 256): 924.0, (256, 128): 632.0, (128, 128): 333.0, (128, 64): 228.0}
+
+
+def _fp16_accepted(M, N, K):
+    """Partial sums of the block with the least estimated time by those figures."""
+    best = None
+    for (rows, tokens), ns in FP16_ACCEPTED.items():
+        tiles, k_tiles = -(-M // rows) * -(-N // tokens), K // 256
+        s = max(1, min(256 // tiles, k_tiles // 4 if k_tiles >= 8 else 1, 16))
+        partials = s * tiles * rows * tokens * 4 if s > 1 else 0
+        cost = -(-tiles * s // 256) * (8.0 * -(-k_tiles // s) * ns + 8000.0)
+        if s > 1:
+            cost += s * rows * tokens * 4.0 / 50.0 + partials * 1.5e-4
+        if best is None or cost < best[0]:
+            best = cost, partials
+    return best[1]
+
+
+def test_fp16_calls_that_ran_still_run(lib):
+    """What a call of fp16_linear asks for at least does not move with the figures that choose its block."""
+    rng = random.Random(4)
+    shapes = [(5328, 352, 3328), (784, 1656, 2048), (2224, 646, 2816)]
+    while len(shapes) < 6000:
+        M, K = 16 * round(2 ** rng.uniform(4, 11.8)), 256 * round(2 ** rng.uniform(1, 6.8))
+        shapes.append((M, round(2 ** rng.uniform(6.1, 12)), K))
+    smaller = without = 0
+    for M, N, K in shapes:
+        partials = _fp16_accepted(M, N, K)
+        have = 4096 + partials if partials else 0
+        p = plan(lib, "fp16", M, N, K, workspace_bytes=have)
+        assert p != REFUSED, (M, N, K, have)
+        assert p.split_k == 1 or p.partial_offset + p.partial_bytes <= have
+        more = have < workspace_bytes(lib, "fp16", M, N, K)
+        smaller += more and have > 0
+        without += more and have == 0
+    assert smaller > 10 and without > 3
