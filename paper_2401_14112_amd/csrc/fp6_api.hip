@@ -118,22 +118,21 @@ struct WorkspaceRef {
 
 // The weights a launch reads, as the plan sees them.
 struct StreamWeights {
-    bool packed, grouped;
+    bool packed;
     int bits;       // per weight
     int tile_cols;  // columns of a weight tile in the streaming kernel
     int lds_tile;   // bytes of LDS that a tile in flight takes
 };
-// Configurations that exist for a format: those that fit the LDS.  Group scales beyond 8 tokens go without the block of two row
-// tiles and keep their k slices (8192 x 2048, N = 16 6.4 us with two slices of four row tiles, 5.7 with that block).
+// Configurations that exist for a format: those that fit the LDS.
 constexpr bool stream_cfg_built(const StreamCfg &c, const StreamWeights &w)
 {
-    return stream_lds_bytes(c, w.tile_cols, w.lds_tile) <= kMaxLds && !(w.grouped && c.nt == 1 && c.wm == 2 && c.xr == 16);
+    return stream_lds_bytes(c, w.tile_cols, w.lds_tile) <= kMaxLds;
 }
 template <class Src>  // the source of a format, as the entry points name it
 constexpr StreamWeights stream_weights_of()
 {
     typedef typename Src::StreamSource S;
-    return {S::kPackedConfigs, std::is_same_v<S, PackedFp6GroupSource>, S::kBits, S::kTileCols, S::kLdsTileBytes};
+    return {S::kPackedConfigs, S::kBits, S::kTileCols, S::kLdsTileBytes};
 }
 
 struct StreamPlan {

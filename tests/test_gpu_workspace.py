@@ -30,7 +30,7 @@ def _call(pkg, width, M, K, seed):
 
 def test_one_workspace_for_formats_and_token_counts(pkg):
     """Bit for bit the outputs of calls with a fresh workspace each.  What lies behind the counters is NaN at first."""
-    M, K = 8192, 2048
+    M, K = 8192, 8192
     lib = pkg.load_library()
     calls = [(w, N) for N in (200, 16, 129, 40) for w in WIDTHS]
     linear = {w: _call(pkg, w, M, K, 3 + i) for i, w in enumerate(WIDTHS)}

@@ -42,3 +42,15 @@ def test_what_a_call_asks_for():
         with_slices += p.split_k > 1
         without += p.split_k == 1 and s > 1
     assert with_slices > 300 and without > 300
+
+
+def test_group_scales_take_every_block_of_six_bits():
+    """Nothing but the LDS, the same for both, says which blocks exist."""
+    import paper_2401_14112_amd as pkg
+
+    lib = pkg.load_library()
+    for N in (1, 2, 3, 8, 9, 16, 17, 32, 33, 48, 49, 64):
+        blocks = {w: {plan(lib, w, M, N, K).block_rows for M in range(256, 16384, 496) for K in (512, 1024, 2048, 4096, 8192, 22016)}
+                  for w in ("fp6", "fp6g")}
+        assert blocks["fp6"] == blocks["fp6g"], N
+    assert plan(lib, "fp6g", 8192, 16, 2048).block_rows == 32
