@@ -35,7 +35,14 @@ def test_what_a_call_asks_for():
         most = REGION + s * (M // 16) * tiles * 1024 if s > 1 else 0
         p = plan(lib, width, M, N, K)
         assert p.kernel == STREAM and p.block_tokens >= N and p.split_k <= s * tiles
-        assert workspace_bytes(lib, width, M, N, K) <= most or width in ("fp6", "fp5", "fp4", "fp6g") and s > 1
+        # the k slices of the plan, or those of blocks of eight row tiles where it has none; the most of the formats that share a query
+        sharing = (width,) if width in ("fp3", "fp16") else ("fp6", "fp5", "fp4", "fp6g")
+        asked = {}
+        for w in sharing:
+            q = plan(lib, w, M, N, K)
+            asked[w] = q.partial_offset + q.partial_bytes if q.split_k > 1 else most
+        assert workspace_bytes(lib, width, M, N, K) == max(asked.values()), (width, M, N, K)
+        assert s == 1 or plan(lib, width, M, N, K, workspace_bytes=asked[width] - 1) == REFUSED
         # what was enough for eight row tiles is enough, and without any the call runs where those took no slices
         assert plan(lib, width, M, N, K, workspace_bytes=most) != REFUSED, (width, M, N, K)
         assert (plan(lib, width, M, N, K, workspace_bytes=0) == REFUSED) == (s > 1), (width, M, N, K)
