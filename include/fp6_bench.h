@@ -63,6 +63,8 @@ typedef struct {
 } fp6_launch_plan;
 fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes,
                            fp6_launch_plan *plan);
+/* Groups of k-tiles of a workgroup of that launch (waves that share an output piece and meet in LDS); 0 where it is refused. */
+int fp6_tuning_plan_k_groups(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes);
 
 #ifdef __cplusplus
 }

@@ -124,6 +124,8 @@ def load_library():
     L.fp6_tuning_set_tile.argtypes = [ci, ci]
     L.fp6_tuning_plan.restype = ci
     L.fp6_tuning_plan.argtypes = [ci, i64, i64, i64, i64, sz, vp]
+    L.fp6_tuning_plan_k_groups.restype = ci
+    L.fp6_tuning_plan_k_groups.argtypes = [ci, i64, i64, i64, i64, sz]
     _lib = L
     return L
 

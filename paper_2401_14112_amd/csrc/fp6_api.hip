@@ -302,6 +302,7 @@ std::atomic<int> g_forced_tile{0};  // 0 = automatic, else rows * 1024 + tokens 
 struct BlockCfg {
     int rows, tokens;
     double fp16_ns, group_ns;
+    constexpr int k_groups() const { return rows == 128 ? 2 : 1; }
 };
 constexpr int kBlockCfgs = 4, kBlock256x256 = 0;
 constexpr BlockCfg kBlockCfg[kBlockCfgs] = {{256, 256, 805, 0}, {256, 128, 590, 480}, {128, 128, 258, 293}, {128, 64, 198, 0}};
@@ -335,12 +336,17 @@ struct BlockPlan {
     size_t counter_bytes, partial_bytes;  // 0 without k slices
 };
 
-enum class Weights { kPacked, kGrouped, kFp16 };
+enum class Weights { kFp6, kFp5, kFp4, kFp3, kGrouped, kFp16 };
+constexpr bool per_row(Weights kind) { return kind != Weights::kGrouped && kind != Weights::kFp16; }  // packed, a scale per row
 template <class Src>
 constexpr Weights weights_of()
 {
-    return std::is_same_v<Src, PlainFp16Source> ? Weights::kFp16
-                                                : std::is_same_v<Src, PackedFp6GroupSource> ? Weights::kGrouped : Weights::kPacked;
+    if constexpr (std::is_same_v<Src, PlainFp16Source>)
+        return Weights::kFp16;
+    else if constexpr (std::is_same_v<Src, PackedFp6GroupSource>)
+        return Weights::kGrouped;
+    else
+        return Src::kBits == 6 ? Weights::kFp6 : Src::kBits == 5 ? Weights::kFp5 : Src::kBits == 4 ? Weights::kFp4 : Weights::kFp3;
 }
 
 // partial_limit: bytes that the partial tiles may take
@@ -374,7 +380,7 @@ BlockPlan block_plan_of(int cfg, int64_t M, int64_t N, int64_t K, size_t partial
 
 struct TiledPlan {
     TileShape tile;
-    int split;
+    int split, k_groups;
     int row_blocks, n_blocks;
     int counter_step;
     size_t counter_bytes, partial_bytes;  // 0 without k slices
@@ -383,7 +389,22 @@ struct TiledPlan {
 // few row blocks and a short prompt: small blocks and little split-K (measured on 8192-row layers)
 bool few_blocks(int64_t M, int64_t N) { return N <= 128 && (M + 255) / 256 < 64; }
 
-TiledPlan tiled_plan_of(const TileShape &tile, int64_t M, int64_t N, int64_t K)
+// Whether the 128 x 64 block of the tiled kernel takes two groups of k-tiles (eight waves) instead of one (four).  Worth it where
+// the conversions are long beside the matrix work and a slice is long enough for the second pipeline fill and the meeting in LDS.
+// Median time with two over one, 1166 calls of 256 to 57344 rows and 65 to 128 tokens, by k-tiles per slice:
+//                  < 8    8-12   12-20  20-40  > 40
+//   3 bits         0.95   0.93   0.91   0.89   0.85    (largest 1.15, 0.96, 0.96, 1.03, 0.88)
+//   4 bits         0.97   0.96   0.95   0.91   0.91    (1.16, 1.09, 0.99, 0.97, 0.94)
+//   5 bits         1.00   0.99   0.98   0.96   0.93    (1.22, 1.04, 1.17, 1.00, 0.95)
+//   6 bits         1.03   1.03   1.02   1.00   1.00
+//   group scales   1.08   1.04   1.01   0.98   0.97    (1.25, 1.14, 1.09, 0.99, 0.99)
+bool two_k_groups(Weights kind, int64_t K, int split)
+{
+    const int64_t k_tiles = K / kTileK / split;
+    return kind != Weights::kFp6 && k_tiles >= (kind == Weights::kFp3 || kind == Weights::kFp4 ? 12 : 20);
+}
+
+TiledPlan tiled_plan_of(const TileShape &tile, int64_t M, int64_t N, int64_t K, Weights kind)
 {
     TiledPlan p;
     const int64_t row_tiles = M / kTileRows;
@@ -402,8 +423,9 @@ TiledPlan tiled_plan_of(const TileShape &tile, int64_t M, int64_t N, int64_t K)
     if (s < 1)
         s = 1;
     p.split = (int)s;
+    p.k_groups = p.tile.wk == 2 && two_k_groups(kind, K, p.split) ? 2 : 1;
     const int bnt = p.tile.nt * p.tile.wn;
-    const size_t counters = (size_t)p.row_blocks * p.n_blocks * p.tile.wm * p.tile.wn * p.tile.wk;  // one per wave
+    const size_t counters = (size_t)p.row_blocks * p.n_blocks * p.tile.wm * p.tile.wn * p.k_groups;  // one per wave
     p.counter_bytes = p.partial_bytes = 0;
     p.counter_step = counter_step(counters);
     if (p.split > 1) {
@@ -413,15 +435,15 @@ TiledPlan tiled_plan_of(const TileShape &tile, int64_t M, int64_t N, int64_t K)
     return p;
 }
 
-// smallest: the 128 x 64 block (weights with group scales; their 128 x 128 one is chosen in plan_prompt)
-TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, bool smallest)
+// Weights with group scales: the 128 x 64 block (their 128 x 128 one is chosen in plan_prompt).
+TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, Weights kind)
 {
     const int forced = g_forced_tile.load(std::memory_order_relaxed);
     const int rows = forced / 1024, tokens = forced % 1024;
     TileShape tile = few_blocks(M, N) ? kTile128x64 : kTile256x128;  // the latter moves the fewest bytes per MFMA
     if (forced > 0)
         tile = rows == 256 ? (tokens == 128 ? kTile256x128 : kTile256x64) : (tokens == 128 ? kTile128x128 : kTile128x64);
-    return tiled_plan_of(smallest ? kTile128x64 : tile, M, N, K);
+    return tiled_plan_of(kind == Weights::kGrouped ? kTile128x64 : tile, M, N, K, kind);
 }
 
 // What a call of more than kStreamMaxN tokens launches: the block kernel where `block.cfg` is set, else the tiled one.
@@ -521,14 +543,14 @@ PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind, size_t par
 {
     PromptPlan p;
     p.block.cfg = -1;
-    p.tiled = plan_tiled(M, N, K, kind == Weights::kGrouped);
+    p.tiled = plan_tiled(M, N, K, kind);
     const int forced = g_forced_tile.load(std::memory_order_relaxed);
     if (forced > 0) {
         const int rows = forced / 1024, tokens = forced % 1024;
         int cfg = -1;
         if (tokens == 256)
             cfg = kind == Weights::kGrouped ? 1 : kBlock256x256;
-        else if (kind != Weights::kPacked && tokens == 128)
+        else if (!per_row(kind) && tokens == 128)
             cfg = rows == 256 ? 1 : 2;
         else if (kind == Weights::kFp16)
             cfg = 3;
@@ -537,7 +559,7 @@ PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind, size_t par
         return p;
     }
     const int64_t row_blocks = (M + 255) / 256;
-    if (kind == Weights::kPacked) {
+    if (per_row(kind)) {
         const int64_t tiles = row_blocks * ((N + 255) / 256), halves = row_blocks * ((N + 127) / 128);
         const int64_t rounds = (tiles + kCus - 1) / kCus, half_rounds = (halves + kCus - 1) / kCus;
         if (20 * rounds <= 11 * half_rounds && 20 * tiles <= 11 * halves)
@@ -558,7 +580,7 @@ PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind, size_t par
         }
     }
     if (kind == Weights::kGrouped) {
-        const TiledPlan tiled = tiled_plan_of(kTile128x128, M, N, K);
+        const TiledPlan tiled = tiled_plan_of(kTile128x128, M, N, K, kind);
         if (tiled.partial_bytes <= partial_limit && short_blocks(p.block, tiled, K)) {
             p.tiled = tiled;
             p.block.cfg = -1;
@@ -573,7 +595,8 @@ fp6_status launch_block_cfg(const BlockPlan &p, const void *weights, const void 
 {
     typedef typename BlockSourceOf<Src>::type Source;
     typedef typename BlockShapeOf<Source::kRunStaged, C>::type Shape;
-    static_assert(Shape::BM == kBlockCfg[C].rows && Shape::BN == kBlockCfg[C].tokens && Shape::WAVES == kBlockWaves,
+    static_assert(Shape::BM == kBlockCfg[C].rows && Shape::BN == kBlockCfg[C].tokens && Shape::WAVES == kBlockWaves
+                      && Shape::WK == kBlockCfg[C].k_groups(),
                   "the table and the shape disagree");
     auto kernel = linear_block_kernel<Source, Shape>;
     constexpr size_t lds = Shape::template lds_bytes<Source>();
@@ -586,24 +609,6 @@ fp6_status launch_block_cfg(const BlockPlan &p, const void *weights, const void 
                        static_cast<const half_t *>(X), static_cast<half_t *>(Y), (int)M, (int)N, (int)K, p.split,
                        p.n_blocks, p.row_blocks, p.chunk, partials, counters, p.counter_step, epi);
     return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
-}
-
-// Whether the 128 x 64 block of the tiled kernel takes two groups of k-tiles (eight waves) instead of one (four).  Worth it where
-// the conversions are long beside the matrix work and a slice is long enough for the second pipeline fill and the meeting in LDS.
-// Median time with two over one, 1166 calls of 256 to 57344 rows and 65 to 128 tokens, by k-tiles per slice:
-//                  < 8    8-12   12-20  20-40  > 40
-//   3 bits         0.95   0.93   0.91   0.89   0.85    (largest 1.15, 0.96, 0.96, 1.03, 0.88)
-//   4 bits         0.97   0.96   0.95   0.91   0.91    (1.16, 1.09, 0.99, 0.97, 0.94)
-//   5 bits         1.00   0.99   0.98   0.96   0.93    (1.22, 1.04, 1.17, 1.00, 0.95)
-//   6 bits         1.03   1.03   1.02   1.00   1.00
-//   group scales   1.08   1.04   1.01   0.98   0.97    (1.25, 1.14, 1.09, 0.99, 0.99)
-template <class Src>
-bool two_k_groups(int64_t K, int split)
-{
-    const int64_t k_tiles = K / kTileK / split;
-    if (weights_of<Src>() == Weights::kPacked && Src::kBits == 6)
-        return false;
-    return k_tiles >= (weights_of<Src>() == Weights::kPacked && Src::kBits < 5 ? 12 : 20);
 }
 
 template <class Src, int RT, int NT, int WM, int WN, int WK>
@@ -660,7 +665,7 @@ size_t counter_region_bytes(int64_t M, int64_t N, int64_t K)
         at_least(plan_stream(M, N, K, stream_weights_of<PlainFp16Source>()).counter_bytes);
         return bytes;
     }
-    for (Weights kind : {Weights::kPacked, Weights::kGrouped, Weights::kFp16})
+    for (Weights kind : {Weights::kFp6, Weights::kFp5, Weights::kFp4, Weights::kFp3, Weights::kGrouped, Weights::kFp16})
         for (int64_t n : prompt_chunks(N, K))
             if (n > 0)
                 at_least(plan_prompt(M, n, K, kind).counter_bytes());
@@ -707,7 +712,7 @@ fp6_status plan_prompt_within(int64_t M, int64_t N, int64_t K, Weights kind, con
     const fp6_status fits = workspace.view(p.counter_bytes(), p.partial_bytes(), buf);
     if (fits != FP6_ERR_WORKSPACE || !p.is_block() || g_forced_split.load(std::memory_order_relaxed) > 0)
         return fits;
-    const TiledPlan least = tiled_plan_of(few_blocks(M, N) ? kTile128x64 : kTile128x128, M, N, K);
+    const TiledPlan least = tiled_plan_of(few_blocks(M, N) ? kTile128x64 : kTile128x128, M, N, K, kind);
     const size_t bytes = workspace.base ? workspace.bytes : 0, region = workspace.counter_region;
     size_t enough = least.partial_bytes;
     if (kind == Weights::kFp16 && fp16_accepted_partials(M, N, K) < enough)
@@ -737,7 +742,7 @@ fp6_status launch_prompt_chunk(const void *weights, const void *scales, const vo
         if constexpr (weights_of<Src>() != Weights::kGrouped) {
             FP6_BLOCK_CASE(0)
         }
-        if constexpr (weights_of<Src>() != Weights::kPacked) {
+        if constexpr (!per_row(weights_of<Src>())) {
             FP6_BLOCK_CASE(1)
             FP6_BLOCK_CASE(2)
         }
@@ -749,17 +754,17 @@ fp6_status launch_prompt_chunk(const void *weights, const void *scales, const vo
     }
     const TileShape &t = p.tiled.tile;
 #define FP6_TILED_CASE(RT_, NT_, WM_, WN_, WK_)                                                                        \
-    if (t.rt == RT_ && t.nt == NT_ && t.wm == WM_ && t.wn == WN_ && t.wk >= WK_)                                                 \
+    if (t.rt == RT_ && t.nt == NT_ && t.wm == WM_ && t.wn == WN_ && p.tiled.k_groups == WK_)                                      \
         return launch_tiled_cfg<Src, RT_, NT_, WM_, WN_, WK_>(p.tiled, weights, scales, X, Y, M, N, K, partials, counters, epi, \
                                                          stream);
     if constexpr (weights_of<Src>() != Weights::kFp16) {
-        if (two_k_groups<Src>(K, p.tiled.split)) {
+        if constexpr (weights_of<Src>() != Weights::kFp6) {
             FP6_TILED_CASE(2, 4, 4, 1, 2)
         }
         FP6_TILED_CASE(2, 4, 4, 1, 1)
         FP6_TILED_CASE(2, 4, 4, 2, 1)
     }
-    if constexpr (weights_of<Src>() == Weights::kPacked) {
+    if constexpr (per_row(weights_of<Src>())) {
         FP6_TILED_CASE(2, 4, 8, 1, 1)
         FP6_TILED_CASE(2, 8, 8, 1, 1)
     }
@@ -935,7 +940,7 @@ fp6_status static_plan(int64_t M, int64_t N, int64_t K, size_t &counter_bytes)
     for (int64_t n : prompt_chunks(N, K)) {
         if (n <= 0)
             continue;
-        const PromptPlan p = plan_prompt(M, n, K, Weights::kPacked);
+        const PromptPlan p = plan_prompt(M, n, K, Weights::kFp6);
         if (p.counter_bytes() > counter_bytes)
             counter_bytes = p.counter_bytes();
         const fp6_status fits = probe.view(p.counter_bytes(), p.partial_bytes(), unused);
@@ -961,6 +966,48 @@ fp6_status packed_linear_impl(const void *packed, const void *scales_f16, const 
     if (N > kStreamMaxN)
         return launch_prompt<Src>(packed, scales_f16, X_f16, Y_f16, M, N, K, ws, epi, static_cast<hipStream_t>(stream));
     return launch_stream<Src>(packed, scales_f16, X_f16, Y_f16, M, N, K, ws, epi, static_cast<hipStream_t>(stream));
+}
+
+// What fp6_tuning_plan reports, and the groups of k-tiles of a workgroup.
+fp6_status plan_of_call(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes, fp6_launch_plan &plan,
+                        int &k_groups)
+{
+    const bool fp16 = weight_bits == 16, grouped = weight_bits == -6;
+    if (!(fp16 ? shape_ok(M, K) : packed_shape_ok(M, K)) || token < 0 || token >= N || N >= (1ll << 31)
+        || !(fp16 || grouped || (weight_bits >= 3 && weight_bits <= 6)))
+        return FP6_ERR_SHAPE;
+    const size_t region = counter_region_bytes(M, N, K);
+    const WorkspaceRef ws{reinterpret_cast<void *>(uintptr_t(256)), workspace_bytes, region};  // never dereferenced
+    SplitBuffers unused;
+    if (N <= kStreamMaxN) {
+        const StreamWeights w = fp16               ? stream_weights_of<PlainFp16Source>()
+                                : weight_bits == 3 ? stream_weights_of<PackedFp3Source>()
+                                : weight_bits == 4 ? stream_weights_of<PackedFp4Source>()
+                                : weight_bits == 5 ? stream_weights_of<PackedFp5Source>()
+                                : grouped          ? stream_weights_of<PackedFp6GroupSource>() : stream_weights_of<PackedFp6Source>();
+        const StreamPlan p = plan_stream(M, N, K, w);
+        const fp6_status fits = stream_buffers(p, ws, unused);
+        if (fits != FP6_OK)
+            return fits;
+        const StreamCfg &c = (fp16 ? kStreamCfgFp16 : kStreamCfg)[p.cfg];
+        plan = {FP6_KERNEL_STREAM, kTileRows * c.wm, 16 * c.nt, p.split, 0, N, p.counter_bytes, region, p.partial_bytes};
+        k_groups = c.wk;
+        return FP6_OK;
+    }
+    const Weights kind = fp16               ? Weights::kFp16
+                         : grouped          ? Weights::kGrouped
+                         : weight_bits == 3 ? Weights::kFp3
+                         : weight_bits == 4 ? Weights::kFp4 : weight_bits == 5 ? Weights::kFp5 : Weights::kFp6;
+    const int64_t chunk = prompt_chunk_tokens(K), first = token / chunk * chunk, tokens = N - first < chunk ? N - first : chunk;
+    PromptPlan p;
+    const fp6_status fits = plan_prompt_within(M, tokens, K, kind, ws, p, unused);
+    if (fits != FP6_OK)
+        return fits;
+    plan = {p.is_block() ? FP6_KERNEL_BLOCK : FP6_KERNEL_TILED, p.is_block() ? kBlockCfg[p.block.cfg].rows : p.tiled.tile.rows(),
+            p.is_block() ? kBlockCfg[p.block.cfg].tokens : p.tiled.tile.tokens(), p.split(), first, tokens, p.counter_bytes(),
+            region, p.partial_bytes()};
+    k_groups = p.is_block() ? kBlockCfg[p.block.cfg].k_groups() : p.tiled.k_groups;
+    return FP6_OK;
 }
 
 }  // namespace
@@ -992,8 +1039,8 @@ size_t fp6_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
         // fp5, fp4 and fp6g ask here too
         return stream_workspace_bytes(M, N, K, {stream_weights_of<PackedFp6Source>(), stream_weights_of<PackedFp6GroupSource>(),
                                                 stream_weights_of<PackedFp5Source>(), stream_weights_of<PackedFp4Source>()});
-    // fp6g_linear asks here too
-    const size_t bytes = prompt_workspace_bytes(M, N, K, Weights::kPacked), grouped = prompt_workspace_bytes(M, N, K, Weights::kGrouped);
+    // fp6g_linear asks here too (fp5 and fp4 have the partial sums of fp6)
+    const size_t bytes = prompt_workspace_bytes(M, N, K, Weights::kFp6), grouped = prompt_workspace_bytes(M, N, K, Weights::kGrouped);
     return bytes > grouped ? bytes : grouped;
 }
 
@@ -1022,39 +1069,15 @@ void fp6_tuning_set_tile(int block_rows, int block_tokens)
 fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes,
                            fp6_launch_plan *plan)
 {
-    if (!plan)
-        return FP6_ERR_NULL;
-    const bool fp16 = weight_bits == 16, grouped = weight_bits == -6;
-    if (!(fp16 ? shape_ok(M, K) : packed_shape_ok(M, K)) || token < 0 || token >= N || N >= (1ll << 31)
-        || !(fp16 || grouped || (weight_bits >= 3 && weight_bits <= 6)))
-        return FP6_ERR_SHAPE;
-    const size_t region = counter_region_bytes(M, N, K);
-    const WorkspaceRef ws{reinterpret_cast<void *>(uintptr_t(256)), workspace_bytes, region};  // never dereferenced
-    SplitBuffers unused;
-    if (N <= kStreamMaxN) {
-        const StreamWeights w = fp16               ? stream_weights_of<PlainFp16Source>()
-                                : weight_bits == 3 ? stream_weights_of<PackedFp3Source>()
-                                : weight_bits == 4 ? stream_weights_of<PackedFp4Source>()
-                                : weight_bits == 5 ? stream_weights_of<PackedFp5Source>()
-                                : grouped          ? stream_weights_of<PackedFp6GroupSource>() : stream_weights_of<PackedFp6Source>();
-        const StreamPlan p = plan_stream(M, N, K, w);
-        const fp6_status fits = stream_buffers(p, ws, unused);
-        if (fits != FP6_OK)
-            return fits;
-        const StreamCfg &c = (fp16 ? kStreamCfgFp16 : kStreamCfg)[p.cfg];
-        *plan = {FP6_KERNEL_STREAM, kTileRows * c.wm, 16 * c.nt, p.split, 0, N, p.counter_bytes, region, p.partial_bytes};
-        return FP6_OK;
-    }
-    const int64_t chunk = prompt_chunk_tokens(K), first = token / chunk * chunk, tokens = N - first < chunk ? N - first : chunk;
-    PromptPlan p;
-    const fp6_status fits = plan_prompt_within(M, tokens, K, fp16 ? Weights::kFp16 : grouped ? Weights::kGrouped : Weights::kPacked,
-                                               ws, p, unused);
-    if (fits != FP6_OK)
-        return fits;
-    *plan = {p.is_block() ? FP6_KERNEL_BLOCK : FP6_KERNEL_TILED, p.is_block() ? kBlockCfg[p.block.cfg].rows : p.tiled.tile.rows(),
-             p.is_block() ? kBlockCfg[p.block.cfg].tokens : p.tiled.tile.tokens(), p.split(), first, tokens, p.counter_bytes(),
-             region, p.partial_bytes()};
-    return FP6_OK;
+    int k_groups;
+    return plan ? plan_of_call(weight_bits, M, N, K, token, workspace_bytes, *plan, k_groups) : FP6_ERR_NULL;
+}
+
+int fp6_tuning_plan_k_groups(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes)
+{
+    fp6_launch_plan plan;
+    int k_groups = 0;
+    return plan_of_call(weight_bits, M, N, K, token, workspace_bytes, plan, k_groups) == FP6_OK ? k_groups : 0;
 }
 
 fp6_status fp6_workspace_init(void *workspace, size_t workspace_bytes, void *stream)
@@ -1214,7 +1237,7 @@ size_t fp3_linear_workspace_bytes(int64_t M, int64_t N, int64_t K)
     if (!packed_shape_ok(M, K) || N <= 0)
         return 0;
     return N <= kStreamMaxN ? stream_workspace_bytes(M, N, K, {stream_weights_of<PackedFp3Source>()})
-                            : prompt_workspace_bytes(M, N, K, Weights::kPacked);
+                            : prompt_workspace_bytes(M, N, K, Weights::kFp3);
 }
 
 fp6_status fp3_quantize_pack(const void *W_f16, int64_t M, int64_t K, void *packed, void *scales_f16, void *stream)

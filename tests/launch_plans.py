@@ -18,6 +18,11 @@ def plan(lib, width, M, N, K, token=0, workspace_bytes=2 ** 64 - 1):
     return p if status == 0 else status
 
 
+def k_groups(lib, width, M, N, K, token=0, workspace_bytes=2 ** 64 - 1):
+    """Groups of k-tiles of a workgroup of the same launch; 0: refused."""
+    return lib.fp6_tuning_plan_k_groups(BITS[width], M, N, K, token, workspace_bytes)
+
+
 def workspace_bytes(lib, width, M, N, K):
     name = "fp6" if width == "fp6g" else width
     return getattr(lib, name + "_linear_workspace_bytes")(M, N, K)

@@ -5,7 +5,7 @@ import random
 
 import pytest
 
-from launch_plans import BITS, plan, workspace_bytes
+from launch_plans import BITS, TILED, k_groups, plan, workspace_bytes
 
 
 @pytest.fixture(scope="module")
@@ -156,3 +156,14 @@ def test_fp16_calls_that_ran_still_run(lib):
         smaller += more and have > 0
         without += more and have == 0
     assert smaller > 10 and without > 3
+
+
+@pytest.mark.parametrize("width,K,groups", [("fp6", 8192, 1), ("fp6", 98304, 1), ("fp5", 65536, 1), ("fp5", 98304, 2), ("fp4", 32768, 1),
+                                            ("fp4", 49152, 2), ("fp3", 65536, 2), ("fp6g", 65536, 1), ("fp6g", 98304, 2)])
+def test_tiled_counters_are_one_per_wave(lib, width, K, groups):
+    """One arrival counter per wave that the launch has, 128 bytes apart where there are few."""
+    M, N = 128, 80
+    p = plan(lib, width, M, N, K)
+    assert (p.kernel, p.block_rows, p.block_tokens) == (TILED, 128, 64) and p.split_k > 1
+    assert k_groups(lib, width, M, N, K) == groups
+    assert p.counter_bytes == 2 * 4 * groups * 128
