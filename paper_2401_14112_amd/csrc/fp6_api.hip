@@ -820,23 +820,10 @@ fp6_status launch_stream_cfg(const StreamPlan &p, const void *weights, const voi
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds, lds_done))
         return FP6_ERR_HIP;
     const dim3 grid((unsigned)p.row_blocks, (unsigned)p.split), block(Shape::kThreads);  // x runs fastest: row blocks of one k slice
-    // tokens are processed 16*nt at a time; each pass re-streams the weights
-    const int64_t step = 16 * c.nt;
-    const int64_t Mout = epi.gated ? M / 2 : M;
-    for (int64_t n0 = 0; n0 < N; n0 += step) {
-        const int64_t n = (N - n0 < step) ? (N - n0) : step;
-        const half_t *Xp = static_cast<const half_t *>(X) + n0 * K;
-        half_t *Yp = static_cast<half_t *>(Y) + n0 * Mout;
-        Epilogue e = epi;
-        if (e.residual)
-            e.residual += n0 * Mout;
-        hipLaunchKernelGGL(kernel, grid, block, lds, stream, weights, static_cast<const half_t *>(scales), Xp, Yp,
-                           (int)M, (int)n, (int)K, p.split, (int)((K + Src::kTileCols - 1) / Src::kTileCols / p.split),
-                           partials, counters, e);
-        if (hipGetLastError() != hipSuccess)
-            return FP6_ERR_HIP;
-    }
-    return FP6_OK;
+    hipLaunchKernelGGL(kernel, grid, block, lds, stream, weights, static_cast<const half_t *>(scales), static_cast<const half_t *>(X),
+                       static_cast<half_t *>(Y), (int)M, (int)N, (int)K, p.split,
+                       (int)((K + Src::kTileCols - 1) / Src::kTileCols / p.split), partials, counters, epi);
+    return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
 }
 
 template <class Src, int C = 0>
