@@ -6,7 +6,7 @@
 // one split-K slice of one row tile (the
 // weight source says how wide a tile is: 256 columns, 512 for the sources whose lane
 // loads only come out as whole 128-bit pieces that way); weights go HBM -> VGPR with a
-// few 128-bit loads per lane per tile (three for 6 bits), prefetched DEPTH tiles ahead,
+// few 128-bit loads per lane per tile (three for 6 bits), requested two tiles ahead,
 // and are used by exactly one wave, so they never touch LDS (one source, row-major fp16
 // weights, stages its tiles in a region of LDS private to the wave instead).  The
 // activations (16*NT tokens) are the only shared operand: the block copies
@@ -168,15 +168,15 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_stream_kernel(
     };
 
     // ---- software pipeline.  Slot t % DEPTH of the register ring holds weight tile t of the wave; it is
-    // requested DEPTH tiles ahead, right after the slot's previous tile has been consumed, so DEPTH-1 tiles
-    // stay in flight while one is being computed.  The activation copies of stage t+1 are requested at the start of
-    // stage t, after its barrier (by then every wave has finished
+    // requested DEPTH tiles ahead, right after the slot's previous tile has been consumed.  The activation copies of stage t+1
+    // are requested at the start of stage t, after its barrier (by then every wave has finished
     // reading the buffer they overwrite).  Loads complete in order, so "at most n outstanding" with n = the
     // loads requested after the ones needed means those have arrived.  The copies of stage t, and the weights of tile t before
-    // them, are followed by the weights of one tile only.  (More in flight, three or four buffers of activations with three
+    // them, are followed by the weights of one tile only: past the wait that tile alone is in flight, joined by the copies of
+    // the next stage while tile t is computed.  A deeper ring alone changes nothing of that, its further tiles have arrived.  (More in flight, three or four buffers of activations with three
     // or four weight tiles: 8192 x 22016, N = 64 36.1 -> 37-43 us, N = 32 equal.)
     // Tiles past the end of the slice read as zeros
-    // through the buffer bounds check (no memory traffic), so the request pattern never varies.
+    // through the buffer bounds check (no memory traffic; but for the 4-byte group scales), so the request pattern never varies.
     static_assert(DEPTH >= 2, "the wait below leaves the weights of one tile in flight");
     typename Src::Tile w[DEPTH];
     w_stream.bind_slots(w, xs_dyn + 2 * STAGE_PIECES + wave * (DEPTH * Src::kLdsTileBytes / 16), lane);
