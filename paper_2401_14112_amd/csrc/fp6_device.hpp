@@ -329,7 +329,7 @@ struct PackedFp6GroupSource {
     struct Stream {
         rsrc_t w_rsrc, s_rsrc;
         int w_off, w_stride, s_off;
-        int s_stride;
+        int s_stride, n_own;
         __device__ __forceinline__ void init(const void *weights, const half_t *scales, int64_t row_tile, int kt_first,
                                              int kt_step, int n_tiles, int64_t RT, int64_t K, int lane)
         {
@@ -337,8 +337,9 @@ struct PackedFp6GroupSource {
             w_off = lane * 16;
             w_stride = __builtin_amdgcn_readfirstlane(PackedFp6Source::tile_stride(RT) * kt_step);
             const int groups = (int)(K / kGroupColumns);  // per row; = 2 * KT
-            // the scales of the 16 rows of the row tile; a tile past the slice reads other finite scales or
-            // zeros, and its weights read as zeros
+            // the scales of the 16 rows of the row tile; past the last tile lie those of another slice or of the next row, which
+            // may be infinite: such a tile, whose weights read as zeros, is sent out of range
+            n_own = n_tiles;
             s_rsrc = make_rsrc(scales + row_tile * kTileRows * groups, (uint32_t)(kTileRows * groups * 2));
             s_off = ((lane & 15) * groups + 2 * kt_first) * 2;
             s_stride = __builtin_amdgcn_readfirstlane(4 * kt_step);
@@ -349,7 +350,7 @@ struct PackedFp6GroupSource {
             t.p0 = issue_load_b128<0, true>(w_rsrc, off);
             t.p1 = issue_load_b128<1024, true>(w_rsrc, off);
             t.p2 = issue_load_b128<2048, true>(w_rsrc, off);
-            t.sc = issue_load_b32<0>(s_rsrc, s_off + i * s_stride);
+            t.sc = issue_load_b32<0>(s_rsrc, i < n_own ? s_off + i * s_stride : kOutOfRange);
         }
         template <int D>
         __device__ __forceinline__ void bind_slots(Tile (&)[D], u32x4 *, int) const

@@ -176,7 +176,7 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_stream_kernel(
     // the next stage while tile t is computed.  A deeper ring alone changes nothing of that, its further tiles have arrived.  (More in flight, three or four buffers of activations with three
     // or four weight tiles: 8192 x 22016, N = 64 36.1 -> 37-43 us, N = 32 equal.)
     // Tiles past the end of the slice read as zeros
-    // through the buffer bounds check (no memory traffic; but for the 4-byte group scales), so the request pattern never varies.
+    // through the buffer bounds check (no memory traffic), so the request pattern never varies.
     static_assert(DEPTH >= 2, "the wait below leaves the weights of one tile in flight");
     typename Src::Tile w[DEPTH];
     w_stream.bind_slots(w, xs_dyn + 2 * STAGE_PIECES + wave * (DEPTH * Src::kLdsTileBytes / 16), lane);

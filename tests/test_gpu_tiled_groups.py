@@ -7,7 +7,7 @@ import torch
 
 import workloads
 from gpu_checks import check_linear
-from launch_plans import TILED, plan
+from launch_plans import TILED, k_groups, plan
 
 pytestmark = pytest.mark.gpu
 
@@ -37,3 +37,31 @@ def test_two_k_groups(width, M, K, N, split):
         pkg.fp6_tuning_set_split_k(0)
     assert torch.equal(runs[0].view(torch.int16), runs[1].view(torch.int16))
     check_linear(runs[0].cpu().numpy(), o.linear(packed, scales, X.numpy(), M, K, *group), "%s %d" % (width, split))
+
+
+def test_rows_stay_apart():
+    """An odd number of k-tiles: the second group multiplies one tile past the end by zero activations.  A row whose neighbour has
+    infinite group scales keeps its bits (the tile past the end of a row is the next row's first)."""
+    import paper_2401_14112_amd as pkg
+
+    M, K, N = 144, 5376, 80
+    print("rows apart M=%d K=%d N=%d" % (M, K, N), flush=True)
+    pkg.fp6_tuning_set_tile(128, 64)
+    pkg.fp6_tuning_set_split_k(1)
+    try:
+        lib = pkg.load_library()
+        assert plan(lib, "fp6g", M, N, K).kernel == TILED and k_groups(lib, "fp6g", M, N, K) == 2
+        packed, scales = pkg.fp6g_quantize_pack(workloads.make_weights(M, K, 1, device="cuda"))
+        X = workloads.make_activations(N, K, 2, device="cuda")
+        clean = pkg.fp6g_linear(packed, scales, X, M, K)
+        bad = torch.arange(0, M, 3)
+        poisoned = scales.clone()
+        poisoned[bad.cuda()] = float("inf")
+        out = pkg.fp6g_linear(packed, poisoned, X, M, K)
+    finally:
+        pkg.fp6_tuning_set_tile(0, 0)
+        pkg.fp6_tuning_set_split_k(0)
+    good = torch.ones(M, dtype=torch.bool)
+    good[bad] = False
+    assert torch.equal(out.cpu()[:, good].view(torch.int16), clean.cpu()[:, good].view(torch.int16))
+    assert not torch.isfinite(out.cpu()[:, bad].float()).any()
