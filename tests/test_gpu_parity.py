@@ -164,8 +164,8 @@ def test_linear_token_counts(pkg, oracle, N):
 
 @pytest.mark.parametrize("M,K,N", [(10256, 1536, 5), (10240, 1536, 16), (28672, 512, 3)])
 def test_linear_tall_stream_blocks(pkg, oracle, M, K, N):
-    """Shapes for which the plan takes the 8-wave block of the N <= 16 streaming kernel (more blocks fit one
-    round than with 4-wave blocks), with and without a ragged last block and with / without split-K."""
+    """Tall layers with few k-tiles: blocks of four row tiles and two groups of k-tiles, with and without a ragged last block, and
+    of eight row tiles."""
     _say("tall stream blocks M=%d K=%d N=%d" % (M, K, N))
     W = workloads.make_weights(M, K, seed=11)
     packed, scales = oracle.quantize_pack(_np16(W))
@@ -259,8 +259,8 @@ def test_fp16_linear(pkg, oracle, N):
 @pytest.mark.parametrize("N", [3, 16, 32, 64])
 @pytest.mark.parametrize("split", [2, 3, 5])
 def test_fp16_linear_stream_forced_split(pkg, oracle, N, split):
-    """The fp16 weight tiles of the streaming kernel pass through LDS: every shape of that kernel (1, 2, 4 token
-    tiles per wave; 4- and 8-wave blocks with a ragged last block) under split-K factors that do not divide
+    """The fp16 weight tiles of the streaming kernel pass through LDS: the blocks that the hook for the split factor pins (eight row
+    tiles, beyond 32 tokens four; 1, 2 and 4 token tiles per wave; a ragged last block) under split-K factors that do not divide
     the 11 k-tiles, twice for identical bits."""
     M, K = 272, 2816
     _say("fp16_linear stream M=%d K=%d N=%d split=%d" % (M, K, N, split))

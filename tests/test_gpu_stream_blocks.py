@@ -1,7 +1,8 @@
 """The streaming kernel's blocks: row tiles, groups of k-tiles and staged tokens, at the sizes where each can go wrong (token
-counts at the edges of what is staged, fewer k-tiles than groups, a padded last tile of 3-bit weights, row tiles that do not
-fill a block, blocks with k slices)."""
+counts at the edges of what is staged, groups with fewer k-tiles than others or none, a padded last tile of 3-bit weights, row
+tiles that do not fill a block), and every block that a plan takes, with k slices and without."""
 import importlib
+import random
 
 import numpy as np
 import pytest
@@ -9,7 +10,7 @@ import torch
 
 import workloads
 from gpu_checks import check_linear
-from launch_plans import STREAM, plan
+from launch_plans import STREAM, k_groups, plan
 
 pytestmark = pytest.mark.gpu
 
@@ -29,7 +30,8 @@ def _oracle(width):
     return fpx_oracle.BY_PREFIX[width] if width in fpx_oracle.BY_PREFIX else importlib.import_module("oracle.%s_oracle" % width)
 
 
-# (M, K): one k-tile for eight groups; an odd number of them; a last row block with one row tile; with and without k slices
+# (M, K): one k-tile; nine for two to eight groups; five, eight groups (packed weights, up to 16 tokens), a last row block with few row
+# tiles; three; 31 in k slices; two, more row blocks than CUs
 SIZES = [(32, 256), (144, 2304), (2192, 1280), (4112, 768), (400, 7936), (6160, 512)]
 
 
@@ -57,6 +59,58 @@ def test_blocks(pkg, width, N):
         assert torch.equal(runs[0].view(torch.int16), runs[1].view(torch.int16))
         check_linear(runs[0].cpu().numpy(), Y_ref, "%s M=%d K=%d N=%d" % (width, M, K, N))
     assert len(rows) > 1, "the sizes are meant to reach several blocks"
+
+
+def _blocks_taken(lib, width, N):
+    """{(row tiles, k groups, has k slices): (M, K)} over the plan's choices, each at the smallest layer drawn for it; where one has a
+    last row block that is not full, at the smallest of those."""
+    rng = random.Random(N)
+    taken = {}
+    for _ in range(20000):
+        M, K = 16 * round(3584 ** rng.random()), 256 * round(112 ** rng.random())
+        p = plan(lib, width, M, N, K)
+        key = (p.block_rows // 16, k_groups(lib, width, M, N, K), p.split_k > 1)
+        size = (M % p.block_rows == 0, M * K)
+        if key not in taken or size < taken[key][0]:
+            taken[key] = size, M, K
+    return {key: (M, K) for key, (_, M, K) in taken.items()}
+
+
+def _blocks(width, N):
+    """(row tiles, k groups) of the blocks that there are for a token count."""
+    if width == "fp16":
+        return {(8, 1), (4, 1), (4, 2), (1, 4)} if N <= 16 else {(8, 1), (6, 1), (2, 2)} if N <= 32 else {(4, 1), (6, 1)}
+    if width == "fp3":  # twice the columns per k-tile: fewer groups fit the LDS
+        return ({(8, 1), (4, 2), (2, 4), (1, 8)} if N <= 8 else {(8, 1), (4, 2), (2, 4)} if N <= 16 else
+                {(8, 1), (6, 1), (4, 2)} if N <= 32 else {(8, 1), (6, 1)})
+    return ({(8, 1), (4, 2), (2, 4), (1, 8)} if N <= 16 else {(8, 1), (6, 1), (4, 2), (2, 4)} if N <= 32 else
+            {(8, 1), (6, 1), (4, 2)})
+
+
+@pytest.mark.parametrize("N", [2, 8, 15, 17, 33, 64])
+@pytest.mark.parametrize("width", ["fp6", "fp6g", "fp5", "fp4", "fp3", "fp16"])
+def test_every_block_with_and_without_slices(pkg, width, N):
+    """Against fp32 products with the code values (fp6g, fp16: with the fp16 weights)."""
+    lib = pkg.load_library()
+    taken = _blocks_taken(lib, width, N)
+    missing = {(rows, groups, slices) for rows, groups in _blocks(width, N) for slices in (False, True)} - set(taken)
+    assert not missing - {(6, 1, True)} if width == "fp16" and N > 48 else not missing, missing
+    assert {key[:2] for key in taken} == _blocks(width, N)
+    for (rows, groups, slices), (M, K) in sorted(taken.items()):
+        print("%s M=%d K=%d N=%d: %d row tiles x %d groups%s" % (width, M, K, N, rows, groups, ", slices" if slices else ""), flush=True)
+        W, X = workloads.make_weights(M, K, M + N, device="cuda"), workloads.make_activations(N, K, K + N, device="cuda")
+        if width == "fp16":
+            runs = [pkg.fp16_linear(W, X) for _ in range(2)]
+            ref = X.float() @ W.float().t()
+        else:
+            packed, scales = getattr(pkg, width + "_quantize_pack")(W)
+            runs = [getattr(pkg, width + "_linear")(packed, scales, X, M, K) for _ in range(2)]
+            if width == "fp6g":
+                ref = X.float() @ pkg.fp6g_unpack(packed, scales, M, K).float().t()
+            else:
+                ref = X.float() @ getattr(pkg, width + "_unpack")(packed, torch.ones_like(scales), M, K).float().t() * scales.float()
+        assert torch.equal(runs[0].view(torch.int16), runs[1].view(torch.int16))
+        check_linear(runs[0].cpu().numpy(), ref.cpu().numpy().astype(np.float64), "%s M=%d K=%d N=%d" % (width, M, K, N))
 
 
 @pytest.mark.parametrize("width", ["fp6", "fp6g", "fp5", "fp4", "fp3", "fp16"])

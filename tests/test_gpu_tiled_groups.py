@@ -12,6 +12,10 @@ from launch_plans import TILED, k_groups, plan
 pytestmark = pytest.mark.gpu
 
 
+# k-tiles of a slice from which a format takes two groups
+TWO_GROUPS_FROM = {"fp6": None, "fp6g": 20, "fp5": 20, "fp4": 12, "fp3": 12}
+
+
 @pytest.mark.parametrize("split", [1, 2])
 @pytest.mark.parametrize("M,K,N", [(32, 256, 65), (144, 2816, 100), (272, 3328, 128), (128, 9472, 77), (144, 10752, 66)])
 @pytest.mark.parametrize("width", ["fp6", "fp6g", "fp5", "fp4", "fp3"])
@@ -30,6 +34,8 @@ def test_two_k_groups(width, M, K, N, split):
     try:
         p = plan(pkg.load_library(), width, M, N, K)
         assert (p.kernel, p.block_rows, p.block_tokens) == (TILED, 128, 64)
+        start = TWO_GROUPS_FROM[width]
+        assert k_groups(pkg.load_library(), width, M, N, K) == (2 if start and K // 256 // p.split_k >= start else 1)
         runs = [getattr(pkg, width + "_linear")(*device, X.cuda(), M, K, *group) for _ in range(2)]
         torch.cuda.synchronize()
     finally:
