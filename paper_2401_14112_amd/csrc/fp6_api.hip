@@ -189,6 +189,8 @@ fp6_status stream_buffers(const StreamPlan &p, const WorkspaceRef &workspace, Sp
 // 9.5 ns per KB of activations and from three token tiles on 80 ns for each, on a CU that does not wait for memory; the
 // launch as a whole is no faster than 6.9 TB/s, and then half of the activation time still shows; a launch with k slices
 // hands them over, one with groups of k-tiles adds them up in LDS.
+// The chosen block against the best of all, each pinned in turn (9900 calls of 512 to 32768 rows and 1024 to 28672 columns, weights
+// from memory): by format and token count 1.6 to 2.8 % slower on average, 4.9 % for 3 bits and 17 to 32 tokens.
 double stream_cost(const StreamCfg &c, int64_t M, int64_t K, int64_t s, const StreamWeights &w)
 {
     const int64_t KT = (K + w.tile_cols - 1) / w.tile_cols;

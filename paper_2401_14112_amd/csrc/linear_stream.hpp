@@ -96,9 +96,9 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_stream_kernel(
 
     // ---- activation staging.  A k-tile is stored as blocks of 1 KB, one copy each: token tile nt, segment of 64 columns, half
     // h of the token tile (rows 8h .. 8h+7).  Lane 8*rho + pi of a copy fetches row 8h + rho, 8-column
-    // chunk pi ^ w_swizzle(row) of the segment, so the eight lanes of a row fetch one whole 128-byte line (in copies of 16
-    // rows x 64 bytes every line is requested twice: 8192 x 22016, N = 64 36.0 -> 34.7 us with nothing but the copies and
-    // the weight loads running).  XR = 8: no second half; XR = 2: a block is two rows of 256 columns, chunk pi ^ 4 * row.
+    // chunk pi ^ w_swizzle(row) of the segment, so the eight lanes of a row fetch one whole 128-byte line (8192 x 22016,
+    // N = 64 36.0 -> 34.7 us against copies of 16 rows x 64 bytes with nothing but the copies and the weight loads running;
+    // the L1 asks the L2 for each line once either way, 2.53 M requests).  XR = 8: no second half; XR = 2: a block is two rows of 256 columns, chunk pi ^ 4 * row.
     // Tokens >= N lie past the end of the buffer; k-tiles past the end of the slice and segments past K (the padding of a
     // last tile) get an offset outside it: nothing is fetched and zeros land in LDS.
     constexpr int ROWS = XR < 8 ? XR : 8, ROW_LANES = 64 / ROWS, SEG = 8 * ROW_LANES, HALVES = XR / ROWS;
