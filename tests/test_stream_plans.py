@@ -61,3 +61,11 @@ def test_group_scales_take_every_block_of_six_bits():
                   for w in ("fp6", "fp6g")}
         assert blocks["fp6"] == blocks["fp6g"], N
     assert plan(lib, "fp6g", 8192, 16, 2048).block_rows == 32
+
+
+def test_fp16_ties_go_to_the_fuller_chip():
+    """Two blocks at the memory's rate have one estimate: 43 row blocks of eight row tiles x 3 slices, or 85 of four x 3."""
+    import paper_2401_14112_amd as pkg
+
+    p = plan(pkg.load_library(), "fp16", 5424, 9, 20992)
+    assert (p.block_rows, p.split_k) == (64, 3)
