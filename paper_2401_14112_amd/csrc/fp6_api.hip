@@ -119,7 +119,7 @@ struct WorkspaceRef {
 
 // The weights a launch reads, as the plan sees them.
 struct StreamWeights {
-    bool packed;
+    bool packed, grouped;
     int bits;       // per weight
     int tile_cols;  // columns of a weight tile in the streaming kernel
     int lds_tile;   // bytes of LDS that a tile in flight takes
@@ -133,7 +133,7 @@ template <class Src>  // the source of a format, as the entry points name it
 constexpr StreamWeights stream_weights_of()
 {
     typedef typename Src::StreamSource S;
-    return {S::kPackedConfigs, S::kBits, S::kTileCols, S::kLdsTileBytes};
+    return {S::kPackedConfigs, std::is_same_v<S, PackedFp6GroupSource>, S::kBits, S::kTileCols, S::kLdsTileBytes};
 }
 
 struct StreamPlan {
@@ -241,6 +241,12 @@ StreamPlan plan_stream(int64_t M, int64_t N, int64_t K, const StreamWeights &w)
         while (s > 1 && (uint64_t)(KT + (c.wk > 4 ? 5 * c.wk : 20) * s) * (uint64_t)row_tiles * kTileBytes >= (1ull << 31))
             s /= 2;
         for (;; s /= 2) {  // the most slices, then halves
+            // Six row tiles with four token tiles (3 bits: with two as well) and no k slices take as many stages as the plan without them and
+            // copy the activations more often.  Median time without them over that with them, drawn calls, weights from memory: 6 bits 0.91, 5 and
+            // 4 bits 0.95, 3 bits 0.91 and 0.96 (5165 calls, largest 1.02), group scales 0.85 up to 128 row blocks of eight (1862 calls, largest
+            // 0.96) but up to 1.06 beyond, where they keep them.  (With slices six row tiles take 0.97 to 1.05 of the time of eight.)
+            if (w.packed && c.wm == 6 && (nt == 4 || (nt == 2 && w.bits == 3)) && s == 1 && !(w.grouped && row_tiles > 8 * 128))
+                break;
             const double cost = stream_cost(c, M, K, s, w);
             // fp16 weights at the memory's rate: where the estimate is the same for two blocks, the one that fills more CUs (5424 x
             // 20992, N = 9 47.1 -> 36.8 us; 5081 drawn calls with such a tie, median time 0.90, largest 1.05; packed weights lose by it)

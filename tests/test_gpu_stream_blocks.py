@@ -94,7 +94,8 @@ def test_every_block_with_and_without_slices(pkg, width, N):
     lib = pkg.load_library()
     taken = _blocks_taken(lib, width, N)
     missing = {(rows, groups, slices) for rows, groups in _blocks(width, N) for slices in (False, True)} - set(taken)
-    assert not missing - {(6, 1, True)} if width == "fp16" and N > 48 else not missing, missing
+    # with four token tiles (3 bits: with two as well) six row tiles take k slices, of fp16 weights none, of group scales both
+    assert missing == ({(6, 1, width == "fp16")} if N > 48 and width != "fp6g" or N == 17 and width == "fp3" else set()), missing
     assert {key[:2] for key in taken} == _blocks(width, N)
     for (rows, groups, slices), (M, K) in sorted(taken.items()):
         print("%s M=%d K=%d N=%d: %d row tiles x %d groups%s" % (width, M, K, N, rows, groups, ", slices" if slices else ""), flush=True)

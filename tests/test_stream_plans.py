@@ -69,3 +69,18 @@ def test_fp16_ties_go_to_the_fuller_chip():
 
     p = plan(pkg.load_library(), "fp16", 5424, 9, 20992)
     assert (p.block_rows, p.split_k) == (64, 3)
+
+
+def test_six_row_tiles_with_four_token_tiles_take_slices():
+    """Without k slices eight are faster (18608 x 22272, N = 57)."""
+    import paper_2401_14112_amd as pkg
+
+    lib = pkg.load_library()
+    rng = random.Random(6)
+    six = 0
+    for _ in range(4000):
+        width, M = rng.choice(["fp6", "fp5", "fp4", "fp3", "fp6g"]), 16 * round(3584 ** rng.random())
+        p = plan(lib, width, M, rng.randint(49, 64), 256 * round(112 ** rng.random()))
+        assert p.block_rows != 96 or p.split_k > 1 or (width == "fp6g" and M > 16384)
+        six += p.block_rows == 96
+    assert six > 100 and plan(lib, "fp5", 18608, 57, 22272).block_rows == 128
