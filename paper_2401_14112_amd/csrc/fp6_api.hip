@@ -199,7 +199,10 @@ double stream_cost(const StreamCfg &c, int64_t M, int64_t K, int64_t s, const St
     const double tile_kb = w.tile_cols / 512.0;  // of one bit per weight
     const double weight_kb = tile_kb * c.wm * c.wk * w.bits, x_kb = tile_kb * 16.0 * c.wk * c.nt * c.xr / 16.0;
     const double x_us = 0.0095 * x_kb + (c.nt > 2 ? 0.08 * c.nt * w.tile_cols / kTileK : 0.0);
-    const double handover = s > 1 ? 0.5 + (double)s * (0.17 + 0.15 * c.nt) : 0.0, groups = c.wk > 1 ? 0.1 + 0.05 * c.wk * c.nt : 0.0;
+    const double handover = s > 1 ? 0.5 + (double)s * (0.17 + 0.15 * c.nt) : 0.0;
+    // (group scales at 9 to 16 tokens: with 0.05 layers of 9 to 12 k-tiles take 2 x 4 blocks, which the scales make slower than 1 x 8; 2746
+    // drawn calls whose block that decides, median time 0.90, largest 1.10 at 304 rows)
+    const double per_group = w.grouped && c.nt == 1 && c.xr == 16 ? 0.045 : 0.05, groups = c.wk > 1 ? 0.1 + per_group * c.wk * c.nt : 0.0;
     const double alone = stages * (0.38 + (w.packed ? 0.005 : 0.016) * weight_kb + x_us) + handover;
     const double memory = (double)M * (double)K * w.bits / 8.0 / (w.packed ? 6.9e6 : 5.4e6) + stages * 0.5 * x_us + 0.3 * handover;
     return (alone > memory ? alone : memory) + groups;
