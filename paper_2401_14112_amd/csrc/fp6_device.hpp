@@ -381,7 +381,8 @@ struct PackedFp6GroupSource {
 // ---- 5-bit (e2m2) weights: the paper's scheme for a width the hardware cannot convert -------------
 // The paper presents its pre-packing and its cast as independent of the bit-width (Sections 5.2, 5.3).
 // CDNA4 has no conversion for e2m2, so this source de-quantizes the way Section 5.3 does, with shifts and
-// masks on whole words (four codes per 32-bit operation) and the exponent-bias multiply of Eq. 3.
+// masks on whole words (four codes per 32-bit operation).  The exponent-bias multiply of Eq. 3 comes with the
+// conversion of the byte "s...EEMM", which is an e5m2 number with three exponent bits of zero.
 // Tile: 16 rows x 256 columns = 2560 bytes = two planes of 16 bytes per lane and one of 8 bytes per lane;
 // lane L = 16q + r owns ten words, D0..D4 for runs 0..3 and another five for runs 4..7.  Of the 32 codes
 // of four runs (index i = 8*(run%4) + j), the first twenty sit in place in byte i%4 of D[i/4] as
@@ -390,17 +391,19 @@ struct PackedFp6GroupSource {
 //   codes 20..23:  s -> D0.6  e1 e0 -> D0.5 D0.4  m1 m0 -> D1.6 D1.5
 //   codes 24..27:  s -> D1.4  e1 e0 m1 -> D2.6 D2.5 D2.4  m0 -> D3.6
 //   codes 28..31:  s -> D3.5  e1 -> D3.4  e0 m1 m0 -> D4.6 D4.5 D4.4
-// Unpack per 32 codes: 5 ANDs, 3 three-term stitches, then per four codes two byte permutes and two
-// packed multiplies by 2^(15-1) (exact, the subnormal binade included).
+// Unpack per 32 codes: 5 ANDs, 3 three-term stitches, then per two codes one conversion times 2^(15-1)
+// (exact, the subnormal binade included).  It issues like any other VALU instruction; two byte permutes and two
+// packed multiplies per four codes took twice as many: 12288 x 12288, N = 45 31.2 -> 27.9 us, 8192 x 22016,
+// N = 16 / 32 / 64 / 100 / 512 21.9 / 26.7 / 36.4 / 57.3 / 155.6 -> 21.0 / 24.7 / 34.9 / 53.5 / 148.8,
+// 16384 x 8192, N = 2048 446 -> 409.
 __device__ __forceinline__ half8_t e2m2_bytes_to_fragment(uint32_t b_lo, uint32_t b_hi)
 {
-    const half2_t k = {(half_t)16384.0f, (half_t)16384.0f};
-    u32x4 r;
-    r[0] = bit_cast<uint32_t>(bit_cast<half2_t>(__builtin_amdgcn_perm(0u, b_lo, 0x010c000cu)) * k);  // [b1 0 b0 0]
-    r[1] = bit_cast<uint32_t>(bit_cast<half2_t>(__builtin_amdgcn_perm(0u, b_lo, 0x030c020cu)) * k);  // [b3 0 b2 0]
-    r[2] = bit_cast<uint32_t>(bit_cast<half2_t>(__builtin_amdgcn_perm(0u, b_hi, 0x010c000cu)) * k);
-    r[3] = bit_cast<uint32_t>(bit_cast<half2_t>(__builtin_amdgcn_perm(0u, b_hi, 0x030c020cu)) * k);
-    return bit_cast<half8_t>(r);
+    constexpr float kBias = 16384.0f;  // 2^(15-1)
+    const half2_t a = __builtin_amdgcn_cvt_scalef32_pk_f16_bf8(b_lo, kBias, false);
+    const half2_t b = __builtin_amdgcn_cvt_scalef32_pk_f16_bf8(b_lo, kBias, true);
+    const half2_t c = __builtin_amdgcn_cvt_scalef32_pk_f16_bf8(b_hi, kBias, false);
+    const half2_t d = __builtin_amdgcn_cvt_scalef32_pk_f16_bf8(b_hi, kBias, true);
+    return (half8_t){a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
 }
 
 struct PackedFp5Source {
