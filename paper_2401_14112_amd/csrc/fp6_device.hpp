@@ -87,7 +87,6 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void *base, uint32_t num_bytes
     return r;
 }
 
-constexpr int kPartialBatch = 4;  // split-K: partial tiles of this many k slices are fetched per trip to memory
 constexpr int kOutOfRange = (int)0x80000000u;  // a lane offset no buffer here reaches: reads as zeros
 
 // The pipelined kernels issue their loads from inline assembly and wait for them with explicit
@@ -166,8 +165,7 @@ __device__ __forceinline__ void issue_load_to_lds_b128(rsrc_t rsrc, int lane_off
 // ---- split-K partial tiles ---------------------------------------------------
 // Written and read 16 bytes per lane, each access performed at the point where all CUs of the device agree: the cache
 // bits (sc1) are those of an agent-scope atomic access, which only comes in pieces of up to 8 bytes.  The address unit
-// takes as long for a 4-byte access per lane as for a 16-byte one.  (The streaming kernel keeps its 4-byte accesses:
-// 16 bytes cost it 1.5 us at 32 and 64 tokens.)
+// takes as long for a 4-byte access per lane as for a 16-byte one.
 typedef __amdgpu_buffer_rsrc_t partial_rsrc_t;
 constexpr int kAgentScope = 16;  // sc1
 __device__ __forceinline__ partial_rsrc_t partial_buffer(void *p, int bytes)
@@ -181,6 +179,43 @@ __device__ __forceinline__ void agent_store(partial_rsrc_t r, int off, const flo
 __device__ __forceinline__ float4_t agent_load(partial_rsrc_t r, int off)
 {
     return bit_cast<float4_t>(__builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kAgentScope));
+}
+
+// The last arrival's sum of G tiles over all S slices, in slice order: its own tiles from registers (own(g): the same bits that
+// it stored), those of the other slices requested PB slices at a time, one trip to memory each (load(part, s)).  Only what is
+// added is read: with a batch of four clamped to the last slice and the own one read back, two slices cost four reads of a
+// tile and three slices four (9216 x 9216, N = 256, fp16, S = 3 83.6 -> 80.3 us; 4096 x 4096, N = 300, fp16, S = 2 26.9 -> 24.8;
+// 8192 x 8192, N = 400, group scales, S = 2 70.9 -> 65.8; 10240 x 8192, N = 64, 6 bits, S = 3 22.6 -> 21.6).
+template <int PB, int G, class Own, class Load>
+__device__ __forceinline__ void add_slices(float4_t (&sum)[G], int S, int split, Own &&own, Load &&load)
+{
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+        sum[g] = (float4_t){0.f, 0.f, 0.f, 0.f};
+    for (int j0 = 0; j0 < S - 1; j0 += PB) {  // slice j of the others is slice j, from the own one on j + 1
+        float4_t part[PB][G];
+#pragma unroll
+        for (int u = 0; u < PB; ++u)
+            if (j0 + u < S - 1)
+                load(part[u], j0 + u < split ? j0 + u : j0 + u + 1);
+#pragma unroll
+        for (int u = 0; u < PB; ++u)
+            if (j0 + u < S - 1) {
+                if (j0 + u == split) {
+#pragma unroll
+                    for (int g = 0; g < G; ++g)
+                        sum[g] += own(g);
+                }
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+                    sum[g] += part[u][g];
+            }
+    }
+    if (split == S - 1) {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            sum[g] += own(g);
+    }
 }
 
 // ---- activation tile layout in LDS -----------------------------------------

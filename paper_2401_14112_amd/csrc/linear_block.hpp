@@ -763,31 +763,17 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     if (arrived != S - 1)
         return;
-    // the partial tiles of a group of output tiles are requested together (one trip to memory per kPartialBatch slices
-    // and group) and added in slice order
-    constexpr int OG = OWN < 4 ? OWN : 4;
+    // groups of output tiles as large as the registers hold
+    constexpr int OG = OWN < 8 ? OWN : OWN <= 16 ? 8 : 2;
 #pragma unroll
     for (int o0 = 0; o0 < OWN; o0 += OG) {
         float4_t sum[OG];
+        add_slices<3>(sum, S, split, [&](int o) { return own[o0 + o]; }, [&](float4_t (&part)[OG], int s) {
+            const partial_rsrc_t src = slice_of(s);
 #pragma unroll
-        for (int o = 0; o < OG; ++o)
-            sum[o] = (float4_t){0.f, 0.f, 0.f, 0.f};
-        for (int s0 = 0; s0 < S; s0 += kPartialBatch) {
-            float4_t part[kPartialBatch][OG];
-#pragma unroll
-            for (int u = 0; u < kPartialBatch; ++u) {
-                const partial_rsrc_t src = slice_of(s0 + u < S ? s0 + u : S - 1);
-#pragma unroll
-                for (int o = 0; o < OG; ++o)
-                    part[u][o] = agent_load(src, (o0 + o) * 1024 + lane * 16);
-            }
-#pragma unroll
-            for (int u = 0; u < kPartialBatch; ++u)
-                if (s0 + u < S)
-#pragma unroll
-                    for (int o = 0; o < OG; ++o)
-                        sum[o] += part[u][o];
-        }
+            for (int o = 0; o < OG; ++o)
+                part[o] = agent_load(src, (o0 + o) * 1024 + lane * 16);
+        });
 #pragma unroll
         for (int o = 0; o < OG; ++o)
             finish(sum[o], o0 + o);

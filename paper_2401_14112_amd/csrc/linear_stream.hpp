@@ -262,16 +262,14 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_stream_kernel(
     // -> arrival count -> the last wave's loads; the signal fences keep the compiler from moving memory
     // operations across those two points.  The last wave adds the S partial tiles in split order, taking its
     // own from registers (the same bits it stored), so the sum does not depend on who is last.
-    float *pf = reinterpret_cast<float *>(partials);
-    auto slot = [&](int s_, int nt) { return pf + ((((int64_t)s_ * n_row_tiles + row_tile) * NT + nt) * 4) * 64 + lane; };
+    auto slice = [&](int s) { return partial_buffer(partials + ((int64_t)s * n_row_tiles + row_tile) * NT * 64, NT * 1024); };
+    {
+        const partial_rsrc_t dst = slice(split);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-        if (nt * 16 + n_in_tile < N) {
-            float *dst = slot(split, nt);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                __hip_atomic_store(dst + i * 64, acc[nt][i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        for (int nt = 0; nt < NT; ++nt)
+            if (nt * 16 + n_in_tile < N)
+                agent_store(dst, nt * 1024 + lane * 16, acc[nt]);
+    }
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's partial stores are done
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -283,36 +281,14 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_stream_kernel(
     if (arrived != S - 1)
         return;
     request_residual();
-    // The partial tiles of kPartialBatch slices are requested together (one trip to memory per batch, not
-    // per slice) and then added in slice order.  Every lane loads (lanes of token columns >= N read
-    // words that nobody stored; their sums are never written).
+    // (every lane loads: lanes of token columns >= N read words that nobody stored, their sums are never written)
     float4_t sum[NT];
+    add_slices<3>(sum, S, split, [&](int nt) { return acc[nt]; }, [&](float4_t (&part)[NT], int s) {
+        const partial_rsrc_t src = slice(s);
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-        sum[nt] = (float4_t){0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < S; s0 += kPartialBatch) {
-        float4_t part[kPartialBatch][NT];
-#pragma unroll
-        for (int u = 0; u < kPartialBatch; ++u) {
-            const int s_ = s0 + u < S ? s0 + u : S - 1;  // clamped: always an existing slot
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const float *src = slot(s_, nt);
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    part[u][nt][i] = __hip_atomic_load(src + i * 64, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kPartialBatch; ++u) {
-            const int s_ = s0 + u;
-            if (s_ < S) {
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    sum[nt] += s_ == split ? acc[nt] : part[u][nt];
-            }
-        }
-    }
+        for (int nt = 0; nt < NT; ++nt)
+            part[nt] = agent_load(src, nt * 1024 + lane * 16);
+    });
     finish(sum);
     if (lane == 0)
         counters[row_tile] = 0;  // re-arm for the next call on this workspace

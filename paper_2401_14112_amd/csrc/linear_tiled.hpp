@@ -287,8 +287,8 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void linear_tiled_kernel(
         return;
     }
 
-    // split-K: see linear_stream.hpp for the protocol (device-scope accesses, ordered sum), here with 16 bytes per lane
-    // and access and one arrival counter per wave, so that no wave waits for its block before the hand-over
+    // split-K: see linear_stream.hpp for the protocol (device-scope accesses, ordered sum), here with one arrival counter per
+    // wave, so that no wave waits for its block before the hand-over
     // (8192 x 22016, N = 512 151.0 -> 148.4 us, N = 256 87.2 -> 85.9, 28672 x 8192, N = 128 66.1 -> 64.8)
     auto slice = [&](int s, int r) {  // the wave's NT tiles of row tile r
         return partial_buffer(partials + (((int64_t)s * n_row_tiles + (row_own + r)) * n_tiles_total + (n_block * WN + wn) * NT) * 64, NT * 1024);
@@ -318,30 +318,12 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void linear_tiled_kernel(
         if (row_own + r >= n_row_tiles)
             continue;
         float4_t sum[NT];
+        add_slices<NT >= 8 ? 2 : 3>(sum, S, split, [&](int nt) { return own[r][nt]; }, [&](float4_t (&part)[NT], int s) {
+            const partial_rsrc_t src = slice(s, r);
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-            sum[nt] = (float4_t){0.f, 0.f, 0.f, 0.f};
-        // PB slices per trip to memory, added in slice order, the wave's own from registers (see linear_stream.hpp);
-        // fewer with wide wave tiles, whose partial tiles take more registers
-        constexpr int PB = NT >= 8 ? kPartialBatch / 2 : kPartialBatch;
-        for (int s0 = 0; s0 < S; s0 += PB) {
-            float4_t part[PB][NT];
-#pragma unroll
-            for (int u = 0; u < PB; ++u)
-                if (s0 + u < S && s0 + u != split) {
-                    const partial_rsrc_t src = slice(s0 + u, r);
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        part[u][nt] = agent_load(src, nt * 1024 + lane * 16);
-                }
-#pragma unroll
-            for (int u = 0; u < PB; ++u)
-                if (s0 + u < S) {
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        sum[nt] += s0 + u == split ? own[r][nt] : part[u][nt];
-                }
-        }
+            for (int nt = 0; nt < NT; ++nt)
+                part[nt] = agent_load(src, nt * 1024 + lane * 16);
+        });
         finish(sum, r);
     }
     if (lane == 0)
