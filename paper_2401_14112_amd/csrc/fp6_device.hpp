@@ -867,55 +867,57 @@ __device__ __forceinline__ void finish_rows(const Epilogue &e, const RowTerms &t
         *reinterpret_cast<half2_t *>(Y + (int64_t)col * (M >> 1) + (m0 >> 1)) = y;
     }
 }
-// The same with the reads in place, one after the other: the form of the prompt-sized kernels, whose last step is a small part
-// of a launch and whose loops lose more by the registers of the other form (group scales, 118.0 -> 120.7 us on 28672 x 8192,
-// N = 201).
-// Y and the residual are [tokens][M] (or [tokens][M/2] when gated).
-template <bool kHasScale>
-__device__ __forceinline__ void finish_rows(const Epilogue &e, const half_t *__restrict__ scales, const float4_t &sum,
-                                            int col, int m0, int M, half_t *Y)
+
+// The R x T tiles of 16 rows x 16 tokens that a wave of a prompt-sized kernel ends up with: rows row0 + 16 r .., tokens col0 + 16 t ...
+// The terms of a row tile are read once, by the caller, and residuals T tiles together: read tile by tile in front of their use, each of
+// them was waited for (65536 x 2816, N = 128, 6 bits: 4.6 us after the k loop).  Calls without steps take a path of their own: with
+// the tests of every step between them the stores leave one by one.  Drawn calls of 256 to 57344 rows and 65 to 4096 tokens, median
+// time over that before: tiled kernel 0.93 without k slices (795 calls), 0.945 with (654); block kernel 0.99 without (564; 256 x 256
+// blocks of 57344 x 2048 0.97), 0.94 with (226, add_slices() included).
+template <bool kHasScale, bool kSteps, int R, int T>
+__device__ __forceinline__ void finish_tiles(const Epilogue &e, const RowTerms (&terms)[R], const float4_t (&v)[R][T], int row0, int col0,
+                                             int M, int N, half_t *Y, int lane)
 {
-    float v[4] = {sum[0], sum[1], sum[2], sum[3]};
-    if (kHasScale) {
-        const half4_t s4 = *reinterpret_cast<const half4_t *>(scales + m0);
+    const int col = col0 + (lane & 15), m0 = row0 + 4 * (lane >> 4);
+    if (!kSteps || !(e.bias || e.residual || e.gated)) {
+        half_t *const y = Y + (int64_t)col * M + m0;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            v[i] *= (float)s4[i];
+        for (int r = 0; r < R; ++r)
+            if (row0 + 16 * r < M) {
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+                    if (col + 16 * t < N) {
+                        half4_t o;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            o[i] = (half_t)(kHasScale ? v[r][t][i] * (float)terms[r].scale[i] : v[r][t][i]);
+                        *reinterpret_cast<half4_t *>(y + (int64_t)(16 * t) * M + 16 * r) = o;
+                    }
+            }
+        return;
     }
-    if (e.bias) {
-        const half4_t b4 = *reinterpret_cast<const half4_t *>(e.bias + m0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            v[i] += (float)b4[i];
-    }
-    if (!e.gated) {
-        const int64_t at = (int64_t)col * M + m0;
-        if (e.residual) {
-            const half4_t r4 = *reinterpret_cast<const half4_t *>(e.residual + at);
+    for (int r = 0; r < R; ++r)
+        if (row0 + 16 * r < M) {
+            half4_t residual[T];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                v[i] += (float)r4[i];
+            for (int t = 0; t < T; ++t)
+                if (e.residual && col + 16 * t < N)
+                    residual[t] = residual_rows(e, col + 16 * t, m0 + 16 * r, M);
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if (col + 16 * t < N)
+                    finish_rows<kHasScale>(e, terms[r], residual[t], v[r][t], col + 16 * t, m0 + 16 * r, M, Y);
         }
-        half4_t y;
+}
+// Their terms; kSteps: whether the calls of the source can have steps.  Row tiles past the end take the last one's.
+template <bool kHasScale, bool kSteps, int R>
+__device__ __forceinline__ void row_terms_of_tiles(RowTerms (&terms)[R], const Epilogue &e, const half_t *__restrict__ scales, int row0, int M, int lane)
+{
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            y[i] = (half_t)v[i];
-        *reinterpret_cast<half4_t *>(Y + at) = y;
-    } else {
-        const int64_t at = (int64_t)col * (M >> 1) + (m0 >> 1);
-        float o[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-            o[i] = v[2 * i] / (1.0f + __expf(-v[2 * i])) * v[2 * i + 1];
-        if (e.residual) {
-            const half2_t r2 = *reinterpret_cast<const half2_t *>(e.residual + at);
-            o[0] += (float)r2[0];
-            o[1] += (float)r2[1];
-        }
-        half2_t y;
-        y[0] = (half_t)o[0];
-        y[1] = (half_t)o[1];
-        *reinterpret_cast<half2_t *>(Y + at) = y;
+    for (int r = 0; r < R; ++r) {
+        const int row = row0 + 16 * r < M ? row0 + 16 * r : M - 16;
+        terms[r] = kHasScale || kSteps ? row_terms<kHasScale>(e, scales, row + 4 * (lane >> 4)) : RowTerms{};
     }
 }
 

@@ -36,7 +36,7 @@ namespace fp6 {
 // tiles into the fragments of a pair.
 struct BlockFp6Source {
     typedef PackedFp6Source::Tile Piece;
-    static constexpr bool kRunStaged = false, kHasScale = true, kGroupScales = false, kHalfTiles = false;
+    static constexpr bool kRunStaged = false, kHasScale = true, kFused = true, kGroupScales = false, kHalfTiles = false;
     static constexpr int kTileBytes = 3072, kPlanes = 3;
     static constexpr int plane_bytes(int) { return 1024; }  // of a 16-row tile
     static constexpr int planes_of(int pair) { return pair == 0 ? 1 : pair == 1 ? 3 : pair == 2 ? 6 : 4; }  // bit p: plane p
@@ -73,7 +73,7 @@ struct BlockFp6GroupSource : BlockFp6Source {
 template <class Src>
 struct BlockPieceSource {
     typedef typename Src::Tile Piece;
-    static constexpr bool kRunStaged = false, kHasScale = true, kGroupScales = false;
+    static constexpr bool kRunStaged = false, kHasScale = true, kFused = true, kGroupScales = false;
     template <int G>
     __device__ static __forceinline__ void fragments(const Piece &a, const Piece &b, half8_t (&fa)[2], half8_t (&fb)[2])
     {
@@ -131,6 +131,7 @@ struct BlockFp3Source : BlockPieceSource<PackedFp3Source> {
 struct BlockFp16Source {
     struct Piece {};
     static constexpr bool kRunStaged = true, kHasScale = false, kGroupScales = false, kHalfTiles = false;
+    static constexpr bool kFused = false;  // no call has steps after the sum
     static constexpr int kTileBytes = 0, kPlanes = 0;
     static constexpr int plane_bytes(int) { return 0; }
     static constexpr int planes_of(int) { return 0; }
@@ -700,86 +701,83 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_block_kernel(
     wait_loads<0>();  // the look-ahead copies land before the block gives up its LDS
 
     // ---- the two waves of a piece meet: each ends up with half of its 16 x 16 tiles
-    constexpr int TILES = RT * NT, OWN = TILES / WK;  // tile u = g * NT + nt
-    static_assert(TILES % WK == 0, "tiles of a wave pair");
-    float4_t own[OWN];
+    constexpr int OWN_ROWS = RT / WK, OWN = OWN_ROWS * NT;  // tile o = r * NT + nt of the wave's own
+    static_assert(RT % WK == 0, "tiles of a wave pair");
+    float4_t own[OWN_ROWS][NT];
     if constexpr (WK == 2) {
         __syncthreads();
         float4_t *ex = reinterpret_cast<float4_t *>(lds);
         static_assert(WAVES * OWN * 1024 <= Shape::template lds_bytes<Src>(), "exchange buffer");
 #pragma unroll
         for (int o = 0; o < OWN; ++o)
-            ex[(wave * OWN + o) * 64 + lane] = wk == 0 ? acc[(OWN + o) / NT][(OWN + o) % NT] : acc[o / NT][o % NT];
+            ex[(wave * OWN + o) * 64 + lane] = wk == 0 ? acc[OWN_ROWS + o / NT][o % NT] : acc[o / NT][o % NT];
         __syncthreads();
         const int partner = wave ^ (WM * WN);
 #pragma unroll
         for (int o = 0; o < OWN; ++o)
-            own[o] = (wk == 0 ? acc[o / NT][o % NT] : acc[(OWN + o) / NT][(OWN + o) % NT]) + ex[(partner * OWN + o) * 64 + lane];
+            own[o / NT][o % NT] = (wk == 0 ? acc[o / NT][o % NT] : acc[OWN_ROWS + o / NT][o % NT]) + ex[(partner * OWN + o) * 64 + lane];
     } else {
 #pragma unroll
         for (int o = 0; o < OWN; ++o)
-            own[o] = acc[o / NT][o % NT];
+            own[o / NT][o % NT] = acc[o / NT][o % NT];
     }
 
     // ---- last step.  Lane L holds rows 4*(L/16) + i of token column L%16 of a 16 x 16 tile.
-    const int u0 = wk * OWN;
-    auto tile_row = [&](int o) { return wrow0 + (u0 + o) / NT * 16; };
-    auto tile_col = [&](int o) { return col0 + (wn * NT + (u0 + o) % NT) * 16; };
-    auto finish = [&](const float4_t &v, int o) {
-        const int col = tile_col(o) + (lane & 15), m0 = tile_row(o) + 4 * (lane >> 4);
-        if (col < N && m0 < M)
-            finish_rows<Src::kHasScale>(epi, scales, v, col, m0, M, Y);
-    };
-    if (S == 1) {
+    const int own_row0 = wrow0 + wk * OWN_ROWS * 16, own_col0 = col0 + wn * NT * 16;
+    RowTerms terms[OWN_ROWS];
+    row_terms_of_tiles<Src::kHasScale, Src::kFused>(terms, epi, scales, own_row0, M, lane);
+    if (S > 1) {
+        // split-K, one arrival counter per wave tile: see linear_stream.hpp for the protocol
+        const int64_t tile_id = (int64_t)row_block * n_blocks + n_block;
+        const int64_t tiles = (int64_t)row_blocks * n_blocks;
+        constexpr int WAVE_BYTES = OWN * 1024;
+        auto slice_of = [&](int s) {
+            return partial_buffer(reinterpret_cast<uint8_t *>(partials) + ((s * tiles + tile_id) * WAVES + wave) * WAVE_BYTES, WAVE_BYTES);
+        };
+        {
+            const partial_rsrc_t dst = slice_of(split);
 #pragma unroll
-        for (int o = 0; o < OWN; ++o)
-            finish(own[o], o);
+            for (int o = 0; o < OWN; ++o)
+                if (own_col0 + o % NT * 16 < N && own_row0 + o / NT * 16 < M)  // the same for every lane
+                    agent_store(dst, o * 1024 + lane * 16, own[o / NT][o % NT]);
+        }
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's partial stores are done
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        int arrived = 0;
+        int *counter = counters + (tile_id * WAVES + wave) * counter_step;
+        if (lane == 0)
+            arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        arrived = __builtin_amdgcn_readfirstlane(arrived);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        if (arrived != S - 1)
+            return;
+        if (lane == 0)
+            *counter = 0;  // re-arm for the next call on this workspace
+        // groups of output tiles as large as the registers hold, finished as they are: brought together with the accumulators of
+        // calls without slices they would spill
+        constexpr int GT = OWN <= 16 ? NT : 2, GR = OWN <= 16 && OWN_ROWS >= 2 ? 2 : 1, OG = GR * GT;
+#pragma unroll
+        for (int o0 = 0; o0 < OWN; o0 += OG) {
+            const int r0 = o0 / NT, t0 = o0 % NT;
+            float4_t sum[OG], group[GR][GT];
+            RowTerms group_terms[GR];
+            add_slices<3>(sum, S, split, [&](int o) { return own[r0 + o / GT][t0 + o % GT]; }, [&](float4_t (&part)[OG], int s) {
+                const partial_rsrc_t src = slice_of(s);
+#pragma unroll
+                for (int o = 0; o < OG; ++o)
+                    part[o] = agent_load(src, (o0 + o) * 1024 + lane * 16);
+            });
+#pragma unroll
+            for (int o = 0; o < OG; ++o) {
+                group[o / GT][o % GT] = sum[o];
+                group_terms[o / GT] = terms[r0 + o / GT];
+            }
+            finish_tiles<Src::kHasScale, Src::kFused>(epi, group_terms, group, own_row0 + r0 * 16, own_col0 + t0 * 16, M, N, Y, lane);
+        }
         return;
     }
-
-    // split-K, one arrival counter per wave tile: see linear_stream.hpp for the protocol
-    const int64_t tile_id = (int64_t)row_block * n_blocks + n_block;
-    const int64_t tiles = (int64_t)row_blocks * n_blocks;
-    constexpr int WAVE_BYTES = OWN * 1024;
-    auto slice_of = [&](int s) {
-        return partial_buffer(reinterpret_cast<uint8_t *>(partials) + ((s * tiles + tile_id) * WAVES + wave) * WAVE_BYTES, WAVE_BYTES);
-    };
-    auto live = [&](int o) { return tile_col(o) < N && tile_row(o) < M; };  // the same for every lane
-    {
-        const partial_rsrc_t dst = slice_of(split);
-#pragma unroll
-        for (int o = 0; o < OWN; ++o)
-            if (live(o))
-                agent_store(dst, o * 1024 + lane * 16, own[o]);
-    }
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's partial stores are done
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    int arrived = 0;
-    int *counter = counters + (tile_id * WAVES + wave) * counter_step;
-    if (lane == 0)
-        arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    arrived = __builtin_amdgcn_readfirstlane(arrived);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    if (arrived != S - 1)
-        return;
-    // groups of output tiles as large as the registers hold
-    constexpr int OG = OWN < 8 ? OWN : OWN <= 16 ? 8 : 2;
-#pragma unroll
-    for (int o0 = 0; o0 < OWN; o0 += OG) {
-        float4_t sum[OG];
-        add_slices<3>(sum, S, split, [&](int o) { return own[o0 + o]; }, [&](float4_t (&part)[OG], int s) {
-            const partial_rsrc_t src = slice_of(s);
-#pragma unroll
-            for (int o = 0; o < OG; ++o)
-                part[o] = agent_load(src, (o0 + o) * 1024 + lane * 16);
-        });
-#pragma unroll
-        for (int o = 0; o < OG; ++o)
-            finish(sum[o], o0 + o);
-    }
-    if (lane == 0)
-        *counter = 0;  // re-arm for the next call on this workspace
+    finish_tiles<Src::kHasScale, Src::kFused>(epi, terms, own, own_row0, own_col0, M, N, Y, lane);
 }
 
 }  // namespace fp6

@@ -283,7 +283,7 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_stream_kernel(
     request_residual();
     // (every lane loads: lanes of token columns >= N read words that nobody stored, their sums are never written)
     float4_t sum[NT];
-    add_slices<3>(sum, S, split, [&](int nt) { return acc[nt]; }, [&](float4_t (&part)[NT], int s) {
+    add_slices<NT == 1 ? 8 : NT == 2 ? 4 : 3>(sum, S, split, [&](int nt) { return acc[nt]; }, [&](float4_t (&part)[NT], int s) {
         const partial_rsrc_t src = slice(s);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)

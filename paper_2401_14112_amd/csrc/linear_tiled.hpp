@@ -269,65 +269,55 @@ __global__ __launch_bounds__(WM * WN * WK * 64) void linear_tiled_kernel(
     // ---- epilogue.  Lane L holds, per (row tile, token tile), rows 4*(L/16)+i of token column L%16.
     const int n_in_tile = lane & 15;
     const int n_tiles_total = n_blocks * BNT;
-    auto finish = [&](const float4_t (&sum)[NT], int r) {
-        const int m0 = (row_own + r) * kTileRows + 4 * (lane >> 4);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const int col = col0 + nt * 16 + n_in_tile;
-            if (col < N)
-                finish_rows<Src::kHasScale>(epi, scales, sum[nt], col, m0, M, Y);
-        }
-    };
+    RowTerms terms[OWN];
+    row_terms_of_tiles<Src::kHasScale, true>(terms, epi, scales, row_own * kTileRows, M, lane);
 
-    if (S == 1) {
+    if (S > 1) {
+        // split-K: see linear_stream.hpp for the protocol (device-scope accesses, ordered sum), here with one arrival counter per
+        // wave, so that no wave waits for its block before the hand-over
+        // (8192 x 22016, N = 512 151.0 -> 148.4 us, N = 256 87.2 -> 85.9, 28672 x 8192, N = 128 66.1 -> 64.8)
+        auto slice = [&](int s, int r) {  // the wave's NT tiles of row tile r
+            return partial_buffer(partials + (((int64_t)s * n_row_tiles + (row_own + r)) * n_tiles_total + (n_block * WN + wn) * NT) * 64, NT * 1024);
+        };
 #pragma unroll
         for (int r = 0; r < OWN; ++r)
-            if (row_own + r < n_row_tiles)
-                finish(own[r], r);
-        return;
-    }
-
-    // split-K: see linear_stream.hpp for the protocol (device-scope accesses, ordered sum), here with one arrival counter per
-    // wave, so that no wave waits for its block before the hand-over
-    // (8192 x 22016, N = 512 151.0 -> 148.4 us, N = 256 87.2 -> 85.9, 28672 x 8192, N = 128 66.1 -> 64.8)
-    auto slice = [&](int s, int r) {  // the wave's NT tiles of row tile r
-        return partial_buffer(partials + (((int64_t)s * n_row_tiles + (row_own + r)) * n_tiles_total + (n_block * WN + wn) * NT) * 64, NT * 1024);
-    };
+            if (row_own + r < n_row_tiles) {
+                const partial_rsrc_t dst = slice(split, r);
 #pragma unroll
-    for (int r = 0; r < OWN; ++r)
-        if (row_own + r < n_row_tiles) {
-            const partial_rsrc_t dst = slice(split, r);
+                for (int nt = 0; nt < NT; ++nt)
+                    if (col0 + nt * 16 + n_in_tile < N)
+                        agent_store(dst, nt * 1024 + lane * 16, own[r][nt]);
+            }
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's partial stores are done
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        int *counter = counters + (((int64_t)row_block * n_blocks + n_block) * WAVES + wave) * counter_step;
+        int arrived = 0;
+        if (lane == 0)
+            arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        arrived = __builtin_amdgcn_readfirstlane(arrived);
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        if (arrived != S - 1)
+            return;
+        if (lane == 0)
+            *counter = 0;  // re-arm for the next call on this workspace
+#pragma unroll
+        for (int r = 0; r < OWN; ++r) {
+            if (row_own + r >= n_row_tiles)
+                continue;
+            float4_t sum[NT];
+            add_slices<NT >= 8 ? 2 : 4>(sum, S, split, [&](int nt) { return own[r][nt]; }, [&](float4_t (&part)[NT], int s) {
+                const partial_rsrc_t src = slice(s, r);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    part[nt] = agent_load(src, nt * 1024 + lane * 16);
+            });
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
-                if (col0 + nt * 16 + n_in_tile < N)
-                    agent_store(dst, nt * 1024 + lane * 16, own[r][nt]);
+                own[r][nt] = sum[nt];
         }
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's partial stores are done
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    int *counter = counters + (((int64_t)row_block * n_blocks + n_block) * WAVES + wave) * counter_step;
-    int arrived = 0;
-    if (lane == 0)
-        arrived = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    arrived = __builtin_amdgcn_readfirstlane(arrived);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    if (arrived != S - 1)
-        return;
-#pragma unroll
-    for (int r = 0; r < OWN; ++r) {
-        if (row_own + r >= n_row_tiles)
-            continue;
-        float4_t sum[NT];
-        add_slices<NT >= 8 ? 2 : 3>(sum, S, split, [&](int nt) { return own[r][nt]; }, [&](float4_t (&part)[NT], int s) {
-            const partial_rsrc_t src = slice(s, r);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                part[nt] = agent_load(src, nt * 1024 + lane * 16);
-        });
-        finish(sum, r);
     }
-    if (lane == 0)
-        *counter = 0;  // re-arm for the next call on this workspace
+    finish_tiles<Src::kHasScale, true>(epi, terms, own, row_own * kTileRows, col0, M, N, Y, lane);
 }
 
 }  // namespace fp6
