@@ -805,6 +805,19 @@ struct Epilogue {
 struct RowTerms {
     half4_t scale, bias;
 };
+// One wait for loaded terms, in front of the stores that follow: the compiler otherwise waits for them again in every branch, and
+// stores count like loads, so that each store then waits for the one before to complete.
+__device__ __forceinline__ void pin(half4_t &v)
+{
+    u32x2 w = bit_cast<u32x2>(v);
+    pin(w);
+    v = bit_cast<half4_t>(w);
+}
+__device__ __forceinline__ void pin(RowTerms &t)
+{
+    pin(t.scale);
+    pin(t.bias);
+}
 template <bool kHasScale>
 __device__ __forceinline__ RowTerms row_terms(const Epilogue &e, const half_t *__restrict__ scales, int m0)
 {
@@ -875,10 +888,15 @@ __device__ __forceinline__ void finish_rows(const Epilogue &e, const RowTerms &t
 // time over that before: tiled kernel 0.93 without k slices (795 calls), 0.945 with (654); block kernel 0.99 without (564; 256 x 256
 // blocks of 57344 x 2048 0.97), 0.94 with (226, add_slices() included).
 template <bool kHasScale, bool kSteps, int R, int T>
-__device__ __forceinline__ void finish_tiles(const Epilogue &e, const RowTerms (&terms)[R], const float4_t (&v)[R][T], int row0, int col0,
+__device__ __forceinline__ void finish_tiles(const Epilogue &e, RowTerms (&terms)[R], const float4_t (&v)[R][T], int row0, int col0,
                                              int M, int N, half_t *Y, int lane)
 {
     const int col = col0 + (lane & 15), m0 = row0 + 4 * (lane >> 4);
+    if constexpr (kHasScale || kSteps) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            pin(terms[r]);
+    }
     if (!kSteps || !(e.bias || e.residual || e.gated)) {
         half_t *const y = Y + (int64_t)col * M + m0;
 #pragma unroll
@@ -900,10 +918,15 @@ __device__ __forceinline__ void finish_tiles(const Epilogue &e, const RowTerms (
     for (int r = 0; r < R; ++r)
         if (row0 + 16 * r < M) {
             half4_t residual[T];
+            if (e.residual) {
 #pragma unroll
-            for (int t = 0; t < T; ++t)
-                if (e.residual && col + 16 * t < N)
-                    residual[t] = residual_rows(e, col + 16 * t, m0 + 16 * r, M);
+                for (int t = 0; t < T; ++t)
+                    if (col + 16 * t < N)
+                        residual[t] = residual_rows(e, col + 16 * t, m0 + 16 * r, M);
+#pragma unroll
+                for (int t = 0; t < T; ++t)
+                    pin(residual[t]);
+            }
 #pragma unroll
             for (int t = 0; t < T; ++t)
                 if (col + 16 * t < N)

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_stream_kernel(
     const int m0 = row_tile * kTileRows + 4 * (lane >> 4);
     // Scales and bias are requested before the partial sums leave (only the last wave needs them, but then they cost it
     // no trip to memory), the residual beside the partial sums of the other slices.
-    const RowTerms terms = row_terms<Src::kHasScale>(epi, scales, m0);
+    RowTerms terms = row_terms<Src::kHasScale>(epi, scales, m0);
     half4_t residual[NT];
     auto request_residual = [&] {
         if (epi.residual) {
@@ -241,6 +241,12 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_stream_kernel(
         }
     };
     auto finish = [&](const float4_t (&sum)[NT]) {
+        pin(terms);
+        if (epi.residual) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+                pin(residual[nt]);
+        }
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             const int col = nt * 16 + n_in_tile;
