@@ -867,6 +867,26 @@ fp6_status launch_stream(const void *weights, const void *scales, const void *X,
                                                           reinterpret_cast<float4_t *>(buf.partials), buf.counters, epi, stream);
 }
 
+// Whether a matrix is quantized in one pass (time over that of two launches, 6 / 4 / 3 bits):
+//   1024 columns and less, no exchange: 0.57-0.62 / 0.61-0.64 / 0.65-0.70 from 1024 to 57344 rows;
+//   more, 6, 5 and 4 bits: 8192 x 2048 0.94 / 0.94, 2048 x 8192 0.93 / 0.94, 4096 x 4096 0.92 / 0.90, 8192 x 22016 0.77 / 0.79,
+//     57344 x 8192 0.63 / 0.64; but 3072 x 4096 0.95 / 1.00, 4096 x 2048 1.09 / 1.08, 1024 x 2048 1.16 / 1.16, and where the last
+//     part is mostly idle 16384 x 1280 1.11 / 1.10 (57344 x 1280 0.89 / 0.93);
+//   many parts wait for one another longer: 8192 x 33024 (33) 0.81 / 0.80, 4096 x 65536 (64) 1.14 / 1.13;
+//   3 bits, which the chip has no conversion for (a block computes while nothing of it is in flight): 8192 x 22016 1.05, 57344 x
+//     8192 0.87.
+template <class Fmt>
+bool one_pass_pack(int64_t M, int64_t K)
+{
+    const int64_t KT = K / kTileK, parts = (KT + kPartWaves - 1) / kPartWaves;
+    if (parts == 1)
+        return true;
+    if (std::is_same_v<Fmt, E2M0Format>)
+        return parts <= 16 && M * K >= 1 << 28;
+    const bool full = 4 * KT >= 3 * kPartWaves * parts;
+    return parts <= kMaxParts && M * K >= (full ? 1 << 24 : 1 << 26);
+}
+
 template <class Fmt>
 fp6_status quantize_pack_impl(const void *W_f16, int64_t M, int64_t K, void *packed, void *scales_f16, void *stream)
 {
@@ -876,15 +896,27 @@ fp6_status quantize_pack_impl(const void *W_f16, int64_t M, int64_t K, void *pac
         return FP6_ERR_SHAPE;
     if (!aligned16(W_f16) || !aligned16(packed) || !aligned16(scales_f16))
         return FP6_ERR_ALIGN;
+    const hipStream_t st = static_cast<hipStream_t>(stream);
+    const half_t *W = static_cast<const half_t *>(W_f16);
+    uint8_t *out = static_cast<uint8_t *>(packed);
+    half_t *scales = static_cast<half_t *>(scales_f16);
+    const int64_t RT = M / kTileRows, KT = K / kTileK, parts = (KT + kPartWaves - 1) / kPartWaves;
+    if (one_pass_pack<Fmt>(M, K)) {
+        if (parts > 1) {
+            hipLaunchKernelGGL(clear_exchange_kernel, dim3((unsigned)((RT * (kExchangeBytes / 16) + 255) / 256)), dim3(256), 0, st, out, (int)RT,
+                               Fmt::kTileBytes);
+            if (hipGetLastError() != hipSuccess)
+                return FP6_ERR_HIP;
+        }
+        hipLaunchKernelGGL(quantize_rows_kernel<Fmt>, dim3((unsigned)(RT * parts)), dim3(kPartWaves * 64), 0, st, W, (int)M, (int)K, out, scales,
+                           (int)parts);
+        return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
+    }
     hipLaunchKernelGGL(row_scale_kernel<Fmt>, dim3((unsigned)((M + kScaleWavesPerBlock - 1) / kScaleWavesPerBlock)),
-                       dim3(kScaleWavesPerBlock * 64), 0, static_cast<hipStream_t>(stream),
-                       static_cast<const half_t *>(W_f16), (int)M, (int)K, static_cast<half_t *>(scales_f16));
+                       dim3(kScaleWavesPerBlock * 64), 0, st, W, (int)M, (int)K, scales);
     if (hipGetLastError() != hipSuccess)
         return FP6_ERR_HIP;
-    const int64_t tiles = (M / kTileRows) * (K / kTileK);
-    hipLaunchKernelGGL(quantize_tiles_kernel<Fmt>, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0,
-                       static_cast<hipStream_t>(stream), static_cast<const half_t *>(W_f16), (int)M, (int)K,
-                       static_cast<uint8_t *>(packed), static_cast<const half_t *>(scales_f16));
+    hipLaunchKernelGGL(quantize_tiles_kernel<Fmt>, dim3((unsigned)((RT * KT + 3) / 4)), dim3(256), 0, st, W, (int)M, (int)K, out, scales);
     return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
 }
 

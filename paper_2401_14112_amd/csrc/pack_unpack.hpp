@@ -1,9 +1,8 @@
 // fp6_quantize_pack and fp6_unpack kernels for gfx950.
 //
-// quantize_pack: a first launch finds the row maxima and the fp16 scales, a second
-// one reads W tile by tile, rounds every weight to its code and writes whole tiles of
-// the packed stream with 16-byte stores per lane and plane (the ahead-of-time re-layout
-// of the paper's Section 5.2, in this library's order).
+// quantize_pack: one pass over W finds the row maxima and the fp16 scales, rounds every weight to its code and writes
+// whole tiles of the packed stream with 16-byte stores per lane and plane (the ahead-of-time re-layout
+// of the paper's Section 5.2, in this library's order); for small matrices two launches, the maxima first.
 //
 // unpack: one wave per tile; the same register-level decode as the GEMM, followed by
 // the row scale and a single rounding to fp16.
@@ -13,23 +12,6 @@
 namespace fp6 {
 
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
-
-// Magnitude code (0..31) of ratio = |w| / scale on the e3m2 grid, round to nearest,
-// ties to the even code, saturating at 28.  The ratio is the correctly rounded fp32
-// quotient of two 11-bit significands; it can only land on a grid midpoint when the
-// exact quotient is that midpoint, so rounding it equals rounding the exact ratio.
-__device__ __forceinline__ uint32_t e3m2_magnitude_code(float ratio)
-{
-    uint32_t g;
-    if (ratio < 0.25f) {
-        g = (uint32_t)__builtin_rintf(ratio * 16.0f);  // subnormal binade: multiples of 1/16
-    } else {
-        uint32_t u = bit_cast<uint32_t>(ratio);
-        u += 0x000fffffu + ((u >> 21) & 1u);  // round the mantissa to 2 bits, half to even
-        g = (u >> 21) - (124u << 2);          // exponent field - 127 + bias 3, then 2 mantissa bits
-    }
-    return g < 31u ? g : 31u;
-}
 
 // The row scale as the encoder needs it: the scale itself and its reciprocal (0 for a zero scale).
 struct RowScale {
@@ -43,50 +25,48 @@ __device__ __forceinline__ RowScale make_row_scale(float scale)
     return r;
 }
 
-// |w| / scale with one Newton correction on top of the reciprocal product.  When the exact quotient is a
-// grid midpoint m (the only case where the last bit matters), q = m(1+e), the fused remainder a - q*scale
+// w / scale with one Newton correction on top of the reciprocal product.  When the exact quotient is a
+// grid midpoint m (the only case where the last bit matters), q = m(1+e), the fused remainder q*scale - w
 // is exact and the corrected value m(1+O(e^2)) rounds to m itself; everywhere else the exact quotient is
-// at least 2^-16 (relative) away from every midpoint, far more than the error of q.
-template <class Fmt>
-__device__ __forceinline__ uint32_t quantize_code(uint32_t w_bits, RowScale rs)
+// at least 2^-16 (relative) away from every midpoint, far more than the error of q.  So rounding the result to a
+// grid (nearest, ties to even) rounds the exact quotient.  The sign of a zero is that of w, also for a zero scale.
+__device__ __forceinline__ float ratio_of(half_t w, RowScale rs)
 {
-    const uint32_t sign = (w_bits >> 15) & 1u;
-    const float a = (float)bit_cast<half_t>((uint16_t)(w_bits & 0x7fffu));
-    const float q = a * rs.inv;
-    const float ratio = __builtin_fmaf(__builtin_fmaf(-q, rs.scale, a), rs.inv, q);
-    return (sign << Fmt::kSignShift) | Fmt::magnitude_code(ratio);  // zero scale: inv = 0 -> ratio = 0 -> sign-only code
+    const float a = (float)w, q = a * rs.inv;
+    return __builtin_fmaf(-__builtin_fmaf(q, rs.scale, -a), rs.inv, q);
 }
 
-// ---- the two weight formats as the encoder sees them ---------------------------------------------
-// magnitude_code(ratio): grid point of |w|/scale (round to nearest, ties to the even code, saturating);
-// store_tile(): the lane's codes [run][j] (columns run*32 + 8q + j of its row) -> the lane's bytes of the tile.
+// ---- the weight formats as the encoder sees them ---------------------------------------------------
+// encode<C>(): the lane's weights of runs 4C .. 4C+3 (run f, columns run*32 + 8q + j: half j of v[f]) -> its kHalfWords words
+// of that half of the tile; store_tile() / store_half(): the lane's words -> its bytes of the tile.  6, 5 and 4 bits: the chip's
+// conversions round to nearest, ties to the even code, saturate (5 bits: by hand) and keep the sign of a zero; they agree with
+// integer arithmetic on the bits of the float for every float of exponents -31 .. 32 (tests/test_host_logic.py pins the
+// arithmetic).  18 VALU instructions per weight before, 4 and a conversion now.
+typedef float float16_t __attribute__((ext_vector_type(16)));
+typedef short short2_t __attribute__((ext_vector_type(2)));
+
 struct E3M2Format {
     static constexpr float kMax = 28.0f;
-    static constexpr int kSignShift = 5;
-    static constexpr int kTileBytes = 3072;
+    static constexpr int kTileBytes = 3072, kHalfWords = 6;
     static constexpr bool kHalfTiles = false;
-    __device__ static __forceinline__ uint32_t magnitude_code(float ratio) { return e3m2_magnitude_code(ratio); }
-    __device__ static __forceinline__ void store_tile(const uint32_t (&code)[8][8], uint8_t *tile, int lane)
+    // a dense stream: code i = 8*(run%4) + j at bits [6i, 6i+6); the conversion takes even and odd codes apart
+    template <int C>
+    __device__ static __forceinline__ void encode(const u32x4 (&v)[8], RowScale rs, uint32_t (&d)[2 * kHalfWords])
     {
-        // two dense streams: code i = 8*(run%4) + j at bits [6i, 6i+6) of stream run/4
-        uint32_t d[12];
+        float16_t even, odd;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            uint64_t a[4] = {0, 0, 0, 0};  // 192 bits (+ spill-over slot)
-#pragma unroll
-            for (int i = 0; i < 32; ++i) {
-                const uint64_t cd = code[4 * c + i / 8][i % 8];
-                const int pos = 6 * i, wd = pos >> 6, sh = pos & 63;
-                a[wd] |= cd << sh;
-                if (sh > 58)
-                    a[wd + 1] |= cd >> (64 - sh);
-            }
-#pragma unroll
-            for (int h = 0; h < 3; ++h) {
-                d[6 * c + 2 * h] = (uint32_t)a[h];
-                d[6 * c + 2 * h + 1] = (uint32_t)(a[h] >> 32);
-            }
+        for (int i = 0; i < 16; ++i) {
+            const half2_t w = bit_cast<half2_t>(v[4 * C + i / 4][i % 4]);
+            even[i] = ratio_of(w[0], rs);
+            odd[i] = ratio_of(w[1], rs);
         }
+        const u32x6 words = __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(even, odd, 1.0f);
+#pragma unroll
+        for (int i = 0; i < kHalfWords; ++i)
+            d[C * kHalfWords + i] = words[i];
+    }
+    __device__ static __forceinline__ void store_tile(const uint32_t (&d)[2 * kHalfWords], uint8_t *tile, int lane)
+    {
         u32x4 *t = reinterpret_cast<u32x4 *>(tile) + lane;
         t[0] = (u32x4){d[0], d[1], d[2], d[3]};
         t[64] = (u32x4){d[4], d[5], d[6], d[7]};
@@ -94,50 +74,40 @@ struct E3M2Format {
     }
 };
 
-// e2m2: grid 0 .25 .5 .75 | 1 .. 1.75 | 2 .. 3.5 | 4 .. 7 (Eq. 1 with bias 1, subnormal E = 0 binade).
+// e2m2: grid 0 .25 .5 .75 | 1 .. 1.75 | 2 .. 3.5 | 4 .. 7 (Eq. 1 with bias 1, subnormal E = 0 binade).  Times 2^-14 that is the
+// lower end of the e5m2 numbers, whose bytes "s 000 e1 e0 m1 m0" are what the layout stores in place.
 struct E2M2Format {
     static constexpr float kMax = 7.0f;
-    static constexpr int kSignShift = 4;
-    static constexpr int kTileBytes = 2560;
+    static constexpr int kTileBytes = 2560, kHalfWords = 5;
     static constexpr bool kHalfTiles = false;
-    __device__ static __forceinline__ uint32_t magnitude_code(float ratio)
+    __device__ static __forceinline__ uint32_t four_bytes(uint32_t w01, uint32_t w23, RowScale rs)
     {
-        uint32_t g;
-        if (ratio < 1.0f) {
-            g = (uint32_t)__builtin_rintf(ratio * 4.0f);  // subnormal binade: multiples of 1/4
-        } else {
-            uint32_t u = bit_cast<uint32_t>(ratio);
-            u += 0x000fffffu + ((u >> 21) & 1u);  // round the mantissa to 2 bits, half to even
-            g = (u >> 21) - (126u << 2);          // exponent field - 127 + bias 1, then 2 mantissa bits
-        }
-        return g < 15u ? g : 15u;
+        float r[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            r[i] = __builtin_amdgcn_fmed3f(ratio_of(bit_cast<half2_t>(i < 2 ? w01 : w23)[i % 2], rs), -kMax, kMax);
+        short2_t b = {0, 0};
+        b = __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(b, r[0], r[1], 16384.0f, false);
+        b = __builtin_amdgcn_cvt_scalef32_pk_bf8_f32(b, r[2], r[3], 16384.0f, true);
+        return bit_cast<uint32_t>(b);
     }
-    // code s e1 e0 m1 m0 -> byte s 0 0 0 e1 e0 m1 m0
-    __device__ static __forceinline__ uint32_t in_place(uint32_t c) { return ((c & 0x10u) << 3) | (c & 0x0fu); }
-    __device__ static __forceinline__ void store_tile(const uint32_t (&code)[8][8], uint8_t *tile, int lane)
+    template <int C>
+    __device__ static __forceinline__ void encode(const u32x4 (&v)[8], RowScale rs, uint32_t (&d)[2 * kHalfWords])
     {
-        uint32_t d[10];
+        uint32_t b[8];  // codes 4i .. 4i+3 of the half, one byte each
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            uint32_t w[5] = {0, 0, 0, 0, 0};
-#pragma unroll
-            for (int i = 0; i < 20; ++i)  // in place: byte i%4 of word i/4
-                w[i / 4] |= in_place(code[4 * c + i / 8][i % 8]) << (8 * (i % 4));
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {  // byte lane b of the three spread groups (codes 20+b, 24+b, 28+b)
-                const uint32_t c0 = code[4 * c + 2][4 + b], c1 = code[4 * c + 3][b], c2 = code[4 * c + 3][4 + b];
-                const int sh = 8 * b;
-                // bits of a code: 4 = s, 3 = e1, 2 = e0, 1 = m1, 0 = m0
-                w[0] |= ((((c0 >> 4) & 1u) << 6) | (((c0 >> 2) & 3u) << 4)) << sh;                       // s, e1 e0
-                w[1] |= (((c0 & 3u) << 5) | (((c1 >> 4) & 1u) << 4)) << sh;                              // m1 m0 | s
-                w[2] |= (((c1 >> 1) & 7u) << 4) << sh;                                                   // e1 e0 m1
-                w[3] |= (((c1 & 1u) << 6) | (((c2 >> 4) & 1u) << 5) | (((c2 >> 3) & 1u) << 4)) << sh;    // m0 | s | e1
-                w[4] |= ((c2 & 7u) << 4) << sh;                                                          // e0 m1 m0
-            }
-#pragma unroll
-            for (int i = 0; i < 5; ++i)
-                d[5 * c + i] = w[i];
-        }
+        for (int i = 0; i < 8; ++i)
+            b[i] = four_bytes(v[4 * C + i / 2][i % 2 * 2], v[4 * C + i / 2][i % 2 * 2 + 1], rs);
+        // codes 0 .. 19 in place, the others in bits 6, 5, 4 of their bytes (fp6_device.hpp lists where)
+        uint32_t *w = d + C * kHalfWords;
+        w[0] = b[0] | ((b[5] >> 1) & 0x40404040u) | ((b[5] << 2) & 0x30303030u);
+        w[1] = b[1] | ((b[5] << 5) & 0x60606060u) | ((b[6] >> 3) & 0x10101010u);
+        w[2] = b[2] | ((b[6] << 3) & 0x70707070u);
+        w[3] = b[3] | ((b[6] << 6) & 0x40404040u) | ((b[7] >> 2) & 0x20202020u) | ((b[7] << 1) & 0x10101010u);
+        w[4] = b[4] | ((b[7] << 4) & 0x70707070u);
+    }
+    __device__ static __forceinline__ void store_tile(const uint32_t (&d)[2 * kHalfWords], uint8_t *tile, int lane)
+    {
         u32x4 *t = reinterpret_cast<u32x4 *>(tile) + lane;
         t[0] = (u32x4){d[0], d[1], d[2], d[3]};
         t[64] = (u32x4){d[4], d[5], d[6], d[7]};
@@ -148,80 +118,70 @@ struct E2M2Format {
 // e2m1: grid 0 .5 | 1 1.5 | 2 3 | 4 6 (Eq. 1 with bias 1, subnormal E = 0 binade).
 struct E2M1Format {
     static constexpr float kMax = 6.0f;
-    static constexpr int kSignShift = 3;
-    static constexpr int kTileBytes = 2048;
+    static constexpr int kTileBytes = 2048, kHalfWords = 4;
     static constexpr bool kHalfTiles = false;
-    __device__ static __forceinline__ uint32_t magnitude_code(float ratio)
+    template <int C>
+    __device__ static __forceinline__ void encode(const u32x4 (&v)[8], RowScale rs, uint32_t (&d)[2 * kHalfWords])
     {
-        uint32_t g;
-        if (ratio < 1.0f) {
-            g = (uint32_t)__builtin_rintf(ratio * 2.0f);  // subnormal binade: multiples of 1/2
-        } else {
-            uint32_t u = bit_cast<uint32_t>(ratio);
-            u += 0x001fffffu + ((u >> 22) & 1u);  // round the mantissa to 1 bit, half to even
-            g = (u >> 22) - (126u << 1);          // exponent field - 127 + bias 1, then 1 mantissa bit
-        }
-        return g < 7u ? g : 7u;
-    }
-    __device__ static __forceinline__ void store_tile(const uint32_t (&code)[8][8], uint8_t *tile, int lane)
-    {
-        uint32_t d[8];
 #pragma unroll
-        for (int run = 0; run < 8; ++run) {
+        for (int run = 0; run < 4; ++run) {
+            const u32x4 &p = v[4 * C + run];
             uint32_t w = 0;
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                w |= code[run][j] << (4 * j);
-            d[run] = w;
+            static_for<4>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                const half2_t h = bit_cast<half2_t>(p[j]);
+                w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, ratio_of(h[0], rs), ratio_of(h[1], rs), 1.0f, j);
+            });
+            d[C * kHalfWords + run] = w;
         }
+    }
+    __device__ static __forceinline__ void store_tile(const uint32_t (&d)[2 * kHalfWords], uint8_t *tile, int lane)
+    {
         u32x4 *t = reinterpret_cast<u32x4 *>(tile) + lane;
         t[0] = (u32x4){d[0], d[1], d[2], d[3]};
         t[64] = (u32x4){d[4], d[5], d[6], d[7]};
     }
 };
 
-// e2m0: grid 0 | 1 | 2 | 4 (Eq. 1 with bias 1 and no mantissa bits; the E = 0 binade holds only 0).
+// e2m0: grid 0 | 1 | 2 | 4 (Eq. 1 with bias 1 and no mantissa bits; the E = 0 binade holds only 0).  No conversion of the chip
+// rounds to it.
 struct E2M0Format {
     static constexpr float kMax = 4.0f;
-    static constexpr int kSignShift = 2;
     static constexpr int kTileBytes = 3072;       // 16 rows x 512 columns: k-tile kt (256 columns) is half kt % 2 of tile kt / 2
+    static constexpr int kHalfWords = 3;
     static constexpr bool kHalfTiles = true;
-    __device__ static __forceinline__ uint32_t magnitude_code(float ratio)
+    // code s e1 e0: the midpoints 0.5, 1.5 and 3 go to the even codes 0, 2 and 2
+    __device__ static __forceinline__ uint32_t code_of(half_t w, RowScale rs)
     {
-        uint32_t g;
-        if (ratio < 1.0f) {
-            g = (uint32_t)__builtin_rintf(ratio);  // 0 or 1, the midpoint 0.5 to the even code 0
-        } else {
-            uint32_t u = bit_cast<uint32_t>(ratio);
-            u += 0x003fffffu + ((u >> 23) & 1u);  // round the mantissa away entirely, half to the even exponent code
-            g = (u >> 23) - 126u;                 // exponent field - 127 + bias 1
+        const float ratio = ratio_of(w, rs), a = __builtin_fabsf(ratio);
+        uint32_t g = bit_cast<uint32_t>(ratio) >> 31 << 2;
+        g += a > 0.5f;
+        g += a >= 1.5f;
+        g += a > 3.0f;
+        return g;
+    }
+    template <int C>
+    __device__ static __forceinline__ void encode(const u32x4 (&v)[8], RowScale rs, uint32_t (&d)[2 * kHalfWords])
+    {
+        uint32_t w[4] = {0, 0, 0, 0};  // codes of a run, four bits each
+#pragma unroll
+        for (int run = 0; run < 4; ++run) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                w[run] |= code_of(bit_cast<half2_t>(v[4 * C + run][j / 2])[j % 2], rs) << (4 * j);
+            __builtin_amdgcn_sched_barrier(0);  // run by run: fewer registers
         }
-        return g < 3u ? g : 3u;
+        // runs 0 .. 2 in place, field "s e1 e0 .", run 3 spread over the free bits
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            d[C * kHalfWords + i] = w[i] << 1 | ((w[3] >> i) & 0x11111111u);
     }
     // the lane's bytes of one half of a tile: 16 in plane 0 (first half) or 2 (second half), 8 in the middle
     // plane; pad_other: the matrix ends with this half (K an odd multiple of 256) and the lane also writes the
     // zero padding of the other half
-    __device__ static __forceinline__ void store_half(const uint32_t (&code)[8][8], uint8_t *tile, int half, bool pad_other,
+    __device__ static __forceinline__ void store_half(const uint32_t (&d)[2 * kHalfWords], uint8_t *tile, int half, bool pad_other,
                                                       int lane)
     {
-        uint32_t d[6];
-#pragma unroll
-        for (int g = 0; g < 2; ++g) {
-            uint32_t w[3] = {0, 0, 0};
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    w[i] |= (code[4 * g + i][j] << 1) << (4 * j);  // in place: field "s e1 e0 ."
-                const uint32_t c = code[4 * g + 3][j];             // spread over the free bits
-#pragma unroll
-                for (int b = 0; b < 3; ++b)
-                    w[b] |= ((c >> b) & 1u) << (4 * j);
-            }
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-                d[3 * g + i] = w[i];
-        }
         *(reinterpret_cast<u32x4 *>(tile + half * 2048) + lane) = (u32x4){d[0], d[1], d[2], d[3]};
         *(reinterpret_cast<u32x2 *>(tile + 1024) + 2 * lane + half) = (u32x2){d[4], d[5]};
         if (pad_other) {
@@ -231,33 +191,23 @@ struct E2M0Format {
     }
 };
 
-// The lane's bytes of k-tile kt (256 columns) of row tile `row_tile` into the packed stream (tiles stored
+// The lane's words of k-tile kt (256 columns) of row tile `row_tile` into the packed stream (tiles stored
 // k-tile major; RT row tiles, KT k-tiles of 256 columns).
-template <class Fmt, class = void>
-struct KTileStore {
-    __device__ static __forceinline__ void store(const uint32_t (&code)[8][8], uint8_t *packed, int64_t kt, int64_t row_tile,
-                                                 int64_t RT, int /*KT*/, int lane)
-    {
-        Fmt::store_tile(code, packed + (kt * RT + row_tile) * Fmt::kTileBytes, lane);
-    }
-};
 template <class Fmt>
-struct KTileStore<Fmt, std::enable_if_t<Fmt::kHalfTiles>> {
-    __device__ static __forceinline__ void store(const uint32_t (&code)[8][8], uint8_t *packed, int64_t kt, int64_t row_tile,
-                                                 int64_t RT, int KT, int lane)
-    {
-        Fmt::store_half(code, packed + ((kt >> 1) * RT + row_tile) * Fmt::kTileBytes, (int)(kt & 1),
-                        (kt & 1) == 0 && kt == KT - 1, lane);
-    }
-};
+__device__ __forceinline__ void store_k_tile(const uint32_t (&d)[2 * Fmt::kHalfWords], uint8_t *packed, int64_t kt, int64_t row_tile, int64_t RT, int KT,
+                                             int lane)
+{
+    if constexpr (Fmt::kHalfTiles)
+        Fmt::store_half(d, packed + ((kt >> 1) * RT + row_tile) * Fmt::kTileBytes, (int)(kt & 1), (kt & 1) == 0 && kt == KT - 1, lane);
+    else
+        Fmt::store_tile(d, packed + (kt * RT + row_tile) * Fmt::kTileBytes, lane);
+}
 
-// ---- per-row scales: two launches ------------------------------------------------------------------
+// ---- per-row scales, small matrices: two launches ---------------------------------------------------
 // row_scale_kernel: one wave per row finds max |W| and writes scale = fp16(max / Fmt::kMax) (a plain read of
 // W at streaming rate).  quantize_tiles_kernel: one wave per 16 x 256 tile reads the tile once, rounds every
 // weight with its row's scale and writes the packed tile.  The scales array is the only thing that passes
-// between the two, so nothing is kept on chip across a row (a row of 22016 fp16 values is 44 KB and a row
-// tile 0.7 MB - more than a CU can hold); W is read twice from memory and that is the algorithmic minimum
-// for a per-row maximum unless rows fit on chip.
+// between the two; W is read twice.
 constexpr int kScaleWavesPerBlock = 4;
 
 template <class Fmt>
@@ -319,15 +269,148 @@ __global__ __launch_bounds__(256) void quantize_tiles_kernel(const half_t *__res
     for (int f = 0; f < 8; ++f)
         v[f] = *reinterpret_cast<const u32x4 *>(row + f * 32);
     const RowScale scale = make_row_scale((float)scales[row_tile * kTileRows + r]);
-    uint32_t code[8][8];
+    uint32_t d[2 * Fmt::kHalfWords];
+    Fmt::template encode<0>(v, scale, d);
+    Fmt::template encode<1>(v, scale, d);
+    store_k_tile<Fmt>(d, packed, kt, row_tile, RT, KT, lane);
+}
+
+// ---- per-row scales, one pass over W -----------------------------------------------------------------
+// A block of four waves holds 16 rows x 1024 columns in registers (a part of a row tile; one k-tile per wave), and the parts
+// of a row tile agree on the row maxima through memory: W is read once.  Each block raises the sixteen maxima with atomics, counts
+// itself as arrived, waits until all parts have, and reads them back.  Bound by memory: 361 MB read + 135 MB written for 8192 x
+// 22016 in 115 us (4.3 TB/s) against 145 in two launches; 57344 x 8192 377 -> 241, 4096 x 4096 15.5 -> 14.4, 4 bits 8192 x 22016
+// 129 -> 103.  Five or six blocks per CU cover the exchange; eight (64 registers, some spilled) gain nothing.  The parts of a row
+// tile follow one another in the grid, that is on different XCDs: all on one XCD 163 us.  Non-temporal loads 121.
+//   The exchange happens in the first 128 bytes of the row tile's first packed tile: cleared by a launch of their own, written
+// over by whichever block is the last to have read the maxima (it fetches k-tile 0 again).  So nothing is waited for but
+// arrivals, and that wait is bounded: a block that has polled kPartWaitPolls times reads its sixteen rows itself.  (In a launch
+// alone on the chip the wait ends without that: blocks start in order on each XCD, so the earliest unfinished row tile always
+// finds room for its parts.)
+constexpr int kPartWaves = 4, kMaxParts = 40, kPartWaitPolls = 1000;
+constexpr int kExchangeBytes = 128, kArrivedWord = 16, kReadWord = 17;  // words 0 .. 15: the maxima
+
+__global__ __launch_bounds__(256) void clear_exchange_kernel(uint8_t *packed, int row_tiles, int tile_bytes)
+{
+    constexpr int kPieces = kExchangeBytes / 16;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i / kPieces < row_tiles)
+        *reinterpret_cast<u32x4 *>(packed + (int64_t)(i / kPieces) * tile_bytes + i % kPieces * 16) = (u32x4){0u, 0u, 0u, 0u};
+}
+
+// the lane's share of a 16 x 256 tile: eight runs of 32 columns
+__device__ __forceinline__ void load_weights(u32x4 (&v)[8], const half_t *p)
+{
+#pragma unroll
+    for (int f = 0; f < 8; ++f)
+        v[f] = *reinterpret_cast<const u32x4 *>(p + f * 32);
+}
+// largest magnitude of the lane's values, as bits: finite fp16 magnitudes order like integers
+__device__ __forceinline__ uint32_t magnitude_max(const u32x4 (&v)[8])
+{
+    ushort2_t mx = {0, 0};
 #pragma unroll
     for (int f = 0; f < 8; ++f)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            code[f][2 * j] = quantize_code<Fmt>(v[f][j] & 0xffffu, scale);
-            code[f][2 * j + 1] = quantize_code<Fmt>(v[f][j] >> 16, scale);
+        for (int j = 0; j < 4; ++j)
+            mx = __builtin_elementwise_max(mx, bit_cast<ushort2_t>(v[f][j] & 0x7fff7fffu));
+    return mx[0] > mx[1] ? mx[0] : mx[1];
+}
+// ... of the four lanes that share a row
+__device__ __forceinline__ uint32_t row_of_tile_max(uint32_t amax)
+{
+#pragma unroll
+    for (int off = 16; off < 64; off <<= 1) {
+        const uint32_t other = __shfl_xor(amax, off, 64);
+        amax = other > amax ? other : amax;
+    }
+    return amax;
+}
+
+template <class Fmt>
+__global__ __launch_bounds__(kPartWaves * 64) void quantize_rows_kernel(const half_t *__restrict__ W, int M, int K, uint8_t *packed,
+                                                                        half_t *__restrict__ scales, int parts)
+{
+    static_assert(Fmt::kTileBytes % kExchangeBytes == 0 && kExchangeBytes <= 1024, "the exchange lies in the first plane of a tile");
+    __shared__ uint32_t part_max[kPartWaves][16], row_max[16], last_reader;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int KT = K / kTileK, RT = M / kTileRows;
+    const int row_tile = blockIdx.x / parts, part = blockIdx.x % parts;
+    const int kt = part * kPartWaves + wave;
+    const int r = lane & 15, q = lane >> 4;
+    const half_t *row = W + ((int64_t)row_tile * kTileRows + r) * K + q * 8;
+    u32x4 v[8];
+    load_weights(v, row + (kt < KT ? kt : KT - 1) * kTileK);  // waves past the last k-tile repeat it
+    const uint32_t tile_max = row_of_tile_max(magnitude_max(v));
+    if (lane < 16)
+        part_max[wave][lane] = tile_max;
+    __syncthreads();
+    if (wave == 0) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int w = 0; w < kPartWaves; ++w)
+            m = part_max[w][r] > m ? part_max[w][r] : m;
+        bool last = true;
+        if (parts > 1) {
+            // order: this part's maxima are in memory (vmcnt) -> its arrival; all arrivals -> the maxima are read -> this part has
+            // read them.  Accesses of agent scope, as in the split-K hand-over (linear_stream.hpp).
+            uint32_t *line = reinterpret_cast<uint32_t *>(packed + (int64_t)row_tile * Fmt::kTileBytes);
+            if (lane < 16)
+                __hip_atomic_fetch_max(line + lane, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            int arrived = 0;
+            if (lane == 0)
+                arrived = (int)__hip_atomic_fetch_add(line + kArrivedWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+            arrived = __builtin_amdgcn_readfirstlane(arrived);
+            for (int i = 0; arrived < parts && i < kPartWaitPolls; ++i) {
+                __builtin_amdgcn_s_sleep(1);
+                arrived = __builtin_amdgcn_readfirstlane((int)__hip_atomic_load(line + kArrivedWord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            }
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            if (arrived >= parts) {
+                m = __hip_atomic_load(line + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                m = 0;
+                for (int t = 0; t < KT; ++t) {
+                    u32x4 other[8];
+                    load_weights(other, row + t * kTileK);
+                    const uint32_t x = magnitude_max(other);
+                    m = x > m ? x : m;
+                }
+                m = row_of_tile_max(m);
+            }
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the maxima have been read
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            uint32_t readers = 0;
+            if (lane == 0)
+                readers = __hip_atomic_fetch_add(line + kReadWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+            last = __builtin_amdgcn_readfirstlane((int)readers) == parts;
         }
-    KTileStore<Fmt>::store(code, packed, kt, row_tile, RT, KT, lane);
+        if (lane < 16)
+            row_max[lane] = m;
+        if (lane == 0)
+            last_reader = last ? 1u : 0u;
+    }
+    __syncthreads();
+    const half_t sc = (half_t)((float)bit_cast<half_t>((uint16_t)row_max[r]) / Fmt::kMax);  // fp32 quotient, one rounding
+    if (part == 0 && wave == 0 && lane < 16)
+        scales[row_tile * kTileRows + lane] = sc;
+    const RowScale scale = make_row_scale((float)sc);
+    uint32_t d[2 * Fmt::kHalfWords];
+    if (kt < KT && (kt > 0 || parts == 1)) {
+        Fmt::template encode<0>(v, scale, d);
+        Fmt::template encode<1>(v, scale, d);
+        store_k_tile<Fmt>(d, packed, kt, row_tile, RT, KT, lane);
+    }
+    if (parts > 1 && wave == 0 && last_reader) {
+        load_weights(v, row);
+        Fmt::template encode<0>(v, scale, d);
+        Fmt::template encode<1>(v, scale, d);
+        store_k_tile<Fmt>(d, packed, 0, row_tile, RT, KT, lane);
+    }
 }
 
 // Group-wise scales (one per row and per 128 columns): a group lies inside one tile and inside one of a
@@ -351,10 +434,10 @@ __global__ __launch_bounds__(256) void quantize_pack_group_kernel(const half_t *
 #pragma unroll
     for (int f = 0; f < 8; ++f)
         v[f] = *reinterpret_cast<const u32x4 *>(row + f * 32);
-    uint32_t code[8][8];
+    uint32_t d[2 * E3M2Format::kHalfWords];
     uint32_t scale_bits[2];
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
+    static_for<2>([&](auto cc) {
+        constexpr int c = decltype(cc)::value;
         ushort2_t mx = {0, 0};
 #pragma unroll
         for (int f = 4 * c; f < 4 * c + 4; ++f)
@@ -369,16 +452,9 @@ __global__ __launch_bounds__(256) void quantize_pack_group_kernel(const half_t *
         }
         const half_t sc = (half_t)((float)bit_cast<half_t>((uint16_t)amax) / E3M2Format::kMax);
         scale_bits[c] = bit_cast<uint16_t>(sc);
-        const RowScale scale = make_row_scale((float)sc);
-#pragma unroll
-        for (int f = 4 * c; f < 4 * c + 4; ++f)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                code[f][2 * j] = quantize_code<E3M2Format>(v[f][j] & 0xffffu, scale);
-                code[f][2 * j + 1] = quantize_code<E3M2Format>(v[f][j] >> 16, scale);
-            }
-    }
-    E3M2Format::store_tile(code, packed + packed_tile * E3M2Format::kTileBytes, lane);
+        E3M2Format::encode<c>(v, make_row_scale((float)sc), d);
+    });
+    E3M2Format::store_tile(d, packed + packed_tile * E3M2Format::kTileBytes, lane);
     if (q == 0) {
         const int64_t groups = K / kGroupColumns;
         *reinterpret_cast<uint32_t *>(scales + (row_tile * kTileRows + r) * groups + 2 * kt) = scale_bits[0] | (scale_bits[1] << 16);
@@ -477,7 +553,6 @@ __global__ __launch_bounds__(256) void probe_read_kernel(const uint8_t *__restri
 }
 
 // probe_mfma_kernel: every wave issues iters x 4 independent v_mfma_f32_32x32x16_f16 on register operands.
-typedef float float16_t __attribute__((ext_vector_type(16)));
 __global__ __launch_bounds__(256) void probe_mfma_kernel(int iters, float *__restrict__ sink)
 {
     const half_t one = (half_t)1.0f, tiny = (half_t)0.0009765625f;

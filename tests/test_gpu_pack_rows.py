@@ -1,0 +1,60 @@
+"""fp6/fp5/fp4/fp3_quantize_pack where one launch reads W once: no exchange (up to 1024 columns), the parts of a row tile agreeing on
+its maxima (large matrices), last parts with one k-tile, uneven numbers of row tiles, output buffers full of other bytes.
+
+Codes and scales have one right value: sampled row tiles are compared bit for bit with the oracle's for those rows alone.
+"""
+import numpy as np
+import pytest
+import torch
+
+from packed_rows import row_tiles_of
+
+pytestmark = pytest.mark.gpu
+
+TILE = {"fp6": (3072, 256), "fp5": (2560, 256), "fp4": (2048, 256), "fp3": (3072, 512)}
+SHAPES = [(16, 256), (48, 768), (4112, 1024), (4096, 4096), (1040, 16640), (416, 40960), (52432, 1280)]
+CASES = [(f, M, K) for f in ("fp6", "fp5", "fp4") for M, K in SHAPES] + [("fp3", 16, 256), ("fp3", 48, 768), ("fp3", 4112, 1024), ("fp3", 16400, 16384)]
+
+
+@pytest.fixture(scope="module")
+def pkg():
+    import paper_2401_14112_amd as p
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    p.load_library()
+    return p
+
+
+def _oracle(fmt):
+    from oracle import fp6_oracle, fpx_oracle
+
+    return fp6_oracle if fmt == "fp6" else fpx_oracle.BY_PREFIX[fmt]
+
+
+@pytest.mark.parametrize("fmt,M,K", CASES)
+def test_one_pass_quantize_pack(pkg, fmt, M, K):
+    print("quantize_pack %s M=%d K=%d" % (fmt, M, K), flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + K)
+    W = torch.empty((M, K), dtype=torch.float16, device="cuda").normal_(0, 0.02, generator=g)
+    tiles = sorted({0, M // 32, M // 16 - 1})
+    for t in tiles:  # rows that differ in where their maximum lies, and rows without one
+        W[16 * t, :] = 0
+        W[16 * t + 1, :] = -0.0
+        W[16 * t + 2, :] = 6e-8  # the scale rounds to zero
+        W[16 * t + 3, 0] = 3.0
+        W[16 * t + 4, K - 1] = -5.0
+        W[16 * t + 5, K // 2] = 65504.0
+    tile_bytes, tile_cols = TILE[fmt]
+    packed = torch.full((-(-K // tile_cols) * (M // 16) * tile_bytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    scales = torch.full((M,), float("nan"), dtype=torch.float16, device="cuda")
+    rows = np.concatenate([np.arange(16 * t, 16 * t + 16) for t in tiles])
+    ref_packed, ref_scales = _oracle(fmt).quantize_pack(W[torch.from_numpy(rows).cuda()].cpu().numpy())
+    first = None
+    for _ in range(2):
+        getattr(pkg, fmt + "_quantize_pack")(W, packed=packed, scales=scales)
+        got = row_tiles_of(packed, M, K, tiles, tile_bytes, tile_cols)
+        assert np.array_equal(got, np.asarray(ref_packed).reshape(-1))
+        assert np.array_equal(scales.cpu().numpy()[rows].view(np.uint16), np.asarray(ref_scales).view(np.uint16))
+        assert first is None or torch.equal(first, packed)
+        first = packed.clone()
