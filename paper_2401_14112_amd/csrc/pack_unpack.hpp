@@ -24,6 +24,19 @@ __device__ __forceinline__ RowScale make_row_scale(float scale)
     r.inv = scale == 0.0f ? 0.0f : 1.0f / scale;
     return r;
 }
+// ... for the weights of runs F0 .. F0 + F - 1.  Infinities and NaN are not weights; a row that has them still gets one well-defined
+// answer, the largest magnitude with the sign of each weight, which is not left to the conversions.
+template <int F0, int F>
+__device__ __forceinline__ RowScale row_scale_of(float scale, u32x4 (&v)[8])
+{
+    if (!(scale <= 65504.0f)) {
+#pragma unroll
+        for (int f = F0; f < F0 + F; ++f)
+            v[f] = (v[f] & 0x80008000u) | 0x7bff7bffu;
+        scale = 1.0f;
+    }
+    return make_row_scale(scale);
+}
 
 // w / scale with one Newton correction on top of the reciprocal product.  When the exact quotient is a
 // grid midpoint m (the only case where the last bit matters), q = m(1+e), the fused remainder q*scale - w
@@ -268,7 +281,7 @@ __global__ __launch_bounds__(256) void quantize_tiles_kernel(const half_t *__res
 #pragma unroll
     for (int f = 0; f < 8; ++f)
         v[f] = *reinterpret_cast<const u32x4 *>(row + f * 32);
-    const RowScale scale = make_row_scale((float)scales[row_tile * kTileRows + r]);
+    const RowScale scale = row_scale_of<0, 8>((float)scales[row_tile * kTileRows + r], v);
     uint32_t d[2 * Fmt::kHalfWords];
     Fmt::template encode<0>(v, scale, d);
     Fmt::template encode<1>(v, scale, d);
@@ -398,7 +411,7 @@ __global__ __launch_bounds__(kPartWaves * 64) void quantize_rows_kernel(const ha
     const half_t sc = (half_t)((float)bit_cast<half_t>((uint16_t)row_max[r]) / Fmt::kMax);  // fp32 quotient, one rounding
     if (part == 0 && wave == 0 && lane < 16)
         scales[row_tile * kTileRows + lane] = sc;
-    const RowScale scale = make_row_scale((float)sc);
+    RowScale scale = row_scale_of<0, 8>((float)sc, v);
     uint32_t d[2 * Fmt::kHalfWords];
     if (kt < KT && (kt > 0 || parts == 1)) {
         Fmt::template encode<0>(v, scale, d);
@@ -407,6 +420,7 @@ __global__ __launch_bounds__(kPartWaves * 64) void quantize_rows_kernel(const ha
     }
     if (parts > 1 && wave == 0 && last_reader) {
         load_weights(v, row);
+        scale = row_scale_of<0, 8>((float)sc, v);
         Fmt::template encode<0>(v, scale, d);
         Fmt::template encode<1>(v, scale, d);
         store_k_tile<Fmt>(d, packed, 0, row_tile, RT, KT, lane);
@@ -452,7 +466,8 @@ __global__ __launch_bounds__(256) void quantize_pack_group_kernel(const half_t *
         }
         const half_t sc = (half_t)((float)bit_cast<half_t>((uint16_t)amax) / E3M2Format::kMax);
         scale_bits[c] = bit_cast<uint16_t>(sc);
-        E3M2Format::encode<c>(v, make_row_scale((float)sc), d);
+        const RowScale scale = row_scale_of<4 * c, 4>((float)sc, v);
+        E3M2Format::encode<c>(v, scale, d);
     });
     E3M2Format::store_tile(d, packed + packed_tile * E3M2Format::kTileBytes, lane);
     if (q == 0) {
