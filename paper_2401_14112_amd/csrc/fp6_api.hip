@@ -319,7 +319,7 @@ struct BlockCfg {
     double fp16_ns, group_ns;
     constexpr int k_groups() const { return rows == 128 ? 2 : 1; }
 };
-constexpr int kBlockCfgs = 4, kBlock256x256 = 0;
+constexpr int kBlockCfgs = 4, kBlock256x256 = 0, kBlock128x128 = 2;
 constexpr BlockCfg kBlockCfg[kBlockCfgs] = {{256, 256, 805, 0}, {256, 128, 590, 480}, {128, 128, 258, 293}, {128, 64, 198, 0}};
 // BlockShape<RT, NT, WM, WN, WK, SR, XST, WD, ADB> of each, for run-staged (fp16) and packed weights
 template <bool RUN_STAGED, int C>
@@ -465,10 +465,14 @@ TiledPlan plan_tiled(int64_t M, int64_t N, int64_t K, Weights kind)
 struct PromptPlan {
     TiledPlan tiled;
     BlockPlan block;
+    bool instead_of_tiled;  // the block where `tiled` says what the call asks its caller for
     bool is_block() const { return block.cfg >= 0; }
     int split() const { return is_block() ? block.split : tiled.split; }
     size_t counter_bytes() const { return is_block() ? block.counter_bytes : tiled.counter_bytes; }
     size_t partial_bytes() const { return is_block() ? block.partial_bytes : tiled.partial_bytes; }
+    // What the size query names and a call is refused without: never less than what the launch uses.
+    size_t required_counters() const { return instead_of_tiled && tiled.counter_bytes > counter_bytes() ? tiled.counter_bytes : counter_bytes(); }
+    size_t required_partials() const { return instead_of_tiled ? tiled.partial_bytes : partial_bytes(); }
 };
 
 // Estimated time of a block plan, ns: rounds of 256 blocks at the measured cost per run, a fixed part per round, and for
@@ -489,6 +493,40 @@ double block_cost(const BlockPlan &p, int64_t K, Weights kind)
     // (258 ns up to K = 12288, 300 to 340 beyond 20000)
     const double long_rows = b.rows == 128 && K > 12288 ? 1.0 + 0.25 * (double)((K < 28672 ? K : 28672) - 12288) / 12288.0 : 1.0;
     return block_cost(p, K, kind == Weights::kFp16 ? b.fp16_ns * long_rows : b.group_ns);
+}
+
+// Estimated time, us, of the plans that weights with a scale per row choose between: rounds of the chip, each with a fixed part and a
+// cost per run of 32 columns that grows with the share of CUs that have a block; what k slices cost; and no faster than the weights
+// come from memory.  Fitted to 20514 drawn calls of 128 to 57344 rows and 65 to 4096 tokens, weights from memory (mean error 4.5 to 5 %).
+struct PerRowCost {
+    double fixed, slices, per_slice, memory_rate, fill, run[4];  // run: 6, 5, 4, 3 bits
+    double operator()(double rounds, int64_t blocks, int split, int64_t M, int64_t K, Weights kind) const
+    {
+        const int f = kind == Weights::kFp6 ? 0 : kind == Weights::kFp5 ? 1 : kind == Weights::kFp4 ? 2 : 3;
+        const double runs = 8.0 * (double)((K / kTileK + split - 1) / split), busy = (double)blocks / kCus / rounds;
+        const double alone = rounds * (fixed + runs * run[f] * (1.0 + fill * (busy < 1.0 ? busy : 1.0))) + (split > 1 ? slices + per_slice * split : 0.0);
+        const double memory = (double)M * (double)K * (6 - f) / 8.0 * 1e-6 / memory_rate;
+        return alone > memory ? alone : memory;
+    }
+};
+constexpr PerRowCost kBlock128Cost{6.62, 2.11, 0.543, 2.68, 0.606, {0.1398, 0.1516, 0.1244, 0.1295}};
+constexpr PerRowCost kTiled256Cost{7.20, 0.995, 1.20, 3.21, 0.534, {0.2476, 0.2487, 0.2268, 0.2257}};
+constexpr PerRowCost kTiled64Cost{4.27, 0.88, 0.425, 2.53, 0.336, {0.0951, 0.1073, 0.0845, 0.0883}};
+
+// Whether the block kernel's 128 x 128 block takes a call from the tiled kernel (256 x 128 blocks, or 128 x 64).  It has half as many k
+// slices where 256-row blocks leave CUs idle and whole units per XCD where those are dealt unevenly.  Median time over the tiled
+// kernel's, drawn calls as above, by their k slices: 256 x 128, two 0.78-0.99, three to five 0.78-0.86, six and more 0.61, none 1.08
+// (a tenth of them below 0.73: rounds); 128 x 64 0.88 to 1.55.  As chosen: 0.805 over all 20514 calls, 0.803 if the faster one were
+// known; 12 calls more than 3 % slower.
+bool block128_is_faster(const BlockPlan &b, const TiledPlan &t, int64_t M, int64_t K, Weights kind)
+{
+    const double fullest = (double)((int64_t)((t.row_blocks + kXcds - 1) / kXcds) * t.n_blocks * t.split) / kCusPerXcd;
+    const bool wide = t.tile.tokens() == 128;
+    // two 128 x 64 blocks share a CU
+    const double rounds = wide ? (double)(int64_t)(fullest + 1.0 - 1e-9) : fullest <= 1.0 ? 1.0 : fullest > 2.0 ? fullest : 1.0 + 0.9 * (fullest - 1.0);
+    const double tiled = (wide ? kTiled256Cost : kTiled64Cost)(rounds, (int64_t)t.row_blocks * t.n_blocks * t.split, t.split, M, K, kind);
+    const double block = kBlock128Cost((double)((b.chunk + kCusPerXcd - 1) / kCusPerXcd), (int64_t)b.row_blocks * b.n_blocks * b.split, b.split, M, K, kind);
+    return 1.03 * block < tiled;
 }
 
 // Partial sums with which fp16_linear runs at any rate: those of the block that kFp16AcceptedNs chooses.  These figures are not
@@ -546,7 +584,7 @@ bool short_blocks(const BlockPlan &b, const TiledPlan &tiled, int64_t K)
 //     202 against 219 with 5, 168 against 193 with 3).  Drawn calls of 256 to 57344 rows and 65 to 4096 tokens, time over
 //     that without it, median and largest: 6 bits 0.87, 0.98; 5 bits 0.93, 1.02; 4 bits 0.88, 0.98; 3 bits 0.90, 1.03 (800
 //     in all).  Beyond that rule it loses: 8192 x 8192, N = 1024 127 against 110, 28672 x 8192, N = 700 344 against 294,
-//     57344 x 4096, N = 300 175 against 155;
+//     57344 x 4096, N = 300 175 against 155.  Elsewhere the 128 x 128 block, where block128_is_faster();
 //   group scales: always, except few rows and few tokens (8192 x 8192, N = 100: 31 against 30; 4096 x 4096 17 against
 //     13; but 28672 x 8192, N = 201 107 against 160, 16384 x 8192, N = 2048 497 against 740) and short blocks, see
 //     short_blocks();
@@ -558,6 +596,7 @@ PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind, size_t par
 {
     PromptPlan p;
     p.block.cfg = -1;
+    p.instead_of_tiled = false;
     p.tiled = plan_tiled(M, N, K, kind);
     const int forced = g_forced_tile.load(std::memory_order_relaxed);
     if (forced > 0) {
@@ -577,8 +616,16 @@ PromptPlan plan_prompt(int64_t M, int64_t N, int64_t K, Weights kind, size_t par
     if (per_row(kind)) {
         const int64_t tiles = row_blocks * ((N + 255) / 256), halves = row_blocks * ((N + 127) / 128);
         const int64_t rounds = (tiles + kCus - 1) / kCus, half_rounds = (halves + kCus - 1) / kCus;
-        if (20 * rounds <= 11 * half_rounds && 20 * tiles <= 11 * halves)
+        if (20 * rounds <= 11 * half_rounds && 20 * tiles <= 11 * halves) {
             p.block = block_plan_of(kBlock256x256, M, N, K);
+        } else if (g_forced_split.load(std::memory_order_relaxed) <= 0) {  // the hook pins the tiled kernel
+            // no more partial sums than the tiled plan, whose size the caller was told
+            const BlockPlan b = block_plan_of(kBlock128x128, M, N, K, p.tiled.partial_bytes);
+            if (block128_is_faster(b, p.tiled, M, K, kind)) {
+                p.block = b;
+                p.instead_of_tiled = true;
+            }
+        }
         return p;
     }
     if (kind == Weights::kGrouped && few_blocks(M, N))
@@ -683,7 +730,7 @@ size_t counter_region_bytes(int64_t M, int64_t N, int64_t K)
     for (Weights kind : {Weights::kFp6, Weights::kFp5, Weights::kFp4, Weights::kFp3, Weights::kGrouped, Weights::kFp16})
         for (int64_t n : prompt_chunks(N, K))
             if (n > 0)
-                at_least(plan_prompt(M, n, K, kind).counter_bytes());
+                at_least(plan_prompt(M, n, K, kind).required_counters());
     return bytes;
 }
 
@@ -710,7 +757,7 @@ size_t prompt_workspace_bytes(int64_t M, int64_t N, int64_t K, Weights kind)
     size_t partial_bytes = 0;
     for (int64_t n : prompt_chunks(N, K))
         if (n > 0) {
-            const size_t b = plan_prompt(M, n, K, kind).partial_bytes();
+            const size_t b = plan_prompt(M, n, K, kind).required_partials();
             partial_bytes = b > partial_bytes ? b : partial_bytes;
         }
     return split_workspace_bytes(partial_bytes, M, N, K);
@@ -724,8 +771,8 @@ size_t prompt_workspace_bytes(int64_t M, int64_t N, int64_t K, Weights kind)
 fp6_status plan_prompt_within(int64_t M, int64_t N, int64_t K, Weights kind, const WorkspaceRef &workspace, PromptPlan &p, SplitBuffers &buf)
 {
     p = plan_prompt(M, N, K, kind);
-    const fp6_status fits = workspace.view(p.counter_bytes(), p.partial_bytes(), buf);
-    if (fits != FP6_ERR_WORKSPACE || !p.is_block() || g_forced_split.load(std::memory_order_relaxed) > 0)
+    const fp6_status fits = workspace.view(p.required_counters(), p.required_partials(), buf);
+    if (fits != FP6_ERR_WORKSPACE || !p.is_block() || p.instead_of_tiled || g_forced_split.load(std::memory_order_relaxed) > 0)
         return fits;
     const TiledPlan least = tiled_plan_of(few_blocks(M, N) ? kTile128x64 : kTile128x128, M, N, K, kind);
     const size_t bytes = workspace.base ? workspace.bytes : 0, region = workspace.counter_region;
@@ -757,9 +804,9 @@ fp6_status launch_prompt_chunk(const void *weights, const void *scales, const vo
         if constexpr (weights_of<Src>() != Weights::kGrouped) {
             FP6_BLOCK_CASE(0)
         }
+        FP6_BLOCK_CASE(2)
         if constexpr (!per_row(weights_of<Src>())) {
             FP6_BLOCK_CASE(1)
-            FP6_BLOCK_CASE(2)
         }
         if constexpr (weights_of<Src>() == Weights::kFp16) {
             FP6_BLOCK_CASE(3)
@@ -975,9 +1022,9 @@ fp6_status static_plan(int64_t M, int64_t N, int64_t K, size_t &counter_bytes)
         if (n <= 0)
             continue;
         const PromptPlan p = plan_prompt(M, n, K, Weights::kFp6);
-        if (p.counter_bytes() > counter_bytes)
-            counter_bytes = p.counter_bytes();
-        const fp6_status fits = probe.view(p.counter_bytes(), p.partial_bytes(), unused);
+        if (p.required_counters() > counter_bytes)
+            counter_bytes = p.required_counters();
+        const fp6_status fits = probe.view(p.required_counters(), p.required_partials(), unused);
         if (fits != FP6_OK)
             return fits;
     }
@@ -1039,7 +1086,7 @@ fp6_status plan_of_call(int weight_bits, int64_t M, int64_t N, int64_t K, int64_
         return fits;
     plan = {p.is_block() ? FP6_KERNEL_BLOCK : FP6_KERNEL_TILED, p.is_block() ? kBlockCfg[p.block.cfg].rows : p.tiled.tile.rows(),
             p.is_block() ? kBlockCfg[p.block.cfg].tokens : p.tiled.tile.tokens(), p.split(), first, tokens, p.counter_bytes(),
-            region, p.partial_bytes()};
+            region, p.split() > 1 ? p.required_partials() : 0};  // with k slices: what the call is refused without
     k_groups = p.is_block() ? kBlockCfg[p.block.cfg].k_groups() : p.tiled.k_groups;
     return FP6_OK;
 }

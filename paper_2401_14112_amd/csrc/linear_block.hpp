@@ -1,5 +1,6 @@
-// Block-tiled linear-layer kernel for prompt-sized token counts: fp16 weights, weights with group scales, and the
-// products that fill the chip with 256 x 256 blocks (the other prompt-sized calls: linear_tiled.hpp).
+// Block-tiled linear-layer kernel for prompt-sized token counts: fp16 weights, weights with group scales, and of those with a
+// scale per row the products that fill the chip with 256 x 256 blocks or that 128 x 128 blocks suit better than the tiled
+// kernel's (linear_tiled.hpp: the others).
 //
 // A block of WM x WN x WK waves computes a BM x BN piece of Y (BM = 16*RT*WM rows, BN = 16*NT*WN tokens); wave
 // (wm, wn) owns RT x NT tiles of 16 rows x 16 tokens in fp32 accumulators of v_mfma_f32_16x16x32_f16.  With WK = 2

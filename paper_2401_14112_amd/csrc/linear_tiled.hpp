@@ -1,5 +1,5 @@
-// Tiled linear-layer kernel for packed weights at prefill-sized token counts (N > 64) that do not fill the chip with
-// the block kernel's 256 x 256 pieces (linear_block.hpp), where the layer is bound by
+// Tiled linear-layer kernel for packed weights at prefill-sized token counts (N > 64) that the block kernel's pieces
+// (linear_block.hpp) do not suit better, where the layer is bound by
 // the matrix cores (Section 7.1 of the paper: all kernels become compute-bound beyond batch 128).
 //
 // A block is WM x WN x WK waves; wave (wm, wn) owns RT 16-row tiles and NT 16-token tiles, i.e. a
