@@ -5,7 +5,7 @@ import random
 
 import pytest
 
-from launch_plans import BITS, TILED, k_groups, plan, workspace_bytes
+from launch_plans import BITS, BLOCK, TILED, k_groups, plan, workspace_bytes
 
 
 @pytest.fixture(scope="module")
@@ -167,3 +167,42 @@ def test_tiled_counters_are_one_per_wave(lib, width, K, groups):
     assert (p.kernel, p.block_rows, p.block_tokens) == (TILED, 128, 64) and p.split_k > 1
     assert k_groups(lib, width, M, N, K) == groups
     assert p.counter_bytes == 2 * 4 * groups * 128
+
+
+def _tiled_partials(M, N, K):
+    """Partial sums of the tiled kernel's plan for weights with a scale per row."""
+    rows, tokens = (128, 64) if N <= 128 and -(-M // 256) < 64 else (256, 128)
+    n_blocks, k_tiles = -(-N // tokens), K // 256
+    s = max(1, min(256 // (-(-M // rows) * n_blocks), k_tiles // 4 if k_tiles >= 8 else 1, 16))
+    return s * (M // 16) * n_blocks * (tokens // 16) * 1024 if s > 1 else 0
+
+
+def test_blocks_in_place_of_tiled_ones_ask_for_what_those_did(lib):
+    """The 128 x 128 block takes calls from the tiled kernel: size query, acceptance and refusal are those of the tiled plan, and what
+    is launched stays within them."""
+    rng = random.Random(7)
+    sliced = whole = 0
+    for _ in range(4000):
+        width = rng.choice(["fp6", "fp5", "fp4", "fp3"])
+        M, K = 16 * round(2 ** rng.uniform(0, 11.8)), 256 * round(2 ** rng.uniform(0, 6.8))
+        N = round(2 ** rng.uniform(6.1, 12))
+        p = plan(lib, width, M, N, K)
+        if (p.kernel, p.block_rows, p.block_tokens) != (BLOCK, 128, 128):
+            continue
+        partials, need = _tiled_partials(M, N, K), workspace_bytes(lib, width, M, N, K)
+        own = p.split_k * -(-M // 128) * -(-N // 128) * 128 * 128 * 4 if p.split_k > 1 else 0
+        assert own <= partials, (width, M, N, K)
+        if not partials:
+            assert p.split_k == 1 and plan(lib, width, M, N, K, workspace_bytes=0) != REFUSED
+            whole += 1
+            continue
+        sliced += 1
+        assert plan(lib, width, M, N, K, workspace_bytes=need) != REFUSED, (width, M, N, K)
+        if p.split_k == 1:  # no counters in use that would say where the partial sums begin
+            assert plan(lib, width, M, N, K, workspace_bytes=partials - 16) == REFUSED, (width, M, N, K)
+            continue
+        least = p.partial_offset + partials
+        assert p.counter_bytes <= p.partial_offset and least <= need, (width, M, N, K)
+        assert plan(lib, width, M, N, K, workspace_bytes=least).split_k == p.split_k
+        assert plan(lib, width, M, N, K, workspace_bytes=least - 16) == REFUSED, (width, M, N, K)
+    assert sliced > 50 and whole > 50
