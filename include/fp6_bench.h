@@ -66,6 +66,16 @@ fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int
 /* Groups of k-tiles of a workgroup of that launch (waves that share an output piece and meet in LDS); 0 where it is refused. */
 int fp6_tuning_plan_k_groups(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes);
 
+/*
+ * quantize_pack calls with a scale per row (weight_bits 6, 5, 4, 3) read W in one launch where that is faster:
+ *   fp6_tuning_pack_parts: blocks that a row tile is divided among in that launch (1: they exchange nothing); 0: two
+ *     launches; -1: the shape or the width is refused.  Host arithmetic only.
+ *   fp6_tuning_set_pack_polls: how often a block looks for the other parts of its row tile before it reads their columns itself
+ *     (0: not once; negative: the default).  Process-wide.  The packed bytes do not depend on it.
+ */
+int fp6_tuning_pack_parts(int weight_bits, int64_t M, int64_t K);
+void fp6_tuning_set_pack_polls(int polls);
+
 #ifdef __cplusplus
 }
 #endif

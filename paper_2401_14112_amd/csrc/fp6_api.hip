@@ -914,6 +914,10 @@ fp6_status launch_stream(const void *weights, const void *scales, const void *X,
                                                           reinterpret_cast<float4_t *>(buf.partials), buf.counters, epi, stream);
 }
 
+std::atomic<int> g_pack_polls{kPartWaitPolls};  // (tuning hook)
+
+int64_t pack_parts(int64_t K) { return (K / kTileK + kPartWaves - 1) / kPartWaves; }
+
 // Whether a matrix is quantized in one pass (time over that of two launches, 6 / 4 / 3 bits):
 //   1024 columns and less, no exchange: 0.57-0.62 / 0.61-0.64 / 0.65-0.70 from 1024 to 57344 rows;
 //   more, 6, 5 and 4 bits: 8192 x 2048 0.94 / 0.94, 2048 x 8192 0.93 / 0.94, 4096 x 4096 0.92 / 0.90, 8192 x 22016 0.77 / 0.79,
@@ -925,7 +929,7 @@ fp6_status launch_stream(const void *weights, const void *scales, const void *X,
 template <class Fmt>
 bool one_pass_pack(int64_t M, int64_t K)
 {
-    const int64_t KT = K / kTileK, parts = (KT + kPartWaves - 1) / kPartWaves;
+    const int64_t KT = K / kTileK, parts = pack_parts(K);
     if (parts == 1)
         return true;
     if (std::is_same_v<Fmt, E2M0Format>)
@@ -947,7 +951,7 @@ fp6_status quantize_pack_impl(const void *W_f16, int64_t M, int64_t K, void *pac
     const half_t *W = static_cast<const half_t *>(W_f16);
     uint8_t *out = static_cast<uint8_t *>(packed);
     half_t *scales = static_cast<half_t *>(scales_f16);
-    const int64_t RT = M / kTileRows, KT = K / kTileK, parts = (KT + kPartWaves - 1) / kPartWaves;
+    const int64_t RT = M / kTileRows, KT = K / kTileK, parts = pack_parts(K);
     if (one_pass_pack<Fmt>(M, K)) {
         if (parts > 1) {
             hipLaunchKernelGGL(clear_exchange_kernel, dim3((unsigned)((RT * (kExchangeBytes / 16) + 255) / 256)), dim3(256), 0, st, out, (int)RT,
@@ -956,7 +960,7 @@ fp6_status quantize_pack_impl(const void *W_f16, int64_t M, int64_t K, void *pac
                 return FP6_ERR_HIP;
         }
         hipLaunchKernelGGL(quantize_rows_kernel<Fmt>, dim3((unsigned)(RT * parts)), dim3(kPartWaves * 64), 0, st, W, (int)M, (int)K, out, scales,
-                           (int)parts);
+                           (int)parts, g_pack_polls.load(std::memory_order_relaxed));
         return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
     }
     hipLaunchKernelGGL(row_scale_kernel<Fmt>, dim3((unsigned)((M + kScaleWavesPerBlock - 1) / kScaleWavesPerBlock)),
@@ -1159,6 +1163,18 @@ int fp6_tuning_plan_k_groups(int weight_bits, int64_t M, int64_t N, int64_t K, i
     fp6_launch_plan plan;
     int k_groups = 0;
     return plan_of_call(weight_bits, M, N, K, token, workspace_bytes, plan, k_groups) == FP6_OK ? k_groups : 0;
+}
+
+void fp6_tuning_set_pack_polls(int polls) { g_pack_polls.store(polls < 0 ? kPartWaitPolls : polls); }
+
+int fp6_tuning_pack_parts(int weight_bits, int64_t M, int64_t K)
+{
+    if (!packed_shape_ok(M, K) || weight_bits < 3 || weight_bits > 6)
+        return -1;
+    const bool one_pass = weight_bits == 6   ? one_pass_pack<E3M2Format>(M, K)
+                          : weight_bits == 5 ? one_pass_pack<E2M2Format>(M, K)
+                          : weight_bits == 4 ? one_pass_pack<E2M1Format>(M, K) : one_pass_pack<E2M0Format>(M, K);
+    return one_pass ? (int)pack_parts(K) : 0;
 }
 
 fp6_status fp6_workspace_init(void *workspace, size_t workspace_bytes, void *stream)

@@ -297,11 +297,15 @@ __global__ __launch_bounds__(256) void quantize_tiles_kernel(const half_t *__res
 // tile follow one another in the grid, that is on different XCDs: all on one XCD 163 us.  Non-temporal loads 121.
 //   The exchange happens in the first 128 bytes of the row tile's first packed tile: cleared by a launch of their own, written
 // over by whichever block is the last to have read the maxima (it fetches k-tile 0 again).  So nothing is waited for but
-// arrivals, and that wait is bounded: a block that has polled kPartWaitPolls times reads its sixteen rows itself.  (In a launch
-// alone on the chip the wait ends without that: blocks start in order on each XCD, so the earliest unfinished row tile always
-// finds room for its parts.)
-constexpr int kPartWaves = 4, kMaxParts = 40, kPartWaitPolls = 1000;
+// arrivals, and that wait is bounded: a block that has polled max_polls times reads its sixteen rows itself, and raises the maxima and
+// the arrival word for the parts that have not started yet, which then neither wait nor read.  (In a launch alone on the chip the wait
+// ends without that: blocks start in order on each XCD, so the earliest unfinished row tile always finds room for its parts.)  The
+// bound is four times what was needed: 8192 x 22016, 0 / 16 / 32 / 64 polls 860 / 117 / 113 / 113 us alone, 1060 / 890 / 500-850 / 298 beside
+// 57344 x 8192, N = 4096 on another stream, 980 / 770 / 240-750 / 245 beside 8192 x 22016, N = 512, 910 / 206 / 160 / 131 beside N = 16; more
+// polls change nothing (two launches, W read twice: 160 alone, 515, 420 and 203).
+constexpr int kPartWaves = 4, kMaxParts = 40, kPartWaitPolls = 256;
 constexpr int kExchangeBytes = 128, kArrivedWord = 16, kReadWord = 17;  // words 0 .. 15: the maxima
+constexpr uint32_t kMaximaComplete = 1u << 16;  // in the arrival word: more than any number of parts
 
 __global__ __launch_bounds__(256) void clear_exchange_kernel(uint8_t *packed, int row_tiles, int tile_bytes)
 {
@@ -342,9 +346,9 @@ __device__ __forceinline__ uint32_t row_of_tile_max(uint32_t amax)
 
 template <class Fmt>
 __global__ __launch_bounds__(kPartWaves * 64) void quantize_rows_kernel(const half_t *__restrict__ W, int M, int K, uint8_t *packed,
-                                                                        half_t *__restrict__ scales, int parts)
+                                                                        half_t *__restrict__ scales, int parts, int max_polls)
 {
-    static_assert(Fmt::kTileBytes % kExchangeBytes == 0 && kExchangeBytes <= 1024, "the exchange lies in the first plane of a tile");
+    static_assert(kMaxParts < (int)kMaximaComplete && Fmt::kTileBytes % kExchangeBytes == 0 && kExchangeBytes <= 1024, "the exchange lies in the first plane of a tile");
     __shared__ uint32_t part_max[kPartWaves][16], row_max[16], last_reader;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int KT = K / kTileK, RT = M / kTileRows;
@@ -377,7 +381,7 @@ __global__ __launch_bounds__(kPartWaves * 64) void quantize_rows_kernel(const ha
             if (lane == 0)
                 arrived = (int)__hip_atomic_fetch_add(line + kArrivedWord, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
             arrived = __builtin_amdgcn_readfirstlane(arrived);
-            for (int i = 0; arrived < parts && i < kPartWaitPolls; ++i) {
+            for (int i = 0; arrived < parts && i < max_polls; ++i) {
                 __builtin_amdgcn_s_sleep(1);
                 arrived = __builtin_amdgcn_readfirstlane((int)__hip_atomic_load(line + kArrivedWord, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             }
@@ -393,6 +397,13 @@ __global__ __launch_bounds__(kPartWaves * 64) void quantize_rows_kernel(const ha
                     m = x > m ? x : m;
                 }
                 m = row_of_tile_max(m);
+                if (lane < 16)
+                    __hip_atomic_fetch_max(line + lane, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): before the word that says so
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                if (lane == 0)
+                    __hip_atomic_fetch_or(line + kArrivedWord, kMaximaComplete, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the maxima have been read

@@ -7,13 +7,16 @@ import numpy as np
 import pytest
 import torch
 
+from launch_plans import BITS
 from packed_rows import row_tiles_of
 
 pytestmark = pytest.mark.gpu
 
 TILE = {"fp6": (3072, 256), "fp5": (2560, 256), "fp4": (2048, 256), "fp3": (3072, 512)}
 SHAPES = [(16, 256), (48, 768), (4112, 1024), (4096, 4096), (1040, 16640), (416, 40960), (52432, 1280)]
-CASES = [(f, M, K) for f in ("fp6", "fp5", "fp4") for M, K in SHAPES] + [("fp3", 16, 256), ("fp3", 48, 768), ("fp3", 4112, 1024), ("fp3", 16400, 16384)]
+# (the last of 3 bits: an odd number of k-tiles, so that the last part ends with half a tile)
+CASES = [(f, M, K) for f in ("fp6", "fp5", "fp4") for M, K in SHAPES] + [("fp3", 16, 256), ("fp3", 48, 768), ("fp3", 4112, 1024), ("fp3", 16400, 16384),
+                                                                         ("fp3", 17200, 15616)]
 
 
 @pytest.fixture(scope="module")
@@ -31,13 +34,14 @@ def _oracle(fmt):
     return fp6_oracle if fmt == "fp6" else fpx_oracle.BY_PREFIX[fmt]
 
 
-@pytest.mark.parametrize("fmt,M,K", CASES)
-def test_one_pass_quantize_pack(pkg, fmt, M, K):
-    print("quantize_pack %s M=%d K=%d" % (fmt, M, K), flush=True)
+def _parts(pkg, fmt, M, K):
+    return pkg.load_library().fp6_tuning_pack_parts(BITS[fmt], M, K)
+
+
+def _matrix(M, K, tiles):
     g = torch.Generator(device="cuda")
     g.manual_seed(M + K)
     W = torch.empty((M, K), dtype=torch.float16, device="cuda").normal_(0, 0.02, generator=g)
-    tiles = sorted({0, M // 32, M // 16 - 1})
     for t in tiles:  # rows that differ in where their maximum lies, and rows without one
         W[16 * t, :] = 0
         W[16 * t + 1, :] = -0.0
@@ -45,6 +49,15 @@ def test_one_pass_quantize_pack(pkg, fmt, M, K):
         W[16 * t + 3, 0] = 3.0
         W[16 * t + 4, K - 1] = -5.0
         W[16 * t + 5, K // 2] = 65504.0
+    return W
+
+
+@pytest.mark.parametrize("fmt,M,K", CASES)
+def test_one_pass_quantize_pack(pkg, fmt, M, K):
+    print("quantize_pack %s M=%d K=%d" % (fmt, M, K), flush=True)
+    assert _parts(pkg, fmt, M, K) == -(-K // 1024)
+    tiles = sorted({0, M // 32, M // 16 - 1})
+    W = _matrix(M, K, tiles)
     tile_bytes, tile_cols = TILE[fmt]
     packed = torch.full((-(-K // tile_cols) * (M // 16) * tile_bytes,), 0xFF, dtype=torch.uint8, device="cuda")
     scales = torch.full((M,), float("nan"), dtype=torch.float16, device="cuda")
@@ -58,3 +71,30 @@ def test_one_pass_quantize_pack(pkg, fmt, M, K):
         assert np.array_equal(scales.cpu().numpy()[rows].view(np.uint16), np.asarray(ref_scales).view(np.uint16))
         assert first is None or torch.equal(first, packed)
         first = packed.clone()
+
+
+@pytest.mark.parametrize("polls", [0, 1])
+@pytest.mark.parametrize("fmt,M,K", [(f, M, K) for f, M, K in CASES if K > 1024])
+def test_parts_that_do_not_wait(pkg, fmt, M, K, polls):
+    """A part that has not seen the others arrive reads its rows itself and answers for the parts that come later: the same bytes and
+    scales, the first tile (where the exchange took place) included."""
+    print("quantize_pack, %d polls, %s M=%d K=%d" % (polls, fmt, M, K), flush=True)
+    lib = pkg.load_library()
+    assert _parts(pkg, fmt, M, K) > 1
+    tiles = sorted({0, M // 32, M // 16 - 1})
+    W = _matrix(M, K, tiles)
+    want, want_scales = getattr(pkg, fmt + "_quantize_pack")(W)
+    tile_bytes, tile_cols = TILE[fmt]
+    rows = np.concatenate([np.arange(16 * t, 16 * t + 16) for t in tiles])
+    ref_packed, ref_scales = _oracle(fmt).quantize_pack(W[torch.from_numpy(rows).cuda()].cpu().numpy())
+    packed, scales = torch.full_like(want, 0xFF), torch.full_like(want_scales, float("nan"))
+    lib.fp6_tuning_set_pack_polls(polls)
+    try:
+        for _ in range(2):
+            getattr(pkg, fmt + "_quantize_pack")(W, packed=packed, scales=scales)
+            torch.cuda.synchronize()
+            assert torch.equal(packed, want) and torch.equal(scales.view(torch.int16), want_scales.view(torch.int16))
+    finally:
+        lib.fp6_tuning_set_pack_polls(-1)
+    assert np.array_equal(row_tiles_of(packed, M, K, tiles, tile_bytes, tile_cols), np.asarray(ref_packed).reshape(-1))
+    assert np.array_equal(scales.cpu().numpy()[rows].view(np.uint16), np.asarray(ref_scales).view(np.uint16))
