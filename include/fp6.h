@@ -94,14 +94,16 @@ fp6_status fp6_unpack(const void *packed, const void *scales_f16, int64_t M, int
  * the size does not depend on the block that the kernel chooses: where output blocks of 128
  * rows (64 rows: fp16_linear on more than 32 tokens, and where they fill the chip better)
  * would take k slices, a workspace is asked for also if the chosen block takes none and
- * leaves it untouched.  Formats that share a query (fp6, fp5, fp4 and fp6g) get the largest
- * of their sizes.  The workspace holds arrival counters, in its
- * first fp6_workspace_zero_bytes(), and behind them split-K partial sums.  It MUST be
- * zero-filled once before its first use (fp6_workspace_init or any device memset; the
- * counters are enough); the kernels leave the counters at zero, so it can be reused by
- * later calls without clearing it again: calls of any shape and any weight format of
- * this library, as long as it has the size that the query gives for each of them.  Two
- * calls that may run concurrently (different streams) need different workspaces.
+ * leaves it untouched.  Above 64 tokens the same holds for formats with a scale per row (fp6,
+ * fp5, fp4, fp3): where 128 x 128 output blocks are launched, the size is that of 256 x 128
+ * ones, which take more k slices.  Formats that share a query (fp6, fp5, fp4 and fp6g) get
+ * the largest of their sizes.  The workspace holds arrival counters, in its first
+ * fp6_workspace_zero_bytes(), and behind them split-K partial sums.  It MUST be zero-filled
+ * once before its first use (fp6_workspace_init or any device memset; the counters are
+ * enough); the kernels leave the counters at zero, so it can be reused by later calls without
+ * clearing it again: calls of any shape and any weight format of this library, as long as it
+ * has the size that the query gives for each of them.  Two calls that may run concurrently
+ * (different streams) need different workspaces.
  * A workspace too small for the call's own format is refused; only fp16_linear and fp6g_linear on more than 64 tokens
  * also run, slower, with one that holds the k slices of 128 x 128 output blocks, hence with
  * none where there are more than 128 such blocks, and fp16_linear in some other cases too

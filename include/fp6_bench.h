@@ -59,12 +59,19 @@ typedef struct {
     int64_t first_token, tokens;   /* of the launch */
     size_t counter_bytes;          /* arrival counters, at the start of the workspace (0 without k slices) */
     size_t partial_offset;         /* where its partial sums start ... */
-    size_t partial_bytes;          /* ... and their size (0 without k slices) */
+    size_t partial_bytes;          /* ... and the room for them that the call asks for (0 without k slices) */
 } fp6_launch_plan;
 fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes,
                            fp6_launch_plan *plan);
 /* Groups of k-tiles of a workgroup of that launch (waves that share an output piece and meet in LDS); 0 where it is refused. */
 int fp6_tuning_plan_k_groups(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes);
+/*
+ * Partial sums of that launch, bytes behind the counters: `used` by it (0 without k slices), and `required` of the workspace, without
+ * which the call is refused or launches something else.  More is required than used where the block that is launched takes fewer
+ * k slices than the one that the size query is made for (then also by a launch without any).
+ */
+fp6_status fp6_tuning_plan_partials(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes, size_t *used,
+                                    size_t *required);
 
 /*
  * quantize_pack calls with a scale per row (weight_bits 6, 5, 4, 3) read W in one launch where that is faster:

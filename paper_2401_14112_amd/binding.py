@@ -126,6 +126,8 @@ def load_library():
     L.fp6_tuning_plan.argtypes = [ci, i64, i64, i64, i64, sz, vp]
     L.fp6_tuning_plan_k_groups.restype = ci
     L.fp6_tuning_plan_k_groups.argtypes = [ci, i64, i64, i64, i64, sz]
+    L.fp6_tuning_plan_partials.restype = ci
+    L.fp6_tuning_plan_partials.argtypes = [ci, i64, i64, i64, i64, sz, vp, vp]
     L.fp6_tuning_pack_parts.restype = ci
     L.fp6_tuning_pack_parts.argtypes = [ci, i64, i64]
     L.fp6_tuning_set_pack_polls.restype = None

@@ -1053,9 +1053,13 @@ fp6_status packed_linear_impl(const void *packed, const void *scales_f16, const 
     return launch_stream<Src>(packed, scales_f16, X_f16, Y_f16, M, N, K, ws, epi, static_cast<hipStream_t>(stream));
 }
 
-// What fp6_tuning_plan reports, and the groups of k-tiles of a workgroup.
+// What fp6_tuning_plan reports, and what the queries beside it do.
+struct PlanDetails {
+    int k_groups;                    // groups of k-tiles of a workgroup
+    size_t used_partials, required_partials;  // that the launch writes; that its caller has to bring
+};
 fp6_status plan_of_call(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes, fp6_launch_plan &plan,
-                        int &k_groups)
+                        PlanDetails &details)
 {
     const bool fp16 = weight_bits == 16, grouped = weight_bits == -6;
     if (!(fp16 ? shape_ok(M, K) : packed_shape_ok(M, K)) || token < 0 || token >= N || N >= (1ll << 31)
@@ -1076,7 +1080,7 @@ fp6_status plan_of_call(int weight_bits, int64_t M, int64_t N, int64_t K, int64_
             return fits;
         const StreamCfg &c = (fp16 ? kStreamCfgFp16 : kStreamCfg)[p.cfg];
         plan = {FP6_KERNEL_STREAM, kTileRows * c.wm, 16 * c.nt, p.split, 0, N, p.counter_bytes, region, p.partial_bytes};
-        k_groups = c.wk;
+        details = {c.wk, p.partial_bytes, p.required_partials};
         return FP6_OK;
     }
     const Weights kind = fp16               ? Weights::kFp16
@@ -1090,8 +1094,8 @@ fp6_status plan_of_call(int weight_bits, int64_t M, int64_t N, int64_t K, int64_
         return fits;
     plan = {p.is_block() ? FP6_KERNEL_BLOCK : FP6_KERNEL_TILED, p.is_block() ? kBlockCfg[p.block.cfg].rows : p.tiled.tile.rows(),
             p.is_block() ? kBlockCfg[p.block.cfg].tokens : p.tiled.tile.tokens(), p.split(), first, tokens, p.counter_bytes(),
-            region, p.split() > 1 ? p.required_partials() : 0};  // with k slices: what the call is refused without
-    k_groups = p.is_block() ? kBlockCfg[p.block.cfg].k_groups() : p.tiled.k_groups;
+            region, p.split() > 1 ? p.required_partials() : 0};
+    details = {p.is_block() ? kBlockCfg[p.block.cfg].k_groups() : p.tiled.k_groups, p.partial_bytes(), p.required_partials()};
     return FP6_OK;
 }
 
@@ -1154,15 +1158,30 @@ void fp6_tuning_set_tile(int block_rows, int block_tokens)
 fp6_status fp6_tuning_plan(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes,
                            fp6_launch_plan *plan)
 {
-    int k_groups;
-    return plan ? plan_of_call(weight_bits, M, N, K, token, workspace_bytes, *plan, k_groups) : FP6_ERR_NULL;
+    PlanDetails details;
+    return plan ? plan_of_call(weight_bits, M, N, K, token, workspace_bytes, *plan, details) : FP6_ERR_NULL;
 }
 
 int fp6_tuning_plan_k_groups(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes)
 {
     fp6_launch_plan plan;
-    int k_groups = 0;
-    return plan_of_call(weight_bits, M, N, K, token, workspace_bytes, plan, k_groups) == FP6_OK ? k_groups : 0;
+    PlanDetails details;
+    return plan_of_call(weight_bits, M, N, K, token, workspace_bytes, plan, details) == FP6_OK ? details.k_groups : 0;
+}
+
+fp6_status fp6_tuning_plan_partials(int weight_bits, int64_t M, int64_t N, int64_t K, int64_t token, size_t workspace_bytes, size_t *used,
+                                    size_t *required)
+{
+    if (!used || !required)
+        return FP6_ERR_NULL;
+    fp6_launch_plan plan;
+    PlanDetails details;
+    const fp6_status status = plan_of_call(weight_bits, M, N, K, token, workspace_bytes, plan, details);
+    if (status == FP6_OK) {
+        *used = details.used_partials;
+        *required = details.required_partials;
+    }
+    return status;
 }
 
 void fp6_tuning_set_pack_polls(int polls) { g_pack_polls.store(polls < 0 ? kPartWaitPolls : polls); }

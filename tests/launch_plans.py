@@ -23,6 +23,13 @@ def k_groups(lib, width, M, N, K, token=0, workspace_bytes=2 ** 64 - 1):
     return lib.fp6_tuning_plan_k_groups(BITS[width], M, N, K, token, workspace_bytes)
 
 
+def partials(lib, width, M, N, K, token=0, workspace_bytes=2 ** 64 - 1):
+    """Bytes of partial sums that the same launch writes, and that the call asks for; or the status of a refusal."""
+    used, required = ctypes.c_size_t(), ctypes.c_size_t()
+    status = lib.fp6_tuning_plan_partials(BITS[width], M, N, K, token, workspace_bytes, ctypes.byref(used), ctypes.byref(required))
+    return (used.value, required.value) if status == 0 else status
+
+
 def workspace_bytes(lib, width, M, N, K):
     name = "fp6" if width == "fp6g" else width
     return getattr(lib, name + "_linear_workspace_bytes")(M, N, K)

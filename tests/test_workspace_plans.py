@@ -5,7 +5,7 @@ import random
 
 import pytest
 
-from launch_plans import BITS, BLOCK, TILED, k_groups, plan, workspace_bytes
+from launch_plans import BITS, BLOCK, STREAM, TILED, k_groups, partials, plan, workspace_bytes
 
 
 @pytest.fixture(scope="module")
@@ -206,3 +206,32 @@ def test_blocks_in_place_of_tiled_ones_ask_for_what_those_did(lib):
         assert plan(lib, width, M, N, K, workspace_bytes=least).split_k == p.split_k
         assert plan(lib, width, M, N, K, workspace_bytes=least - 16) == REFUSED, (width, M, N, K)
     assert sliced > 50 and whole > 50
+
+
+def test_partial_sums_used_and_required(lib):
+    """What a launch writes, from its block and k slices, lies within what the call asks for; with that much it runs, with less it is
+    refused or takes another plan."""
+    rng = random.Random(11)
+    more_than_used = untouched = 0
+    for _ in range(4000):
+        width = rng.choice(list(BITS))
+        M, K = 16 * round(2 ** rng.uniform(0, 11.8)), 256 * round(2 ** rng.uniform(0, 6.8))
+        N = round(2 ** rng.uniform(0, 12))
+        p, (used, required) = plan(lib, width, M, N, K), partials(lib, width, M, N, K)
+        rows = M if p.kernel != BLOCK else -(-M // p.block_rows) * p.block_rows  # the block kernel keeps whole blocks
+        tokens = p.block_tokens if p.kernel == STREAM else -(-N // p.block_tokens) * p.block_tokens
+        assert used == (p.split_k * rows * tokens * 4 if p.split_k > 1 else 0), (width, M, N, K)
+        assert used <= required <= workspace_bytes(lib, width, M, N, K)
+        assert p.partial_bytes == (required if p.split_k > 1 else 0)
+        more_than_used += 0 < used < required
+        untouched += used == 0 < required
+        if required == 0:
+            assert partials(lib, width, M, N, K, workspace_bytes=0) == (0, 0)
+            continue
+        least = p.partial_offset + required
+        assert partials(lib, width, M, N, K, workspace_bytes=least) == (used, required)
+        less = plan(lib, width, M, N, K, workspace_bytes=least - 16)
+        assert less == REFUSED or (less.kernel, less.block_rows, less.block_tokens, less.split_k) != (p.kernel, p.block_rows, p.block_tokens,
+                                                                                                    p.split_k), (width, M, N, K)
+        assert less == REFUSED or width in ("fp16", "fp6g")
+    assert more_than_used > 50 and untouched > 50
