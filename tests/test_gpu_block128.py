@@ -1,5 +1,5 @@
 """The block kernel's 128 x 128 block with weights of a scale per row (6, 5, 4 and 3 bits), as the plan picks it: ragged last row and
-token blocks, one row tile, odd numbers of k-tiles (half a 3-bit tile at the end), with k slices and without, on a workspace of the
+token blocks, one row tile, one and two k-tiles, odd numbers of k-tiles (half a 3-bit tile at the end), with k slices and without, on a workspace of the
 queried size, and the steps after the sum."""
 import pytest
 import torch
@@ -11,7 +11,7 @@ from launch_plans import BLOCK, plan, workspace_bytes
 pytestmark = pytest.mark.gpu
 
 # M, K, N, k slices
-SHAPES = [(16, 2048, 200, 1), (144, 2048, 130, 1), (272, 2304, 129, 1), (1040, 1024, 257, 1), (2064, 768, 129, 1), (656, 4352, 140, 3),
+SHAPES = [(16, 256, 129, 1), (272, 256, 300, 1), (144, 512, 130, 1), (1040, 512, 257, 1), (16, 2048, 200, 1), (144, 2048, 130, 1), (272, 2304, 129, 1), (1040, 1024, 257, 1), (2064, 768, 129, 1), (656, 4352, 140, 3),
           (1024, 4096, 256, 4), (1152, 8192, 193, 8)]
 NARROW = ["fp5", "fp4", "fp3"]
 
