@@ -837,6 +837,45 @@ __device__ __forceinline__ half4_t residual_rows(const Epilogue &e, int col, int
     return (half4_t){a[0], a[1], b[0], b[1]};
 }
 
+// ... of R x T tiles of 16 rows x 16 tokens from row row0 on, one load for each (residual_rows() takes two)
+// and nothing but loads before they are waited for together: a branch, or a word made of another
+// one, between them, and the compiler waits for each (1712 x 1280, N = 225, group scales 18.0 -> 16.1 us, 4960 x 1024, N = 1917, gated 48.7
+// -> 43.4; 18000 x 1280, N = 149, 6 bits 25.7 -> 22.3; 327 drawn calls with a residual, median 0.95 of the time).  Rows and tokens past
+// the end take those of the last.
+template <int R, int T>
+__device__ __forceinline__ void load_residuals(half4_t (&residual)[R][T], const Epilogue &e, int row0, int col0, int M, int N, int lane)
+{
+    u32x2 words[R][T];
+    const int64_t pitch = e.gated ? M >> 1 : M;
+    const half_t *p[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int col = col0 + 16 * t + (lane & 15);
+        p[t] = e.residual + (col < N ? col : N - 1) * pitch;
+    }
+    auto row = [&](int r) { return (row0 + 16 * r < M ? row0 + 16 * r : M - 16) + 4 * (lane >> 4); };
+    if (e.gated) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                words[r][t][0] = *reinterpret_cast<const uint32_t *>(p[t] + (row(r) >> 1));
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                words[r][t] = *reinterpret_cast<const u32x2 *>(p[t] + row(r));
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            pin(words[r][t]);
+            residual[r][t] = bit_cast<half4_t>(words[r][t]);
+        }
+}
+
 // Rows m0 .. m0+3 of token column `col`: the four sums one lane holds after the MFMAs.
 // Y and the residual are [tokens][M] (or [tokens][M/2] when gated).
 template <bool kHasScale>
@@ -882,8 +921,8 @@ __device__ __forceinline__ void finish_rows(const Epilogue &e, const RowTerms &t
 }
 
 // The R x T tiles of 16 rows x 16 tokens that a wave of a prompt-sized kernel ends up with: rows row0 + 16 r .., tokens col0 + 16 t ...
-// The terms of a row tile are read once, by the caller, and residuals T tiles together: read tile by tile in front of their use, each of
-// them was waited for (65536 x 2816, N = 128, 6 bits: 4.6 us after the k loop).  Calls without steps take a path of their own: with
+// The terms of a row tile are read once, by the caller, and residuals of up to sixteen tiles together: read tile by tile in front of their
+// use, each of them was waited for (65536 x 2816, N = 128, 6 bits: 4.6 us after the k loop).  Calls without steps take a path of their own: with
 // the tests of every step between them the stores leave one by one.  Drawn calls of 256 to 57344 rows and 65 to 4096 tokens, median
 // time over that before: tiled kernel 0.93 without k slices (795 calls), 0.945 with (654); block kernel 0.99 without (564; 256 x 256
 // blocks of 57344 x 2048 0.97), 0.94 with (226, add_slices() included).
@@ -914,24 +953,22 @@ __device__ __forceinline__ void finish_tiles(const Epilogue &e, RowTerms (&terms
             }
         return;
     }
+    constexpr int G = R * T <= 16 ? R : 16 / T;  // rows of tiles whose residuals the registers hold beside the sums
+    static_assert(G > 0 && R % G == 0, "groups of rows");
 #pragma unroll
-    for (int r = 0; r < R; ++r)
-        if (row0 + 16 * r < M) {
-            half4_t residual[T];
-            if (e.residual) {
+    for (int r0 = 0; r0 < R; r0 += G) {
+        half4_t residual[G][T];
+        if (e.residual)
+            load_residuals(residual, e, row0 + 16 * r0, col0, M, N, lane);
+#pragma unroll
+        for (int r = 0; r < G; ++r)
+            if (row0 + 16 * (r0 + r) < M) {
 #pragma unroll
                 for (int t = 0; t < T; ++t)
                     if (col + 16 * t < N)
-                        residual[t] = residual_rows(e, col + 16 * t, m0 + 16 * r, M);
-#pragma unroll
-                for (int t = 0; t < T; ++t)
-                    pin(residual[t]);
+                        finish_rows<kHasScale>(e, terms[r0 + r], residual[r][t], v[r0 + r][t], col + 16 * t, m0 + 16 * (r0 + r), M, Y);
             }
-#pragma unroll
-            for (int t = 0; t < T; ++t)
-                if (col + 16 * t < N)
-                    finish_rows<kHasScale>(e, terms[r], residual[t], v[r][t], col + 16 * t, m0 + 16 * r, M, Y);
-        }
+    }
 }
 // Their terms; kSteps: whether the calls of the source can have steps.  Row tiles past the end take the last one's.
 template <bool kHasScale, bool kSteps, int R>
