@@ -289,14 +289,20 @@ __global__ __launch_bounds__(Shape::kThreads) void linear_stream_kernel(
     request_residual();
     // (every lane loads: lanes of token columns >= N read words that nobody stored, their sums are never written)
     float4_t sum[NT];
-    // Three slices together (four of two token tiles): with eight, the tests of slices that are not there cost more than trips to memory
-    // saved (S = 4, 8192 x 8192, N = 8 11.65 -> 11.53 us, 8192 x 22016, N = 1 22.83 -> 22.65; S up to 16 within 1.5 % either way).
-    add_slices<NT == 2 ? 4 : 3>(sum, S, split, [&](int nt) { return acc[nt]; }, [&](float4_t (&part)[NT], int s) {
+    auto own = [&](int nt) { return acc[nt]; };
+    auto load = [&](float4_t (&part)[NT], int s) {
         const partial_rsrc_t src = slice(s);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
             part[nt] = agent_load(src, nt * 1024 + lane * 16);
-    });
+    };
+    // Three slices together (four of one or two token tiles): with eight, the tests of slices that are not there cost more than trips to
+    // memory saved (S = 4, 8192 x 8192, N = 8 11.65 -> 11.53 us, 8192 x 22016, N = 1 22.83 -> 22.65).  One token tile in threes took up to
+    // 5.5 % longer from six slices on than in fours with the own tile among them (1376 x 20736, N = 3, fp16, S = 11 15.3 -> 15.8).
+    if constexpr (NT == 1)
+        add_slices_untested<4>(sum, S, split, own, load);
+    else
+        add_slices<NT == 2 ? 4 : 3>(sum, S, split, own, load);
     finish(sum);
     if (lane == 0)
         counters[row_tile] = 0;  // re-arm for the next call on this workspace

@@ -114,6 +114,30 @@ def test_every_block_with_and_without_slices(pkg, width, N):
         check_linear(runs[0].cpu().numpy(), ref.cpu().numpy().astype(np.float64), "%s M=%d K=%d N=%d" % (width, M, K, N))
 
 
+@pytest.mark.parametrize("width,M,K,N,slices", [("fp16", 1504, 2304, 6, 2), ("fp16", 1088, 2816, 2, 3), ("fp6g", 64, 4352, 16, 4), ("fp5", 96, 5120, 11, 5),
+                                                ("fp6", 112, 6400, 9, 6), ("fp16", 64, 14848, 5, 7), ("fp16", 112, 17152, 2, 8), ("fp16", 128, 9216, 4, 9),
+                                                ("fp16", 96, 21760, 6, 10), ("fp6", 176, 21248, 10, 11), ("fp16", 304, 13312, 2, 13)])
+def test_slice_counts_of_one_token_tile(pkg, width, M, K, N, slices):
+    """Whole and last batches of the other slices' partial tiles, the own one first, between and last: any wave may be the last to
+    arrive, and the bits may not depend on which."""
+    print("slices %s M=%d K=%d N=%d: %d" % (width, M, K, N, slices), flush=True)
+    assert plan(pkg.load_library(), width, M, N, K).split_k == slices
+    W, X = workloads.make_weights(M, K, M + N, device="cuda"), workloads.make_activations(N, K, K + N, device="cuda")
+    if width == "fp16":
+        call, ref = (lambda: pkg.fp16_linear(W, X)), X.float() @ W.float().t()
+    else:
+        packed, scales = getattr(pkg, width + "_quantize_pack")(W)
+        call = lambda: getattr(pkg, width + "_linear")(packed, scales, X, M, K)
+        if width == "fp6g":
+            ref = X.float() @ pkg.fp6g_unpack(packed, scales, M, K).float().t()
+        else:
+            ref = X.float() @ getattr(pkg, width + "_unpack")(packed, torch.ones_like(scales), M, K).float().t() * scales.float()
+    first = call()
+    for _ in range(20):
+        assert torch.equal(call().view(torch.int16), first.view(torch.int16))
+    check_linear(first.cpu().numpy(), ref.cpu().numpy().astype(np.float64), "%s M=%d K=%d N=%d" % (width, M, K, N))
+
+
 @pytest.mark.parametrize("width", ["fp6", "fp6g", "fp5", "fp4", "fp3", "fp16"])
 @pytest.mark.parametrize("M,K,N", [(32, 256, 2), (144, 2304, 7), (2192, 1280, 16), (400, 7936, 33)])
 def test_tokens_stay_apart(pkg, width, M, K, N):
