@@ -938,6 +938,18 @@ bool one_pass_pack(int64_t M, int64_t K)
     return parts <= kMaxParts && M * K >= (full ? 1 << 24 : 1 << 26);
 }
 
+// LDS that a block of the second of two launches is given, and does not use, so that few enough of them share a CU.  A wave's weights lie in
+// sixteen rows, and with all the waves that the registers hold (20 to 32 per CU) a large matrix is read out of order: time over that of the
+// kernel which held 16, by weights, without -> with 12 waves (3 bits 16):
+//   6 bits 1024 x 65536 0.97 -> 0.94, 4096 x 65536 1.01 -> 0.98, 16384 x 57344 1.01 -> 0.98 (744 us); 5 bits 0.97 -> 0.96, 1.005 -> 0.995,
+//   1.02 -> 1.00; 4 bits 0.97 -> 0.95, 1.01 -> 0.98, 1.01 -> 0.99; 3 bits 0.99 -> 0.965, 1.02 -> 1.00, 1.01 -> 0.99, 8192 x 22016 0.99 -> 0.98.
+// Smaller ones lose by it: 32768 x 1280 0.87 -> 0.90, 0.87 -> 0.92, 0.86 -> 0.90, 0.92 -> 0.945.
+template <class Fmt>
+unsigned tiles_lds(int64_t M, int64_t K)
+{
+    return M * K < 1 << 26 ? 0 : std::is_same_v<Fmt, E2M0Format> ? kMaxLds / 4 : (kMaxLds / 3) & ~1023;
+}
+
 template <class Fmt>
 fp6_status quantize_pack_impl(const void *W_f16, int64_t M, int64_t K, void *packed, void *scales_f16, void *stream)
 {
@@ -967,7 +979,7 @@ fp6_status quantize_pack_impl(const void *W_f16, int64_t M, int64_t K, void *pac
                        dim3(kScaleWavesPerBlock * 64), 0, st, W, (int)M, (int)K, scales);
     if (hipGetLastError() != hipSuccess)
         return FP6_ERR_HIP;
-    hipLaunchKernelGGL(quantize_tiles_kernel<Fmt>, dim3((unsigned)((RT * KT + 3) / 4)), dim3(256), 0, st, W, (int)M, (int)K, out, scales);
+    hipLaunchKernelGGL(quantize_tiles_kernel<Fmt>, dim3((unsigned)((RT * KT + 3) / 4)), dim3(256), tiles_lds<Fmt>(M, K), st, W, (int)M, (int)K, out, scales);
     return hipGetLastError() == hipSuccess ? FP6_OK : FP6_ERR_HIP;
 }
 

@@ -53,7 +53,7 @@ __device__ __forceinline__ float ratio_of(half_t w, RowScale rs)
 // encode<C>(): the lane's weights of runs 4C .. 4C+3 (run f, columns run*32 + 8q + j: half j of v[f]) -> its kHalfWords words
 // of that half of the tile; store_tile() / store_half(): the lane's words -> its bytes of the tile.  6, 5 and 4 bits: the chip's
 // conversions round to nearest, ties to the even code, saturate (5 bits: by hand) and keep the sign of a zero: every fp16 magnitude
-// under 512 row maxima of all binades, ratios down to 2^-38 among them, gets the oracle's code (tests/test_gpu_pack_rounding.py; the
+// under 512 row maxima of all binades, ratios down to 2^-37 among them, gets the oracle's code (tests/test_gpu_pack_rounding.py; the
 // quotient: tests/test_host_logic.py).  18 VALU instructions per weight before, 4 and a conversion now.
 typedef float float16_t __attribute__((ext_vector_type(16)));
 typedef short short2_t __attribute__((ext_vector_type(2)));
