@@ -4,6 +4,7 @@
 #include "../../include/fp6_bench.h"
 
 #include <atomic>
+#include <cmath>
 #include <initializer_list>
 
 #include "fp6_device.hpp"
@@ -500,11 +501,11 @@ double block_cost(const BlockPlan &p, int64_t K, Weights kind)
 // come from memory.  Fitted to 20514 drawn calls of 128 to 57344 rows and 65 to 4096 tokens, weights from memory (mean error 4.5 to 5 %).
 struct PerRowCost {
     double fixed, slices, per_slice, memory_rate, fill, run[4];  // run: 6, 5, 4, 3 bits
-    double operator()(double rounds, int64_t blocks, int split, int64_t M, int64_t K, Weights kind) const
+    double operator()(double rounds, int64_t blocks, int split, int64_t M, int64_t K, Weights kind, double run_share = 1.0) const
     {
         const int f = kind == Weights::kFp6 ? 0 : kind == Weights::kFp5 ? 1 : kind == Weights::kFp4 ? 2 : 3;
         const double runs = 8.0 * (double)((K / kTileK + split - 1) / split), busy = (double)blocks / kCus / rounds;
-        const double alone = rounds * (fixed + runs * run[f] * (1.0 + fill * (busy < 1.0 ? busy : 1.0))) + (split > 1 ? slices + per_slice * split : 0.0);
+        const double alone = rounds * (fixed + runs * run[f] * run_share * (1.0 + fill * (busy < 1.0 ? busy : 1.0))) + (split > 1 ? slices + per_slice * split : 0.0);
         const double memory = (double)M * (double)K * (6 - f) / 8.0 * 1e-6 / memory_rate;
         return alone > memory ? alone : memory;
     }
@@ -518,13 +519,20 @@ constexpr PerRowCost kTiled64Cost{4.27, 0.88, 0.425, 2.53, 0.336, {0.0951, 0.107
 // kernel's, drawn calls as above, by their k slices: 256 x 128, two 0.78-0.99, three to five 0.78-0.86, six and more 0.61, none 1.08
 // (a tenth of them below 0.73: rounds); 128 x 64 0.88 to 1.55.  As chosen: 0.805 over all 20514 calls, 0.803 if the faster one were
 // known; 12 calls more than 3 % slower.
+//   Fewer rows: the waves of a 256-row block that have none leave its runs cheaper, and the little that the tiled plan asks its caller for
+// holds the 128 x 128 block to fewer k slices still (16 x 22016, N = 309, 3 bits, 2 for 16: 64.3 us for 40.3; 16 x 14080, N = 847, 1 for 13:
+// 79.4 for 51.6).  Where it has a third of them or less the estimate counts that: of 3078 drawn calls of 16 to 272 rows 36 stay with
+// the tiled kernel, 29 of them more than 3 % faster there; of 4065 others five are 3 to 17 % slower, the median 0.63 of its time.
+//   128 x 64 tiles: the block only wins for rows of more than 100 000 columns (1152 x 211968, N = 103, 5 bits 152.5 -> 114.4 us; 24 such calls
+// 0.74 to 0.91), where those take 14 slices of long runs.
 bool block128_is_faster(const BlockPlan &b, const TiledPlan &t, int64_t M, int64_t K, Weights kind)
 {
     const double fullest = (double)((int64_t)((t.row_blocks + kXcds - 1) / kXcds) * t.n_blocks * t.split) / kCusPerXcd;
     const bool wide = t.tile.tokens() == 128;
     // two 128 x 64 blocks share a CU
     const double rounds = wide ? (double)(int64_t)(fullest + 1.0 - 1e-9) : fullest <= 1.0 ? 1.0 : fullest > 2.0 ? fullest : 1.0 + 0.9 * (fullest - 1.0);
-    const double tiled = (wide ? kTiled256Cost : kTiled64Cost)(rounds, (int64_t)t.row_blocks * t.n_blocks * t.split, t.split, M, K, kind);
+    const double share = wide && M < 200 && t.split >= 3 * b.split ? 0.2 + 0.8 * std::sqrt((double)M / 200.0) : 1.0;
+    const double tiled = (wide ? kTiled256Cost : kTiled64Cost)(rounds, (int64_t)t.row_blocks * t.n_blocks * t.split, t.split, M, K, kind, share);
     const double block = kBlock128Cost((double)((b.chunk + kCusPerXcd - 1) / kCusPerXcd), (int64_t)b.row_blocks * b.n_blocks * b.split, b.split, M, K, kind);
     return 1.03 * block < tiled;
 }

@@ -208,6 +208,12 @@ def test_blocks_in_place_of_tiled_ones_ask_for_what_those_did(lib):
     assert sliced > 50 and whole > 50
 
 
+@pytest.mark.parametrize("width,M,N,K", [("fp3", 16, 309, 22016), ("fp3", 16, 847, 14080), ("fp4", 16, 694, 8448), ("fp5", 32, 183, 14592), ("fp6", 32, 183, 23552)])
+def test_few_rows_keep_their_k_slices(lib, width, M, N, K):
+    """The partial sums of few rows are small, and the 128 x 128 block, held to them, would take a third of the tiled kernel's slices or less."""
+    assert plan(lib, width, M, N, K).kernel == TILED
+
+
 def test_partial_sums_used_and_required(lib):
     """What a launch writes, from its block and k slices, lies within what the call asks for; with that much it runs, with less it is
     refused or takes another plan."""
