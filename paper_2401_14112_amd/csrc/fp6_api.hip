@@ -518,7 +518,8 @@ constexpr PerRowCost kTiled64Cost{4.27, 0.88, 0.425, 2.53, 0.336, {0.0951, 0.107
 // slices where 256-row blocks leave CUs idle and whole units per XCD where those are dealt unevenly.  Median time over the tiled
 // kernel's, drawn calls as above, by their k slices: 256 x 128, two 0.78-0.99, three to five 0.78-0.86, six and more 0.61, none 1.08
 // (a tenth of them below 0.73: rounds); 128 x 64 0.88 to 1.55.  As chosen: 0.805 over all 20514 calls, 0.803 if the faster one were
-// known; 12 calls more than 3 % slower.
+// known; 12 calls more than 3 % slower.  3443 of the calls that it moves, drawn anew, each with the tiled kernel pinned in turn: median 0.69
+// (by format and k slices 0.54 to 0.90), five more than 3 % slower, the most 1.10.
 //   Fewer rows: the waves of a 256-row block that have none leave its runs cheaper, and the little that the tiled plan asks its caller for
 // holds the 128 x 128 block to fewer k slices still (16 x 22016, N = 309, 3 bits, 2 for 16: 64.3 us for 40.3; 16 x 14080, N = 847, 1 for 13:
 // 79.4 for 51.6).  Where it has a third of them or less the estimate counts that: of 3078 drawn calls of 16 to 272 rows 36 stay with

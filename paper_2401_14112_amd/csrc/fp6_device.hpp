@@ -165,7 +165,8 @@ __device__ __forceinline__ void issue_load_to_lds_b128(rsrc_t rsrc, int lane_off
 // ---- split-K partial tiles ---------------------------------------------------
 // Written and read 16 bytes per lane, each access performed at the point where all CUs of the device agree: the cache
 // bits (sc1) are those of an agent-scope atomic access, which only comes in pieces of up to 8 bytes.  The address unit
-// takes as long for a 4-byte access per lane as for a 16-byte one.
+// takes as long for a 4-byte access per lane as for a 16-byte one (streaming kernel, nothing else varied: 1197 drawn calls with k slices
+// take 0.991, 0.993, 0.988, 0.984 of the time of 4-byte accesses with one to four token tiles).
 typedef __amdgpu_buffer_rsrc_t partial_rsrc_t;
 constexpr int kAgentScope = 16;  // sc1
 __device__ __forceinline__ partial_rsrc_t partial_buffer(void *p, int bytes)
@@ -185,7 +186,7 @@ __device__ __forceinline__ float4_t agent_load(partial_rsrc_t r, int off)
 // it stored), those of the other slices requested PB slices at a time, one trip to memory each (load(part, s)).  Only what is
 // added is read: with a batch of four clamped to the last slice and the own one read back, two slices cost four reads of a
 // tile and three slices four (9216 x 9216, N = 256, fp16, S = 3 83.6 -> 80.3 us; 4096 x 4096, N = 300, fp16, S = 2 26.9 -> 24.8;
-// 8192 x 8192, N = 400, group scales, S = 2 70.9 -> 65.8; 10240 x 8192, N = 64, 6 bits, S = 3 22.6 -> 21.6).
+// 8192 x 8192, N = 400, group scales, S = 2 70.9 -> 65.8; 10240 x 8192, N = 64, 6 bits, S = 3 21.0 -> 20.4).
 template <int PB, int G, class Own, class Load>
 __device__ __forceinline__ void add_slices(float4_t (&sum)[G], int S, int split, Own &&own, Load &&load)
 {
@@ -458,7 +459,7 @@ struct PackedFp6GroupSource {
 //   codes 28..31:  s -> D3.5  e1 -> D3.4  e0 m1 m0 -> D4.6 D4.5 D4.4
 // Unpack per 32 codes: 5 ANDs, 3 three-term stitches, then per two codes one conversion times 2^(15-1)
 // (exact, the subnormal binade included).  It issues like any other VALU instruction; two byte permutes and two
-// packed multiplies per four codes took twice as many: 12288 x 12288, N = 45 31.2 -> 27.9 us, 8192 x 22016,
+// packed multiplies per four codes took twice as many: 12288 x 12288, N = 45 30.3 -> 28.6 us, 8192 x 22016,
 // N = 16 / 32 / 64 / 100 / 512 21.9 / 26.7 / 36.4 / 57.3 / 155.6 -> 21.0 / 24.7 / 34.9 / 53.5 / 148.8,
 // 16384 x 8192, N = 2048 446 -> 409.
 __device__ __forceinline__ half8_t e2m2_bytes_to_fragment(uint32_t b_lo, uint32_t b_hi)
