@@ -98,3 +98,46 @@ def test_parts_that_do_not_wait(pkg, fmt, M, K, polls):
         lib.fp6_tuning_set_pack_polls(-1)
     assert np.array_equal(row_tiles_of(packed, M, K, tiles, tile_bytes, tile_cols), np.asarray(ref_packed).reshape(-1))
     assert np.array_equal(scales.cpu().numpy()[rows].view(np.uint16), np.asarray(ref_scales).view(np.uint16))
+
+
+@pytest.mark.parametrize("fmt", ["fp6", "fp4"])
+def test_one_pass_in_a_graph(pkg, fmt):
+    """The exchange is cleared by a launch of the graph: replays on new weights, other work between, give the bytes of eager calls."""
+    print("quantize_pack %s in a graph" % fmt, flush=True)
+    M, K = 4096, 4096
+    assert _parts(pkg, fmt, M, K) > 1
+    call = getattr(pkg, fmt + "_quantize_pack")
+    W = torch.empty((M, K), dtype=torch.float16, device="cuda")
+    packed, scales = call(W.fill_(1.0))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(W, packed=packed, scales=scales)
+    for seed in range(4):
+        W.normal_(0, 0.01 + seed, generator=torch.Generator(device="cuda").manual_seed(seed))
+        want, want_scales = call(W)
+        packed.fill_(0xA5)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(packed, want) and torch.equal(scales, want_scales), seed
+
+
+def test_one_pass_on_two_streams(pkg):
+    """Parts of two matrices wait for their row tiles on the chip together."""
+    print("quantize_pack on two streams", flush=True)
+    sizes = {"fp6": (4096, 16640), "fp5": (8192, 8192)}
+    jobs = []
+    for fmt, (M, K) in sizes.items():
+        W = torch.empty((M, K), dtype=torch.float16, device="cuda").normal_(0, 0.02, generator=torch.Generator(device="cuda").manual_seed(M))
+        call = getattr(pkg, fmt + "_quantize_pack")
+        assert _parts(pkg, fmt, M, K) > 1
+        want = call(W)
+        jobs.append((call, W, want, [t.clone().fill_(1) for t in want], torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(6):
+        for call, W, _, out, stream in jobs:
+            with torch.cuda.stream(stream):
+                call(W, packed=out[0], scales=out[1])
+    torch.cuda.synchronize()
+    for _, _, want, out, _ in jobs:
+        assert torch.equal(out[0], want[0]) and torch.equal(out[1], want[1])
